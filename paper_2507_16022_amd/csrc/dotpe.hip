@@ -2023,12 +2023,12 @@ int dotpe_sample_posterior(dotpe_ctx* ctx, dotpe_event* ev, int64_t n_samples, d
   auto alloc = [&](void** p, size_t n) { return dev_alloc(ctx, p, n, &bufs, &held); };
   const int64_t nt = a.n_tiles, nb = scan_tmp_size(nt);
   double *cum = nullptr, *blk = nullptr, *res = nullptr, *smp = nullptr;
-  int *tile = nullptr, *list = nullptr;
-  int64_t *first = nullptr, *n_u_dev = nullptr;
+  int *tile = nullptr, *list = nullptr, *item = nullptr;
+  int64_t* n_u_dev = nullptr;
   int rc;
   if ((rc = alloc((void**)&cum, (size_t)nt * 8)) || (rc = alloc((void**)&blk, (size_t)nb * 8)) ||
       (rc = alloc((void**)&tile, (size_t)ns * 4)) || (rc = alloc((void**)&res, (size_t)ns * 8)) ||
-      (rc = alloc((void**)&list, (size_t)ns * 4)) || (rc = alloc((void**)&first, (size_t)(ns + 1) * 8)) ||
+      (rc = alloc((void**)&list, (size_t)ns * 4)) || (rc = alloc((void**)&item, (size_t)ns * 4)) ||
       (rc = alloc((void**)&n_u_dev, 8)) || (rc = alloc((void**)&smp, (size_t)ns * 6 * 8)))
     return rc;
   hipLaunchKernelGGL(k_tile_mass, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, ev->partials,
@@ -2036,21 +2036,48 @@ int dotpe_sample_posterior(dotpe_ctx* ctx, dotpe_event* ev, int64_t n_samples, d
   scan_inclusive(cum, nt, blk, s);
   hipLaunchKernelGGL(k_place_draws, dim3((unsigned)((ns + 255) / 256)), dim3(256), 0, s, cum, nt, ns,
                      u0, tile, res);
-  hipLaunchKernelGGL(k_group_draws, dim3(1), dim3(64), 0, s, tile, ns, list, first, n_u_dev);
+  hipLaunchKernelGGL(k_group_draws, dim3(1), dim3(1024), 0, s, tile, ns, list, item, n_u_dev);
   HIP_OK(hipGetLastError());
   int64_t n_u = 0;
   HIP_OK(hipMemcpyAsync(&n_u, n_u_dev, 8, hipMemcpyDeviceToHost, s));
   HIP_OK(hipStreamSynchronize(s));
   a.work_list = list;
   a.n_work_list = n_u;
-  a.sample_first = first;
+  a.n_samples = ns;
+  a.sample_item = item;
   a.sample_res = res;
   a.samples = smp;
-  const int64_t C = ev->coef_tiles;
+  // the listed tiles' ln p and running sums: in the event's candidate buffer
+  // (free once the evidence call has returned) where that holds them, else
+  // allocated; short of memory, in chunks of as many tiles as the candidate
+  // buffer or what can be had holds
+  int tm, tn;
+  tile_shape(prec, &tm, &tn);
+  const size_t tile_vals = (size_t)tm * tn;
+  int64_t C = std::min(ev->coef_tiles, n_u);
+  const int64_t in_cand = (int64_t)((size_t)ev->cand_cap * 4 / (2 * tile_vals));
+  double* vals = in_cand >= C ? ev->cand : nullptr;
+  if (!vals) {
+    rc = alloc((void**)&vals, (size_t)C * 2 * tile_vals * 8);
+    if (rc && in_cand > 0) {
+      C = in_cand;
+      vals = ev->cand;
+      rc = DOTPE_OK;
+    }
+    while (rc && C > 1) {
+      C /= 2;
+      rc = alloc((void**)&vals, (size_t)C * 2 * tile_vals * 8);
+    }
+    if (rc) return rc;
+  }
+  a.coef_tiles = C;
+  a.sample_lnp = vals;
+  a.sample_cum = vals + (size_t)C * tile_vals;
   for (int64_t c = 0; c * C < n_u; ++c) {
     a.work0 = c * C;
-    if ((rc = launch_fused<kCoef>(prec, a, std::min(C, kCoefGrid), s))) return rc;
-    if ((rc = launch_fused<kSample>(prec, a, std::min(C, kE2Grid), s))) return rc;
+    const int64_t n = std::min(C, n_u - a.work0);
+    if ((rc = launch_fused<kCoef>(prec, a, std::min(n, kCoefGrid), s))) return rc;
+    if ((rc = launch_fused<kSample>(prec, a, n, s))) return rc;
   }
   std::vector<double> h((size_t)ns * 6);
   HIP_OK(hipMemcpyAsync(h.data(), smp, (size_t)ns * 6 * 8, hipMemcpyDeviceToHost, s));

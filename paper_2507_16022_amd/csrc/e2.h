@@ -281,164 +281,229 @@ __device__ inline double draw_distance(double dh, double hh, double u0, double d
   const unsigned long long hit = __ballot(pre > target && part > 0.0);
   const int src = hit ? __ffsll((long long)hit) - 1 : 63;
   double x = x0 + hx * (NG - 1);
-  if (lane == src && hit) {
-    double run = pre - part, fa = exp(lg(lane * PER) - mx);
-    for (int q = 0; q < PER; ++q) {
-      const int j = lane * PER + q;
-      if (j + 1 >= NG) break;
-      const double fb = exp(lg(j + 1) - mx), cell = 0.5 * hx * (fa + fb);
-      if (run + cell > target) {
-        x = x0 + hx * (j + (target - run) / cell);
-        break;
-      }
-      run += cell;
-      fa = fb;
+  if (hit) {
+    // the PER = 64 cells of lane src, one per lane: the first whose running
+    // sum exceeds the target
+    static_assert(PER == 64, "a cell per lane");
+    const int j = src * PER + lane;
+    const bool in = j + 1 < NG;
+    const double cell = in ? 0.5 * hx * (exp(lg(j) - mx) + exp(lg(j + 1) - mx)) : 0.0;
+    double run = cell;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const double v = __shfl_up(run, off, 64);
+      if (lane >= off) run += v;
+    }
+    const double before = __shfl(pre - part, src, 64);
+    const unsigned long long cross = __ballot(in && before + run > target);
+    if (cross) {
+      const int c = __ffsll((long long)cross) - 1;
+      const double xc = x0 + hx * (j + (target - (before + run - cell)) / cell);
+      x = __shfl(xc, c, 64);
     }
   }
-  x = __shfl(x, src, 64);
   return d0 / exp(x);
 }
 
+// The listed tiles' pairs: ln p of every pair as the evidence pass evaluated
+// it (-inf where it was cut), a pair per thread, to sample_lnp [item][NPT].
+// Few tiles are drawn (tens, where the posterior is narrow), so a tile is
+// spread over NPT / 256 workgroups; with a workgroup per tile that also
+// resolved the tile's draws, 4096 draws in ~30 tiles kept ~30 of the 256 CUs
+// busy: a call took 34 ms at 65536 x 4096 pairs, 1.7 ms with the pairs, the
+// running sums and the draws in kernels of their own.
 template <int PREC, int G>
-__global__ __launch_bounds__(256) void k_sample_tiles(FusedArgs a) {
+__global__ __launch_bounds__(256, 3) void k_sample_pairs(FusedArgs a) {
   typedef Tile<PREC> TL;
   typedef typename std::conditional<PREC == kFP64, double, float>::type AT;
   constexpr int NRT = (G == 1) ? 1 : kMaxNR;
   constexpr int NCO = 2 * G + NRT;
-  constexpr int TM = TL::TM, TN = TL::TN, NPT = TM * TN, NT = 256, NW = NT / 64;
+  constexpr int TM = TL::TM, TN = TL::TN, NPT = TM * TN, NT = 256, PARTS = NPT / NT;
   __shared__ DistParams dp;
   __shared__ double lds_cs[kMaxM * kMaxPhi * 2];
   __shared__ double rowd[TM * 4], cold[TN * 3], rowq[TM * 2];
-  __shared__ double lnp_pair[NPT];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x;
   for (int t = tid; t < kMaxM * a.n_phi * 2; t += NT) lds_cs[t] = a.phase_cs[t];
   for (int t = tid; t < (int)(sizeof(DistParams) / 4); t += NT)
     ((unsigned*)&dp)[t] = ((const unsigned*)a.dist.prm)[t];
   const bool on = cut_on(a);
   const double thr_ml = on ? __longlong_as_double(a.state[3]) - a.cut_delta : -INFINITY;
   const float thr_f = (float)thr_ml;
-  const double M = a.final_out[9];
-  const int64_t end = min(a.work0 + a.coef_tiles, coef_work_count(a));
-
-  for (int64_t q = a.work0 + blockIdx.x; q < end; q += gridDim.x) {
-    const int64_t t = coef_tile(a, q);
-    const int64_t tm = t / a.n_tiles_n, tn = t % a.n_tiles_n;
-    const int64_t row0 = tm * TM, col0 = tn * TN;
+  const int64_t end = (min(a.work0 + a.coef_tiles, a.n_work_list) - a.work0) * PARTS;
+  for (int64_t w = blockIdx.x; w < end; w += gridDim.x) {
+    const int64_t item = w / PARTS;
+    const int p = (int)(w % PARTS) * NT + tid, tr = p / TN, tc = p % TN;
+    const int64_t t = a.work_list[a.work0 + item];
+    const int64_t row0 = t / a.n_tiles_n * TM, col0 = t % a.n_tiles_n * TN;
+    __syncthreads();   // (the scalars of the block's last item are no longer read)
     e2_scalars<PREC, TM, TN>(a, row0, col0, rowd, cold, rowq);
     __syncthreads();
-    const int rows_in = (int)min((int64_t)TM, a.n_sub - row0);
-    const int cols_in = (int)min((int64_t)TN, a.n_ext - col0);
-    const AT* cf = (const AT*)a.coef + (q - a.work0) * (int64_t)(NCO * NPT);
-    // every pair's ln p, as the evidence pass evaluated it
-#pragma unroll 1
-    for (int k = 0; k < NPT / NT; ++k) {
-      const int p = k * NT + tid, tr = p / TN, tc = p % TN;
-      lnp_pair[p] = -INFINITY;
-      if (!(tr < rows_in && tc < cols_in)) continue;
+    double lnp = -INFINITY;
+    if (row0 + tr < a.n_sub && col0 + tc < a.n_ext) {
       PairCoef<AT, G, NRT> pc;
-      pc.template load<NPT>(cf, p);
+      pc.template load<NPT>((const AT*)a.coef + item * (int64_t)(NCO * NPT), p);
       float bound, lw;
-      if (on && pc.bounded(rowq, cold, tr, tc, thr_f, bound, lw)) continue;
-      double2 X[G];
-      double S0, Sr[kMaxND], Si[kMaxND], lnw;
-      pc.unscale(rowd, cold, tr, tc, X, S0, Sr, Si, lnw);
-      EvAcc ev;
-      ev.init();
-      LsePh lse;
-      lse.init();
-      double best = -INFINITY, mlmax = 0.0;
-      int ob = 0;
-      pair_phases<kEvidence, G, false>(a, lds_cs, dp, row0 + tr, col0 + tc, X, S0, Sr, Si, lnw,
-                                      thr_ml, 0, 1, ev, lse, best, ob, mlmax);
-      if (lse.m == -INFINITY) continue;
-      lnp_pair[p] = lnw + (lse.m + log(lse.s) - a.ln_nphi);
-    }
-    __syncthreads();
-    // the tile's reference: its largest ln p in the evidence pass
-    const double pm = a.partials[t * kNPart];
-    for (int64_t s = a.sample_first[q] + wave; s < a.sample_first[q + 1]; s += NW) {
-      // the pair: the draw's residual mass within the tile, against the
-      // running sum of the pairs' weights in index order
-      const double r = a.sample_res[s] * exp(M - pm);
-      double run = 0.0;
-      int sel = -1, last = -1;
-      for (int c0 = 0; c0 < NPT; c0 += 64) {
-        const double v = lnp_pair[c0 + lane];
-        const double x = v == -INFINITY ? 0.0 : exp(v - pm);
-        const unsigned long long live = __ballot(v > -INFINITY);
-        if (live) last = c0 + 63 - __clzll((long long)live);
-        double pre = x;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const double y = __shfl_up(pre, off, 64);
-          if (lane >= off) pre += y;
-        }
-        if (sel < 0) {
-          const unsigned long long hit = __ballot(x > 0.0 && run + pre > r);
-          if (hit) sel = c0 + __ffsll((long long)hit) - 1;
-        }
-        run += __shfl(pre, 63, 64);
-      }
-      if (sel < 0) sel = last;       // rounding past the tile's total
-      if (sel < 0) continue;         // (a tile with mass always has a pair)
-      const int tr = sel / TN, tc = sel % TN;
-      PairCoef<AT, G, NRT> pc;
-      pc.template load<NPT>(cf, sel);
-      double2 X[G];
-      double S0, Sr[kMaxND], Si[kMaxND], lnw;
-      pc.unscale(rowd, cold, tr, tc, X, S0, Sr, Si, lnw);
-      // the phase: probability Lbar_ieo over the phases kept by the cut
-      double v_o[2], dh_o[2], hh_o[2];
-      for (int h = 0; h < 2; ++h) {
-        const int o = lane + 64 * h;
-        v_o[h] = -INFINITY;
-        dh_o[h] = 0.0;
-        hh_o[h] = 0.0;
-        if (o < a.n_phi) {
-          phase_dh_hh<G>(a, lds_cs, X, S0, Sr, Si, o, dh_o[h], hh_o[h]);
-          const bool keep = thr_ml <= 0.0 || (dh_o[h] > 0.0 && dh_o[h] * dh_o[h] >= 2.0 * thr_ml * hh_o[h]);
-          if (keep) v_o[h] = dr_ln_marg(dh_o[h], hh_o[h], a.r0, a.dist.tab, dp.ghx, dp.ghw);
-        }
-      }
-      const double vmax = wave_max(fmax(v_o[0], v_o[1]));
-      const double w0 = v_o[0] == -INFINITY ? 0.0 : exp(v_o[0] - vmax);
-      const double w1 = v_o[1] == -INFINITY ? 0.0 : exp(v_o[1] - vmax);
-      double pre0 = w0, pre1 = w1;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const double y0 = __shfl_up(pre0, off, 64), y1 = __shfl_up(pre1, off, 64);
-        if (lane >= off) { pre0 += y0; pre1 += y1; }
-      }
-      const double tot0 = __shfl(pre0, 63, 64);
-      const double tot = tot0 + __shfl(pre1, 63, 64);
-      const double target = sm64_uniform(a.seed, 2 * (uint64_t)s) * tot;
-      const unsigned long long h0 = __ballot(w0 > 0.0 && pre0 > target);
-      const unsigned long long h1 = __ballot(w1 > 0.0 && tot0 + pre1 > target);
-      int osel;
-      if (h0) osel = __ffsll((long long)h0) - 1;
-      else if (h1) osel = 64 + __ffsll((long long)h1) - 1;
-      else {   // rounding past the total: the last kept phase
-        const unsigned long long k0 = __ballot(w0 > 0.0), k1 = __ballot(w1 > 0.0);
-        osel = k1 ? 64 + 63 - __clzll((long long)k1) : 63 - __clzll((long long)k0);
-      }
-      const int src = osel & 63, hs = osel >> 6;
-      const double dh = __shfl(hs ? dh_o[1] : dh_o[0], src, 64);
-      const double hh = __shfl(hs ? hh_o[1] : hh_o[0], src, 64);
-      const double v = __shfl(hs ? v_o[1] : v_o[0], src, 64);
-      const double D = draw_distance(dh, hh, a.r0, a.d0,
-                                     sm64_uniform(a.seed, 2 * (uint64_t)s + 1), lane);
-      if (lane == 0) {
-        double* out = a.samples + 6 * s;
-        out[0] = rowd[tr * 4 + 3];
-        out[1] = (double)(col0 + tc);
-        out[2] = (double)osel;
-        out[3] = D;
-        out[4] = lnp_pair[sel];
-        out[5] = lnw + v - a.ln_nphi;
+      if (!(on && pc.bounded(rowq, cold, tr, tc, thr_f, bound, lw))) {
+        double2 X[G];
+        double S0, Sr[kMaxND], Si[kMaxND], lnw;
+        pc.unscale(rowd, cold, tr, tc, X, S0, Sr, Si, lnw);
+        EvAcc ev;
+        ev.init();
+        LsePh lse;
+        lse.init();
+        double best = -INFINITY, mlmax = 0.0;
+        int ob = 0;
+        pair_phases<kEvidence, G, true>(a, lds_cs, dp, row0 + tr, col0 + tc, X, S0, Sr, Si, lnw,
+                                        thr_ml, 0, 1, ev, lse, best, ob, mlmax);
+        if (lse.m != -INFINITY) lnp = lnw + (lse.m + log(lse.s) - a.ln_nphi);
       }
     }
-    __syncthreads();   // the tile's scalars and pair values are reused
+    a.sample_lnp[item * NPT + p] = lnp;
+  }
+}
+
+// Running sums of each listed tile's pair weights e^(ln p - m) in index
+// order (m: the tile's largest ln p in the evidence pass), for the draws to
+// search: chunks of 64 by lane scans, then the chunks' totals in order.
+template <int NPT>
+__global__ __launch_bounds__(256) void k_sample_cum(FusedArgs a) {
+  constexpr int NC = NPT / 64, PER = NC / 4;
+  __shared__ double tot[NC];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t item = blockIdx.x;
+  const double pm = a.partials[a.work_list[a.work0 + item] * kNPart];
+  const double* v = a.sample_lnp + item * NPT;
+  double pre[PER];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int c = wave * PER + q;
+    const double x = v[c * 64 + lane];
+    pre[q] = x == -INFINITY ? 0.0 : exp(x - pm);
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const double y = __shfl_up(pre[q], off, 64);
+      if (lane >= off) pre[q] += y;
+    }
+    if (lane == 63) tot[c] = pre[q];
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double run = 0.0;
+    for (int c = 0; c < NC; ++c) {
+      const double x = tot[c];
+      tot[c] = run;
+      run += x;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int c = wave * PER + q;
+    a.sample_cum[item * NPT + c * 64 + lane] = tot[c] + pre[q];
+  }
+}
+
+// The draws, a wave per draw: the pair by the running sums of its tile, the
+// phase by those of the pair's Lbar_ieo, the distance from its posterior.
+template <int PREC, int G>
+__global__ __launch_bounds__(256) void k_sample_draws(FusedArgs a) {
+  typedef Tile<PREC> TL;
+  typedef typename std::conditional<PREC == kFP64, double, float>::type AT;
+  constexpr int NRT = (G == 1) ? 1 : kMaxNR;
+  constexpr int NCO = 2 * G + NRT;
+  constexpr int TM = TL::TM, TN = TL::TN, NPT = TM * TN;
+  __shared__ DistParams dp;
+  __shared__ double lds_cs[kMaxM * kMaxPhi * 2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int t = tid; t < kMaxM * a.n_phi * 2; t += 256) lds_cs[t] = a.phase_cs[t];
+  for (int t = tid; t < (int)(sizeof(DistParams) / 4); t += 256)
+    ((unsigned*)&dp)[t] = ((const unsigned*)a.dist.prm)[t];
+  __syncthreads();
+  const double thr_ml = cut_on(a) ? __longlong_as_double(a.state[3]) - a.cut_delta : -INFINITY;
+  const int64_t s = (int64_t)blockIdx.x * 4 + wave;
+  if (s >= a.n_samples) return;
+  const int64_t item = (int64_t)a.sample_item[s] - a.work0;
+  if (item < 0 || item >= a.coef_tiles) return;   // another chunk's
+  const int64_t t = a.work_list[a.work0 + item];
+  const int64_t row0 = t / a.n_tiles_n * TM, col0 = t % a.n_tiles_n * TN;
+  const double pm = a.partials[t * kNPart];
+  // the pair: the draw's residual mass within the tile against the running
+  // sums (the first that exceeds it; a pair with weight)
+  const double r = a.sample_res[s] * exp(a.final_out[9] - pm);
+  const double* cum = a.sample_cum + item * NPT;
+  const double* lnp = a.sample_lnp + item * NPT;
+  int lo = 0, hi = NPT;
+  while (lo < hi) {
+    const int mid = (lo + hi) / 2;
+    if (cum[mid] > r) hi = mid;
+    else lo = mid + 1;
+  }
+  int sel = lo;
+  while (sel < NPT && lnp[sel] == -INFINITY) ++sel;
+  if (sel == NPT) {                // rounding past the tile's total: its last pair
+    for (sel = NPT - 1; sel >= 0 && lnp[sel] == -INFINITY;) --sel;
+    if (sel < 0) return;           // (a tile with mass always has a pair)
+  }
+  const int tr = sel / TN, tc = sel % TN;
+  const int64_t ie = row0 + tr, e = col0 + tc;
+  const int64_t i = a.sub_idx ? a.sub_idx[ie] : a.sub0 + ie;
+  const AT* cf = (const AT*)a.coef + item * (int64_t)(NCO * NPT);
+  PairCoef<AT, G, NRT> pc;
+  pc.template load<NPT>(cf, sel);
+  const double rowd[4] = {a.ln_w_bank ? a.ln_w_bank[i] : 0.0, PREC == kFP64 ? 1.0 : a.row_scale[i],
+                          PREC == kFP64 ? 1.0 : a.ah_scale[ie], (double)i};
+  const double cold[3] = {a.ln_w_ext ? a.ln_w_ext[e] : 0.0, PREC == kFP64 ? 1.0 : a.col_scale[e],
+                          PREC == kFP64 ? 1.0 : a.bh_scale[e]};
+  double2 X[G];
+  double S0, Sr[kMaxND], Si[kMaxND], lnw;
+  pc.unscale(rowd, cold, 0, 0, X, S0, Sr, Si, lnw);
+  // the phase: probability Lbar_ieo over the phases kept by the cut
+  double v_o[2], dh_o[2], hh_o[2];
+  for (int h = 0; h < 2; ++h) {
+    const int o = lane + 64 * h;
+    v_o[h] = -INFINITY;
+    dh_o[h] = 0.0;
+    hh_o[h] = 0.0;
+    if (o < a.n_phi) {
+      phase_dh_hh<G>(a, lds_cs, X, S0, Sr, Si, o, dh_o[h], hh_o[h]);
+      const bool keep = thr_ml <= 0.0 || (dh_o[h] > 0.0 && dh_o[h] * dh_o[h] >= 2.0 * thr_ml * hh_o[h]);
+      if (keep) v_o[h] = dr_ln_marg(dh_o[h], hh_o[h], a.r0, a.dist.tab, dp.ghx, dp.ghw);
+    }
+  }
+  const double vmax = wave_max(fmax(v_o[0], v_o[1]));
+  const double w0 = v_o[0] == -INFINITY ? 0.0 : exp(v_o[0] - vmax);
+  const double w1 = v_o[1] == -INFINITY ? 0.0 : exp(v_o[1] - vmax);
+  double pre0 = w0, pre1 = w1;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const double y0 = __shfl_up(pre0, off, 64), y1 = __shfl_up(pre1, off, 64);
+    if (lane >= off) { pre0 += y0; pre1 += y1; }
+  }
+  const double tot0 = __shfl(pre0, 63, 64);
+  const double tot = tot0 + __shfl(pre1, 63, 64);
+  const double target = sm64_uniform(a.seed, 2 * (uint64_t)s) * tot;
+  const unsigned long long h0 = __ballot(w0 > 0.0 && pre0 > target);
+  const unsigned long long h1 = __ballot(w1 > 0.0 && tot0 + pre1 > target);
+  int osel;
+  if (h0) osel = __ffsll((long long)h0) - 1;
+  else if (h1) osel = 64 + __ffsll((long long)h1) - 1;
+  else {   // rounding past the total: the last kept phase
+    const unsigned long long k0 = __ballot(w0 > 0.0), k1 = __ballot(w1 > 0.0);
+    osel = k1 ? 64 + 63 - __clzll((long long)k1) : 63 - __clzll((long long)k0);
+  }
+  const int src = osel & 63, hs = osel >> 6;
+  const double dh = __shfl(hs ? dh_o[1] : dh_o[0], src, 64);
+  const double hh = __shfl(hs ? hh_o[1] : hh_o[0], src, 64);
+  const double v = __shfl(hs ? v_o[1] : v_o[0], src, 64);
+  const double D = draw_distance(dh, hh, a.r0, a.d0, sm64_uniform(a.seed, 2 * (uint64_t)s + 1), lane);
+  if (lane == 0) {
+    double* out = a.samples + 6 * s;
+    out[0] = rowd[3];
+    out[1] = (double)e;
+    out[2] = (double)osel;
+    out[3] = D;
+    out[4] = lnp[sel];
+    out[5] = lnw + v - a.ln_nphi;
   }
 }
 

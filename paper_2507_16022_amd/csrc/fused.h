@@ -100,11 +100,14 @@ struct FusedArgs {
   // largest ln p (partial [9]): the intrinsic and extrinsic marginals of
   // eqs. int_ess and ext_ess are their sums over tiles
   double* rowcol;
-  // posterior sampling: the tiles to evaluate again (ascending), and per
-  // tile the range of samples that fall in it
+  // posterior sampling: the tiles to evaluate again (ascending), and the
+  // draws that fall in them
   const int* work_list;
   int64_t n_work_list;
-  const int64_t* sample_first;   // [n_work_list + 1]
+  int64_t n_samples;
+  const int* sample_item;        // [n_samples] the draw's place in work_list
+  double* sample_lnp;            // [coef_tiles or fewer][TM * TN] ln p of the listed tiles' pairs
+  double* sample_cum;            // and the running sums of their weights in index order
   const double* sample_res;      // [n_samples] residual mass within the tile (relative to e^M)
   double* samples;               // [n_samples][6]: i, e, o, D, ln p_ie, ln p_ieo
   uint64_t seed;                 // counter-based uniforms for the phase and distance draws
@@ -157,7 +160,9 @@ __device__ __forceinline__ FusedArgs pack_args(const PackLaunch& p, int e, int q
   a.trip_out = nullptr;
   a.bound_out = nullptr;
   a.work_list = nullptr;
-  a.sample_first = nullptr;
+  a.sample_item = nullptr;
+  a.sample_lnp = nullptr;
+  a.sample_cum = nullptr;
   a.sample_res = nullptr;
   a.samples = nullptr;
   a.final_out = nullptr;

@@ -1111,20 +1111,32 @@ __global__ void k_place_draws(const double* __restrict__ cum, int64_t n_tiles, i
   res[s] = ts - (lo > 0 ? cum[lo - 1] : 0.0);
 }
 
-// the distinct tiles of the (ascending) draws and, per distinct tile, its
-// first draw; n_out[0] = number of distinct tiles (one thread, in order)
-__global__ void k_group_draws(const int* __restrict__ tile, int64_t n_s, int* __restrict__ list,
-                              int64_t* __restrict__ first, int64_t* __restrict__ n_out) {
-  if (threadIdx.x != 0) return;
-  int64_t u = 0;
-  for (int64_t s = 0; s < n_s; ++s)
-    if (s == 0 || tile[s] != tile[s - 1]) {
-      list[u] = tile[s];
-      first[u] = s;
-      ++u;
-    }
-  first[u] = n_s;
-  n_out[0] = u;
+// the distinct tiles of the (ascending) draws, and per draw its tile's place
+// among them; n_out[0] = number of distinct tiles.  One block: each thread
+// counts the distinct tiles that start in its range of draws, a scan of the
+// counts places them (one thread over all draws took 0.21 ms at 4096).
+__global__ __launch_bounds__(1024) void k_group_draws(const int* __restrict__ tile, int64_t n_s,
+                                                      int* __restrict__ list, int* __restrict__ item,
+                                                      int64_t* __restrict__ n_out) {
+  __shared__ int sh[1024];
+  const int t = threadIdx.x;
+  const int64_t per = (n_s + 1023) / 1024, lo = min(n_s, t * per), hi = min(n_s, lo + per);
+  int n = 0;
+  for (int64_t s = lo; s < hi; ++s) n += (s == 0 || tile[s] != tile[s - 1]) ? 1 : 0;
+  sh[t] = n;
+  __syncthreads();
+  for (int k = 1; k < 1024; k <<= 1) {
+    const int v = t >= k ? sh[t - k] : 0;
+    __syncthreads();
+    sh[t] += v;
+    __syncthreads();
+  }
+  int u = sh[t] - n;               // distinct tiles that start before this range
+  for (int64_t s = lo; s < hi; ++s) {
+    if (s == 0 || tile[s] != tile[s - 1]) list[u++] = tile[s];
+    item[s] = u - 1;
+  }
+  if (t == 1023) n_out[0] = sh[1023];
 }
 
 __global__ void k_fill_cand(double* __restrict__ c, int64_t from, int64_t to) {
