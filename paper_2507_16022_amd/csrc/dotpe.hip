@@ -53,6 +53,7 @@ int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 // kernel's fast epilogue (fewer would leave the device partly idle)
 constexpr int64_t kBoundMinTiles = 2048;
 constexpr int64_t kMargPer = 256;     // tiles summed by one thread of the marginal pass
+constexpr int kNormBlocks = 256;      // block sums of (d|d) over full-resolution data
 
 }  // namespace
 
@@ -1156,7 +1157,7 @@ int set_event_impl(dotpe_ctx* ctx, const dotpe_bank* bk, const dotpe_event_desc*
     // (d|d) as given (full resolution)
     e_dd = hipMemcpyAsync(ev->final_out + kNPart, &d->dd, 8, hipMemcpyHostToDevice, s);
   } else {
-    hipLaunchKernelGGL(k_data_norm, dim3(1), dim3(256), 0, s, nk * nb, (const double2*)st.d, st.w,
+    hipLaunchKernelGGL(k_data_norm, dim3(1), dim3(256), 0, s, (int64_t)nk * nb, (const double2*)st.d, st.w,
                        ev->final_out + kNPart);
   }
   e = hipGetLastError();
@@ -2363,7 +2364,7 @@ int dotpe_rb_weights(dotpe_ctx* ctx, const dotpe_rb_desc* d, double* w_dh, doubl
       (rc = dev_alloc(ctx, (void**)&idx, (size_t)nn * 8, &owned, &acct)) ||
       (rc = dev_alloc(ctx, (void**)&wdh, n_dh * 16, &owned, &acct)) ||
       (rc = dev_alloc(ctx, (void**)&whh, n_hh * 16, &owned, &acct)) ||
-      (rc = dev_alloc(ctx, (void**)&ddv, 8, &owned, &acct)))
+      (rc = dev_alloc(ctx, (void**)&ddv, (1 + kNormBlocks) * 8, &owned, &acct)))
     return release(rc);
   std::vector<double> t0h(nk, 0.0);
   if (d->t0) t0h.assign(d->t0, d->t0 + nk);
@@ -2379,9 +2380,13 @@ int dotpe_rb_weights(dotpe_ctx* ctx, const dotpe_rb_desc* d, double* w_dh, doubl
   H2D(idx, d->node_idx, (size_t)nn * 8);
   if (e == hipSuccess) {
     const int64_t n = (int64_t)(n_dh + n_hh);
-    hipLaunchKernelGGL(k_rb_weights, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, nk, nc, nf,
+    // four waves per block, a weight each
+    hipLaunchKernelGGL(k_rb_weights, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, nk, nc, nf,
                        nn, f, dv, w, h0, t0, idx, wdh, whh);
-    hipLaunchKernelGGL(k_data_norm, dim3(1), dim3(256), 0, s, (int)(nk * nf), dv, w, ddv);
+    const int64_t nbl = std::min<int64_t>(kNormBlocks, (nk * nf + 1023) / 1024);
+    hipLaunchKernelGGL(k_data_norm, dim3((unsigned)nbl), dim3(256), 0, s, (int64_t)nk * nf, dv, w,
+                       ddv + 1);
+    hipLaunchKernelGGL(k_sum_blocks, dim3(1), dim3(256), 0, s, ddv + 1, nbl, ddv);
     e = hipGetLastError();
   }
   if (e == hipSuccess && w_dh) e = hipMemcpyAsync(w_dh, wdh, n_dh * 16, hipMemcpyDeviceToHost, s);

@@ -3,7 +3,7 @@
 // finalisation and the top-k sort.  Included by the host runtime only.
 #pragma once
 
-#include "common.h"
+#include "fused.h"
 
 namespace dotpe {
 
@@ -348,19 +348,24 @@ __global__ void k_operand_norms(const void* __restrict__ P0, const void* __restr
 }
 
 // ---------------------------------------------------------------------------
-// relative-binning weights (App. A, eqs. dh_weights, hh_weights): a thread
-// per (k, c, b) of W^dh and per (k, c, c', b) of W^hh, each a sum over the
+// relative-binning weights (App. A, eqs. dh_weights, hh_weights): a wave
+// per (k, c, b) of W^dh and per (k, c, c', b) of W^hh, its lanes over the
 // full-resolution points of the hat function s_b's support (from the node
 // before to the node after).  Reference of detector k: h0_c(f) exp(-2 pi i
 // f t0_k), so W^dh carries exp(2 pi i (f - f_b) t0_k), reduced in cycles,
-// and W^hh none.
+// and W^hh none.  Bound by the latency of its loads (21 MB that the L2s
+// hold, ~0.5 GFLOP): with a thread per weight, 3 x 5 channels x 256 nodes
+// were 90 workgroups of serial sums over ~1000 points, 2.0 ms at 2^17
+// frequencies (the call, host transfers included, 4.25 ms); with a wave per
+// weight the call takes 1.88 ms, most of it the transfers.
 // ---------------------------------------------------------------------------
 __global__ void k_rb_weights(int n_det, int n_c, int64_t n_full, int n_nodes,
                              const double* __restrict__ f, const double2* __restrict__ d,
                              const double* __restrict__ w, const double2* __restrict__ h0,
                              const double* __restrict__ t0, const int64_t* __restrict__ node_idx,
                              double2* __restrict__ wdh, double2* __restrict__ whh) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int64_t idx = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int64_t n_dh = (int64_t)n_det * n_c * n_nodes;
   const int64_t n_hh = (int64_t)n_det * n_c * n_c * n_nodes;
   if (idx >= n_dh + n_hh) return;
@@ -381,7 +386,7 @@ __global__ void k_rb_weights(int n_det, int n_c, int64_t n_full, int n_nodes,
   const double fb = f[qb], flo = f[lo], fhi = f[hi];
   const double tk = t0 ? t0[k] : 0.0;
   double2 acc = make_double2(0.0, 0.0);
-  for (int64_t q = lo; q <= hi; ++q) {
+  for (int64_t q = lo + lane; q <= hi; q += 64) {
     const double fq = f[q];
     const double s = q < qb ? (fq - flo) / (fb - flo) : q > qb ? (fhi - fq) / (fhi - fb) : 1.0;
     const double ws = w[(int64_t)k * n_full + q] * s;
@@ -397,6 +402,10 @@ __global__ void k_rb_weights(int n_det, int n_c, int64_t n_full, int n_nodes,
     acc.x += ws * v.x;
     acc.y += ws * v.y;
   }
+  auto add = [](double x, double y) { return x + y; };
+  acc.x = wave_reduce(acc.x, 0.0, add);
+  acc.y = wave_reduce(acc.y, 0.0, add);
+  if (lane != 63) return;          // the lane with the sums
   // divide by conj(h0_c(f_b)), or by h0_c(f_b) conj(h0_c'(f_b))
   double2 den = cconj(h0[(int64_t)c * n_full + qb]);
   if (!is_dh) den = cmul(h0[(int64_t)c * n_full + qb], cconj(h0[(int64_t)c2 * n_full + qb]));
@@ -614,19 +623,22 @@ __global__ void k_prop_stats(const double* __restrict__ out, int64_t n_s,
   }
 }
 
-// (d|d)
-__global__ void k_data_norm(int n, const double2* __restrict__ d, const double* __restrict__ w,
+// (d|d): block sums over grid-strided entries (one block: the sum itself;
+// more, for full-resolution data, reduced by k_sum_blocks)
+__global__ void k_data_norm(int64_t n, const double2* __restrict__ d, const double* __restrict__ w,
                             double* __restrict__ out) {
   __shared__ double red[256];
   double s = 0.0;
-  for (int t = threadIdx.x; t < n; t += blockDim.x) s += w[t] * (d[t].x * d[t].x + d[t].y * d[t].y);
+  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n;
+       t += (int64_t)gridDim.x * blockDim.x)
+    s += w[t] * (d[t].x * d[t].x + d[t].y * d[t].y);
   red[threadIdx.x] = s;
   __syncthreads();
   for (int k = blockDim.x / 2; k > 0; k >>= 1) {
     if (threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[0] = red[0];
+  if (threadIdx.x == 0) out[blockIdx.x] = red[0];
 }
 
 // ---------------------------------------------------------------------------
