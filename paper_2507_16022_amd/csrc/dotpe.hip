@@ -1013,6 +1013,50 @@ uint64_t block_bytes(const std::vector<EvBuf>& v) {
   return round_up(off, kBlockAlign);
 }
 
+// The device buffers of one call in one allocation, released on every return:
+// host inputs first (copied to the device as one piece), then work buffers.
+struct Carve {
+  struct Piece {
+    void** p;
+    uint64_t off;
+  };
+  std::vector<Piece> pieces;
+  std::vector<unsigned char> host;
+  uint64_t off = 0;
+  dotpe_ctx* ctx = nullptr;
+  hipStream_t s = nullptr;
+  void* base = nullptr;
+  uint64_t held = 0;
+
+  template <class T>
+  void in(const T** p, const T* src, size_t n) {
+    add((void**)p, n * sizeof(T));
+    host.resize(off);
+    std::memcpy(host.data() + pieces.back().off, src, n * sizeof(T));
+  }
+  void add(void** p, size_t n) {
+    off = round_up(off, kBlockAlign);
+    pieces.push_back({p, off});
+    off += n;
+  }
+  int alloc(dotpe_ctx* c, hipStream_t st) {
+    int rc = dev_alloc(c, &base, off, nullptr, &held);
+    if (rc) return rc;
+    ctx = c;
+    s = st;
+    for (Piece& x : pieces) *x.p = (char*)base + x.off;
+    if (host.empty()) return DOTPE_OK;
+    HIP_OK(hipMemcpyAsync(base, host.data(), host.size(), hipMemcpyHostToDevice, s));
+    return DOTPE_OK;
+  }
+  ~Carve() {
+    if (!base) return;
+    (void)hipStreamSynchronize(s);
+    (void)hipFree(base);
+    ctx->bytes -= held;
+  }
+};
+
 // Stage one event.  With block == nullptr every buffer is its own device
 // allocation (staging buffers are freed before returning); otherwise all of
 // them are packed into the caller's device block of block_len bytes and
@@ -2191,53 +2235,44 @@ int dotpe_extrinsic_samples(dotpe_ctx* ctx, const dotpe_bank* bk, const dotpe_ex
   a.dt = d->dt;
   a.K2p = 2 * (int64_t)bk->n_bp;
   a.delta = 20.0;
-  const int64_t n_grid = (int64_t)nk * d->n_t;
-  std::vector<void*> bufs;
-  uint64_t held = 0;
-  struct Release {
-    dotpe_ctx* ctx;
-    std::vector<void*>* bufs;
-    uint64_t* held;
-    hipStream_t s;
-    ~Release() {
-      (void)hipStreamSynchronize(s);
-      for (void* p : *bufs) (void)hipFree(p);
-      ctx->bytes -= *held;
-    }
-  } release{ctx, &bufs, &held, s};
-  int rc;
-  auto alloc = [&](void** p, size_t n) { return dev_alloc(ctx, p, n, &bufs, &held); };
-  void *dd = nullptr, *ww = nullptr, *tt = nullptr, *ci = nullptr, *st = nullptr;
-  double *ml = nullptr, *rmax = nullptr, *tab = nullptr, *lnZ = nullptr, *mix = nullptr,
-         *blk = nullptr, *draws = nullptr, *stats = nullptr, *lse_part = nullptr;
-  unsigned long long* n_supp = nullptr;
-  const int64_t nblk = scan_tmp_size(CSJ);
-  if ((rc = alloc(&dd, (size_t)nk * nb * 16)) || (rc = alloc(&ww, (size_t)nk * nb * 8)) ||
-      (rc = alloc(&tt, (size_t)nk * 8)) || (rc = alloc(&ci, (size_t)C * 8)) ||
-      (rc = alloc((void**)&a.B0, (size_t)n_grid * a.K2p * 2)) ||
-      (rc = alloc((void**)&a.B1, (size_t)n_grid * a.K2p * 2)) ||
-      (rc = alloc((void**)&a.col_scale, (size_t)n_grid * 8)) ||
-      (rc = alloc((void**)&a.gram, (size_t)nk * pre_pairs(mt.n_c) * 16)) ||
-      (rc = alloc((void**)&a.ml_det, (size_t)nk * 8)) || (rc = alloc((void**)&a.lnl, 8)) ||
-      (rc = alloc(&st, 64)) || (rc = alloc((void**)&a.counts, 4)) ||
-      (rc = alloc((void**)&a.offsets, 8)) || (rc = alloc((void**)&a.selected, 8)) ||
-      (rc = alloc((void**)&ml, (size_t)C * n_grid * 8)) ||
-      (rc = alloc((void**)&rmax, (size_t)C * nk * 8)) ||
-      (rc = alloc((void**)&tab, (size_t)CSJ * 8)) || (rc = alloc((void**)&lnZ, (size_t)C * 8)) ||
-      (rc = alloc((void**)&mix, (size_t)SJ * 8)) || (rc = alloc((void**)&blk, (size_t)nblk * 8)) ||
-      (rc = alloc((void**)&draws, (size_t)d->n_samples * 7 * 8)) ||
-      (rc = alloc((void**)&stats, 16)) ||
-      (rc = alloc((void**)&lse_part, (size_t)C * kPropParts * 16)) ||
-      (rc = alloc((void**)&n_supp, 8)))
-    return rc;
+  const int64_t n_grid = (int64_t)nk * d->n_t, ns = d->n_samples;
+  a.n_rows = C;
+  // one device block for the call: the host inputs (copied as one piece),
+  // then the series' and the proposals' buffers
+  Carve m;
+  const double *dd, *ww, *tt, *ci;
+  const int64_t* rw;
+  double *ml, *rmax, *tau, *lnZ, *mass, *blk, *draws, *stats, *lse_part;
+  int* supp;
+  const int64_t nb_cells = (SJ + 255) / 256, nblk = scan_tmp_size(nb_cells * C);
+  m.in(&dd, d->d, (size_t)nk * nb * 2);
+  m.in(&ww, d->w, (size_t)nk * nb);
+  m.in(&tt, d->t0, (size_t)nk);
+  m.in(&ci, d->cos_iota, (size_t)C);
+  m.in(&rw, d->rows, (size_t)C);
+  m.add((void**)&a.B0, (size_t)n_grid * a.K2p * 2);
+  m.add((void**)&a.B1, (size_t)n_grid * a.K2p * 2);
+  m.add((void**)&a.col_scale, (size_t)n_grid * 8);
+  m.add((void**)&a.gram, (size_t)C * nk * pre_pairs(mt.n_c) * 16);
+  m.add((void**)&a.ml_det, (size_t)C * nk * 8);
+  m.add((void**)&ml, (size_t)C * n_grid * 8);
+  m.add((void**)&rmax, (size_t)C * nk * 8);
+  m.add((void**)&tau, (size_t)d->n_sky * nk * 8);
+  m.add((void**)&lnZ, (size_t)C * 8);
+  m.add((void**)&mass, (size_t)C * nb_cells * 8);
+  m.add((void**)&blk, (size_t)nblk * 8);
+  m.add((void**)&supp, (size_t)nb_cells * 4);
+  m.add((void**)&lse_part, (size_t)C * kPropParts * 16);
+  m.add((void**)&draws, (size_t)ns * 6 * 8);      // (the results: copied back as one piece)
+  m.add((void**)&stats, 16);
+  int rc = m.alloc(ctx, s);
+  if (rc) return rc;
   a.d = (const double2*)dd;
-  a.w = (const double*)ww;
-  a.t0 = (const double*)tt;
-  a.state = (uint64_t*)st;
-  HIP_OK(hipMemcpyAsync(dd, d->d, (size_t)nk * nb * 16, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(ww, d->w, (size_t)nk * nb * 8, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(tt, d->t0, (size_t)nk * 8, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(ci, d->cos_iota, (size_t)C * 8, hipMemcpyHostToDevice, s));
+  a.w = ww;
+  a.t0 = tt;
+  a.cos_iota = ci;
+  a.rows = rw;
+  a.ml_t = ml;
   hipEvent_t e0, e1;
   HIP_OK(hipEventCreate(&e0));
   HIP_OK(hipEventCreate(&e1));
@@ -2249,15 +2284,8 @@ int dotpe_extrinsic_samples(dotpe_ctx* ctx, const dotpe_bank* bk, const dotpe_ex
     }
   } evs{e0, e1};
   HIP_OK(hipEventRecord(e0, s));
-  const uint64_t st0[2] = {0x000fffffffffffffull, 0ull};
-  for (int c = 0; c < C; ++c) {
-    HIP_OK(hipMemcpyAsync(st, st0, sizeof(st0), hipMemcpyHostToDevice, s));
-    a.row0 = d->rows[c];
-    a.cos_iota = (const double*)ci + c;
-    a.ml_t = ml + (size_t)c * n_grid;
-    hipError_t e = preselect_launch(bk->prec, a, s);
-    if (e != hipSuccess) return fail(DOTPE_E_DEVICE, "arrival-time series: %s", hipGetErrorString(e));
-  }
+  hipError_t e = preselect_series_launch(bk->prec, a, s);
+  if (e != hipSuccess) return fail(DOTPE_E_DEVICE, "arrival-time series: %s", hipGetErrorString(e));
   // the proposals over (sky, geocentre-time) cells, their mixture, the draws
   PropGeom g;
   std::memset(&g, 0, sizeof(g));
@@ -2274,33 +2302,27 @@ int dotpe_extrinsic_samples(dotpe_ctx* ctx, const dotpe_bank* bk, const dotpe_ex
   g.tg_lo = d->tg_lo;
   g.dtg = (d->tg_hi - d->tg_lo) / d->n_tg;
   g.beta = d->beta > 0.0 ? d->beta : 0.5;
-  hipLaunchKernelGGL(k_prop_max, dim3((unsigned)((C * nk + 63) / 64)), dim3(64), 0, s, ml, g, rmax);
-  hipLaunchKernelGGL(k_prop_table, dim3((unsigned)((CSJ + 255) / 256)), dim3(256), 0, s, ml, rmax, g,
-                     tab);
-  hipLaunchKernelGGL(k_prop_lse_part, dim3((unsigned)kPropParts, (unsigned)C), dim3(256), 0, s, tab,
-                     g, lse_part);
-  hipLaunchKernelGGL(k_prop_lse, dim3((unsigned)C), dim3(256), 0, s, (const double*)lse_part, lnZ);
-  hipLaunchKernelGGL(k_prop_prob, dim3((unsigned)((SJ + 255) / 256)), dim3(256), 0, s, tab, lnZ, g,
-                     mix);
-  scan_inclusive(tab, CSJ, blk, s);
-  hipLaunchKernelGGL(k_prop_draw, dim3((unsigned)((d->n_samples + 255) / 256)), dim3(256), 0, s,
-                     (const double*)tab, (const double*)mix, g, d->n_samples, d->seed, draws);
-  HIP_OK(hipMemsetAsync(n_supp, 0, 8, s));
-  hipLaunchKernelGGL(k_count_support, dim3((unsigned)((SJ + 255) / 256)), dim3(256), 0, s,
-                     (const double*)mix, SJ, n_supp);
-  hipLaunchKernelGGL(k_prop_stats, dim3(1), dim3(256), 0, s, (const double*)draws, d->n_samples,
-                     (const unsigned long long*)n_supp, SJ, stats);
+  const dim3 b256(256);
+  hipLaunchKernelGGL(k_prop_max, dim3((unsigned)((C * nk + 3) / 4)), b256, 0, s, ml, g, rmax);
+  hipLaunchKernelGGL(k_prop_sky, dim3((unsigned)((d->n_sky + 255) / 256)), b256, 0, s, g, tau);
+  hipLaunchKernelGGL(k_prop_lse_part, dim3((unsigned)kPropParts, (unsigned)C), b256, 0, s, ml, rmax,
+                     tau, g, lse_part);
+  hipLaunchKernelGGL(k_prop_lse, dim3((unsigned)C), b256, 0, s, (const double*)lse_part, lnZ);
+  hipLaunchKernelGGL(k_prop_mass, dim3((unsigned)nb_cells), b256, 0, s, ml, rmax, tau, lnZ, g, mass,
+                     supp);
+  scan_inclusive(mass, nb_cells * C, blk, s);
+  hipLaunchKernelGGL(k_prop_draw, dim3((unsigned)((ns + 3) / 4)), b256, 0, s, ml, rmax, tau, lnZ,
+                     (const double*)mass, nb_cells, g, ns, d->seed, draws);
+  hipLaunchKernelGGL(k_prop_stats, dim3(1), dim3(1024), 0, s, (const double*)draws + 5 * ns, ns, supp,
+                     nb_cells, SJ, stats);
   HIP_OK(hipGetLastError());
   HIP_OK(hipEventRecord(e1, s));
-  std::vector<double> h((size_t)d->n_samples * 7);
   double sth[2];
-  HIP_OK(hipMemcpyAsync(h.data(), draws, h.size() * 8, hipMemcpyDeviceToHost, s));
-  HIP_OK(hipMemcpyAsync(sth, stats, 16, hipMemcpyDeviceToHost, s));
-  HIP_OK(hipStreamSynchronize(s));
   double* outs[6] = {lat, lon, psi, cos_iota, t_geo, ln_w};
   for (int f = 0; f < 6; ++f)
-    if (outs[f])
-      for (int64_t q = 0; q < d->n_samples; ++q) outs[f][q] = h[(size_t)q * 7 + f];
+    if (outs[f]) HIP_OK(hipMemcpyAsync(outs[f], draws + f * ns, (size_t)ns * 8, hipMemcpyDeviceToHost, s));
+  HIP_OK(hipMemcpyAsync(sth, stats, 16, hipMemcpyDeviceToHost, s));
+  HIP_OK(hipStreamSynchronize(s));
   float ms = 0.f;
   HIP_OK(hipEventElapsedTime(&ms, e0, e1));
   dotpe_extrinsic_result r;

@@ -433,40 +433,60 @@ __device__ __forceinline__ void fib_sky(int s, int S, double* lat, double* lon) 
   *lon = fmod((double)s * ga, 2.0 * M_PI);
 }
 
-// rmax[c][k] = max_j of the per-time maxima ml[c][k][j]
+// rmax[c][k] = max_j of the per-time maxima ml[c][k][j], a wave each
 __global__ void k_prop_max(const double* __restrict__ ml, PropGeom g, double* __restrict__ rmax) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  const int t = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (t >= g.C * g.K) return;
   double m = -INFINITY;
-  for (int j = 0; j < g.n_t; ++j) m = fmax(m, ml[(int64_t)t * g.n_t + j]);
-  rmax[t] = m;
+  for (int j = lane; j < g.n_t; j += 64) m = fmax(m, ml[(int64_t)t * g.n_t + j]);
+  m = wave_max(m);
+  if (lane == 0) rmax[t] = m;
 }
 
-// ln W_c(s, j) = sum_k beta (rho^2_ck(t_i) - max rho^2_ck), i the grid point
-// nearest to t_j - r_k . n_s / c (-inf off the grid); rho^2 = 2 ml
-__global__ void k_prop_table(const double* __restrict__ ml, const double* __restrict__ rmax,
-                             PropGeom g, double* __restrict__ lnW) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t SJ = (int64_t)g.S * g.J;
-  if (idx >= (int64_t)g.C * SJ) return;
-  const int c = (int)(idx / SJ);
-  const int s = (int)((idx % SJ) / g.J), j = (int)(idx % g.J);
+// tau[s][k] = r_k . n_s / c of the sky lattice points
+__global__ void k_prop_sky(PropGeom g, double* __restrict__ tau) {
+  const int s = blockIdx.x * blockDim.x + threadIdx.x;
+  if (s >= g.S) return;
   double lat, lon;
   fib_sky(s, g.S, &lat, &lon);
   const double n0 = cos(lat) * cos(lon), n1 = cos(lat) * sin(lon), n2 = sin(lat);
+  for (int k = 0; k < g.K; ++k)
+    tau[s * g.K + k] = (g.r[k][0] * n0 + g.r[k][1] * n1 + g.r[k][2] * n2) / 299792458.0;
+}
+
+// The proposals are formed where they are used, from the detectors' series
+// (a few KB per component, in the caches), and never stored: a table of
+// C x S x J doubles (0.5 GB at 16 x 16384 x 256) written, normalised, summed
+// and scanned in place took 2.7 ms of memory passes and per-cell sky
+// arithmetic, and 0.6 GB of buffers.
+
+// Cell (s, j): per detector the place in its series of the grid point nearest
+// to t_j - r_k . n_s / c; false when one lies off its grid (W = 0 for every
+// component)
+__device__ __forceinline__ bool prop_cell(const PropGeom& g, const double* tau, unsigned s,
+                                          unsigned j, int (&x)[kMaxDet]) {
   const double tj = g.tg_lo + (j + 0.5) * g.dtg;
+  bool in = true;
+  for (int k = 0; k < g.K; ++k) {
+    const double y = rint(((tj - tau[s * g.K + k]) - g.t0[k]) / g.dt);
+    const bool ok = y >= 0.0 && y < g.n_t;
+    x[k] = ok ? (int)y : 0;
+    in = in && ok;
+  }
+  return in;
+}
+// ln W_c(s, j) = sum_k beta (rho^2_ck(x_k) - max rho^2_ck); rho^2 = 2 ml
+__device__ __forceinline__ double prop_lnw(const PropGeom& g, const double* ml, const double* rmax,
+                                           int c, const int (&x)[kMaxDet]) {
   double acc = 0.0;
   for (int k = 0; k < g.K; ++k) {
-    const double tk = tj - (g.r[k][0] * n0 + g.r[k][1] * n1 + g.r[k][2] * n2) / 299792458.0;
-    const double x = rint((tk - g.t0[k]) / g.dt);
-    if (!(x >= 0.0 && x < g.n_t)) {
-      acc = -INFINITY;
-      break;
-    }
-    const int64_t ck = (int64_t)c * g.K + k;
-    acc += g.beta * 2.0 * (ml[ck * g.n_t + (int)x] - rmax[ck]);
+    const int ck = c * g.K + k;
+    acc += g.beta * 2.0 * (ml[(int64_t)ck * g.n_t + x[k]] - rmax[ck]);
   }
-  lnW[idx] = acc;
+  return acc;
+}
+__device__ __forceinline__ double prop_p(double lnw, double lnz) {
+  return (lnw == -INFINITY || lnz == -INFINITY) ? 0.0 : exp(lnw - lnz);
 }
 
 // ln Z_c = LSE over the cells of ln W_c, in two steps: blocks (part, c) each
@@ -485,7 +505,7 @@ __device__ __forceinline__ void lse_merge(double& m, double& s, double m2, doubl
   }
 }
 
-// (m, s) of the 256 threads' (m, s) in LDS, tree order; thread 0 gets them
+// (m, s) of the 256 threads' (m, s) in LDS, tree order; every thread gets them
 __device__ __forceinline__ void lse_block_256(double* sm, double* ss, double& m, double& s) {
   sm[threadIdx.x] = m;
   ss[threadIdx.x] = s;
@@ -503,15 +523,20 @@ __device__ __forceinline__ void lse_block_256(double* sm, double* ss, double& m,
   s = ss[0];
 }
 
-__global__ __launch_bounds__(256) void k_prop_lse_part(const double* __restrict__ lnW, PropGeom g,
+__global__ __launch_bounds__(256) void k_prop_lse_part(const double* __restrict__ ml,
+                                                        const double* __restrict__ rmax,
+                                                        const double* __restrict__ tau, PropGeom g,
                                                         double* __restrict__ part) {
   __shared__ double sm[256], ss[256];
   const int c = blockIdx.y, p = blockIdx.x;
-  const int64_t SJ = (int64_t)g.S * g.J, per = (SJ + kPropParts - 1) / kPropParts;
-  const int64_t lo = p * per, hi = min(SJ, lo + per);
-  const double* x = lnW + (int64_t)c * SJ;
+  const unsigned SJ = (unsigned)g.S * g.J, per = (SJ + kPropParts - 1) / kPropParts;
+  const unsigned lo = p * per, hi = min(SJ, lo + per);
   double m = -INFINITY, s = 0.0;
-  for (int64_t t = lo + threadIdx.x; t < hi; t += 256) lse_merge(m, s, x[t], 1.0);
+  for (unsigned t = lo + threadIdx.x; t < hi; t += 256) {
+    int x[kMaxDet];
+    if (!prop_cell(g, tau, t / g.J, t % g.J, x)) continue;
+    lse_merge(m, s, prop_lnw(g, ml, rmax, c, x), 1.0);
+  }
   lse_block_256(sm, ss, m, s);
   if (threadIdx.x == 0) {
     part[2 * ((int64_t)c * kPropParts + p)] = m;
@@ -530,96 +555,157 @@ __global__ __launch_bounds__(256) void k_prop_lse(const double* __restrict__ par
   if (threadIdx.x == 0) lnZ[c] = m == -INFINITY ? -INFINITY : m + log(s);
 }
 
-// P_c(cell) = W_c / Z_c (in place over ln W), and the mixture (1/C) sum_c P_c
-__global__ void k_prop_prob(double* __restrict__ x, const double* __restrict__ lnZ, PropGeom g,
-                            double* __restrict__ mix) {
-  const int64_t cell = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t SJ = (int64_t)g.S * g.J;
-  if (cell >= SJ) return;
-  double m = 0.0;
+// Blocks of 256 cells: per component the block's mass sum_cell P_c (P_c =
+// W_c / Z_c) to mass[c][block], for the draws' search, and the block's cells
+// in the mixture's support (some P_c > 0).  The sky point and places of a
+// cell are formed once for all components.
+__global__ __launch_bounds__(256) void k_prop_mass(const double* __restrict__ ml,
+                                                    const double* __restrict__ rmax,
+                                                    const double* __restrict__ tau,
+                                                    const double* __restrict__ lnZ, PropGeom g,
+                                                    double* __restrict__ mass, int* __restrict__ supp) {
+  __shared__ double sh[4][64];
+  __shared__ int cnt[4];
+  const unsigned SJ = (unsigned)g.S * g.J, cell = blockIdx.x * 256u + threadIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int x[kMaxDet] = {};
+  const bool in = cell < SJ && prop_cell(g, tau, cell / g.J, cell % g.J, x);
+  bool any = false;
   for (int c = 0; c < g.C; ++c) {
-    const double v = x[(int64_t)c * SJ + cell];
-    const double p = (v == -INFINITY || lnZ[c] == -INFINITY) ? 0.0 : exp(v - lnZ[c]);
-    x[(int64_t)c * SJ + cell] = p;
-    m += p;
+    const double p = in ? prop_p(prop_lnw(g, ml, rmax, c, x), lnZ[c]) : 0.0;
+    any = any || p > 0.0;
+    const double sum = wave_reduce(p, 0.0, [](double u, double v) { return u + v; });
+    if (lane == 63) sh[wave][c] = sum;
   }
-  mix[cell] = m / g.C;
+  const unsigned long long b = __ballot(any);
+  if (lane == 0) cnt[wave] = (int)__popcll(b);
+  __syncthreads();
+  if ((int)threadIdx.x < g.C) {
+    const int c = threadIdx.x;
+    mass[(int64_t)c * gridDim.x + blockIdx.x] = ((sh[0][c] + sh[1][c]) + sh[2][c]) + sh[3][c];
+  }
+  if (threadIdx.x == 0) supp[blockIdx.x] = cnt[0] + cnt[1] + cnt[2] + cnt[3];
 }
 
-// draws: q from component q mod C, its cell the first whose running sum
-// (cum: inclusive running sums over the components back to back) exceeds
-// u times the component's total
-__global__ void k_prop_draw(const double* __restrict__ cum, const double* __restrict__ mix,
-                            PropGeom g, int64_t n_s, uint64_t seed, double* __restrict__ out) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// draws, a wave each: q from component q mod C, its cell the first whose
+// running sum exceeds u times the component's total -- the block by bisection
+// over the blocks' running sums (cum: the components back to back, nb blocks
+// each), the cell by the block's own running sums, four cells per lane.
+// out: six arrays of n_s (lat, lon, psi, cos iota, t_geo, ln w).
+__global__ __launch_bounds__(256) void k_prop_draw(const double* __restrict__ ml,
+                                                    const double* __restrict__ rmax,
+                                                    const double* __restrict__ tau,
+                                                    const double* __restrict__ lnZ,
+                                                    const double* __restrict__ cum, int64_t nb,
+                                                    PropGeom g, int64_t n_s, uint64_t seed,
+                                                    double* __restrict__ out) {
+  const int lane = threadIdx.x & 63;
+  const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (q >= n_s) return;
-  const int64_t SJ = (int64_t)g.S * g.J;
+  const unsigned SJ = (unsigned)g.S * g.J;
   const int c = (int)(q % g.C);
-  const int64_t lo0 = (int64_t)c * SJ;
-  const double base = c > 0 ? cum[lo0 - 1] : 0.0;
-  const double tot = cum[lo0 + SJ - 1] - base;
+  const double* cc = cum + c * nb;
+  const double base = c > 0 ? cc[-1] : 0.0;
+  const double tot = cc[nb - 1] - base;
   const double target = sm64_uniform(seed, 4 * (uint64_t)q) * tot;
-  int64_t lo = 0, hi = SJ - 1;          // first x with cum[lo0 + x] - base > target (the last if none)
+  int64_t lo = 0, hi = nb - 1;          // first block with running sum > target (the last if none)
   while (lo < hi) {
     const int64_t mid = (lo + hi) / 2;
-    if (cum[lo0 + mid] - base > target) hi = mid;
+    if (cc[mid] - base > target) hi = mid;
     else lo = mid + 1;
   }
-  const int s = (int)(lo / g.J), j = (int)(lo % g.J);
+  const double left = target - (lo > 0 ? cc[lo - 1] - base : 0.0);
+  const unsigned c0 = (unsigned)lo * 256u + 4u * lane;
+  double p[4], part = 0.0;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    int x[kMaxDet] = {};
+    const unsigned cell = c0 + u;
+    const bool in = cell < SJ && prop_cell(g, tau, cell / g.J, cell % g.J, x);
+    p[u] = in ? prop_p(prop_lnw(g, ml, rmax, c, x), lnZ[c]) : 0.0;
+    part += p[u];
+  }
+  double run = part;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const double v = __shfl_up(run, off, 64);
+    if (lane >= off) run += v;
+  }
+  run -= part;
+  // this lane's first cell past the target, and its last with mass
+  int first = -1, last = -1;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    run += p[u];
+    if (p[u] > 0.0) {
+      last = u;
+      if (first < 0 && run > left) first = u;
+    }
+  }
+  const unsigned long long hit = __ballot(first >= 0), live = __ballot(last >= 0);
+  unsigned cell = min((unsigned)lo * 256u + 255u, SJ - 1);
+  if (hit) {
+    const int src = __ffsll((long long)hit) - 1;
+    cell = (unsigned)lo * 256u + 4u * src + __shfl(first, src, 64);
+  } else if (live) {                    // rounding past the block's total: its last cell with mass
+    const int src = 63 - __clzll((long long)live);
+    cell = (unsigned)lo * 256u + 4u * src + __shfl(last, src, 64);
+  }
+  // the mixture at the drawn cell, a component per lane
+  int x[kMaxDet] = {};
+  const bool in = prop_cell(g, tau, cell / g.J, cell % g.J, x);
+  double m = (in && lane < g.C) ? prop_p(prop_lnw(g, ml, rmax, lane, x), lnZ[lane]) : 0.0;
+  m = wave_reduce(m, 0.0, [](double u, double v) { return u + v; });
+  if (lane != 63) return;
+  const unsigned s = cell / g.J, j = cell % g.J;
   double lat, lon;
-  fib_sky(s, g.S, &lat, &lon);
-  double* o = out + 7 * q;
-  o[0] = lat;
-  o[1] = lon;
-  o[2] = M_PI * sm64_uniform(seed, 4 * (uint64_t)q + 2);
-  o[3] = 2.0 * sm64_uniform(seed, 4 * (uint64_t)q + 3) - 1.0;
-  o[4] = g.tg_lo + (j + sm64_uniform(seed, 4 * (uint64_t)q + 1)) * g.dtg;
-  o[5] = -log((double)SJ) - log(mix[lo]);
-  o[6] = (double)lo;
-}
-
-// cells of the mixture's support (mix > 0), counted into *n (zeroed before)
-__global__ __launch_bounds__(256) void k_count_support(const double* __restrict__ mix, int64_t SJ,
-                                                       unsigned long long* __restrict__ n) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const unsigned long long v = __ballot(t < SJ && mix[t] > 0.0);
-  if ((threadIdx.x & 63) == 0 && v) atomicAdd(n, (unsigned long long)__popcll(v));
+  fib_sky((int)s, g.S, &lat, &lon);
+  out[q] = lat;
+  out[n_s + q] = lon;
+  out[2 * n_s + q] = M_PI * sm64_uniform(seed, 4 * (uint64_t)q + 2);
+  out[3 * n_s + q] = 2.0 * sm64_uniform(seed, 4 * (uint64_t)q + 3) - 1.0;
+  out[4 * n_s + q] = g.tg_lo + (j + sm64_uniform(seed, 4 * (uint64_t)q + 1)) * g.dtg;
+  out[5 * n_s + q] = -log((double)SJ) - log(m / g.C);
 }
 
 // N_eff over the draws' weights and the prior mass of the mixture's support:
-// one block; st[0] = (sum w)^2 / sum w^2, st[1] = support (from the count)
-__global__ void k_prop_stats(const double* __restrict__ out, int64_t n_s,
-                             const unsigned long long* __restrict__ n_support, int64_t SJ,
-                             double* __restrict__ st) {
-  __shared__ double a[256], b[256], m[256];
+// one block; st[0] = (sum w)^2 / sum w^2, st[1] = support (from the blocks'
+// counts)
+__global__ __launch_bounds__(1024) void k_prop_stats(const double* __restrict__ ln_w, int64_t n_s,
+                                                      const int* __restrict__ supp, int64_t nb,
+                                                      int64_t SJ, double* __restrict__ st) {
+  __shared__ double a[1024], b[1024];
+  const int t = threadIdx.x;
+  auto tree = [&](double* v, auto op) {
+    __syncthreads();
+    for (int k = 512; k > 0; k >>= 1) {
+      if (t < k) v[t] = op(v[t], v[t + k]);
+      __syncthreads();
+    }
+    return v[0];
+  };
+  auto add = [](double x, double y) { return x + y; };
   double mx = -INFINITY;
-  for (int64_t q = threadIdx.x; q < n_s; q += 256) mx = fmax(mx, out[7 * q + 5]);
-  m[threadIdx.x] = mx;
+  for (int64_t q = t; q < n_s; q += 1024) mx = fmax(mx, ln_w[q]);
+  a[t] = mx;
+  const double M = tree(a, [](double x, double y) { return fmax(x, y); });
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double M = -INFINITY;
-    for (int t = 0; t < 256; ++t) M = fmax(M, m[t]);
-    m[0] = M;
-  }
-  __syncthreads();
-  const double M = m[0];
-  double s1 = 0.0, s2 = 0.0;
-  for (int64_t q = threadIdx.x; q < n_s; q += 256) {
-    const double v = exp(out[7 * q + 5] - M);
+  double s1 = 0.0, s2 = 0.0, n = 0.0;
+  for (int64_t q = t; q < n_s; q += 1024) {
+    const double v = exp(ln_w[q] - M);
     s1 += v;
     s2 += v * v;
   }
-  a[threadIdx.x] = s1;
-  b[threadIdx.x] = s2;
+  for (int64_t q = t; q < nb; q += 1024) n += (double)supp[q];
+  a[t] = s1;
+  b[t] = s2;
+  const double A = tree(a, add), B = tree(b, add);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double A = 0.0, B = 0.0;
-    for (int t = 0; t < 256; ++t) {
-      A += a[t];
-      B += b[t];
-    }
+  a[t] = n;
+  const double N = tree(a, add);
+  if (t == 0) {
     st[0] = A * A / B;
-    st[1] = (double)*n_support / (double)SJ;
+    st[1] = N / (double)SJ;
   }
 }
 

@@ -42,6 +42,7 @@ struct PreArgs {
   int G;
   // rows: bank rows row0 .. row0 + n_rows - 1; this launch's block of them
   int64_t row0, n_rows, chunk0, n_chunk;
+  const int64_t* rows;       // the n_rows bank rows one by one instead (NULL: the range)
   const double* cos_iota;    // [n_rows]
   // data side
   int n_det, n_t, n_phi;
@@ -72,5 +73,10 @@ __host__ __device__ inline int pre_pairs(int n_c) { return n_c * (n_c + 1) / 2; 
 // rows the Gram matrices and the grid maximum, then the incoherent sums and
 // the selection.  prec: kFP16X2 or kBF16X2.  Returns the first launch error.
 hipError_t preselect_launch(int prec, PreArgs a, hipStream_t s);
+
+// The arrival-time series alone (ml_t) for the rows of the list a.rows (at
+// most kPreChunk): data operand, Gram matrices and grid maxima of all rows at
+// once, one launch each.
+hipError_t preselect_series_launch(int prec, PreArgs a, hipStream_t s);
 
 }  // namespace dotpe

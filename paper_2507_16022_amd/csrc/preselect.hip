@@ -38,6 +38,11 @@ __device__ __forceinline__ double load_split(const void* p0, const void* p1, int
   else return (double)(float)((const __bf16*)p0)[o] + (double)(float)((const __bf16*)p1)[o];
 }
 
+// bank row of entry q of the rows
+__device__ __forceinline__ int64_t pre_row(const PreArgs& a, int64_t q) {
+  return a.rows ? a.rows[q] : a.row0 + q;
+}
+
 // w_kb d_kb exp(2 pi i f_b t) with f_b t reduced to a fraction of a cycle in FP64
 __device__ __forceinline__ double2 pre_data(const PreArgs& a, int k, int b, double t) {
   const double x = a.f[b] * t;
@@ -95,7 +100,7 @@ __global__ __launch_bounds__(256) void k_pre_gram(PreArgs a) {
   const int lane = threadIdx.x & 63;
   const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (q >= a.n_chunk) return;
-  const int64_t i = a.row0 + a.chunk0 + q;
+  const int64_t i = pre_row(a, a.chunk0 + q);
   const double s2 = a.row_scale[i] * a.row_scale[i];
   auto add = [](double x, double y) { return x + y; };
   for (int k = 0; k < a.n_det; ++k) {
@@ -226,7 +231,7 @@ __global__ __launch_bounds__(64 * kPreMaxT / 32) void k_preselect(PreArgs a) {
 
   // ---- Y_ikc for this wave's 32 grid times, every channel ----
   const int h = lane >> 5;
-  const int64_t ia = a.row0 + min(rb0 + (lane & 31), a.n_rows - 1);   // (rows past the end re-read the last)
+  const int64_t ia = pre_row(a, min(rb0 + (lane & 31), a.n_rows - 1));   // (rows past the end re-read the last)
   const int64_t abase = ((ia >> 5) * (a.K2 >> 5)) * 1024 + h * 256 + (ia & 31) * 8;
   const int64_t rbB = (int64_t)k * a.n_t + 32 * wave + (lane & 31);
   const int64_t bbase = ((rbB >> 5) * (a.K2p >> 5)) * 1024 + h * 256 + (rbB & 31) * 8;
@@ -294,7 +299,7 @@ __global__ __launch_bounds__(64 * kPreMaxT / 32) void k_preselect(PreArgs a) {
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int rr = 8 * (r >> 2) + 4 * h + (r & 3);
-    const float sc = (float)((rr < rows_in ? a.row_scale[a.row0 + rb0 + rr] : 0.0) * csc);
+    const float sc = (float)((rr < rows_in ? a.row_scale[pre_row(a, rb0 + rr)] : 0.0) * csc);
     float wpr[NC], wpi[NC], wxr[NC], wxi[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -453,7 +458,24 @@ hipError_t run_all(PreArgs a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int PREC>
+hipError_t run_series(PreArgs a, hipStream_t s) {
+  if (a.n_rows > kPreChunk) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_pre_build_B<PREC>, dim3((unsigned)(a.n_det * a.n_t)), dim3(256), 0, s, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  a.chunk0 = 0;
+  a.n_chunk = a.n_rows;
+  return launch_pre_nc<PREC>(a, s);
+}
+
 }  // namespace
+
+hipError_t preselect_series_launch(int prec, PreArgs a, hipStream_t s) {
+  if (prec == kFP16X2) return run_series<kFP16X2>(a, s);
+  if (prec == kBF16X2) return run_series<kBF16X2>(a, s);
+  return hipErrorInvalidValue;
+}
 
 hipError_t preselect_launch(int prec, PreArgs a, hipStream_t s) {
   if (prec == kFP16X2) return run_all<kFP16X2>(a, s);
