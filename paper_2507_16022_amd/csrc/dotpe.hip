@@ -154,6 +154,7 @@ struct dotpe_event {
   float2* ah_nrm = nullptr;    //   and left-out parts (the bound pass's margin)
   float2* bh_nrm = nullptr;
   bool norms_done = false;     // b_nrm, ah_nrm, bh_nrm computed (before the first bound pass)
+  bool ah_norms_done = false;  // ah_nrm written with the row-side operand
   bool ctx_block = false;      // its buffers sit in the context's event block
   double2* Q = nullptr;
   double* R2 = nullptr;
@@ -419,8 +420,62 @@ void launch_convert_B(dotpe_event* ev, const double2* Btmp, int* err) {
                      ev->B[3], ev->col_scale, err);
 }
 
+// chunk ranges of the m groups of a (d|h) operand row
+NormRanges group_ranges(const ModeTables& mt) {
+  NormRanges r{};
+  r.n = mt.G;
+  for (int g = 0; g <= mt.G; ++g) r.c0[g] = mt.gk0[g];
+  return r;
+}
+
+// (h|h) phase-coefficient outputs the kernels use: S0, and Re, Im of
+// S_1..3 with more than one m group
+int hh_outputs(int G) { return G == 1 ? 1 : kMaxNR; }
+
+// chunk ranges of those outputs in a (h|h) operand row (one chunk each)
+NormRanges output_ranges(int G) {
+  NormRanges r{};
+  r.n = hh_outputs(G);
+  for (int q = 0; q <= r.n; ++q) r.c0[q] = q;
+  return r;
+}
+
+template <int PREC, int NC>
+void launch_hh_rows(dotpe_event* ev, const double* w) {
+  const dotpe_bank* bk = ev->bank;
+  const size_t sh = (size_t)16 * ev->n_det * bk->mt.NP * 16;
+  // (more than 64 KB with eight channels and many detectors)
+  static std::once_flag attr_once;
+  std::call_once(attr_once, [] {
+    if (hipFuncSetAttribute((const void*)k_hh_rows<PREC, NC>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            16 * kMaxDet * (NC * (NC + 1) / 2) * 16) != hipSuccess)
+      (void)hipGetLastError();
+  });
+  hipLaunchKernelGGL((k_hh_rows<PREC, NC>), dim3((unsigned)((ev->n_sub + 15) / 16)), dim3(256), sh, ev->stream,
+                     ev->n_sub, ev->sub_idx, ev->sub0, bk->R0, bk->R1, bk->K2, bk->row_scale, bk->n_bp,
+                     bk->n_b, ev->n_det, w, bk->mt, ev->hh_terms, ev->Ah[0], ev->Ah[1], ev->ah_scale,
+                     ev->ah_nrm, hh_outputs(bk->mt.G));
+  ev->ah_norms_done = true;
+}
+
+// the row-side (h|h) operand from Gram sums a wave per row (split precisions,
+// plain bins)
 template <int PREC>
-void launch_hh(dotpe_event* ev, const double* w, const double2* whh) {
+void launch_hh_rows(dotpe_event* ev, const double* w) {
+  switch (ev->bank->n_c) {
+    case 1: return launch_hh_rows<PREC, 1>(ev, w);
+    case 2: return launch_hh_rows<PREC, 2>(ev, w);
+    case 3: return launch_hh_rows<PREC, 3>(ev, w);
+    case 4: return launch_hh_rows<PREC, 4>(ev, w);
+    case 5: return launch_hh_rows<PREC, 5>(ev, w);
+    case 6: return launch_hh_rows<PREC, 6>(ev, w);
+    case 7: return launch_hh_rows<PREC, 7>(ev, w);
+    default: return launch_hh_rows<PREC, 8>(ev, w);
+  }
+}
+
+template <int PREC>
+void launch_hh_block(dotpe_event* ev, const double* w, const double2* whh) {
   const dotpe_bank* bk = ev->bank;
   // the row's amplitudes and the noise weights in LDS when they fit (the
   // kernel applies the same test)
@@ -443,36 +498,28 @@ void launch_hh(dotpe_event* ev, const double* w, const double2* whh) {
                      ev->n_sub, ev->sub_idx, ev->sub0, bk->A0, bk->A1, bk->row_scale, bk->n_bp,
                      bk->n_b, ev->n_det, w, whh, bk->mt, ev->hh_terms, ev->KH, ev->Ah[0],
                      ev->Ah[1], ev->ah_scale, bk->R0, bk->R1);
+}
+
+template <int PREC>
+void launch_hh(dotpe_event* ev, const double* w, const double2* whh) {
+  const dotpe_bank* bk = ev->bank;
+  if constexpr (PREC == kFP64) {
+    launch_hh_block<PREC>(ev, w, whh);
+  } else {
+    static_assert(kMaxC == 8, "launch_hh_rows");
+    if (whh) launch_hh_block<PREC>(ev, w, whh);
+    else launch_hh_rows<PREC>(ev, w);
+  }
   hipLaunchKernelGGL(k_build_Bhh<PREC>, dim3((unsigned)ev->n_ext_p), dim3(64), 0, ev->stream,
                      ev->n_ext, ev->n_ext_p, ev->n_det, ev->Q, bk->mt, ev->hh_terms, ev->KH,
                      ev->Bh[0], ev->Bh[1], ev->bh_scale);
-}
-
-// chunk ranges of the m groups of a (d|h) operand row
-NormRanges group_ranges(const ModeTables& mt) {
-  NormRanges r{};
-  r.n = mt.G;
-  for (int g = 0; g <= mt.G; ++g) r.c0[g] = mt.gk0[g];
-  return r;
-}
-
-// (h|h) phase-coefficient outputs the kernels use: S0, and Re, Im of
-// S_1..3 with more than one m group
-int hh_outputs(int G) { return G == 1 ? 1 : kMaxNR; }
-
-// chunk ranges of those outputs in a (h|h) operand row (one chunk each)
-NormRanges output_ranges(int G) {
-  NormRanges r{};
-  r.n = hh_outputs(G);
-  for (int q = 0; q <= r.n; ++q) r.c0[q] = q;
-  return r;
 }
 
 // per-row, per-range norms of a split operand (no-op for FP64)
 void launch_norms(int prec, const void* P0, const void* P1, int64_t n_rows, int64_t K,
                   const NormRanges& rg, float2* out, hipStream_t s) {
   if (prec == kFP64 || n_rows <= 0) return;
-  const dim3 g((unsigned)((n_rows + 255) / 256));
+  const dim3 g((unsigned)((n_rows + 31) / 32));
   if (prec == kFP16X2)
     hipLaunchKernelGGL(k_operand_norms<kFP16X2>, g, dim3(256), 0, s, P0, P1, n_rows, K, rg, out);
   else
@@ -486,7 +533,8 @@ void event_norms(dotpe_event* ev, hipStream_t s) {
   const dotpe_bank* bk = ev->bank;
   const ModeTables& mt = bk->mt;
   launch_norms(bk->prec, ev->B[0], ev->B[1], ev->n_ext_p, bk->K2, group_ranges(mt), ev->b_nrm, s);
-  launch_norms(bk->prec, ev->Ah[0], ev->Ah[1], ev->n_sub, ev->KH, output_ranges(mt.G), ev->ah_nrm, s);
+  if (!ev->ah_norms_done)
+    launch_norms(bk->prec, ev->Ah[0], ev->Ah[1], ev->n_sub, ev->KH, output_ranges(mt.G), ev->ah_nrm, s);
   launch_norms(bk->prec, ev->Bh[0], ev->Bh[1], ev->n_ext_p, ev->KH, output_ranges(mt.G), ev->bh_nrm,
                s);
   ev->norms_done = true;

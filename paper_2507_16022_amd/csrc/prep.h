@@ -3,7 +3,7 @@
 // finalisation and the top-k sort.  Included by the host runtime only.
 #pragma once
 
-#include "fused.h"
+#include "gram.h"
 
 namespace dotpe {
 
@@ -313,19 +313,24 @@ struct NormRanges {
 // product of the hi parts alone leaves out -- the lo parts, plus any hi part
 // below the format's normal range in case the matrix cores flush it -- each
 // rounded up to float: out[row * n + r] = (hi, left out).  The bound pass
-// builds its margin from them.  A thread per row: the lanes of a wave read
-// 16 contiguous bytes each, 512 contiguous bytes per 32-row block.
+// builds its margin from them.  A workgroup takes a block of 32 rows, its
+// eight half waves the chunks of a range in turn (32 lanes read 512
+// contiguous bytes per piece): a thread per row left a few dozen workgroups
+// with a serial loop over all chunks, ~90 us for the 4096 extrinsic rows of
+// an event.
 template <int PREC>
-__global__ void k_operand_norms(const void* __restrict__ P0, const void* __restrict__ P1,
-                                int64_t n_rows, int64_t K, NormRanges rg, float2* __restrict__ out) {
+__global__ __launch_bounds__(256) void k_operand_norms(const void* __restrict__ P0,
+                                                       const void* __restrict__ P1, int64_t n_rows,
+                                                       int64_t K, NormRanges rg, float2* __restrict__ out) {
   typedef typename std::conditional<PREC == kFP16X2, _Float16, __bf16>::type H;
-  const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (row >= n_rows) return;
-  const int64_t base = (row >> 5) * (K >> 5) * 1024 + (row & 31) * 8;
+  __shared__ double sh[2][8][32];
+  const int r32 = threadIdx.x & 31, sub = threadIdx.x >> 5;
+  const int64_t row = (int64_t)blockIdx.x * 32 + r32;
+  const int64_t base = (int64_t)blockIdx.x * (K >> 5) * 1024 + r32 * 8;
   const double tiny = PREC == kFP16X2 ? 0x1p-14 : 0x1p-126;
   for (int r = 0; r < rg.n; ++r) {
-    double sh = 0.0, sl = 0.0;
-    for (int64_t c = rg.c0[r]; c < rg.c0[r + 1]; ++c)
+    double s_hi = 0.0, s_lo = 0.0;
+    for (int64_t c = rg.c0[r] + sub; row < n_rows && c < rg.c0[r + 1]; c += 8)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {     // (slice, piece) of the chunk
         const int64_t o = base + c * 1024 + q * 256;
@@ -338,12 +343,22 @@ __global__ void k_operand_norms(const void* __restrict__ P0, const void* __restr
         for (int j = 0; j < 8; ++j) {
           const double h = (double)(float)xh[j], l = (double)(float)xl[j];
           const double t = fabs(h) < tiny ? l + h : l;
-          sh += h * h;
-          sl += t * t;
+          s_hi += h * h;
+          s_lo += t * t;
         }
       }
-    out[row * rg.n + r] = make_float2((float)(sqrt(sh) * (1.0 + 0x1p-20)),
-                                      (float)(sqrt(sl) * (1.0 + 0x1p-20)));
+    __syncthreads();                    // (the last range's sums have been read)
+    sh[0][sub][r32] = s_hi;
+    sh[1][sub][r32] = s_lo;
+    __syncthreads();
+    if (sub == 0 && row < n_rows) {
+      for (int k = 1; k < 8; ++k) {
+        s_hi += sh[0][k][r32];
+        s_lo += sh[1][k][r32];
+      }
+      out[row * rg.n + r] = make_float2((float)(sqrt(s_hi) * (1.0 + 0x1p-20)),
+                                        (float)(sqrt(s_lo) * (1.0 + 0x1p-20)));
+    }
   }
 }
 
@@ -740,7 +755,8 @@ __global__ void k_data_norm(int64_t n, const double2* __restrict__ d, const doub
 // member's (every member has the same F_kp F_kp').
 // ---------------------------------------------------------------------------
 
-__device__ __forceinline__ double term_value(int code, const double2* X, const ModeTables& mt,
+template <typename XT>      // XT: [k NP + p] -> the pair's (re, im)
+__device__ __forceinline__ double term_value(int code, const XT& X, const ModeTables& mt,
                                              bool row_side) {
   if (!(code & 0x8000)) return 0.0;
   const int NP = mt.NP;
@@ -774,8 +790,8 @@ __device__ __forceinline__ double2 to_d2(float2 v) { return make_double2(v.x, v.
 // binning: sum_b W_kcc'b h_icb conj(h_ic'b), whh [n_det][NP][n_b]) for the
 // event's bank subset, from the same operand values the contraction uses,
 // written as the row-side (h|h) operand (n_sub rows of KH, op_index layout)
-// with a power-of-two
-// row scale in the split precisions
+// with a power-of-two row scale in the split precisions: FP64 banks and
+// relative binning (plain bins of split banks: k_hh_rows)
 template <int PREC>
 __global__ void k_hh_precompute(int64_t n_sub, const int64_t* __restrict__ sub_idx, int64_t sub0,
                                 const void* __restrict__ A0, const void* __restrict__ A1,
@@ -926,6 +942,94 @@ __global__ void k_hh_precompute(int64_t n_sub, const int64_t* __restrict__ sub_i
   if (threadIdx.x == 0 && hscale) hscale[ie] = ldexp(1.0, ex);
   for (int j = threadIdx.x; j < KH; j += blockDim.x)
     store_split<PREC>(H0, H1, op_index<PREC>(ie, j, KH), ldexp(vals[j], -ex));
+}
+
+// The same operand rows for plain bins and split precisions, 16 lanes per row:
+// the Gram sums (gram.h), the (h|h) terms 16 positions per lane (KH = 256), the
+// row scale, the split parts, and the norms per output that the bound pass's
+// margin takes (nrm [n_sub][n_nrm], as k_operand_norms).  A workgroup per row
+// with a lane per (detector, channel pair) and a third of the lanes idle, the
+// row staged in LDS and five barriers took 9.8 ms at 2^20 rows, five channels,
+// three detectors; 4.4 ms now, against 2.5 ms to read the bank and write the
+// operand.
+template <int PREC, int NC>
+__global__ __launch_bounds__(256, 2) void k_hh_rows(int64_t n_sub, const int64_t* __restrict__ sub_idx,
+                                                    int64_t sub0, const void* __restrict__ R0,
+                                                    const void* __restrict__ R1, int64_t K2,
+                                                    const double* __restrict__ row_scale, int n_bp, int n_b,
+                                                    int n_det, const double* __restrict__ w, ModeTables mt,
+                                                    const int* __restrict__ terms, void* __restrict__ H0,
+                                                    void* __restrict__ H1, double* __restrict__ hscale,
+                                                    float2* __restrict__ nrm, int n_nrm) {
+  typedef typename std::conditional<PREC == kFP16X2, _Float16, __bf16>::type H;
+  constexpr int NP = NC * (NC + 1) / 2, KH = (kMaxNR + 1) * 32;
+  static_assert(KH == 256, "16 positions per lane");
+  extern __shared__ __align__(16) double hh_sums[];      // [16][n_det][NP] (re, im), row order of c <= c'
+  const int lane = threadIdx.x & 63, l16 = lane & 15;
+  const int64_t ie = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+  const bool live = ie < n_sub;
+  const int64_t i = sub_idx ? sub_idx[live ? ie : 0] : sub0 + (live ? ie : 0);
+  double* G = hh_sums + (size_t)(threadIdx.x >> 4) * n_det * NP * 2;
+  const double sc = row_scale[i];
+  gram_row_all<PREC, NC>((const uint16_t*)R0 + i * K2, (const uint16_t*)R1 + i * K2, n_b, n_bp, w, n_det,
+                         sc * sc, lane, G, live);
+  __syncthreads();
+  if (!live) return;
+  // the sums in the mode tables' pair order: term_value's X[k NP + p]
+  struct Sums {
+    const double* g;
+    const ModeTables& mt;
+    __device__ double2 operator[](int t) const {
+      const int k = t / NP, p = t % NP, c = mt.pc[p], c2 = mt.pc2[p];
+      const double* x = g + 2 * (k * NP + c * NC - c * (c - 1) / 2 + (c2 - c));
+      return make_double2(x[0], x[1]);
+    }
+  };
+  const Sums X{G, mt};
+  double v[16], mx = 0.0;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    v[q] = term_value(terms[16 * l16 + q], X, mt, true);
+    mx = fmax(mx, fabs(v[q]));
+  }
+  // over the 16 lanes of the row
+  mx = fmax(mx, dpp_mov<0xB1, 0xF>(0.0, mx));
+  mx = fmax(mx, dpp_mov<0x4E, 0xF>(0.0, mx));
+  mx = fmax(mx, dpp_mov<0x141, 0xF>(0.0, mx));
+  mx = fmax(mx, dpp_mov<0x140, 0xF>(0.0, mx));
+  int ex = 0;
+  if (mx > 0.0 && isfinite(mx)) ex = ilogb(mx) - 13;
+  if (l16 == 0) hscale[ie] = ldexp(1.0, ex);
+  struct alignas(16) H8 {
+    H x[8];
+  };
+  const double tiny = PREC == kFP16X2 ? 0x1p-14 : 0x1p-126;
+  double s_hi = 0.0, s_lo = 0.0;
+#pragma unroll
+  for (int piece = 0; piece < 2; ++piece) {
+    H8 hi, lo;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const double x = ldexp(v[8 * piece + q], -ex);
+      if (PREC == kFP16X2) hi.x[q] = (H)x;
+      else hi.x[q] = (H)(float)x;
+      const double xh = (double)(float)hi.x[q];
+      if (PREC == kFP16X2) lo.x[q] = (H)(x - xh);
+      else lo.x[q] = (H)(float)(x - xh);
+      const double xl = (double)(float)lo.x[q], t = fabs(xh) < tiny ? xl + xh : xl;
+      s_hi += xh * xh;
+      s_lo += t * t;
+    }
+    const int64_t o = op_index<PREC>(ie, 16 * l16 + 8 * piece, KH);
+    *(H8*)((H*)H0 + o) = hi;
+    *(H8*)((H*)H1 + o) = lo;
+  }
+  // output r: the 32 positions of lanes 2 r, 2 r + 1
+  s_hi += dpp_mov<0xB1, 0xF>(0.0, s_hi);
+  s_lo += dpp_mov<0xB1, 0xF>(0.0, s_lo);
+  if ((l16 & 1) == 0 && (l16 >> 1) < n_nrm)
+    nrm[ie * n_nrm + (l16 >> 1)] = make_float2((float)(sqrt(s_hi) * (1.0 + 0x1p-20)),
+                                               (float)(sqrt(s_lo) * (1.0 + 0x1p-20)));
 }
 
 // column-side (h|h) operand (n_ext_p rows of KH, op_index layout) from
