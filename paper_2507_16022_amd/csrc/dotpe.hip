@@ -1062,11 +1062,14 @@ uint64_t block_bytes(const std::vector<EvBuf>& v) {
 }
 
 // The device buffers of one call in one allocation, released on every return:
-// host inputs first (copied to the device as one piece), then work buffers.
+// host inputs first (small ones copied to the device as one piece, long ones
+// from where they are), then work buffers.
 struct Carve {
   struct Piece {
     void** p;
     uint64_t off;
+    const void* src;     // a long input
+    size_t n;
   };
   std::vector<Piece> pieces;
   std::vector<unsigned char> host;
@@ -1076,15 +1079,27 @@ struct Carve {
   void* base = nullptr;
   uint64_t held = 0;
 
+  // (the small inputs before the long ones and the work buffers)
   template <class T>
   void in(const T** p, const T* src, size_t n) {
-    add((void**)p, n * sizeof(T));
+    const size_t bytes = n * sizeof(T);
+    add((void**)p, bytes);
+    if (bytes > 65536) {
+      pieces.back().src = src;
+      pieces.back().n = bytes;
+      return;
+    }
     host.resize(off);
-    std::memcpy(host.data() + pieces.back().off, src, n * sizeof(T));
+    std::memcpy(host.data() + pieces.back().off, src, bytes);
+  }
+  void reset() {
+    pieces.clear();
+    host.clear();
+    off = 0;
   }
   void add(void** p, size_t n) {
     off = round_up(off, kBlockAlign);
-    pieces.push_back({p, off});
+    pieces.push_back({p, off, nullptr, 0});
     off += n;
   }
   int alloc(dotpe_ctx* c, hipStream_t st) {
@@ -1093,8 +1108,9 @@ struct Carve {
     ctx = c;
     s = st;
     for (Piece& x : pieces) *x.p = (char*)base + x.off;
-    if (host.empty()) return DOTPE_OK;
-    HIP_OK(hipMemcpyAsync(base, host.data(), host.size(), hipMemcpyHostToDevice, s));
+    if (!host.empty()) HIP_OK(hipMemcpyAsync(base, host.data(), host.size(), hipMemcpyHostToDevice, s));
+    for (Piece& x : pieces)
+      if (x.src) HIP_OK(hipMemcpyAsync((char*)base + x.off, x.src, x.n, hipMemcpyHostToDevice, s));
     return DOTPE_OK;
   }
   ~Carve() {
@@ -1980,47 +1996,39 @@ int dotpe_preselect(dotpe_ctx* ctx, const dotpe_bank* bk, const dotpe_preselect_
   a.delta = d->delta_lnl > 0.0 ? d->delta_lnl : 20.0;
   const int64_t n_grid = (int64_t)nk * d->n_t;
   const int64_t nblk = (n_rows + 1023) / 1024;
-  const int64_t n_chunk = std::min<int64_t>(n_rows, kPreChunk);
-  // the pass's buffers, freed on every return below
-  std::vector<void*> bufs;
-  uint64_t held = 0;
-  struct Release {
-    dotpe_ctx* ctx;
-    std::vector<void*>* bufs;
-    uint64_t* held;
-    hipStream_t s;
-    ~Release() {
-      (void)hipStreamSynchronize(s);
-      for (void* p : *bufs) (void)hipFree(p);
-      ctx->bytes -= *held;
-    }
-  } release{ctx, &bufs, &held, s};
-  int rc;
-  auto alloc = [&](void** p, size_t n) { return dev_alloc(ctx, p, n, &bufs, &held); };
-  void *dd = nullptr, *ww = nullptr, *tt = nullptr, *ci = nullptr, *st = nullptr;
-  if ((rc = alloc(&dd, (size_t)nk * nb * 16)) || (rc = alloc(&ww, (size_t)nk * nb * 8)) ||
-      (rc = alloc(&tt, (size_t)nk * 8)) || (rc = alloc(&ci, (size_t)n_rows * 8)) ||
-      (rc = alloc((void**)&a.B0, (size_t)n_grid * a.K2p * 2)) ||
-      (rc = alloc((void**)&a.B1, (size_t)n_grid * a.K2p * 2)) ||
-      (rc = alloc((void**)&a.col_scale, (size_t)n_grid * 8)) ||
-      (rc = alloc((void**)&a.gram, (size_t)n_chunk * nk * pre_pairs(mt.n_c) * 16)) ||
-      (rc = alloc((void**)&a.ml_det, (size_t)n_rows * nk * 8)) ||
-      (rc = alloc((void**)&a.lnl, (size_t)n_rows * 8)) || (rc = alloc(&st, 64)) ||
-      (rc = alloc((void**)&a.counts, (size_t)nblk * 4)) ||
-      (rc = alloc((void**)&a.offsets, (size_t)nblk * 8)) ||
-      (rc = alloc((void**)&a.selected, (size_t)n_rows * 8)))
-    return rc;
+  // one device block for the call: the host inputs (copied as one piece),
+  // then the pass's buffers; rows in blocks of kPreChunk, or fewer when the
+  // device (or the budget) does not hold their Gram matrices
+  Carve m;
+  const double *dd, *ww, *tt, *ci;
+  const uint64_t* st;
+  const uint64_t st0[8] = {0x000fffffffffffffull};   // below every ordered value; count 0
+  int rc = DOTPE_OK;
+  for (a.chunk_rows = std::min<int64_t>(n_rows, kPreChunk);; a.chunk_rows = (a.chunk_rows + 1) / 2) {
+    m.reset();
+    m.in(&dd, d->d, (size_t)nk * nb * 2);
+    m.in(&ww, d->w, (size_t)nk * nb);
+    m.in(&tt, d->t0, (size_t)nk);
+    m.in(&st, st0, 8);
+    m.in(&ci, d->cos_iota, (size_t)n_rows);
+    m.add((void**)&a.B0, (size_t)n_grid * a.K2p * 2);
+    m.add((void**)&a.B1, (size_t)n_grid * a.K2p * 2);
+    m.add((void**)&a.col_scale, (size_t)n_grid * 8);
+    m.add((void**)&a.gram, (size_t)a.chunk_rows * nk * pre_pairs(mt.n_c) * 16);
+    m.add((void**)&a.factors, (size_t)a.chunk_rows * mt.n_c * 16);
+    m.add((void**)&a.ml_det, (size_t)n_rows * nk * 8);
+    m.add((void**)&a.lnl, (size_t)n_rows * 8);
+    m.add((void**)&a.counts, (size_t)nblk * 4);
+    m.add((void**)&a.offsets, (size_t)nblk * 8);
+    m.add((void**)&a.selected, (size_t)n_rows * 8);
+    if ((rc = m.alloc(ctx, s)) == DOTPE_OK) break;
+    if (a.chunk_rows <= 32 || (rc != DOTPE_E_ADMISSION && rc != DOTPE_E_OOM)) return rc;
+  }
   a.d = (const double2*)dd;
-  a.w = (const double*)ww;
-  a.t0 = (const double*)tt;
-  a.cos_iota = (const double*)ci;
+  a.w = ww;
+  a.t0 = tt;
+  a.cos_iota = ci;
   a.state = (uint64_t*)st;
-  const uint64_t st0[2] = {0x000fffffffffffffull, 0ull};   // below every ordered value; count
-  HIP_OK(hipMemcpyAsync(dd, d->d, (size_t)nk * nb * 16, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(ww, d->w, (size_t)nk * nb * 8, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(tt, d->t0, (size_t)nk * 8, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(ci, d->cos_iota, (size_t)n_rows * 8, hipMemcpyHostToDevice, s));
-  HIP_OK(hipMemcpyAsync(st, st0, sizeof(st0), hipMemcpyHostToDevice, s));
   hipEvent_t e0, e1;
   HIP_OK(hipEventCreate(&e0));
   HIP_OK(hipEventCreate(&e1));
@@ -2301,7 +2309,9 @@ int dotpe_extrinsic_samples(dotpe_ctx* ctx, const dotpe_bank* bk, const dotpe_ex
   m.add((void**)&a.B0, (size_t)n_grid * a.K2p * 2);
   m.add((void**)&a.B1, (size_t)n_grid * a.K2p * 2);
   m.add((void**)&a.col_scale, (size_t)n_grid * 8);
+  a.chunk_rows = C;
   m.add((void**)&a.gram, (size_t)C * nk * pre_pairs(mt.n_c) * 16);
+  m.add((void**)&a.factors, (size_t)C * mt.n_c * 16);
   m.add((void**)&a.ml_det, (size_t)C * nk * 8);
   m.add((void**)&ml, (size_t)C * n_grid * 8);
   m.add((void**)&rmax, (size_t)C * nk * 8);
@@ -2353,7 +2363,8 @@ int dotpe_extrinsic_samples(dotpe_ctx* ctx, const dotpe_bank* bk, const dotpe_ex
   const dim3 b256(256);
   hipLaunchKernelGGL(k_prop_max, dim3((unsigned)((C * nk + 3) / 4)), b256, 0, s, ml, g, rmax);
   hipLaunchKernelGGL(k_prop_sky, dim3((unsigned)((d->n_sky + 255) / 256)), b256, 0, s, g, tau);
-  hipLaunchKernelGGL(k_prop_lse_part, dim3((unsigned)kPropParts, (unsigned)C), b256, 0, s, ml, rmax,
+  hipLaunchKernelGGL(k_prop_lse_part,
+                     dim3((unsigned)kPropParts, (unsigned)((C + kPropComps - 1) / kPropComps)), b256, 0, s, ml, rmax,
                      tau, g, lse_part);
   hipLaunchKernelGGL(k_prop_lse, dim3((unsigned)C), b256, 0, s, (const double*)lse_part, lnZ);
   hipLaunchKernelGGL(k_prop_mass, dim3((unsigned)nb_cells), b256, 0, s, ml, rmax, tau, lnZ, g, mass,

@@ -482,7 +482,9 @@ __device__ __forceinline__ bool prop_cell(const PropGeom& g, const double* tau, 
                                           unsigned j, int (&x)[kMaxDet]) {
   const double tj = g.tg_lo + (j + 0.5) * g.dtg;
   bool in = true;
-  for (int k = 0; k < g.K; ++k) {
+#pragma unroll
+  for (int k = 0; k < kMaxDet; ++k) {      // (unrolled: the places stay in registers)
+    if (k >= g.K) break;
     const double y = rint(((tj - tau[s * g.K + k]) - g.t0[k]) / g.dt);
     const bool ok = y >= 0.0 && y < g.n_t;
     x[k] = ok ? (int)y : 0;
@@ -494,7 +496,9 @@ __device__ __forceinline__ bool prop_cell(const PropGeom& g, const double* tau, 
 __device__ __forceinline__ double prop_lnw(const PropGeom& g, const double* ml, const double* rmax,
                                            int c, const int (&x)[kMaxDet]) {
   double acc = 0.0;
-  for (int k = 0; k < g.K; ++k) {
+#pragma unroll
+  for (int k = 0; k < kMaxDet; ++k) {
+    if (k >= g.K) break;
     const int ck = c * g.K + k;
     acc += g.beta * 2.0 * (ml[(int64_t)ck * g.n_t + x[k]] - rmax[ck]);
   }
@@ -504,11 +508,13 @@ __device__ __forceinline__ double prop_p(double lnw, double lnz) {
   return (lnw == -INFINITY || lnz == -INFINITY) ? 0.0 : exp(lnw - lnz);
 }
 
-// ln Z_c = LSE over the cells of ln W_c, in two steps: blocks (part, c) each
-// reduce one of kPropParts contiguous ranges of component c's cells to (max,
-// sum of exp(x - max)), lanes then threads in a fixed tree order; then a
-// block per c merges its parts the same way.
+// ln Z_c = LSE over the cells of ln W_c, in two steps: blocks (part, group of
+// kPropComps components) each reduce one of kPropParts contiguous ranges of
+// cells to (max, sum of exp(x - max)) per component -- the places of a cell
+// formed once for the group -- lanes then threads in a fixed tree order; then
+// a block per component merges its parts the same way.
 constexpr int kPropParts = 256;
+constexpr int kPropComps = 4;
 
 __device__ __forceinline__ void lse_merge(double& m, double& s, double m2, double s2) {
   if (m2 == -INFINITY) return;
@@ -543,19 +549,31 @@ __global__ __launch_bounds__(256) void k_prop_lse_part(const double* __restrict_
                                                         const double* __restrict__ tau, PropGeom g,
                                                         double* __restrict__ part) {
   __shared__ double sm[256], ss[256];
-  const int c = blockIdx.y, p = blockIdx.x;
+  const int c0 = blockIdx.y * kPropComps, p = blockIdx.x;
   const unsigned SJ = (unsigned)g.S * g.J, per = (SJ + kPropParts - 1) / kPropParts;
   const unsigned lo = p * per, hi = min(SJ, lo + per);
-  double m = -INFINITY, s = 0.0;
+  double m[kPropComps], s[kPropComps];
+#pragma unroll
+  for (int u = 0; u < kPropComps; ++u) {
+    m[u] = -INFINITY;
+    s[u] = 0.0;
+  }
   for (unsigned t = lo + threadIdx.x; t < hi; t += 256) {
     int x[kMaxDet];
     if (!prop_cell(g, tau, t / g.J, t % g.J, x)) continue;
-    lse_merge(m, s, prop_lnw(g, ml, rmax, c, x), 1.0);
+#pragma unroll
+    for (int u = 0; u < kPropComps; ++u)
+      if (c0 + u < g.C) lse_merge(m[u], s[u], prop_lnw(g, ml, rmax, c0 + u, x), 1.0);
   }
-  lse_block_256(sm, ss, m, s);
-  if (threadIdx.x == 0) {
-    part[2 * ((int64_t)c * kPropParts + p)] = m;
-    part[2 * ((int64_t)c * kPropParts + p) + 1] = s;
+#pragma unroll
+  for (int u = 0; u < kPropComps; ++u) {
+    if (c0 + u >= g.C) break;
+    lse_block_256(sm, ss, m[u], s[u]);
+    if (threadIdx.x == 0) {
+      part[2 * ((int64_t)(c0 + u) * kPropParts + p)] = m[u];
+      part[2 * ((int64_t)(c0 + u) * kPropParts + p) + 1] = s[u];
+    }
+    __syncthreads();
   }
 }
 

@@ -57,6 +57,8 @@ struct PreArgs {
   int64_t K2p;               // 2 n_bp
   // work and outputs
   double2* gram;             // [n_chunk][n_det][NP], c <= c'
+  double2* factors;          // [n_chunk][n_c] K_c+ and K_cx / i
+  int64_t chunk_rows;        // rows per block: what gram and factors hold
   double* ml_det;            // [n_rows][n_det]: max over (t, o) per detector
   double* lnl;               // [n_rows]: sum over detectors
   uint64_t* state;           // [0] largest lnl (ordered bits), [1] rows selected
@@ -69,13 +71,13 @@ struct PreArgs {
 
 __host__ __device__ inline int pre_pairs(int n_c) { return n_c * (n_c + 1) / 2; }
 
-// The whole pass on stream s: data operand, then per block of kPreChunk
+// The whole pass on stream s: data operand, then per block of chunk_rows
 // rows the Gram matrices and the grid maximum, then the incoherent sums and
 // the selection.  prec: kFP16X2 or kBF16X2.  Returns the first launch error.
 hipError_t preselect_launch(int prec, PreArgs a, hipStream_t s);
 
 // The arrival-time series alone (ml_t) for the rows of the list a.rows (at
-// most kPreChunk): data operand, Gram matrices and grid maxima of all rows at
+// most chunk_rows): data operand, Gram matrices and grid maxima of all rows at
 // once, one launch each.
 hipError_t preselect_series_launch(int prec, PreArgs a, hipStream_t s);
 

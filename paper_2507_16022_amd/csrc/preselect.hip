@@ -11,9 +11,10 @@
 // per-row maximum for its detector.
 #include <hip/hip_runtime.h>
 
+#include <mutex>
 #include <type_traits>
 
-#include "fused.h"
+#include "gram.h"
 #include "preselect.h"
 
 namespace dotpe {
@@ -30,12 +31,6 @@ __device__ __forceinline__ void store_split(void* p0, void* p1, int64_t o, doubl
     ((__bf16*)p0)[o] = hi;
     ((__bf16*)p1)[o] = (__bf16)(float)(x - (double)(float)hi);
   }
-}
-
-template <int PREC>
-__device__ __forceinline__ double load_split(const void* p0, const void* p1, int64_t o) {
-  if constexpr (PREC == kFP16X2) return (double)((const _Float16*)p0)[o] + (double)((const _Float16*)p1)[o];
-  else return (double)(float)((const __bf16*)p0)[o] + (double)(float)((const __bf16*)p1)[o];
 }
 
 // bank row of entry q of the rows
@@ -90,46 +85,67 @@ __global__ __launch_bounds__(256) void k_pre_build_B(PreArgs a) {
 }
 
 // G_ikcc' = sum_b w_kb h_icb conj(h_ic'b) (c <= c') from the split bank
-// values (h = conj(A) 2^e_i), in FP64: a wave per row, its lanes over the
-// bins, one wave sum per output.  The row is read from the row-major copy
-// of the split parts: in the fragment layout a single row's 16-byte pieces
-// lie 512 bytes apart, one per cache line.
+// values (h = conj(A) 2^e_i) in FP64, a wave per row, its lanes over the bins
+// (b = lane mod 64), the sums over the lanes in the order of wave_reduce.  The
+// pseudo-inverse below divides by H's smaller eigenvalue, down to 1e-10 of the
+// larger one, so the last bits of G reach the results: products, sums and
+// their order are fixed.  A pass over the row per detector and a full wave sum
+// per output took 1.95 ms per 2^18 rows of five channels and three detectors;
+// one pass for three detectors, and sums that share the lane steps (gram.h),
+// 1.2 ms, against 0.56 ms to read the rows.
 template <int PREC, int NC>
-__global__ __launch_bounds__(256) void k_pre_gram(PreArgs a) {
-  constexpr int NP = NC * (NC + 1) / 2;
+__global__ __launch_bounds__(256, 2) void k_pre_gram(PreArgs a) {
+  typedef typename std::conditional<PREC == kFP16X2, _Float16, __bf16>::type H;
+  constexpr int NP = NC * (NC + 1) / 2, KD = gram_dets(NC), N = KD * 2 * NP;
+  constexpr int N1 = (N + 1) / 2, N2 = (N1 + 1) / 2, N3 = (N2 + 1) / 2, N4 = (N3 + 1) / 2;
   const int lane = threadIdx.x & 63;
   const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (q >= a.n_chunk) return;
   const int64_t i = pre_row(a, a.chunk0 + q);
+  const H* r0 = (const H*)a.R0 + i * a.K2;
+  const H* r1 = (const H*)a.R1 + i * a.K2;
   const double s2 = a.row_scale[i] * a.row_scale[i];
-  auto add = [](double x, double y) { return x + y; };
-  for (int k = 0; k < a.n_det; ++k) {
-    double gr[NP], gi[NP];
+  for (int k0 = 0; k0 < a.n_det; k0 += KD) {
+    const int nk = min(KD, a.n_det - k0);
+    double v[N];                     // per detector (re, im) of the pairs
 #pragma unroll
-    for (int p = 0; p < NP; ++p) { gr[p] = 0.0; gi[p] = 0.0; }
+    for (int t = 0; t < N; ++t) v[t] = 0.0;
     for (int b = lane; b < a.n_b; b += 64) {
       double hr[NC], hi[NC];
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        const int64_t base = ((int64_t)c * (a.n_bp / kChunk) + b / kChunk) * 32 + (b % kChunk);
-        hr[c] = load_split<PREC>(a.R0, a.R1, i * a.K2 + base);
-        hi[c] = -load_split<PREC>(a.R0, a.R1, i * a.K2 + base + 16);
+        const int o = (c * (a.n_bp / kChunk) + b / kChunk) * 32 + b % kChunk;
+        hr[c] = (double)(float)r0[o] + (double)(float)r1[o];
+        hi[c] = -((double)(float)r0[o + 16] + (double)(float)r1[o + 16]);
       }
-      const double w = a.w[(int64_t)k * a.n_b + b];
+      double w[KD];
+#pragma unroll
+      for (int k = 0; k < KD; ++k) w[k] = k < nk ? a.w[(int64_t)(k0 + k) * a.n_b + b] : 0.0;
       int p = 0;
 #pragma unroll
       for (int c = 0; c < NC; ++c)
 #pragma unroll
         for (int c2 = c; c2 < NC; ++c2, ++p) {
-          gr[p] += w * (hr[c] * hr[c2] + hi[c] * hi[c2]);
-          gi[p] += w * (hi[c] * hr[c2] - hr[c] * hi[c2]);
+          const double x = hr[c] * hr[c2] + hi[c] * hi[c2], y = hi[c] * hr[c2] - hr[c] * hi[c2];
+#pragma unroll
+          for (int k = 0; k < KD; ++k) {
+            v[(k * NP + p) * 2] += w[k] * x;
+            v[(k * NP + p) * 2 + 1] += w[k] * y;
+          }
         }
     }
-    double2* out = a.gram + (q * a.n_det + k) * NP;
+    // wave_reduce's tree: lanes ^ 1, quads, halves of a row, rows, pairs of rows
+    gram_halve<N, 0xB1>(v, lane & 1);
+    gram_halve<N1, 0x4E>(v, lane & 2);
+    gram_halve<N2, kDppXor4>(v, lane & 4);
+    gram_halve<N3, 0x128>(v, lane & 8);
+    double* out = (double*)(a.gram + (q * a.n_det + k0) * NP);
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      const double r = wave_reduce(gr[p], 0.0, add), m = wave_reduce(gi[p], 0.0, add);
-      if (lane == 63) out[p] = make_double2(s2 * r, s2 * m);
+    for (int g = 0; g < N4; ++g) {
+      v[g] += __shfl_xor(v[g], 16, 64);
+      v[g] += __shfl_xor(v[g], 32, 64);
+      const int t = 16 * g + (lane & 15);     // (the steps took the lane's bits in order)
+      if (lane < 16 && t < nk * 2 * NP) out[t] = s2 * v[g];
     }
   }
 }
@@ -141,20 +157,210 @@ __device__ __forceinline__ uint4 neg16(const uint4& x) {
   return make_uint4(x.x ^ 0x80008000u, x.y ^ 0x80008000u, x.z ^ 0x80008000u, x.w ^ 0x80008000u);
 }
 
-template <int PREC, int NC>
-__global__ __launch_bounds__(64 * kPreMaxT / 32) void k_preselect(PreArgs a) {
+// One phase of one (row, time): the projections b+ and bx and the form
+// a1 (c b+ + s bx)^2 + a2 (-s b+ + c bx)^2, q = (c, s, a1, a2), in FP32 with
+// every rounding written out, so that the paths below agree bit for bit.
+__device__ __forceinline__ float pre_form(float bp, float bx, const float4& q) {
+#pragma clang fp contract(off)
+  const float u = __builtin_fmaf(bp, q.x, bx * q.y), v = __builtin_fmaf(bx, q.x, -(bp * q.y));
+  return __builtin_fmaf(u, q.z * u, v * (q.w * v));
+}
+__device__ __forceinline__ float pre_term(float cn, float sn, float re, float im) {
+#pragma clang fp contract(off)
+  return __builtin_fmaf(cn, re, -(sn * im));
+}
+
+// Phase grids with a power of two of at least four phases: the table's
+// entries for o, n - o, n / 2 + o and n / 2 - o are the same numbers up to
+// sign (2 (m o mod n) / n is exact, and so is the reduction of its cosine and
+// sine), so the four phases share their products: seven operations per
+// channel and polarisation instead of twelve.  Negating a factor negates the
+// rounded result, so every sum is the one the plain loop forms.
+__host__ __device__ __forceinline__ bool pre_fours(int n) { return n >= 4 && (n & (n - 1)) == 0; }
+// groups of four phases (o = 0 .. n / 4) or single phases, as the forms are stored
+__host__ __device__ __forceinline__ int pre_slots(int n) { return pre_fours(n) ? n + 4 : n; }
+// phase o's place: group g = 0 .. n / 4 holds g, n - g, n / 2 + g, n / 2 - g
+__device__ __forceinline__ int pre_slot(int o, int n) {
+  if (!pre_fours(n)) return o;
+  if (o <= n / 4) return 4 * o;
+  if (o < n / 2) return 4 * (n / 2 - o) + 3;
+  return o <= 3 * n / 4 ? 4 * (o - n / 2) + 2 : 4 * (n - o) + 1;
+}
+// channels per phase in the FP32 phase table, padded so that two channels'
+// (cos, sin) are one aligned 16-byte read
+constexpr int pre_ncp(int nc) { return (nc + 1) / 2 * 2; }
+
+// The maximum of pre_form over the phase grid for one (row, time): w = (conj(K_c+)
+// Y re, im, conj(K_cx) Y re, im) per channel, cs [phase][pre_ncp(NC)] (cos,
+// sin) (m_c phi), qf the row's forms by pre_slot, sg +1 for even m, -1 for odd.
+template <int NC, bool FOURS>
+__device__ __forceinline__ float pre_best(int n, const float (&sg)[NC], const float2* cs, const float4* qf,
+                                          const float (&wpr)[NC], const float (&wpi)[NC],
+                                          const float (&wxr)[NC], const float (&wxi)[NC]) {
+  constexpr int NCP = pre_ncp(NC);
+  float best = 0.f;
+  struct Cs {
+    float2 v[NCP];
+  };
+  auto load_cs = [&](int o) {
+    Cs c;
+    const float4* p = (const float4*)(cs + o * NCP);
+#pragma unroll
+    for (int q = 0; q < NCP / 2; ++q) {
+      const float4 x = p[q];
+      c.v[2 * q] = make_float2(x.x, x.y);
+      c.v[2 * q + 1] = make_float2(x.z, x.w);
+    }
+    return c;
+  };
+  if constexpr (FOURS) {
+    auto pair = [&](int g) {         // g = 0 or n / 4: two phases
+      const Cs k = load_cs(g);
+      const float4 q0 = qf[4 * g], q2 = qf[4 * g + 2];
+      float p0, p2, x0, x2;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const float tp = pre_term(k.v[c].x, k.v[c].y, wpr[c], wpi[c]);
+        const float tx = pre_term(k.v[c].x, k.v[c].y, wxr[c], wxi[c]);
+        p0 = c ? p0 + tp : tp;
+        x0 = c ? x0 + tx : tx;
+        p2 = c ? __builtin_fmaf(sg[c], tp, p2) : sg[c] * tp;
+        x2 = c ? __builtin_fmaf(sg[c], tx, x2) : sg[c] * tx;
+      }
+      best = fmaxf(best, fmaxf(pre_form(p0, x0, q0), pre_form(p2, x2, q2)));
+    };
+    pair(0);
+    pair(n / 4);
+    // the next group's table entries and forms are read while one is
+    // evaluated (held by the pins: the reads would otherwise move to their
+    // uses, an LDS latency per group in front of its arithmetic)
+    struct Group {
+      Cs k;
+      float4 q[4];
+    };
+    auto load = [&](int g) {
+      Group r;
+      r.k = load_cs(g);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) r.q[u] = qf[4 * g + u];
+      return r;
+    };
+    auto hold = [&](Group& r) {
+#pragma unroll
+      for (int c = 0; c < NCP; ++c) __asm__ __volatile__("" : "+v"(r.k.v[c].x), "+v"(r.k.v[c].y));
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        __asm__ __volatile__("" : "+v"(r.q[u].x), "+v"(r.q[u].y), "+v"(r.q[u].z), "+v"(r.q[u].w));
+    };
+    auto eval = [&](const Group& r) {
+      float p0, p1, p2, p3, x0, x1, x2, x3;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+#pragma clang fp contract(off)
+        const float cn = r.k.v[c].x, sp = r.k.v[c].y * wpi[c], sx = r.k.v[c].y * wxi[c];
+        const float tp = __builtin_fmaf(cn, wpr[c], -sp), tx = __builtin_fmaf(cn, wxr[c], -sx);
+        const float up = __builtin_fmaf(cn, wpr[c], sp), ux = __builtin_fmaf(cn, wxr[c], sx);
+        p0 = c ? p0 + tp : tp;
+        x0 = c ? x0 + tx : tx;
+        p1 = c ? p1 + up : up;
+        x1 = c ? x1 + ux : ux;
+        p2 = c ? __builtin_fmaf(sg[c], tp, p2) : sg[c] * tp;
+        x2 = c ? __builtin_fmaf(sg[c], tx, x2) : sg[c] * tx;
+        p3 = c ? __builtin_fmaf(sg[c], up, p3) : sg[c] * up;
+        x3 = c ? __builtin_fmaf(sg[c], ux, x3) : sg[c] * ux;
+      }
+      best = fmaxf(best, fmaxf(pre_form(p0, x0, r.q[0]), pre_form(p2, x2, r.q[2])));
+      best = fmaxf(best, fmaxf(pre_form(p1, x1, r.q[1]), pre_form(p3, x3, r.q[3])));
+    };
+    // groups 1 .. n / 4 - 1, an odd number of them, in turns of two
+    Group even = load(1);
+    for (int g = 1; g < n / 4; g += 2) {
+      Group odd = load(g + 1);
+      eval(even);
+      hold(odd);
+      if (g + 1 < n / 4) {
+        even = load(g + 2);
+        eval(odd);
+        hold(even);
+      }
+    }
+    return best;
+  }
+  for (int o = 0; o < n; ++o) {
+    const Cs k = load_cs(o);
+    float bp = 0.f, bx = 0.f;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      bp += pre_term(k.v[c].x, k.v[c].y, wpr[c], wpi[c]);
+      bx += pre_term(k.v[c].x, k.v[c].y, wxr[c], wxi[c]);
+    }
+    best = fmaxf(best, pre_form(bp, bx, qf[o]));
+  }
+  return best;
+}
+
+// K_c+ and K_cx / i of the chunk's rows, [n_chunk][NC], a thread each
+template <int NC>
+__global__ __launch_bounds__(256) void k_pre_factors(PreArgs a) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (t >= a.n_chunk * NC) return;
+  const int c = (int)(t % NC);
+  const double ci = a.cos_iota[a.chunk0 + t / NC];
+  const double yn = swsh_m2(a.l[c], -a.m[c], ci), yp = swsh_m2(a.l[c], a.m[c], ci);
+  const double sg = (a.l[c] & 1) ? -1.0 : 1.0;
+  a.factors[t] = make_double2(0.5 * (yn + sg * yp), 0.5 * (yn - sg * yp));
+}
+
+// FOURS: pre_fours(n_phi)
+template <int PREC, int NC, bool FOURS>
+__global__ __launch_bounds__(64 * kPreMaxT / 32, NC <= 5 ? 2 : 1) void k_preselect(PreArgs a) {
   typedef typename Pol<PREC>::Acc Acc;
   extern __shared__ __align__(16) double pls[];
   const int n_phi = a.n_phi;
+  constexpr int NCP = pre_ncp(NC);
+  const int slots = pre_slots(n_phi);
   double* cs = pls;                          // [kMaxM][n_phi][2] cos, sin of m phi_o
   double* kp = cs + kMaxM * n_phi * 2;       // [32][NC] K_c+
   double* kx = kp + 32 * NC;                 // [32][NC] K_cx / i
-  float* qf = (float*)(kx + 32 * NC);        // [32][n_phi][4] H^+ / 2 as (cos, sin, a1, a2)
-  double* red = (double*)(qf + 32 * n_phi * 4);   // [NW][32]
-  float* csf = (float*)(red + 32 * (kPreMaxT / 32));   // [kMaxM][n_phi][2] in FP32
+  float* qf = (float*)(kx + 32 * NC);        // [32][slots][4] H^+ / 2 as (cos, sin, a1, a2), by pre_slot
+  float2* csf = (float2*)(qf + 32 * slots * 4);   // [n_phi][NCP] cos, sin of m_c phi_o in FP32
+  double* red = (double*)(csf + n_phi * NCP);     // [NW][32]
+  unsigned char* stage = (unsigned char*)(red + (kPreMaxT / 32) * 32);   // [2][NC][4][1 KB]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nt = blockDim.x;
-  const int k = blockIdx.y;
-  const int64_t rb0 = a.chunk0 + (int64_t)blockIdx.x * 32;   // first row of the block
+  // workgroup -> (row block, detector): consecutive ids go to the XCDs in
+  // turn; each XCD takes a contiguous range with the detectors of one row
+  // block next to each other, so that its L2 serves the bank rows to all of
+  // them (the grid is a multiple of 8)
+  const int64_t wg = (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+  const int k = (int)(wg % a.n_det);
+  const int64_t rb0 = a.chunk0 + wg / a.n_det * 32;          // first row of the block
+  if (rb0 >= a.chunk0 + a.n_chunk) return;
+  // the A stages' loads: slice u = 4 c + (0 hi 0, 1 hi 1, 2 lo 0, 3 lo 1) of a
+  // chunk by wave u mod (number of waves), 1 KB each.  M0 carries the LDS
+  // address; the asm saves and restores it and waits the state an M0 write
+  // needs.
+  typedef __attribute__((address_space(1))) const unsigned char gbyte;
+  typedef __attribute__((address_space(3))) void lvoid;
+  const int h = lane >> 5, nj = a.n_bp / kChunk;    // chunks: a multiple of 4 (bins padded to 64)
+  const int64_t ia = pre_row(a, min(rb0 + (lane & 31), a.n_rows - 1));   // (rows past the end re-read the last)
+  const int64_t abase = ((ia >> 5) * (a.K2 >> 5)) * 1024 + h * 256 + (ia & 31) * 8;
+  const unsigned lds_stage = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lvoid*)stage);
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave), nw = nt >> 6;
+  auto issue = [&](int j) {
+    for (int u = wave_u; u < 4 * NC; u += nw) {
+      const int64_t o = abase + (int64_t)((u >> 2) * nj + j) * 1024 + (u & 1) * 512;
+      gbyte* p = (gbyte*)((u & 2) ? a.A1 : a.A0) + 2 * o;
+      const unsigned m0v = lds_stage + (unsigned)((j & 1) * (NC * 4096) + u * 1024);
+      unsigned m0_saved;
+      __asm__ __volatile__(
+          "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+          "global_load_lds_dwordx4 %2, off\n\ts_mov_b32 m0, %0"
+          : "=&s"(m0_saved)
+          : "s"(__builtin_amdgcn_readfirstlane(m0v)), "v"(p)
+          : "memory");
+    }
+  };
+  issue(0);
   const int rows_in = (int)min((int64_t)32, a.chunk0 + a.n_chunk - rb0);
 
   for (int t = tid; t < kMaxM * n_phi; t += nt) {
@@ -163,16 +369,14 @@ __global__ __launch_bounds__(64 * kPreMaxT / 32) void k_preselect(PreArgs a) {
     sincospi(2.0 * (double)((mm * o) % n_phi) / n_phi, &sn, &cn);
     cs[2 * t] = cn;
     cs[2 * t + 1] = sn;
-    csf[2 * t] = (float)cn;
-    csf[2 * t + 1] = (float)sn;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (a.m[c] == mm) csf[o * NCP + c] = make_float2((float)cn, (float)sn);
   }
   for (int t = tid; t < 32 * NC; t += nt) {
-    const int rr = t / NC, c = t % NC;
-    const double ci = rr < rows_in ? a.cos_iota[rb0 + rr] : 0.0;
-    const double yn = swsh_m2(a.l[c], -a.m[c], ci), yp = swsh_m2(a.l[c], a.m[c], ci);
-    const double sg = (a.l[c] & 1) ? -1.0 : 1.0;
-    kp[t] = 0.5 * (yn + sg * yp);
-    kx[t] = 0.5 * (yn - sg * yp);
+    const double2 f = t / NC < rows_in ? a.factors[(rb0 - a.chunk0) * NC + t] : make_double2(0.0, 0.0);
+    kp[t] = f.x;
+    kx[t] = f.y;
   }
   __syncthreads();
   // H_pp'(row, o) from the Gram matrix, then its pseudo-inverse / 2 (an
@@ -223,16 +427,11 @@ __global__ __launch_bounds__(64 * kPreMaxT / 32) void k_preselect(PreArgs a) {
       const double lm = (h00 * h11 - h01 * h01) / lp;
       a2 = lm > 1e-10 * lp ? 0.5 / lm : 0.0;
     }
-    qf[4 * t] = (float)ec;
-    qf[4 * t + 1] = (float)es;
-    qf[4 * t + 2] = (float)a1;
-    qf[4 * t + 3] = (float)a2;
+    *(float4*)(qf + 4 * (rr * slots + pre_slot(o, n_phi))) =
+        make_float4((float)ec, (float)es, (float)a1, (float)a2);
   }
 
   // ---- Y_ikc for this wave's 32 grid times, every channel ----
-  const int h = lane >> 5;
-  const int64_t ia = pre_row(a, min(rb0 + (lane & 31), a.n_rows - 1));   // (rows past the end re-read the last)
-  const int64_t abase = ((ia >> 5) * (a.K2 >> 5)) * 1024 + h * 256 + (ia & 31) * 8;
   const int64_t rbB = (int64_t)k * a.n_t + 32 * wave + (lane & 31);
   const int64_t bbase = ((rbB >> 5) * (a.K2p >> 5)) * 1024 + h * 256 + (rbB & 31) * 8;
   Acc acc[NC][2];
@@ -241,61 +440,65 @@ __global__ __launch_bounds__(64 * kPreMaxT / 32) void k_preselect(PreArgs a) {
     acc[c][0] = Acc{};
     acc[c][1] = Acc{};
   }
-  // fragments of one bin chunk: B hi/lo of both slices, A hi/lo of both
-  // slices for every channel; the next chunk's are loaded while this one's
-  // products run (one wave per SIMD: the loads' latency is hidden by the
-  // wave's own work)
-  struct Frag {
-    uint4 b[4];          // bh0, bh1, bl0, bl1
-    uint4 a[NC][4];      // ah0, ah1, al0, al1
+  // The waves of the workgroup (grid times) share the bank rows: a bin chunk's
+  // A slices of every channel (hi, lo of both slices, NC x 4 KB) go straight
+  // into one of two LDS stages, shared out over the waves, while the chunk
+  // before is multiplied (each wave reading A from global memory for itself
+  // moved four times the bytes through the L1s: 5.5 of 7.8 ms per 2^18 rows).
+  // B is the wave's own: registers, a chunk ahead.  Two waves per SIMD (256
+  // registers: 160 accumulators at five channels), so that one's epilogue,
+  // all VALU, runs under another's products.
+  struct FB {
+    uint4 h0, h1, l0, l1;
   };
-  const int nj = a.n_bp / kChunk;    // a multiple of 4 (bins padded to 64)
-  auto load = [&](Frag& f, int j) {
+  auto load_b = [&](FB& f, int j) {
     const int64_t bo = bbase + (int64_t)j * 1024;
-    f.b[0] = ld16(a.B0, bo);
-    f.b[1] = ld16(a.B0, bo + 512);
-    f.b[2] = ld16(a.B1, bo);
-    f.b[3] = ld16(a.B1, bo + 512);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int64_t ao = abase + (int64_t)(c * nj + j) * 1024;
-      f.a[c][0] = ld16(a.A0, ao);
-      f.a[c][1] = ld16(a.A0, ao + 512);
-      f.a[c][2] = ld16(a.A1, ao);
-      f.a[c][3] = ld16(a.A1, ao + 512);
-    }
+    f.h0 = ld16(a.B0, bo);
+    f.h1 = ld16(a.B0, bo + 512);
+    f.l0 = ld16(a.B1, bo);
+    f.l1 = ld16(a.B1, bo + 512);
   };
-  auto compute = [&](const Frag& f) {
-    const uint4 &bh0 = f.b[0], &bh1 = f.b[1], &bl0 = f.b[2], &bl1 = f.b[3];
-    const uint4 nbh1 = neg16(bh1), nbl1 = neg16(bl1);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const uint4 &ah0 = f.a[c][0], &ah1 = f.a[c][1], &al0 = f.a[c][2], &al1 = f.a[c][3];
-      // A = [Re conj h | Im conj h], B_re = [Br | -Bi], B_im = [Bi | Br]:
-      // 3 split products per real product
-      Acc& re = acc[c][0];
-      Acc& im = acc[c][1];
-      mma<PREC>(re, al0, bh0);  mma<PREC>(im, al0, nbh1);
-      mma<PREC>(re, ah0, bl0);  mma<PREC>(im, ah0, nbl1);
-      mma<PREC>(re, ah0, bh0);  mma<PREC>(im, ah0, nbh1);
-      mma<PREC>(re, al1, bh1);  mma<PREC>(im, al1, bh0);
-      mma<PREC>(re, ah1, bl1);  mma<PREC>(im, ah1, bl0);
-      mma<PREC>(re, ah1, bh1);  mma<PREC>(im, ah1, bh0);
-    }
+  // A = [Re conj h | Im conj h], B_re = [Br | -Bi], B_im = [Bi | Br]: 3 split
+  // products per real product
+  auto compute = [&](int j, const FB& b) {
+    const uint4 nh1 = neg16(b.h1), nl1 = neg16(b.l1);
+    const unsigned char* st = stage + (j & 1) * (NC * 4096) + lane * 16;
+    static_for<NC>([&](auto ci) {
+      constexpr int c = decltype(ci)::value;
+      Acc &re = acc[c][0], &im = acc[c][1];
+      const uint4 h0 = *(const uint4*)(st + c * 4096), h1 = *(const uint4*)(st + c * 4096 + 1024);
+      const uint4 l0 = *(const uint4*)(st + c * 4096 + 2048), l1 = *(const uint4*)(st + c * 4096 + 3072);
+      mma<PREC>(re, l0, b.h0);  mma<PREC>(im, l0, nh1);
+      mma<PREC>(re, h0, b.l0);  mma<PREC>(im, h0, nl1);
+      mma<PREC>(re, h0, b.h0);  mma<PREC>(im, h0, nh1);
+      mma<PREC>(re, l1, b.h1);  mma<PREC>(im, l1, b.h0);
+      mma<PREC>(re, h1, b.l1);  mma<PREC>(im, h1, b.l0);
+      mma<PREC>(re, h1, b.h1);  mma<PREC>(im, h1, b.h0);
+    });
   };
-  Frag f0, f1;
-  load(f0, 0);
+  FB b0, b1;
+  load_b(b0, 0);
   for (int j = 0; j < nj; j += 2) {
-    load(f1, j + 1);
-    compute(f0);
-    if (j + 2 < nj) load(f0, j + 2);
-    compute(f1);
+    // chunk j has landed (every wave's part), and every wave is done with j - 1
+    pipeline_barrier<0>();
+    issue(j + 1);
+    load_b(b1, j + 1);
+    compute(j, b0);
+    pipeline_barrier<0>();
+    if (j + 2 < nj) {
+      issue(j + 2);
+      load_b(b0, j + 2);
+    }
+    compute(j + 1, b1);
   }
   __syncthreads();   // (the forms in qf are complete)
 
   // ---- epilogue: polarisation projections, 2x2 form, maximum ----
   // (in FP32: the accumulators are FP32 and the form is a sum of squares)
   const double csc = a.col_scale[rbB];
+  float sg[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) sg[c] = (a.m[c] & 1) ? -1.f : 1.f;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int rr = 8 * (r >> 2) + 4 * h + (r & 3);
@@ -310,25 +513,19 @@ __global__ __launch_bounds__(64 * kPreMaxT / 32) void k_preselect(PreArgs a) {
       wxr[c] = xk * yi;     // conj(K_cx) Y = -i (K_cx / i) Y
       wxi[c] = -xk * yr;
     }
-    float bestf = 0.f;
-    for (int o = 0; o < n_phi; ++o) {
-      float bp = 0.f, bx = 0.f;
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const float cn = csf[((a.m[c] - 1) * n_phi + o) * 2], sn = csf[((a.m[c] - 1) * n_phi + o) * 2 + 1];
-        bp += cn * wpr[c] - sn * wpi[c];
-        bx += cn * wxr[c] - sn * wxi[c];
-      }
-      const float4 q = *(const float4*)(qf + 4 * (rr * n_phi + o));
-      const float u = q.x * bp + q.y * bx, v = q.x * bx - q.y * bp;
-      bestf = fmaxf(bestf, q.z * u * u + q.w * v * v);
-    }
+    const float bestf = pre_best<NC, FOURS>(n_phi, sg, csf, (const float4*)(qf + 4 * rr * slots), wpr, wpi, wxr,
+                                     wxi);
     if (a.ml_t && rr < rows_in)
       a.ml_t[((rb0 + rr) * a.n_det + k) * a.n_t + 32 * wave + (lane & 31)] = (double)bestf;
-    double best = (double)bestf;
-#pragma unroll
-    for (int off = 16; off > 0; off >>= 1) best = fmax(best, __shfl_xor(best, off, 32));
-    if ((lane & 31) == 0) red[wave * 32 + rr] = best;
+    // the maximum over the 32 times of this half wave (non-negative values),
+    // complete in its last lane
+    float m = bestf;
+    m = fmaxf(m, dpp_mov<0xB1, 0xF>(0.f, m));
+    m = fmaxf(m, dpp_mov<0x4E, 0xF>(0.f, m));
+    m = fmaxf(m, dpp_mov<0x141, 0xF>(0.f, m));
+    m = fmaxf(m, dpp_mov<0x140, 0xF>(0.f, m));
+    m = fmaxf(m, dpp_mov<0x142, 0xA>(0.f, m));
+    if ((lane & 31) == 31) red[wave * 32 + rr] = (double)m;
   }
   __syncthreads();
   if (tid < rows_in) {
@@ -348,7 +545,8 @@ __global__ __launch_bounds__(256) void k_pre_final(PreArgs a) {
     a.lnl[i] = v;
   }
   const double m = wave_max(v);
-  if ((threadIdx.x & 63) == 0 && m > -INFINITY)
+  // (most waves cannot raise the maximum: a read, maybe stale, spares the atomic)
+  if ((threadIdx.x & 63) == 0 && m > -INFINITY && order_bits(m) > a.state[0])
     atomicMax((unsigned long long*)&a.state[0], (unsigned long long)order_bits(m));
 }
 
@@ -377,13 +575,26 @@ __global__ __launch_bounds__(256) void k_pre_count(PreArgs a) {
 }
 
 __global__ __launch_bounds__(256) void k_pre_scan(PreArgs a, int64_t nb) {
-  if (threadIdx.x != 0) return;
-  int64_t run = 0;
-  for (int64_t b = 0; b < nb; ++b) {
+  // each thread a contiguous range of blocks, a scan of the ranges' totals
+  __shared__ int64_t sh[256];
+  const int t = threadIdx.x;
+  const int64_t per = (nb + 255) / 256, lo = min(nb, t * per), hi = min(nb, lo + per);
+  int64_t n = 0;
+  for (int64_t b = lo; b < hi; ++b) n += a.counts[b];
+  sh[t] = n;
+  __syncthreads();
+  for (int k = 1; k < 256; k <<= 1) {
+    const int64_t v = t >= k ? sh[t - k] : 0;
+    __syncthreads();
+    sh[t] += v;
+    __syncthreads();
+  }
+  int64_t run = sh[t] - n;
+  for (int64_t b = lo; b < hi; ++b) {
     a.offsets[b] = run;
     run += a.counts[b];
   }
-  a.state[1] = (uint64_t)run;
+  if (t == 255) a.state[1] = (uint64_t)sh[255];
 }
 
 __global__ __launch_bounds__(256) void k_pre_write(PreArgs a) {
@@ -404,25 +615,33 @@ __global__ __launch_bounds__(256) void k_pre_write(PreArgs a) {
     if (f & (1u << q)) a.selected[pos++] = a.row0 + r0 + q;
 }
 
-template <int PREC, int NC>
+template <int PREC, int NC, bool FOURS>
 hipError_t launch_pre_main(const PreArgs& a, hipStream_t s) {
-  const size_t lds = sizeof(double) * ((size_t)kMaxM * a.n_phi * 2 + 64 * NC + 32 * (size_t)a.n_phi * 2 +
-                                       (kPreMaxT / 32) * 32 + (size_t)kMaxM * a.n_phi);
-  static bool attr_done = false;
-  if (!attr_done) {
-    const size_t most = sizeof(double) * ((size_t)kMaxM * kMaxPhi * 2 + 64 * NC + 32 * (size_t)kMaxPhi * 2 +
-                                          (kPreMaxT / 32) * 32 + (size_t)kMaxM * kMaxPhi);
-    if (hipFuncSetAttribute((const void*)k_preselect<PREC, NC>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)most) != hipSuccess)
+  auto lds_bytes = [](int n_phi) {
+    return sizeof(double) * ((size_t)kMaxM * n_phi * 2 + 64 * NC + 32 * (size_t)pre_slots(n_phi) * 2 +
+                             (size_t)n_phi * pre_ncp(NC) + (kPreMaxT / 32) * 32) +
+           2 * NC * 4096;
+  };
+  const size_t lds = lds_bytes(a.n_phi);
+  static std::once_flag attr_once;
+  std::call_once(attr_once, [&] {
+    if (hipFuncSetAttribute((const void*)k_preselect<PREC, NC, FOURS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds_bytes(kMaxPhi)) != hipSuccess)
       (void)hipGetLastError();
-    attr_done = true;
-  }
+  });
+  hipLaunchKernelGGL((k_pre_factors<NC>), dim3((unsigned)((a.n_chunk * NC + 255) / 256)), dim3(256), 0, s,
+                     a);
   hipLaunchKernelGGL((k_pre_gram<PREC, NC>), dim3((unsigned)((a.n_chunk + 3) / 4)), dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  dim3 grid((unsigned)((a.n_chunk + 31) / 32), (unsigned)a.n_det);
-  hipLaunchKernelGGL((k_preselect<PREC, NC>), grid, dim3(64 * (a.n_t / 32)), lds, s, a);
+  const dim3 grid((unsigned)(((a.n_chunk + 31) / 32 * a.n_det + 7) / 8 * 8));
+  hipLaunchKernelGGL((k_preselect<PREC, NC, FOURS>), grid, dim3(64 * (a.n_t / 32)), lds, s, a);
   return hipGetLastError();
+}
+
+template <int PREC, int NC>
+hipError_t launch_pre_main(const PreArgs& a, hipStream_t s) {
+  return pre_fours(a.n_phi) ? launch_pre_main<PREC, NC, true>(a, s) : launch_pre_main<PREC, NC, false>(a, s);
 }
 
 template <int PREC>
@@ -445,9 +664,9 @@ hipError_t run_all(PreArgs a, hipStream_t s) {
   hipLaunchKernelGGL(k_pre_build_B<PREC>, dim3((unsigned)(a.n_det * a.n_t)), dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  for (int64_t c0 = 0; c0 < a.n_rows; c0 += kPreChunk) {
+  for (int64_t c0 = 0; c0 < a.n_rows; c0 += a.chunk_rows) {
     a.chunk0 = c0;
-    a.n_chunk = std::min<int64_t>(kPreChunk, a.n_rows - c0);
+    a.n_chunk = std::min<int64_t>(a.chunk_rows, a.n_rows - c0);
     if ((e = launch_pre_nc<PREC>(a, s)) != hipSuccess) return e;
   }
   hipLaunchKernelGGL(k_pre_final, dim3((unsigned)((a.n_rows + 255) / 256)), dim3(256), 0, s, a);
@@ -460,7 +679,7 @@ hipError_t run_all(PreArgs a, hipStream_t s) {
 
 template <int PREC>
 hipError_t run_series(PreArgs a, hipStream_t s) {
-  if (a.n_rows > kPreChunk) return hipErrorInvalidValue;
+  if (a.n_rows > a.chunk_rows) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_pre_build_B<PREC>, dim3((unsigned)(a.n_det * a.n_t)), dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
