@@ -744,8 +744,8 @@ __device__ __forceinline__ void survivor_pass(const FusedArgs& a, int64_t wg_id,
       lse.init();
       double best = -INFINITY, mlmax = 0.0;
       int ob = 0;
-      pair_phases<kEvidence, G, true>(a, lds_cs, *dp, ie, e, X, S0, Sr, Si, lnw, thr_ml, lane, 64, ev, lse,
-                                best, ob, mlmax);
+      pair_phases<kEvidence, G, true>(a, lds_cs, *dp, X, S0, Sr, Si, lnw, thr_ml, lane, 64, ev, lse, best,
+                                      ob, mlmax);
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) {
         const double lm = __shfl_xor(lse.m, off, 64), ls = __shfl_xor(lse.s, off, 64);

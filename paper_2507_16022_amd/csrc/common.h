@@ -145,16 +145,17 @@ struct Lse {
 struct LsePh {
   double m, s, s2;     // s2: sum of the squared terms (the triples' squares)
   __device__ void init() { m = -INFINITY; s = 0.0; s2 = 0.0; }
-  __device__ void add(double x) {
+  // x = -inf leaves it unchanged; true when x is the largest so far
+  __device__ bool add(double x) {
     const double d = x - m;                       // +inf while empty
-    const double t = (double)__expf(-fabsf((float)d));
+    // (below -150 the exponential is zero; -inf - -inf is taken for that too)
+    const double t = (double)__expf(fmaxf(-fabsf((float)d), -150.f));
     const bool up = d > 0.0;
-    const double ns = up ? fma(s, t, 1.0) : s + t;
-    const double ns2 = up ? fma(s2, t * t, 1.0) : fma(t, t, s2);
-    const bool skip = !(x > -INFINITY);
-    s = skip ? s : ns;
-    s2 = skip ? s2 : ns2;
-    m = (up && !skip) ? x : m;
+    // (t has 24 bits, so t * t is exact)
+    s = fma(up ? s : 1.0, t, up ? 1.0 : s);
+    s2 = fma(up ? s2 : 1.0, t * t, up ? 1.0 : s2);
+    m = up ? x : m;
+    return up;
   }
   __device__ void merge(double mb, double sb, double s2b) {
     if (mb == -INFINITY) return;

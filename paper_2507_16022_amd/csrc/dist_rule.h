@@ -104,19 +104,27 @@ static_assert(dr_exact_recip(kDrSegStep[0]) && dr_exact_recip(kDrSegStep[1]) &&
                   dr_exact_recip(kDrRowStep[2]) && dr_exact_recip(kDrRowStep[3]),
               "table steps with whole reciprocals");
 
+// 1 / d for d > 0 of moderate range: the hardware's estimate (24 bits) and one
+// third-order step (1 / d = y (1 + e + e^2 + ...), e = 1 - d y; the rest is
+// e^3 < 2^-66), a quarter of the instructions of an IEEE division
+__device__ __forceinline__ double dr_rcp(double d) {
+  const double y = __builtin_amdgcn_rcp(d);
+  const double e = fma(-d, y, 1.0);
+  return fma(y, fma(e, e, e), y);
+}
+
 // Natural logarithm of a positive normal x: x = m 2^e with m in
 // [sqrt(1/2), sqrt(2)), ln m = 2 atanh(t) with t = (m - 1) / (m + 1),
 // |t| < 0.172, by the atanh series through t^17 (the rest is below 3e-16).
-// About a quarter of the instructions of the math library's version, and
-// accurate to a few units in the last place of ln x's absolute value.
+// Far fewer instructions than the math library's version, and accurate to a
+// few units in the last place of ln x's absolute value.
 __device__ __forceinline__ double dr_log(double x) {
   int e;
   double m = frexp(x, &e);             // m in [1/2, 1)
-  if (m < 0.70710678118654752) {
-    m *= 2.0;
-    --e;
-  }
-  const double t = (m - 1.0) / (m + 1.0), t2 = t * t;
+  const bool up = m < 0.70710678118654752;
+  m = up ? m + m : m;
+  e -= up ? 1 : 0;
+  const double t = (m - 1.0) * dr_rcp(m + 1.0), t2 = t * t;
   double p = 1.0 / 17.0;
   p = fma(p, t2, 1.0 / 15.0);
   p = fma(p, t2, 1.0 / 13.0);
@@ -127,14 +135,6 @@ __device__ __forceinline__ double dr_log(double x) {
   p = fma(p, t2, 1.0 / 3.0);
   p = fma(p, t2, 1.0);
   return fma((double)e, 0.69314718055994531, 2.0 * t * p);
-}
-
-// 1 / d for d > 0 of moderate range: the FP32 reciprocal refined by two
-// Newton steps in FP64 (relative error squared per step: below 1e-15)
-__device__ __forceinline__ double dr_rcp(double d) {
-  double y = (double)__builtin_amdgcn_rcpf((float)d);
-  y = y * fma(-d, y, 2.0);
-  return y * fma(-d, y, 2.0);
 }
 
 // z of stored column `col` (any segment)
@@ -266,14 +266,19 @@ __host__ __device__ inline __attribute__((noinline)) double dr_ln_exact(double z
   return log(3.0) + pmax + log(total);
 }
 
-// ln E[(z + eps)^-4], eps ~ N(0,1), by probabilists' Gauss-Hermite nodes
-// (the tail formula is used for z >= 8 only, so z + x_k > 2 for every node)
+// ln E[(z + eps)^-4], eps ~ N(0,1), by probabilists' Gauss-Hermite nodes (the
+// tail formula is used for z >= 8 only, so z + x_k > 2 for every node).  The
+// nodes come in pairs +-x of equal weight, so a pair takes one reciprocal:
+// (z + x)^-4 + (z - x)^-4 = 2 ((Z + X)^2 + 4 Z X) / (Z - X)^4, Z = z^2, X = x^2.
 __device__ __forceinline__ double dr_gh_ln_moment(double z, const double* ghx, const double* ghw) {
+  static_assert(kGH % 2 == 0, "nodes in pairs");
+  const double Z = z * z;
   double acc = 0.0;
-  for (int k = 0; k < kGH; ++k) {
-    const double y = dr_rcp(z + ghx[k]);
-    const double y2 = y * y;
-    acc = fma(ghw[k], y2 * y2, acc);
+#pragma unroll 2
+  for (int k = 0; k < kGH / 2; ++k) {
+    const double X = ghx[k] * ghx[k], sum = Z + X;
+    const double r = dr_rcp(Z - X), r2 = r * r;
+    acc = fma((ghw[k] + ghw[k]) * (r2 * r2), fma(4.0 * Z, X, sum * sum), acc);
   }
   return dr_log(acc);
 }
@@ -296,69 +301,123 @@ __device__ __forceinline__ bool dr_tail_ok(double z, double s) {
 // 4x4 cubic Lagrange interpolation in the table
 __device__ __forceinline__ void dr_lagrange4(double t, double* c) {
   // nodes at -1, 0, 1, 2; t in [0, 1)
-  const double tm1 = t - 1.0, tm2 = t - 2.0, tp1 = t + 1.0;
-  c[0] = -t * tm1 * tm2 * (1.0 / 6.0);
-  c[1] = tp1 * tm1 * tm2 * 0.5;
-  c[2] = -tp1 * t * tm2 * 0.5;
-  c[3] = tp1 * t * tm1 * (1.0 / 6.0);
+  const double tp1 = t + 1.0, tm1 = t - 1.0, tm2 = t - 2.0;
+  const double in = t * tm1 * (1.0 / 6.0), out = tp1 * tm2 * 0.5;
+  c[0] = -in * tm2;
+  c[1] = out * tm1;
+  c[2] = -out * t;
+  c[3] = in * tp1;
 }
 
-// ln Lbar at (z, s) from the table; false when (z, s) lies outside it
-__device__ __forceinline__ bool dr_table_lookup(const double* tab, double z, double s,
-                                                double* out) {
+// A coordinate's place along one axis of the table: x ih + b of its segment,
+// with b = 2 - edge ih + the segment's offset (two guard lines below its
+// edge).  Steps, edges and offsets are such that ih and b are whole numbers,
+// exact in the upper word of a double: a segment costs one comparison and two
+// selects.
+template <int N>
+struct DrAxis {
+  double lo[N], ih[N], b[N];
+};
+__host__ __device__ constexpr DrAxis<kDrSeg> dr_z_axis() {
+  DrAxis<kDrSeg> a{};
+  for (int k = 0; k < kDrSeg; ++k) {
+    a.lo[k] = kDrGeom.zlo[k];
+    a.ih[k] = kDrGeom.ihz[k];
+    a.b[k] = 2.0 - kDrGeom.zlo[k] * kDrGeom.ihz[k] + kDrGeom.off[k];
+  }
+  return a;
+}
+__host__ __device__ constexpr DrAxis<kDrRowSeg> dr_w_axis() {
+  DrAxis<kDrRowSeg> a{};
+  for (int k = 0; k < kDrRowSeg; ++k) {
+    a.lo[k] = kDrGeom.wlo[k];
+    a.ih[k] = kDrGeom.ihw[k];
+    a.b[k] = 2.0 - kDrGeom.wlo[k] * kDrGeom.ihw[k] + kDrGeom.roff[k];
+  }
+  return a;
+}
+template <int N>
+constexpr bool dr_whole(const DrAxis<N>& a) {
+  for (int k = 0; k < N; ++k)
+    if (a.b[k] != (double)(int)a.b[k] || a.ih[k] != (double)(int)a.ih[k]) return false;
+  return true;
+}
+static_assert(dr_whole(dr_z_axis()) && dr_whole(dr_w_axis()), "whole table coordinates");
+
+template <int N>
+__device__ __forceinline__ double dr_place(const DrAxis<N>& a, double x) {
+  double ih = a.ih[0], b = a.b[0];
+#pragma unroll
+  for (int q = 1; q < N; ++q) {
+    const bool up = x >= a.lo[q];
+    ih = up ? a.ih[q] : ih;
+    b = up ? a.b[q] : b;
+  }
+  return fma(x, ih, b);
+}
+
+// the table's coordinate of s: ln s below 1, s - 1 above
+__device__ __forceinline__ double dr_w(double s) { return s < 1.0 ? dr_log(s) : s - 1.0; }
+__device__ __forceinline__ bool dr_in_table(double z, double w) {
   constexpr DistTableGeom g = kDrGeom;
-  const double w = s < 1.0 ? dr_log(s) : s - 1.0;
-  if (!(z >= g.zlo[0] && z < g.zhi[kDrSeg - 1] && w >= g.wlo[0] && w < g.whi[kDrRowSeg - 1]))
-    return false;
-  // each axis' segment: segments are contiguous, so the last one whose lower
-  // edge is at or below the coordinate.  The position is formed from the
-  // edge and the reciprocal step, which are exact in binary (the guard lines
-  // add 2), so the selected constants are immediate operands.
-  double zlo = g.zlo[0], ihz = g.ihz[0], wlo = g.wlo[0], ihw = g.ihw[0];
-  int nz = g.nz[0], off = g.off[0], nw = g.nw[0], roff = g.roff[0];
-#pragma unroll
-  for (int q = 1; q < kDrSeg; ++q) {
-    if (z >= g.zlo[q]) {
-      zlo = g.zlo[q];
-      ihz = g.ihz[q];
-      nz = g.nz[q];
-      off = g.off[q];
-    }
-  }
-#pragma unroll
-  for (int q = 1; q < kDrRowSeg; ++q) {
-    if (w >= g.wlo[q]) {
-      wlo = g.wlo[q];
-      ihw = g.ihw[q];
-      nw = g.nw[q];
-      roff = g.roff[q];
-    }
-  }
-  const double fz = fma(z - zlo, ihz, 2.0), fw = fma(w - wlo, ihw, 2.0);
+  return z >= g.zlo[0] && z < g.zhi[kDrSeg - 1] && w >= g.wlo[0] && w < g.whi[kDrRowSeg - 1];
+}
+// ln Lbar at a (z, w) inside the table.  A place just below a segment's upper
+// edge may round to the edge: the guard lines above serve its stencil too.  The
+// 16 values are asked for together, ahead of the weights (left to itself the
+// compiler spares registers and waits for each row in turn: four latencies
+// per triple).
+__device__ __forceinline__ double dr_table_value(const double* tab, double z, double w) {
+  constexpr DistTableGeom g = kDrGeom;
+  constexpr DrAxis<kDrSeg> az = dr_z_axis();
+  constexpr DrAxis<kDrRowSeg> aw = dr_w_axis();
+  const double fz = dr_place(az, z), fw = dr_place(aw, w);
   const double flz = floor(fz), flw = floor(fw);
-  const int jz = (int)flz, jw = (int)flw;
-  if (jz < 1 || jz > nz - 3 || jw < 1 || jw > nw - 3) return false;
+  const unsigned at = __umul24((unsigned)(int)flw, (unsigned)g.ncol) + (unsigned)(int)flz - (unsigned)g.ncol - 1u;
+  typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
+  d2 y[4][2];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) y[a][q] = *(const d2*)(tab + at + a * g.ncol + 2 * q);
+  __builtin_amdgcn_sched_barrier(0);
   double cz[4], cw[4];
   dr_lagrange4(fz - flz, cz);
   dr_lagrange4(fw - flw, cw);
-  const double* base = tab + ((roff + jw - 1) * g.ncol + off + (jz - 1));
   double v = 0.0;
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
-    const double* row = base + a * g.ncol;
-    const double rv = cz[0] * row[0] + cz[1] * row[1] + cz[2] * row[2] + cz[3] * row[3];
+    const double rv = fma(cz[3], y[a][1].y, fma(cz[2], y[a][1].x, fma(cz[1], y[a][0].y, cz[0] * y[a][0].x)));
     v = fma(cw[a], rv, v);
   }
-  *out = v;
+  return v;
+}
+// ln Lbar at (z, s) from the table; false when (z, s) lies outside it
+__device__ __forceinline__ bool dr_table_lookup(const double* tab, double z, double s,
+                                                double* out) {
+  const double w = dr_w(s);
+  if (!dr_in_table(z, w)) return false;
+  *out = dr_table_value(tab, z, w);
   return true;
 }
 
-// z and s of a triple: z = dh / sqrt(hh), s = sqrt(hh) d0 / D_max (hh > 0)
+// z and s of a triple: z = dh / sqrt(hh), s = sqrt(hh) d0 / D_max (hh > 0), by
+// the hardware's reciprocal square root (24 bits) and one third-order step (the
+// rest is below 2^-66); by square root and division where hh's square root or
+// the estimate's square could leave the double range
 __device__ __forceinline__ void dr_zs(double dh, double hh, double d0_over_dmax, double& z,
                                       double& s) {
-  const double sq = sqrt(hh);
-  z = dh / sq;
-  s = sq * d0_over_dmax;
+  if (hh > 0x1p-900 && hh < 0x1p900) {
+    const double y = __builtin_amdgcn_rsq(hh);
+    const double e = fma(-hh * y, y, 1.0);
+    const double r = fma(y * e, fma(e, 0.375, 0.5), y);
+    z = dh * r;
+    s = hh * r * d0_over_dmax;
+  } else {
+    const double sq = sqrt(hh);
+    z = dh / sq;
+    s = sq * d0_over_dmax;
+  }
 }
 
 // full rule: ln Lbar for one triple given dh, hh at distance d0
@@ -393,14 +452,41 @@ __device__ __attribute__((noinline)) inline double dr_ln_marg(double dh, double 
   return dr_ln_marg_body(dh, hh, d0_over_dmax, tab, ghx, ghw);
 }
 
-// The rule inlined (the same arithmetic, so the same values), only the
-// adaptive quadrature called: for kernels whose lanes evaluate many triples
-// in a loop (a call there makes every value live across it occupy a saved
-// register).
-__device__ __attribute__((always_inline)) inline double dr_ln_marg_inl(
-    double dh, double hh, double d0_over_dmax, const double* tab, const double* ghx,
-    const double* ghw) {
-  return dr_ln_marg_body(dh, hh, d0_over_dmax, tab, ghx, ghw);
+// The rule for kernels whose lanes evaluate many triples in a loop: the same
+// arithmetic, so the same values, inlined and without the adaptive quadrature;
+// false where that is needed.
+__device__ __forceinline__ bool dr_ln_marg_try(double dh, double hh, double d0_over_dmax,
+                                               const double* tab, const double* ghx, const double* ghw,
+                                               double& out) {
+  const bool pos = hh > 0.0;
+  double z, s;
+  dr_zs(dh, pos ? hh : 1.0, d0_over_dmax, z, s);
+  const bool small = s < kDrSMin;
+  // dr_tail_ok with an FP32 logarithm (within 1e-5 of ln(z / s)) where that decides
+  bool tail = z >= 8.0 && z - s >= 8.0 && !small;
+  if (tail) {
+    const double sq = 0.5 * (z - s) * (z - s) - 40.0;
+    const double l4 = 4.0 * (double)__logf((float)z * __builtin_amdgcn_rcpf((float)s));
+    tail = sq >= l4;
+    if (fabs(sq - l4) < 1e-3) tail = dr_tail_ok(z, s);
+  }
+  bool ok = true;
+  double v = 0.0;
+  if (pos && !tail && !small) {
+    const double w = dr_w(s);
+    ok = dr_in_table(z, w);
+    if (ok) v = dr_table_value(tab, z, w);
+  }
+  if (pos && tail) v = dr_ln_tail(z, s, ghx, ghw);
+  if (pos && small) {
+    v = 1.5 * z * s;
+    if (z >= 8.0) {
+      const double lp = dr_ln_tail(z, s, ghx, ghw);
+      v += lp > 0.0 ? lp + log1p(exp(-lp)) : log1p(exp(lp));
+    }
+  }
+  out = v;
+  return ok;
 }
 
 }  // namespace dotpe

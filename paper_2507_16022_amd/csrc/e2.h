@@ -2,11 +2,11 @@
 // kernel (mode kCoef) has stored the raw accumulators of every pair of the
 // chunk's tiles; this kernel bounds (E1) and evaluates (E2: per-phase
 // distance marginalisation, eq. lnl_dist_marginalized, and the phase
-// average) every pair, one lane per pair with the phases in a loop, and
-// writes each tile's partial.  Apart from the accumulators it holds a
-// handful of doubles per lane, so several waves share every SIMD and hide
-// the latency of the distance rule's table reads, which the fused kernel,
-// one wave per SIMD, cannot.
+// average) every pair and writes each tile's partial.  Apart from the
+// accumulators it holds a handful of doubles per lane, so several waves share
+// every SIMD and hide the latency of the distance rule's table reads, which
+// the fused kernel, one wave per SIMD, cannot.  The (i, e) matrix of ln L is
+// written by the same kernel without the cut and the sums.
 #pragma once
 
 #include "fused.h"
@@ -103,121 +103,386 @@ struct PairCoef {
   }
 };
 
-template <int PREC, int G>
+// The pairs that E1 leaves, a wave's batch of up to 64 at a time, in three
+// steps, each with the lanes full whatever the cut leaves:
+//  - a pair per lane: which phases the cut keeps (a mask), the cut phases'
+//    bounds and the largest lnL^ML, from the pair's coefficients in registers
+//    and the phase table in scalar registers;
+//  - a kept phase per lane, the pairs' phases in order: the distance rule.  Its
+//    table reads are bound by the rate at which a CU's L1 serves gathered
+//    lines (64 lanes at random: ~150 cycles per load of 16 bytes, within a few
+//    lines: ~25), and the phases of one pair fall into few lines;
+//  - a pair per lane: the running sum over its kept phases, in order.
+// Where a posterior is broad, one pair in ten survives E1 and one phase in
+// ten of a survivor the cut: with a lane per pair of the tile and every phase
+// in its loop (as before), the wave took each step that any lane needed.  At
+// 30011 x 3001 pairs and 32 phases a pass with every phase kept went from 52.4
+// to 36.1 ms (8.0e10 triples/s, its FP64 instructions 60% of the cycles), at
+// 8192 x 4096 pairs with 11% and 7% kept this kernel from 5.1 to 2.0 ms.  (A
+// phase per lane throughout, with scans for the running sums, took 45 ms and
+// 6.4 ms.)
+//
+// Slot of a pair in its wave's batch: the accumulators, the pair's place in
+// the tile (in the last element before the scales), and the two scales as
+// doubles (FP32 accumulators; FP64 ones carry none).  An odd number of
+// 16-byte units, so that consecutive slots start in different banks.
+template <typename AT, int NCO>
+struct PairSlot {
+  static constexpr int U = 16 / (int)sizeof(AT);
+  static constexpr int CP = (NCO + 1 + U - 1) / U * U;
+  static constexpr int UNITS = CP / U + (sizeof(AT) == 4 ? 1 : 0);
+  static constexpr int STRIDE = (UNITS | 1) * U;
+};
+
+// MODE kEvidence: the second half of an evidence pass; kEval: every pair's
+// ln L (and largest lnL^ML, and triples) of the tiles from work0 on.
+template <int PREC, int G, int MODE>
 __device__ __forceinline__ void e2_pass(const FusedArgs& a, int64_t wg_id, int64_t wg_count) {
   typedef Tile<PREC> TL;
   typedef typename std::conditional<PREC == kFP64, double, float>::type AT;
+  constexpr bool EVAL = MODE == kEval;
   constexpr int NRT = (G == 1) ? 1 : kMaxNR;
   constexpr int NCO = 2 * G + NRT;
-  constexpr int TM = TL::TM, TN = TL::TN, NPT = TM * TN, NT = 256, NW = NT / 64;
-  static_assert(NPT % NT == 0, "whole pairs per thread");
+  constexpr int TM = TL::TM, TN = TL::TN, NPT = TM * TN, NT = 256, NW = NT / 64, NK = NPT / NT;
+  static_assert(NPT % NT == 0 && (TN == 64 || TN == 32), "whole rows per wave");
+  constexpr int PARTS = EVAL ? kEvalParts : 1;
+  static_assert(NK % PARTS == 0, "whole turns per part");
+  typedef PairSlot<AT, NCO> SL;
+  // kept phases per turn of the distance rule: as LDS allows three workgroups
+  // per CU
+  constexpr int CH = PREC == kFP64 ? 256 : 512;
+  extern __shared__ __align__(16) double lds_cs[];     // [kMaxM][n_phi][2]
   __shared__ DistParams dp;
-  __shared__ double lds_cs[kMaxM * kMaxPhi * 2];
   __shared__ double rowd[TM * 4], cold[TN * 3], rowq[TM * 2], red[NW * kNPart];
-  __shared__ double lnp_pair[NPT];       // ln p of each evaluated pair, -inf otherwise
+  __shared__ __align__(16) AT slots[NW][64 * SL::STRIDE];
+  __shared__ double val[NW][CH];         // ln Lbar of the turn's kept phases
+  __shared__ uint16_t ent[NW][CH];       // slot << 8 | phase
+  // sums of the waves' e^(ln p - m) by row and by column, m the wave's largest
+  // ln p so far
+  __shared__ double rsum[TM], csum[NW][TN], wmax[NW];
   __shared__ unsigned long long tile_lnp_max;
+  static_assert(kMaxPhi <= 256, "a phase in 8 bits");
 
-  const int tid = threadIdx.x;
-  for (int t = tid; t < kMaxM * a.n_phi * 2; t += NT) lds_cs[t] = a.phase_cs[t];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_phi = a.n_phi;
+  for (int t = tid; t < kMaxM * n_phi * 2; t += NT) lds_cs[t] = a.phase_cs[t];
   static_assert(sizeof(DistParams) % 4 == 0, "DistParams words");
   for (int t = tid; t < (int)(sizeof(DistParams) / 4); t += NT)
     ((unsigned*)&dp)[t] = ((const unsigned*)a.dist.prm)[t];
+  // the phase table again, for wave-uniform reads
+  typedef const double __attribute__((address_space(4))) cdouble;
+  cdouble* cs_u = (cdouble*)(uintptr_t)a.phase_cs;
   // the cut as the fused kernel's epilogue applies it
-  const bool on = cut_on(a);
+  const bool on = !EVAL && cut_on(a);
   const double thr_ml = on ? __longlong_as_double(a.state[3]) - a.cut_delta : -INFINITY;
+  const double thr2 = 2.0 * thr_ml;
   const float thr_f = (float)thr_ml;
   const int64_t end = min(a.work0 + a.coef_tiles, coef_work_count(a));
+  AT* const my_slots = slots[wave];
+  double* const my_val = val[wave];
+  uint16_t* const my_ent = ent[wave];
 
-  for (int64_t q = a.work0 + wg_id; q < end; q += wg_count) {
+  // a pair's coefficients and scales from its slot
+  struct Coef {
+    double2 X[G];
+    double S0, Sr[kMaxND], Si[kMaxND], sx, sh;
+    int place;
+  };
+  auto read_slot = [&](int s, Coef& c) {
+    const AT* q = my_slots + s * SL::STRIDE;
+    AT v[SL::CP];
+#pragma unroll
+    for (int u = 0; u < SL::CP; u += SL::U) {
+      typedef AT VT __attribute__((ext_vector_type(SL::U)));
+      const VT w = *(const VT*)(q + u);
+#pragma unroll
+      for (int x = 0; x < SL::U; ++x) v[u + x] = w[x];
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) c.X[g] = make_double2((double)v[2 * g], (double)v[2 * g + 1]);
+    c.S0 = (double)v[2 * G];
+#pragma unroll
+    for (int d = 0; d < kMaxND; ++d) { c.Sr[d] = 0.0; c.Si[d] = 0.0; }
+#pragma unroll
+    for (int d = 1; d < (NRT + 1) / 2; ++d) {
+      c.Sr[d] = (double)v[2 * G + 2 * d - 1];
+      c.Si[d] = (double)v[2 * G + 2 * d];
+    }
+    c.place = *(const int*)(q + SL::CP - 1);
+    if constexpr (PREC == kFP64) {
+      c.sx = c.sh = 1.0;
+    } else {
+      const double2 w = *(const double2*)(q + SL::CP);
+      c.sx = w.x;
+      c.sh = w.y;
+    }
+  };
+  auto wave_sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+
+  for (int64_t w = wg_id; w < (end - a.work0) * PARTS; w += wg_count) {
+    const int64_t q = a.work0 + w / PARTS;
+    const int part = (int)(w % PARTS);
     const int64_t t = coef_tile(a, q);
     const int64_t tm = t / a.n_tiles_n, tn = t % a.n_tiles_n;
     const int64_t row0 = tm * TM, col0 = tn * TN;
     e2_scalars<PREC, TM, TN>(a, row0, col0, rowd, cold, rowq);
     if (tid == 0) tile_lnp_max = 0ull;
+    if (tid < TM) rsum[tid] = 0.0;
+    if (lane < TN) csum[wave][lane] = 0.0;
     __syncthreads();
-    const double thr_topk_glob = order_value(a.state[1]) - a.topk_window;
+    const double thr_topk_glob = EVAL ? 0.0 : order_value(a.state[1]) - a.topk_window;
     const int rows_in = (int)min((int64_t)TM, a.n_sub - row0);
     const int cols_in = (int)min((int64_t)TN, a.n_ext - col0);
     const AT* cf = (const AT*)a.coef + (q - a.work0) * (int64_t)(NCO * NPT);
     EvAcc ev;
     ev.init();
     int n_pairs_i = 0, n_bounded_i = 0;
+    double wm = -INFINITY;
+    const int k1 = (part + 1) * (NK / PARTS);
+    int k = part * (NK / PARTS);
 #pragma unroll 1
-    for (int k = 0; k < NPT / NT; ++k) {
-      // a wave takes consecutive pairs of a row: coalesced component reads
-      const int p = k * NT + tid, tr = p / TN, tc = p % TN;
-      lnp_pair[p] = -INFINITY;
-      if (!(tr < rows_in && tc < cols_in)) continue;
-      ++n_pairs_i;
-      PairCoef<AT, G, NRT> pc;
-      pc.template load<NPT>(cf, p);
-      if (on) {
-        float bound, lw;
-        if (pc.bounded(rowq, cold, tr, tc, thr_f, bound, lw)) {
-          ev.drop.add(lw + bound);
-          ev.max_bound = fmaxf(ev.max_bound, lw + bound);
-          ++n_bounded_i;
-          continue;
+    for (;;) {
+      // fill the batch: consecutive pairs of a row per wave, coalesced
+      // component reads; a turn whose survivors do not fit is read again for
+      // the next batch (held in registers instead, or asked for a turn ahead,
+      // it was 5% slower)
+      int used = 0;
+#pragma unroll 1
+      for (; k < k1 && used < 64; ++k) {
+        const int p = k * NT + tid, tr = p / TN, tc = p % TN;
+        const bool in = tr < rows_in && tc < cols_in;
+        PairCoef<AT, G, NRT> pc;
+        pc.template load<NPT>(cf, p);
+        float bound = 0.f, lw = 0.f;
+        const bool bounded = on && pc.bounded(rowq, cold, tr, tc, thr_f, bound, lw) && in;
+        const bool live = in && !bounded;
+        const unsigned long long lv = __ballot(live);
+        const int n_live = (int)__popcll(lv);
+        if (used + n_live > 64) break;
+        n_pairs_i += in ? 1 : 0;
+        if (on) {
+          ev.drop.add(bounded ? lw + bound : -INFINITY);
+          ev.max_bound = bounded ? fmaxf(ev.max_bound, lw + bound) : ev.max_bound;
+          n_bounded_i += bounded ? 1 : 0;
         }
+        if (live) {
+          AT* o = my_slots + SL::STRIDE * (used + (int)__builtin_amdgcn_mbcnt_hi(
+                                                      (unsigned)(lv >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo((unsigned)lv, 0u)));
+#pragma unroll
+          for (int c = 0; c < 2 * G; ++c) o[c] = pc.x[c];
+#pragma unroll
+          for (int c = 0; c < NRT; ++c) o[2 * G + c] = pc.sv[c];
+          *(int*)(o + SL::CP - 1) = p;
+          if constexpr (PREC != kFP64)
+            *(double2*)(o + SL::CP) = make_double2(rowd[tr * 4 + 1] * cold[tc * 3 + 1],
+                                                   rowd[tr * 4 + 2] * cold[tc * 3 + 2]);
+        }
+        used += n_live;
       }
-      // E2
-      double2 X[G];
-      double S0, Sr[kMaxND], Si[kMaxND], lnw;
-      pc.unscale(rowd, cold, tr, tc, X, S0, Sr, Si, lnw);
-      const int64_t e = col0 + tc;
+      if (!used) break;
+      wave_sync();
+      const bool act = lane < used;
+      int tr, tc, ob = 0;
+      double lnw, mn = 0.0, md = 1.0;
       LsePh lse;
       lse.init();
-      double best = -INFINITY, mlmax = 0.0;
-      int ob = 0;
-      pair_phases<kEvidence, G, true>(a, lds_cs, dp, row0 + tr, e, X, S0, Sr, Si, lnw, thr_ml, 0, 1,
-                                      ev, lse, best, ob, mlmax);
-      ev.ml_max = fmax(ev.ml_max, mlmax);
-      if (lse.m == -INFINITY) continue;
-      const double lnp = lnw + (lse.m + log(lse.s) - a.ln_nphi);
-      ev.p.add(lnp, lse.sq_ratio());
-      lnp_pair[p] = lnp;
-      // top-k candidates within the window of the running maxima
-      const unsigned long long ob_bits = order_bits(lnp);
-      const unsigned long long prev = atomicMax(&tile_lnp_max, ob_bits);
-      const double tmax = order_value(prev > ob_bits ? prev : ob_bits);
-      append_candidate(a, lnp >= fmax(thr_topk_glob, tmax - a.topk_window), lnp, rowd[tr * 4 + 3],
-                       (double)e, ob);
+      {
+        const int place = *(const int*)(my_slots + (act ? lane : 0) * SL::STRIDE + SL::CP - 1);
+        tr = place / TN;
+        tc = place % TN;
+        lnw = rowd[tr * 4] + cold[tc * 3];
+      }
+      // phases in blocks of 32, or of 16 where all are kept: 64 pairs then fill
+      // two turns, and half of the lanes have a pair in each turn's sums
+      const int blk = on ? 32 : 16;
+#pragma unroll 1
+      for (int o0 = 0; o0 < n_phi; o0 += blk) {
+        const int no = min(blk, n_phi - o0);
+        unsigned mask = act ? (no == 32 ? ~0u : (1u << no) - 1u) : 0u;
+        // a pair per lane
+        if (!EVAL || a.ml_out) {
+          Coef c;
+          read_slot(act ? lane : 0, c);
+          unsigned keeps = 0u;
+#pragma unroll 1
+          for (int b = 0; b < no; ++b) {
+            double dh, hh;
+            phase_dh_hh<G>(a.mt.gm, n_phi, cs_u, c.X, c.S0, c.Sr, c.Si, o0 + b, dh, hh);
+            dh *= c.sx;
+            hh *= c.sh;
+            const bool pos = dh > 0.0 && hh > 0.0;
+            const double dh2 = dh * dh;
+            const bool more = pos && dh2 * md > mn * hh;
+            mn = more ? dh2 : mn;
+            md = more ? hh : md;
+            if (on) {
+              // lnL^ML >= thr  <=>  dh > 0 and dh^2 >= 2 thr hh (no division)
+              const bool keep = thr_ml <= 0.0 || (dh > 0.0 && dh2 >= thr2 * hh);
+              keeps |= keep ? 1u << b : 0u;
+              double ml = 0.0;
+              if (pos) ml = hh > 0x1p-900 && hh < 0x1p900 ? dh2 * dr_rcp(2.0 * hh) : dh2 / (2.0 * hh);
+              const float x = (float)(lnw + ml - a.ln_nphi);
+              // (the rounding margin keeps it a bound)
+              ev.drop.add(act && !keep ? x + fabsf(x) * 1e-6f + 1e-5f : -INFINITY);
+            }
+          }
+          if (on) mask &= keeps;
+        }
+        // the kept phases' places, pair by pair
+        const int cnt = __popc(mask);
+        if (!EVAL) ev.n_marg += cnt;
+        int incl = cnt;
+        incl += (int)dpp_mov<0x111, 0xF>(0u, (unsigned)incl);   // row_shr:1, 2, 4, 8
+        incl += (int)dpp_mov<0x112, 0xF>(0u, (unsigned)incl);
+        incl += (int)dpp_mov<0x114, 0xF>(0u, (unsigned)incl);
+        incl += (int)dpp_mov<0x118, 0xF>(0u, (unsigned)incl);
+        incl += (int)dpp_mov<0x142, 0xA>(0u, (unsigned)incl);   // row_bcast:15, 31
+        incl += (int)dpp_mov<0x143, 0xC>(0u, (unsigned)incl);
+        const int off = incl - cnt, total = __builtin_amdgcn_readlane(incl, 63);
+        int at = off;
+        const unsigned inv_no = (65536u + no - 1) / no;
+#pragma unroll 1
+        for (int c0 = 0; c0 < total; c0 += CH) {
+          const int c1 = min(c0 + CH, total);
+          const int lo = at;
+          if (on) {
+            while (mask && at < c1) {
+              my_ent[at - c0] = (uint16_t)(lane << 8 | (o0 + __builtin_ctz(mask)));
+              mask &= mask - 1u;
+              ++at;
+            }
+            wave_sync();
+          } else {
+            at = max(at, min(off + cnt, c1));
+          }
+          // a kept phase per lane
+#pragma unroll 1
+          for (int e0 = c0; e0 < c1; e0 += 64) {
+            const int e = e0 + lane, ec = min(e, c1 - 1);
+            int src, o;
+            if (on) {
+              const unsigned en = my_ent[ec - c0];
+              src = (int)(en >> 8);
+              o = (int)(en & 255u);
+            } else {
+              src = (int)((unsigned)ec * inv_no >> 16);      // ec / no (ec < 2^10, no <= 16)
+              o = o0 + ec - src * no;
+            }
+            Coef c;
+            read_slot(src, c);
+            double dh, hh, v;
+            phase_dh_hh<G>(a.mt.gm, n_phi, (const double*)lds_cs, c.X, c.S0, c.Sr, c.Si, o, dh, hh);
+            dh *= c.sx;
+            hh *= c.sh;
+            if (EVAL && a.trip_out && e < c1) {
+              const size_t to = (((size_t)(row0 + c.place / TN) * a.n_ext + (col0 + c.place % TN)) *
+                                     n_phi + o) * 2;
+              a.trip_out[to] = dh;
+              a.trip_out[to + 1] = hh;
+            }
+            if (!dr_ln_marg_try(dh, hh, a.r0, a.dist.tab, dp.ghx, dp.ghw, v))
+              v = dr_ln_marg(dh, hh, a.r0, a.dist.tab, dp.ghx, dp.ghw);
+            if (e < c1) my_val[e - c0] = v;
+          }
+          wave_sync();
+          // a pair per lane: its phases of this turn, in order
+          int jb = -1;
+          for (int j = lo; j < at; ++j) jb = lse.add(my_val[j - c0]) ? j : jb;
+          if (jb >= 0) ob = on ? my_ent[jb - c0] & 255 : o0 + jb - off;
+          wave_sync();
+        }
+      }
+      const bool have = act && lse.m != -INFINITY;
+      const double lnl = have ? lse.m + log(lse.s) - a.ln_nphi : -INFINITY;
+      if (EVAL) {
+        if (act) {
+          const size_t to = (size_t)(row0 + tr) * a.n_ext + (col0 + tc);
+          a.lnl_out[to] = lnl;
+          if (a.ml_out) a.ml_out[to] = mn / (2.0 * md);
+        }
+        continue;
+      }
+      if (act) ev.ml_max = fmax(ev.ml_max, mn / (2.0 * md));
+      const double lnp = lnw + lnl;
+      if (have) {
+        // top-k candidates within the window of the running maxima
+        const unsigned long long ob_bits = order_bits(lnp);
+        const unsigned long long prev = atomicMax(&tile_lnp_max, ob_bits);
+        const double tmax = order_value(prev > ob_bits ? prev : ob_bits);
+        append_candidate(a, lnp >= fmax(thr_topk_glob, tmax - a.topk_window), lnp, rowd[tr * 4 + 3],
+                         (double)(col0 + tc), ob);
+      }
+      // the row and column sums, a row of the batch at a time (a fixed order;
+      // a row belongs to one wave)
+      const bool sums = have && lnp != -INFINITY;
+      unsigned long long todo = __ballot(sums);
+      if (!todo) continue;
+      const double mx = wave_max(lnp);
+      if (mx > wm) {
+        const double f = wm == -INFINITY ? 0.0 : exp(wm - mx);
+        ev.p.s *= f;
+        ev.p.s2 *= f * f;
+        ev.p.s3 *= f * f;
+        if (lane < TN) csum[wave][lane] *= f;
+        if (lane < TM && (lane * TN / 64) % NW == wave) rsum[lane] *= f;
+        wm = mx;
+        wave_sync();
+      }
+      const double ex = sums ? exp(lnp - wm) : 0.0;
+      ev.p.s += ex;
+      ev.p.s2 = fma(ex, ex, ev.p.s2);
+      ev.p.s3 = fma(ex * ex, sums ? lse.sq_ratio() : 0.0, ev.p.s3);
+      while (todo) {
+        const int r = __builtin_amdgcn_readlane(tr, __builtin_ctzll(todo));
+        const bool mine = sums && tr == r;
+        todo &= ~__ballot(mine);
+        const double sum = wave_reduce(mine ? ex : 0.0, 0.0, [](double x, double y) { return x + y; });
+        if (lane == 63) rsum[r] += sum;
+        if (mine) csum[wave][tc] += ex;
+        wave_sync();
+      }
     }
+    if (EVAL) {
+      __syncthreads();
+      continue;
+    }
+    if (lane == 0) wmax[wave] = wm;
+    // (every lane's sums are relative to wm)
+    auto add_d = [](double x, double y) { return x + y; };
+    ev.p.s = wave_reduce(ev.p.s, 0.0, add_d);
+    ev.p.s2 = wave_reduce(ev.p.s2, 0.0, add_d);
+    ev.p.s3 = wave_reduce(ev.p.s3, 0.0, add_d);
+    ev.p.m = lane == 63 ? wm : -INFINITY;
     tile_partial<NW>(a, ev, n_pairs_i, n_bounded_i, red, &tile_lnp_max, t);
-    // (every pair's ln p and the tile maximum are final: tile_partial has a
-    // barrier) the row and column sums relative to the tile maximum, each
-    // summed in index order
+    // (the sums and the tile maximum are final: tile_partial has a barrier)
+    // relative to the tile maximum
     {
       const unsigned long long mb = tile_lnp_max;
       const double mxp = mb == 0ull ? -INFINITY : order_value(mb);
+      auto rel = [&](int w) { return wmax[w] == -INFINITY ? 0.0 : exp(wmax[w] - mxp); };
       double* rc = a.rowcol + t * 128;
       if (tid < TM) {
-        double sum = 0.0;
-        for (int c = 0; c < TN; ++c) {
-          const double v = lnp_pair[tid * TN + c];
-          sum += v == -INFINITY ? 0.0 : exp(v - mxp);
-        }
-        rc[tid] = sum;
+        rc[tid] = rsum[tid] * rel((tid * TN / 64) % NW);
       } else if (tid < TM + TN) {
-        const int c = tid - TM;
         double sum = 0.0;
-        for (int r = 0; r < TM; ++r) {
-          const double v = lnp_pair[r * TN + c];
-          sum += v == -INFINITY ? 0.0 : exp(v - mxp);
-        }
-        rc[64 + c] = sum;
+        for (int w = 0; w < NW; ++w) sum += csum[w][tid - TM] * rel(w);
+        rc[64 + tid - TM] = sum;
       }
     }
     __syncthreads();   // the tile's scalars and reduction area are reused
   }
 }
 
-template <int PREC, int G>
+template <int PREC, int G, int MODE>
 __global__ __launch_bounds__(256, 3) void k_e2_tiles(FusedArgs a) {
-  e2_pass<PREC, G>(a, blockIdx.x, gridDim.x);
+  e2_pass<PREC, G, MODE>(a, blockIdx.x, gridDim.x);
 }
 
-// one chunk of the coefficient route's second half for several events
+// one chunk's second half of several events
 template <int PREC, int G>
 __global__ __launch_bounds__(256, 3) void k_e2_tiles_packed(PackLaunch p) {
   int64_t blk, nblk;
@@ -225,7 +490,7 @@ __global__ __launch_bounds__(256, 3) void k_e2_tiles_packed(PackLaunch p) {
   const int e = pack_locate(p, blockIdx.x, &blk, &nblk, &q);
   FusedArgs a = pack_args(p, e, q);
   a.work0 = p.chunk * a.coef_tiles;
-  e2_pass<PREC, G>(a, blk, nblk);
+  e2_pass<PREC, G, kEvidence>(a, blk, nblk);
 }
 
 // ---------------------------------------------------------------------------
@@ -353,8 +618,8 @@ __global__ __launch_bounds__(256, 3) void k_sample_pairs(FusedArgs a) {
         lse.init();
         double best = -INFINITY, mlmax = 0.0;
         int ob = 0;
-        pair_phases<kEvidence, G, true>(a, lds_cs, dp, row0 + tr, col0 + tc, X, S0, Sr, Si, lnw,
-                                        thr_ml, 0, 1, ev, lse, best, ob, mlmax);
+        pair_phases<kEvidence, G, true>(a, lds_cs, dp, X, S0, Sr, Si, lnw, thr_ml, 0, 1, ev, lse, best,
+                                        ob, mlmax);
         if (lse.m != -INFINITY) lnp = lnw + (lse.m + log(lse.s) - a.ln_nphi);
       }
     }
@@ -465,7 +730,7 @@ __global__ __launch_bounds__(256) void k_sample_draws(FusedArgs a) {
     dh_o[h] = 0.0;
     hh_o[h] = 0.0;
     if (o < a.n_phi) {
-      phase_dh_hh<G>(a, lds_cs, X, S0, Sr, Si, o, dh_o[h], hh_o[h]);
+      phase_dh_hh<G>(a.mt.gm, a.n_phi, lds_cs, X, S0, Sr, Si, o, dh_o[h], hh_o[h]);
       const bool keep = thr_ml <= 0.0 || (dh_o[h] > 0.0 && dh_o[h] * dh_o[h] >= 2.0 * thr_ml * hh_o[h]);
       if (keep) v_o[h] = dr_ln_marg(dh_o[h], hh_o[h], a.r0, a.dist.tab, dp.ghx, dp.ghw);
     }

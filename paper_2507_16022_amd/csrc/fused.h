@@ -280,6 +280,7 @@ __device__ __forceinline__ void mma(typename Pol<PREC>::Acc& acc, const uint4& a
 
 enum Mode { kEval = 0, kEvidence = 1, kPilot = 2, kBound = 3, kSurvivors = 4, kCoef = 5, kE2 = 6,
             kSample = 7 };
+constexpr int kEvalParts = 4;    // workgroups per tile of kEval's marginalisation
 
 // The cut of an evidence pass is on when the threshold frozen after the
 // pilot (state[3], the pilot's largest lnL^ML) less cut_delta is above
@@ -401,63 +402,59 @@ struct EvAcc {
   }
 };
 
-// phases o = o0, o0 + os, ... of one pair given X_g and the (h|h)
-// coefficients: cut, distance marginalisation.  The kept phases' ln L go to
-// lse, the best one to best / o_best (first of equal values), the largest
-// lnL^ML to mlmax; cut phases' upper bounds go to ev.drop.  The caller
-// combines the parts of one pair.  INL: the distance rule inlined (for a
-// kernel whose lanes each evaluate many pairs).
 // dh and hh of phase o of one pair from X_g and the (h|h) phase
-// coefficients (hh clamped at zero)
-template <int G>
-__device__ __forceinline__ void phase_dh_hh(const FusedArgs& a, const double* lds_cs,
+// coefficients (hh clamped at zero; coefficients past the largest difference
+// of m are zero).  CS: a pointer to the phase table in the memory it is read
+// from.
+template <int G, typename CS>
+__device__ __forceinline__ void phase_dh_hh(const int* gm, int n_phi, CS phase_cs,
                                             const double2 (&X)[G], double S0,
                                             const double (&Sr)[kMaxND], const double (&Si)[kMaxND],
                                             int o, double& dh_out, double& hh_out) {
-  const ModeTables& mt = a.mt;
-  double dh = 0.0;
+  static_assert(kMaxG == kMaxM && kMaxND <= kMaxM, "four groups are m = 1 .. 4");
+  double dh = 0.0, hh = S0;
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    const double* cs = lds_cs + ((mt.gm[g] - 1) * a.n_phi + o) * 2;
-    dh += X[g].x * cs[0] - X[g].y * cs[1];
+    const int m = G == kMaxM ? g + 1 : gm[g];
+    const CS cs = phase_cs + ((m - 1) * n_phi + o) * 2;
+    dh = fma(X[g].x, cs[0], fma(-X[g].y, cs[1], dh));
   }
-  double hh = S0;
+  if constexpr (G > 1) {
 #pragma unroll
-  for (int d = 1; d < kMaxND; ++d) {
-    if (d < mt.ND) {
-      const double* cs = lds_cs + ((d - 1) * a.n_phi + o) * 2;
-      hh += 2.0 * (Sr[d] * cs[0] + Si[d] * cs[1]);
+    for (int d = 1; d < kMaxND; ++d) {
+      const CS cs = phase_cs + ((d - 1) * n_phi + o) * 2;
+      hh = fma(2.0 * Sr[d], cs[0], fma(2.0 * Si[d], cs[1], hh));
     }
   }
   dh_out = dh;
   hh_out = fmax(hh, 0.0);
 }
 
+// phases o = o0, o0 + os, ... of one pair given X_g and the (h|h)
+// coefficients: cut, distance marginalisation.  The kept phases' ln L go to
+// lse, the best one to best / o_best (first of equal values), the largest
+// lnL^ML to mlmax; cut phases' upper bounds go to ev.drop.  The caller
+// combines the parts of one pair.  INL: the distance rule inlined (for a
+// kernel whose lanes each evaluate many pairs).
 template <int MODE, int G, bool INL = false>
-__device__ void pair_phases(const FusedArgs& a, const double* lds_cs, const DistParams& dp,
-                            int64_t ie, int64_t e,
-                            const double2 (&X)[G], double S0, const double (&Sr)[kMaxND],
-                            const double (&Si)[kMaxND], double lnw, double thr_ml, int o0, int os,
-                            EvAcc& ev, LsePh& lse, double& best, int& o_best, double& mlmax) {
-  constexpr bool EVAL = MODE == kEval;
+__device__ __forceinline__ void pair_phases(const FusedArgs& a, const double* lds_cs, const DistParams& dp,
+                                            const double2 (&X)[G], double S0,
+                                            const double (&Sr)[kMaxND], const double (&Si)[kMaxND],
+                                            double lnw, double thr_ml, int o0, int os, EvAcc& ev,
+                                            LsePh& lse, double& best, int& o_best, double& mlmax) {
   const double thr2 = 2.0 * thr_ml;
   // the largest lnL^ML = dh^2 / (2 hh), kept as a fraction (mn / md) and
   // divided once at the end
   double mn = 0.0, md = 1.0;
   for (int o = o0; o < a.n_phi; o += os) {
     double dh, hh;
-    phase_dh_hh<G>(a, lds_cs, X, S0, Sr, Si, o, dh, hh);
-    if (EVAL && a.trip_out) {
-      size_t t = (((size_t)ie * a.n_ext + e) * a.n_phi + o) * 2;
-      a.trip_out[t] = dh;
-      a.trip_out[t + 1] = hh;
-    }
+    phase_dh_hh<G>(a.mt.gm, a.n_phi, lds_cs, X, S0, Sr, Si, o, dh, hh);
     const bool pos = dh > 0.0 && hh > 0.0;
     const double dh2 = dh * dh;
     if (pos && dh2 * md > mn * hh) { mn = dh2; md = hh; }
     if (MODE == kPilot) continue;
     // lnL^ML >= thr  <=>  dh > 0 and dh^2 >= 2 thr hh (no division)
-    const bool keep = EVAL || thr_ml <= 0.0 || (dh > 0.0 && dh2 >= thr2 * hh);
+    const bool keep = thr_ml <= 0.0 || (dh > 0.0 && dh2 >= thr2 * hh);
     if (!keep) {
       const double ml = pos ? dh2 / (2.0 * hh) : 0.0;
       float x = (float)(lnw + ml - a.ln_nphi);
@@ -465,18 +462,18 @@ __device__ void pair_phases(const FusedArgs& a, const double* lds_cs, const Dist
       continue;
     }
     double v;
-    if constexpr (INL) v = dr_ln_marg_inl(dh, hh, a.r0, a.dist.tab, dp.ghx, dp.ghw);
+    if constexpr (INL) v = dr_ln_marg_body(dh, hh, a.r0, a.dist.tab, dp.ghx, dp.ghw);
     else v = dr_ln_marg(dh, hh, a.r0, a.dist.tab, dp.ghx, dp.ghw);
     if (v > best) { best = v; o_best = o; }
     lse.add(v);
-    if (!EVAL) ev.n_marg += 1;
+    ev.n_marg += 1;
   }
   mlmax = fmax(mlmax, mn / (2.0 * md));
 }
 
 // The tile's partial from the per-thread accumulators: counts and maxima
 // by wave reductions, evaluated and dropped mass merged lane by lane, then
-// the waves' parts merged in wave order by thread 0 (a fixed order); red is
+// the waves' parts by lanes of the first wave (a fixed order); red is
 // LDS [NW][kNPart], tile_lnp_max the tile's largest ln p (ordered bits).
 template <int NW>
 __device__ __forceinline__ void tile_partial(const FusedArgs& a, const EvAcc& ev, int n_pairs_i,
@@ -526,17 +523,33 @@ __device__ __forceinline__ void tile_partial(const FusedArgs& a, const EvAcc& ev
     }
   }
   __syncthreads();
-  if (tid == 0) {
+  if (wave == 0) {
+    // the waves' parts, a lane each (a fixed tree over the first NW lanes)
+    static_assert(NW >= 2 && NW <= 16 && (NW & (NW - 1)) == 0, "parts within a row of lanes");
+    const bool in = lane < NW;
+    const double* r = red + (in ? lane : 0) * kNPart;
+    auto over = [&](double v, double ident, auto op) {
+      v = in ? v : ident;
+      v = op(v, dpp_mov<0xB1, 0xF>(ident, v));
+      if (NW > 2) v = op(v, dpp_mov<0x4E, 0xF>(ident, v));
+      if (NW > 4) v = op(v, dpp_mov<0x141, 0xF>(ident, v));
+      if (NW > 8) v = op(v, dpp_mov<0x140, 0xF>(ident, v));
+      return v;
+    };
+    auto add_d = [](double x, double y) { return x + y; };
+    auto max_d = [](double x, double y) { return fmax(x, y); };
+    const double pm = r[0], dm = r[3];
     Lse p, d;
-    p.init(); d.init();
-    double mlm = 0.0, mb = -INFINITY, nm = 0, nb = 0, np_ = 0;
-    for (int w = 0; w < NW; ++w) {
-      const double* r = red + w * kNPart;
-      p.merge(r[0], r[1], r[2], r[11]);
-      d.merge(r[3], r[4], 0.0);
-      mlm = fmax(mlm, r[5]);
-      nm += r[6]; nb += r[7]; mb = fmax(mb, r[8]); np_ += r[10];
-    }
+    p.m = over(pm, -INFINITY, max_d);
+    d.m = over(dm, -INFINITY, max_d);
+    const double fp = pm == -INFINITY ? 0.0 : exp(pm - p.m), fd = dm == -INFINITY ? 0.0 : exp(dm - d.m);
+    p.s = over(r[1] * fp, 0.0, add_d);
+    p.s2 = over(r[2] * fp * fp, 0.0, add_d);
+    p.s3 = over(r[11] * fp * fp, 0.0, add_d);
+    d.s = over(r[4] * fd, 0.0, add_d);
+    const double mlm = over(r[5], 0.0, max_d), mb = over(r[8], -INFINITY, max_d);
+    const double nm = over(r[6], 0.0, add_d), nb = over(r[7], 0.0, add_d), np_ = over(r[10], 0.0, add_d);
+    if (lane != 0) return;
     // every wave's E2 has finished (barrier above): the tile maximum is final
     const double mxp = order_value(*tile_lnp_max == 0ull ? 0x000fffffffffffffull : *tile_lnp_max);
     double* out = a.partials + tile_id * kNPart;
@@ -553,7 +566,7 @@ __device__ __forceinline__ void tile_partial(const FusedArgs& a, const EvAcc& ev
 template <int PREC, int G, int MODE, bool FAST>
 __device__ __forceinline__ void fused_tile(const FusedArgs& a, unsigned char* smem, int64_t tm,
                                            int64_t tn, int64_t slot) {
-  constexpr bool EVAL = MODE == kEval;
+  static_assert(MODE == kEvidence || MODE == kPilot || MODE == kCoef, "modes of the fused kernel");
   // (h|h) outputs: a single m group has S0 only; otherwise up to 7, padded
   // to an even number of K blocks
   constexpr int NRT = (G == 1) ? 1 : kMaxNR;
@@ -1070,7 +1083,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, unsigned char* sm
   }
   // the pilot only needs pairs that can raise the running maximum
   if (MODE == kPilot) thr_ml = __longlong_as_double(a.state[0]);
-  const bool use_bound = MODE != kEval && thr_ml > 0.0;
+  const bool use_bound = thr_ml > 0.0;
   const float thr_f = (float)thr_ml;
   EvAcc ev;
   ev.init();
@@ -1220,8 +1233,8 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, unsigned char* sm
       lse.init();
       double best = -INFINITY, mlmax = 0.0;
       int ob = 0;
-      pair_phases<MODE, G>(a, lds_cs, *lds_dp, ie, e, X, S0, Sr, Si, lnw, thr_ml, gl, LPS, ev, lse,
-                           best, ob, mlmax);
+      pair_phases<MODE, G>(a, lds_cs, *lds_dp, X, S0, Sr, Si, lnw, thr_ml, gl, LPS, ev, lse, best, ob,
+                           mlmax);
 #pragma unroll
       for (int off = LPS / 2; off > 0; off >>= 1) {
         const double lm = __shfl_xor(lse.m, off, LPS), ls = __shfl_xor(lse.s, off, LPS);
@@ -1234,12 +1247,6 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, unsigned char* sm
       }
       if (gl != 0) continue;
       const double lnl = (lse.m == -INFINITY) ? -INFINITY : lse.m + log(lse.s) - a.ln_nphi;
-      if (EVAL) {
-        const size_t t = (size_t)ie * a.n_ext + e;
-        a.lnl_out[t] = lnl;
-        if (a.ml_out) a.ml_out[t] = mlmax;
-        continue;
-      }
       ev.ml_max = fmax(ev.ml_max, mlmax);
       if (MODE == kPilot || lnl == -INFINITY) continue;
       const double lnp = lnw + lnl;
@@ -1323,7 +1330,6 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, unsigned char* sm
       __syncthreads();
     });
   }
-  if (EVAL) return;
   if (MODE == kPilot) {
     double mlm = wave_max(ev.ml_max);
     if (lane == 0)

@@ -102,7 +102,7 @@ hipError_t launch_any_packed(int mode, const PackLaunch& p, int n_phi, hipStream
     case kBound: return launch_bound_packed<PREC, G>(p, s);
     case kCoef: return launch_one_packed<PREC, G, kCoef, false>(p, n_phi, s);
     case kSurvivors:
-    case kE2: return DOTPE_MARGP_NAME(DOTPE_INST_PREC, DOTPE_INST_G)(mode, p, s);
+    case kE2: return DOTPE_MARGP_NAME(DOTPE_INST_PREC, DOTPE_INST_G)(mode, p, n_phi, s);
   }
   return hipErrorInvalidValue;
 }
@@ -110,7 +110,6 @@ hipError_t launch_any_packed(int mode, const PackLaunch& p, int n_phi, hipStream
 template <int PREC, int G>
 hipError_t launch_any(int mode, bool fast, const FusedArgs& a, int64_t grid, hipStream_t s) {
   switch (mode) {
-    case kEval: return launch_one<PREC, G, kEval, false>(a, grid, s);
     case kPilot: return launch_one<PREC, G, kPilot, false>(a, grid, s);
     case kEvidence:
       // only the fast pass: without the cut every tile takes the
@@ -120,6 +119,7 @@ hipError_t launch_any(int mode, bool fast, const FusedArgs& a, int64_t grid, hip
     case kCoef: return launch_one<PREC, G, kCoef, false>(a, grid, s);
     case kSurvivors:
     case kE2:
+    case kEval:
     case kSample: return DOTPE_MARG_NAME(DOTPE_INST_PREC, DOTPE_INST_G)(mode, a, grid, s);
   }
   return hipErrorInvalidValue;

@@ -13,13 +13,13 @@
 
 namespace dotpe {
 
-// mode: kEval, kPilot, kEvidence (the fast pass: fast must be true),
-// kBound (split precisions; `grid` counts 128 x 128 tiles), kSurvivors
-// (split precisions; workgroups of 4 waves that take the listed tiles in
-// turn), kCoef or kE2 (the coefficient route: workgroups that take the
-// chunk's work items in turn), kSample (posterior draws in the listed
-// tiles, after kCoef over the same list).  Launches `grid` workgroups on stream s and
-// returns the launch status.
+// mode: kPilot, kEvidence (the fast pass: fast must be true), kBound (split
+// precisions; `grid` counts 128 x 128 tiles), kSurvivors (split precisions;
+// workgroups of 4 waves that take the listed tiles in turn), kCoef (the
+// coefficient route: workgroups that take the chunk's work items in turn) and
+// after it kE2 (evidence), kEval (every pair written out) or kSample
+// (posterior draws in the listed tiles).  Launches `grid` workgroups on
+// stream s and returns the launch status.
 typedef hipError_t (*FusedLaunchFn)(int mode, bool fast, const FusedArgs& a, int64_t grid,
                                     hipStream_t s);
 
@@ -65,7 +65,7 @@ typedef hipError_t (*PackedLaunchFn)(int mode, const PackLaunch& p, int n_phi, h
 
 #define DOTPE_PACKED_DECL(P, G)                                                            \
   hipError_t launch_packed_p##P##_g##G(int mode, const PackLaunch& p, int n_phi, hipStream_t s); \
-  hipError_t launch_marg_packed_p##P##_g##G(int mode, const PackLaunch& p, hipStream_t s);
+  hipError_t launch_marg_packed_p##P##_g##G(int mode, const PackLaunch& p, int n_phi, hipStream_t s);
 DOTPE_PACKED_DECL(0, 1)
 DOTPE_PACKED_DECL(0, 2)
 DOTPE_PACKED_DECL(0, 3)

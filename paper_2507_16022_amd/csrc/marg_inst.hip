@@ -20,6 +20,9 @@
 namespace dotpe {
 namespace {
 
+// dynamic LDS of the second half of the coefficient route: the phase table
+size_t e2_lds(int n_phi) { return sizeof(double) * kMaxM * (size_t)n_phi * 2; }
+
 template <int PREC, int G>
 hipError_t launch_marg(int mode, const FusedArgs& a, int64_t grid, hipStream_t s) {
   switch (mode) {
@@ -31,7 +34,12 @@ hipError_t launch_marg(int mode, const FusedArgs& a, int64_t grid, hipStream_t s
         return hipGetLastError();
       }
     case kE2:
-      hipLaunchKernelGGL((k_e2_tiles<PREC, G>), dim3((unsigned)grid), dim3(256), 0, s, a);
+      hipLaunchKernelGGL((k_e2_tiles<PREC, G, kEvidence>), dim3((unsigned)grid), dim3(256),
+                         e2_lds(a.n_phi), s, a);
+      return hipGetLastError();
+    case kEval:
+      hipLaunchKernelGGL((k_e2_tiles<PREC, G, kEval>), dim3((unsigned)grid), dim3(256),
+                         e2_lds(a.n_phi), s, a);
       return hipGetLastError();
     case kSample:
       {
@@ -49,7 +57,7 @@ hipError_t launch_marg(int mode, const FusedArgs& a, int64_t grid, hipStream_t s
 }
 
 template <int PREC, int G>
-hipError_t launch_marg_packed(int mode, const PackLaunch& p, hipStream_t s) {
+hipError_t launch_marg_packed(int mode, const PackLaunch& p, int n_phi, hipStream_t s) {
   const dim3 grid((unsigned)p.off[p.n]);
   switch (mode) {
     case kSurvivors:
@@ -60,7 +68,7 @@ hipError_t launch_marg_packed(int mode, const PackLaunch& p, hipStream_t s) {
         return hipGetLastError();
       }
     case kE2:
-      hipLaunchKernelGGL((k_e2_tiles_packed<PREC, G>), grid, dim3(256), 0, s, p);
+      hipLaunchKernelGGL((k_e2_tiles_packed<PREC, G>), grid, dim3(256), e2_lds(n_phi), s, p);
       return hipGetLastError();
   }
   return hipErrorInvalidValue;
@@ -78,9 +86,9 @@ hipError_t DOTPE_NAME(DOTPE_INST_PREC, DOTPE_INST_G)(int mode, const FusedArgs& 
 
 #define DOTPE_PNAME(P, G) DOTPE_CAT4(launch_marg_packed_p, P, _g, G)
 
-hipError_t DOTPE_PNAME(DOTPE_INST_PREC, DOTPE_INST_G)(int mode, const PackLaunch& p,
+hipError_t DOTPE_PNAME(DOTPE_INST_PREC, DOTPE_INST_G)(int mode, const PackLaunch& p, int n_phi,
                                                       hipStream_t s) {
-  return launch_marg_packed<DOTPE_INST_PREC, DOTPE_INST_G>(mode, p, s);
+  return launch_marg_packed<DOTPE_INST_PREC, DOTPE_INST_G>(mode, p, n_phi, s);
 }
 
 }  // namespace dotpe
