@@ -572,7 +572,7 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
         n_surv += (int)__popcll(__ballot((smask[bn] >> __builtin_ctz(m)) & 1u));
     }
   }
-  if (n_surv > kSurvCap) {
+  if (n_surv > a.surv_cap) {
     // the whole tile goes to the coefficient route
     if (lane == 0) {
       const unsigned long long k = atomicAdd((unsigned long long*)&a.state[4], 1ull);

@@ -50,8 +50,19 @@ int fail(int code, const char* fmt, ...) {
 int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
 // 128 x 128 tiles an event needs before the bound pass replaces the fused
-// kernel's fast epilogue (fewer would leave the device partly idle)
-constexpr int64_t kBoundMinTiles = 2048;
+// kernel's fast epilogue: one per CU.  The pass takes one product per operand
+// pair instead of three, on tiles four times as large; with the operand norms
+// that it needs a call of 128 tiles takes as long either way (fast 0.081,
+// bound 0.063 ms), one of 256 tiles 0.155 against 0.075 ms for the pass and
+// one of 1920 tiles 1.13 against 0.53 ms.
+// And the tiles it needs before the bound pass lists a tile's few survivors
+// for the survivor pass: with fewer, every tile with a survivor takes the
+// coefficient route, as after the fast pass.
+constexpr int64_t kBoundMinTiles = 256;
+constexpr int64_t kSurvMinTiles = 2048;
+int64_t big_tiles(int64_t n_tiles_m, int64_t n_tiles_n) {
+  return ((n_tiles_m + 1) / 2) * ((n_tiles_n + 1) / 2);
+}
 constexpr int64_t kMargPer = 256;     // tiles summed by one thread of the marginal pass
 constexpr int kNormBlocks = 256;      // block sums of (d|d) over full-resolution data
 
@@ -1424,6 +1435,7 @@ static FusedArgs pass_args(dotpe_ctx* ctx, dotpe_event* ev, double cut_delta) {
   a.surv = ev->surv;
   a.surv_list = ev->surv_list;
   a.rec_cap = 0;
+  a.surv_cap = big_tiles(a.n_tiles_m, a.n_tiles_n) >= kSurvMinTiles ? kSurvCap : 0;
   a.pilot_stride = std::max<int64_t>(1, std::min<int64_t>(64, a.n_tiles_m / 16));
   return a;
 }
@@ -1431,8 +1443,8 @@ static FusedArgs pass_args(dotpe_ctx* ctx, dotpe_event* ev, double cut_delta) {
 // The pass's decisions that the host takes from sizes alone.  The cut needs
 // a pilot over other rows of tiles than the ones it cuts; without one the
 // frozen threshold stays at zero and the cut is off.  The bound pass (128 x
-// 128 tiles, split precisions) runs when the event has enough of them to
-// fill the device, else the fused kernel's fast pass; both return at once
+// 128 tiles, split precisions) runs when the event has enough of them
+// (kBoundMinTiles), else the fused kernel's fast pass; both return at once
 // when the frozen threshold does not cut.
 struct PassPlan {
   bool may_cut = false, bound_pass = false;
@@ -1446,11 +1458,11 @@ static PassPlan pass_plan(const dotpe_event* ev, const FusedArgs& a) {
   if (p.may_cut) {
     const int64_t npr = (a.n_tiles_m + a.pilot_stride - 1) / a.pilot_stride;
     p.pilot_grid = round_up(npr * a.n_tiles_n, 8);
-    const int64_t n_big = ((a.n_tiles_m + 1) / 2) * ((a.n_tiles_n + 1) / 2);
+    const int64_t n_big = big_tiles(a.n_tiles_m, a.n_tiles_n);
     p.bound_pass = prec != kFP64 && n_big >= kBoundMinTiles &&
                    !(ev->flags & (DOTPE_FLAG_NO_BOUND_PASS | DOTPE_FLAG_RERUN_ALL));
     p.cut_grid = round_up(p.bound_pass ? n_big : a.n_tiles, 8);
-    if (p.bound_pass) p.surv_grid = std::min<int64_t>(kSurvGrid, (a.n_tiles + 3) / 4);
+    if (p.bound_pass && a.surv_cap > 0) p.surv_grid = std::min<int64_t>(kSurvGrid, (a.n_tiles + 3) / 4);
   }
   // coefficient route: chunks of coef_tiles work items, as many chunks as
   // every tile would need; the kernels of a chunk past the device's count
@@ -1573,7 +1585,7 @@ static int evidence_pass(dotpe_ctx* ctx, dotpe_event* ev, double cut_delta,
       event_norms(ev, s);
       if ((rc = launch_fused<kBound>(prec, a, pl.cut_grid, s))) return rc;
       if (timed) HIP_OK(hipEventRecord(ev->ev_t[3], s));
-      if ((rc = launch_fused<kSurvivors>(prec, a, pl.surv_grid, s))) return rc;
+      if (pl.surv_grid && (rc = launch_fused<kSurvivors>(prec, a, pl.surv_grid, s))) return rc;
     } else {
       if ((rc = launch_fused<kEvidence, true>(prec, a, pl.cut_grid, s))) return rc;
       if (timed) HIP_OK(hipEventRecord(ev->ev_t[3], s));

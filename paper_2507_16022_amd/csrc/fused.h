@@ -68,6 +68,7 @@ struct FusedArgs {
   int64_t pilot_stride;      // pilot pass: every pilot_stride-th row of tiles
   int* rerun;                // fast or bound pass: tiles left to the coefficient route
   int rec_cap;               // fast pass: survivors a tile may have (<= the record area)
+  int surv_cap;              // bound pass: survivors a tile may have and be listed (<= kSurvCap)
   // bound pass: survivors of tiles with at most kSurvCap of them, as
   // (row << 8 | column) within the tile, [n_tiles][kSurvCap]; and the list
   // of such tiles, (tile id, count) pairs, its length in state[5]
