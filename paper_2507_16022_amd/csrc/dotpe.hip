@@ -1517,15 +1517,20 @@ static int pass_tail(dotpe_event* ev, const FusedArgs& a, hipStream_t s, double*
   return DOTPE_OK;
 }
 
+// whether a pass with this state cuts (cut_on of the kernels)
+static bool cut_from_state(const uint64_t* st, double cut_delta) {
+  double thr_frozen;
+  std::memcpy(&thr_frozen, &st[3], 8);
+  return cut_delta > 0.0 && thr_frozen - cut_delta > 0.0;
+}
+
 // the pass's results from the reduced partials fo and the state st: fills
 // *out except the top-k fields and the timings, and returns the raw
 // candidate count in *n_cand
 static void pass_results(const dotpe_event* ev, const FusedArgs& a, const double* fo,
                          const uint64_t* st, dotpe_evidence_result* out, uint64_t* n_cand) {
   const double cut_delta = a.cut_delta;
-  double thr_frozen;
-  std::memcpy(&thr_frozen, &st[3], 8);
-  const bool cut = cut_delta > 0.0 && thr_frozen - cut_delta > 0.0;
+  const bool cut = cut_from_state(st, cut_delta);
   const double ln_norm = std::log(ev->n_norm) + std::log((double)ev->n_ext);
   dotpe_evidence_result r;
   std::memset(&r, 0, sizeof(r));
@@ -1563,7 +1568,7 @@ static void pass_results(const dotpe_event* ev, const FusedArgs& a, const double
 // pass (or the fused kernel's fast pass on small events) with the survivor
 // pass; then the coefficient route over the tiles those leave (every tile
 // when the cut is off), chunk by chunk; then the fixed-order finalisation.
-// The host waits once, for the results.  Fills *out except the top-k
+// The host waits for the results, and on events of many chunks for the cut.  Fills *out except the top-k
 // fields and returns the raw candidate count in *n_cand.
 static int evidence_pass(dotpe_ctx* ctx, dotpe_event* ev, double cut_delta,
                          dotpe_evidence_result* out, uint64_t* n_cand) {
@@ -1593,7 +1598,18 @@ static int evidence_pass(dotpe_ctx* ctx, dotpe_event* ev, double cut_delta,
   } else if (timed) {
     HIP_OK(hipEventRecord(ev->ev_t[3], s));
   }
-  for (int64_t c = 0; c < pl.n_chunks; ++c) {
+  // With many chunks the host waits for the cut and launches the ones it left:
+  // an empty chunk's two kernels take 10 us, the wait 15 (65536 x 4096 pairs:
+  // 32 chunks, none of them needed, 0.33 of 5.6 ms).
+  int64_t n_chunks = pl.n_chunks;
+  if (pl.may_cut && n_chunks > 2) {
+    uint64_t st_cut[6];
+    HIP_OK(hipMemcpyAsync(st_cut, ev->state, sizeof(st_cut), hipMemcpyDeviceToHost, s));
+    HIP_OK(hipStreamSynchronize(s));
+    if (cut_from_state(st_cut, cut_delta))
+      n_chunks = ((int64_t)st_cut[4] + ev->coef_tiles - 1) / ev->coef_tiles;
+  }
+  for (int64_t c = 0; c < n_chunks; ++c) {
     a.work0 = c * ev->coef_tiles;
     if ((rc = launch_fused<kCoef>(prec, a, pl.coef_grid, s))) return rc;
     if ((rc = launch_fused<kE2>(prec, a, pl.e2_grid, s))) return rc;
