@@ -24,15 +24,21 @@
 // coefficients come first,
 // folded into lo as each output completes, then the (d|h) contraction one m
 // group at a time, each group's |X_g| added into U as the group completes.
-// So a wave keeps lo, U and one group's accumulators: 64 x 64 pairs per
-// wave, a 128 x 128 tile per workgroup.
+// So a wave keeps lo, U and one group's accumulators for 64 x 32 pairs, a
+// workgroup of four waves takes 128 x 64, and two workgroups share a CU, out
+// of step with each other: the folds, the loads' latency and the bounds at the
+// end of one (more cycles than the products) run beside the products of the
+// other.  With 64 x 64 pairs per wave, one wave per SIMD, the matrix cores
+// were busy for 37% of the cycles, now for 51%; the clock falls meanwhile
+// (2.1 to 1.8 GHz), so 65536 x 4096 pairs went from 3.72 to 3.21 ms and
+// 2^20 x 16384 from 208 to 192 ms (0.90 PFLOP/s of the hi products).
 //
-// Each wave's 64 x 64 quadrant is one tile of the fused kernel's grid.  A
-// quadrant all of whose pairs are bounded writes that tile's partial (the
-// bounded mass and counts); one with a few survivors lists them for the
-// survivor pass, which adds their evaluation to the partial; one with more
-// is listed whole for the coefficient route, which bounds and evaluates the
-// tile again.
+// Two waves share one tile of the fused kernel's grid (64 x 64 pairs), a half
+// of its columns each.  A tile all of whose pairs are bounded writes its
+// partial (the bounded mass and counts); one with a few survivors lists them
+// for the survivor pass, which adds their evaluation to the partial; one with
+// more is listed whole for the coefficient route, which bounds and evaluates
+// the tile again.
 #pragma once
 
 #include "fused.h"
@@ -40,20 +46,24 @@
 namespace dotpe {
 
 struct BoundTile {
-  static constexpr int NT = 256;           // 4 waves, one per SIMD
-  static constexpr int TS = 128;           // rows and columns per tile
-  static constexpr int NS = 7;             // LDS stages
-  static constexpr int LPC = 4;            // 1 KB loads per wave per chunk
-  static constexpr int ARR = 8192;         // bytes of one operand's hi part per stage
-  static constexpr int STAGE = 2 * ARR;    // A hi, B hi
+  static constexpr int NT = 256;           // 4 waves
+  static constexpr int TM = 128, TN = 64;  // rows and columns per workgroup
+  static constexpr int NS = 6;             // LDS stages
+  static constexpr int LPC = 3;            // 1 KB loads per wave per chunk
+  static constexpr int ARR = 8192;         // bytes of A's hi part per stage
+  static constexpr int STAGE = ARR + 4096; // A hi, B hi
   static constexpr int NV = 24;            // margin factors per row or column
-  static constexpr int ROWQ_OFF = NS * STAGE;            // double2 [128]: q factor, ln w
-  static constexpr int COLQ_OFF = ROWQ_OFF + TS * 16;    // double2 [128]
-  static constexpr int ROWN_OFF = COLQ_OFF + TS * 16;    // float4 [128]: the norms of whole rows
-  static constexpr int COLN_OFF = ROWN_OFF + TS * 16;    // float4 [128]
-  static constexpr int ROWT_OFF = COLN_OFF + TS * 16;    // float [128][NV]: per group and output
-  static constexpr int COLT_OFF = ROWT_OFF + TS * NV * 4;
-  static constexpr int LDS_BYTES = COLT_OFF + TS * NV * 4;
+  static constexpr int ROWQ_OFF = NS * STAGE;            // double2 [TM]: q factor, ln w
+  static constexpr int COLQ_OFF = ROWQ_OFF + TM * 16;    // double2 [TN]
+  static constexpr int ROWN_OFF = COLQ_OFF + TN * 16;    // float4 [TM]: the norms of whole rows
+  static constexpr int COLN_OFF = ROWN_OFF + TM * 16;    // float4 [TN]
+  static constexpr int PART_OFF = COLN_OFF + TN * 16;    // float4 [4]: the waves' survivors and bounded mass
+  static constexpr int LDS_BYTES = PART_OFF + 4 * 16;
+  // the margin factors per group and output of a wave's 64 rows and 32
+  // columns, where it needs them: in the stages, once the products are done
+  static constexpr int TIGHT_BYTES = (64 + 32) * NV * 4;
+  static_assert(4 * TIGHT_BYTES <= NS * STAGE, "factors fit the stages");
+  static_assert(2 * LDS_BYTES <= 160 * 1024, "two workgroups per CU");
 };
 
 // Keep a value computed here: without it the compiler may defer the
@@ -92,9 +102,9 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
 
-  // workgroup -> 128 x 128 tile: consecutive ids spread over the XCDs, each
+  // workgroup -> 128 x 64 tile: consecutive ids spread over the XCDs, each
   // XCD walking a contiguous band of tiles in bands of 4 tile rows
-  const int64_t nst_m = (a.n_tiles_m + 1) / 2, nst_n = (a.n_tiles_n + 1) / 2;
+  const int64_t nst_m = (a.n_tiles_m + 1) / 2, nst_n = a.n_tiles_n;
   int64_t wg = wg_id;
   {
     const int64_t nwg = wg_count;   // multiple of 8
@@ -110,66 +120,80 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
     sm_ = band * GM + in % rows_in_band;
     sn_ = in / rows_in_band;
   }
-  const int64_t row0 = sm_ * BT::TS, col0 = sn_ * BT::TS;
+  const int64_t row0 = sm_ * BT::TM, col0 = sn_ * BT::TN;
 
   // per row and column: the factors of the bound (q = row_scale^2 /
   // ah_scale x the column's: powers of two, each possibly outside float
   // range, so multiplied in double; ln w) and of its margin, per group and
   // output (row: ah_g, al_g, nh_r, nl_r at 0, 4, 8, 16; column: bl_g +
   // sqrt2 gamma_g bh_g, bh_g + bl_g, c_r (ql_r + gamma_32 qh_r), c_r (qh_r +
-  // ql_r) at the same places) and the norms of those four vectors (rounded
-  // up) for the margin of whole rows
+  // ql_r) at the same places), and the norms of those four vectors (rounded
+  // up) for the margin of whole rows.  Only the norms are kept: a wave that
+  // needs the factors forms them again.
   double2* rowq = (double2*)(smem + BT::ROWQ_OFF);
   double2* colq = (double2*)(smem + BT::COLQ_OFF);
   float4* rown = (float4*)(smem + BT::ROWN_OFF);
   float4* coln = (float4*)(smem + BT::COLN_OFF);
-  float* rowt = (float*)(smem + BT::ROWT_OFF);
-  float* colt = (float*)(smem + BT::COLT_OFF);
-  {
-    const bool is_row = tid < BT::TS;
-    const int t = is_row ? tid : tid - BT::TS;
-    double2 v = make_double2(1.0, 0.0);
-    float f[BT::NV];
+  auto row_factors = [&](int t, float (&f)[BT::NV]) {
 #pragma unroll
     for (int k = 0; k < BT::NV; ++k) f[k] = 0.f;
+    const int64_t ie = row0 + t;
+    if (ie < a.n_sub) {
+      const int64_t i = a.sub_idx ? a.sub_idx[ie] : a.sub0 + ie;
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const float2 x = a.a_nrm[i * G + g];
+        f[g] = x.x;
+        f[4 + g] = x.y;
+      }
+#pragma unroll
+      for (int r = 0; r < NRT; ++r) {
+        const float2 x = a.ah_nrm[ie * NRT + r];
+        f[8 + r] = x.x;
+        f[16 + r] = x.y;
+      }
+    }
+  };
+  auto col_factors = [&](int t, float (&f)[BT::NV]) {
+#pragma unroll
+    for (int k = 0; k < BT::NV; ++k) f[k] = 0.f;
+    const int64_t e = col0 + t;
+    if (e < a.n_ext) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const float2 x = a.b_nrm[e * G + g];
+        f[g] = x.y + a.gam_dh[g] * x.x;
+        f[4 + g] = x.x + x.y;
+      }
+#pragma unroll
+      for (int r = 0; r < NRT; ++r) {
+        const float2 x = a.bh_nrm[e * NRT + r];
+        const float c = r == 0 ? 1.f : 2.f;
+        f[8 + r] = c * (x.y + a.gam_hh * x.x);
+        f[16 + r] = c * (x.x + x.y);
+      }
+    }
+  };
+  if (tid < BT::TM + BT::TN) {
+    const bool is_row = tid < BT::TM;
+    const int t = is_row ? tid : tid - BT::TM;
+    double2 v = make_double2(1.0, 0.0);
+    float f[BT::NV];
     if (is_row) {
       const int64_t ie = row0 + t;
       if (ie < a.n_sub) {
         const int64_t i = a.sub_idx ? a.sub_idx[ie] : a.sub0 + ie;
         const double rs = a.row_scale[i];
         v = make_double2(rs * rs / a.ah_scale[ie], a.ln_w_bank ? a.ln_w_bank[i] : 0.0);
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          const float2 x = a.a_nrm[i * G + g];
-          f[g] = x.x;
-          f[4 + g] = x.y;
-        }
-#pragma unroll
-        for (int r = 0; r < NRT; ++r) {
-          const float2 x = a.ah_nrm[ie * NRT + r];
-          f[8 + r] = x.x;
-          f[16 + r] = x.y;
-        }
       }
+      row_factors(t, f);
     } else {
       const int64_t e = col0 + t;
       if (e < a.n_ext) {
         const double cs = a.col_scale[e];
         v = make_double2(cs * cs / a.bh_scale[e], a.ln_w_ext ? a.ln_w_ext[e] : 0.0);
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          const float2 x = a.b_nrm[e * G + g];
-          f[g] = x.y + a.gam_dh[g] * x.x;
-          f[4 + g] = x.x + x.y;
-        }
-#pragma unroll
-        for (int r = 0; r < NRT; ++r) {
-          const float2 x = a.bh_nrm[e * NRT + r];
-          const float c = r == 0 ? 1.f : 2.f;
-          f[8 + r] = c * (x.y + a.gam_hh * x.x);
-          f[16 + r] = c * (x.x + x.y);
-        }
       }
+      col_factors(t, f);
     }
     float nv[4];
 #pragma unroll
@@ -179,71 +203,61 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
       for (int k = 0; k < nk; ++k) s += f[k0 + k] * f[k0 + k];
       nv[q] = __builtin_sqrtf(s) * (1.f + 0x1p-18f);
     }
-    float* dst = (is_row ? rowt : colt) + t * BT::NV;
-#pragma unroll
-    for (int k = 0; k < BT::NV; k += 4) *(float4*)(dst + k) = make_float4(f[k], f[k + 1], f[k + 2], f[k + 3]);
     (is_row ? rowq : colq)[t] = v;
     (is_row ? rown : coln)[t] = make_float4(nv[0], nv[1], nv[2], nv[3]);
   }
 
-  // ---- operand streams: waves 0, 1 load the A hi rows of 32-row blocks
-  // 2 w, 2 w + 1, waves 2, 3 the B hi rows of blocks 2 (w - 2), 2 (w - 2) + 1:
-  // of every chunk, slices 0 and 1 of both blocks, 1 KB each copied as it
-  // sits in HBM (fragment order).  A lane's address of block q, slice 0;
-  // slice 1 is 1 KB further.  Rows past the subset re-read the last row;
-  // columns run to the padded sample count (a multiple of 128, zero rows
-  // past n_ext). ----
-  gbyte* src_dh[2];
-  gbyte* src_hh[2];
+  // ---- operand streams: of every chunk, wave w loads slices 0 and 1 of the
+  // 32-row block w of A hi, and of B hi slice w mod 2 of block w / 2, 1 KB
+  // each copied as it sits in HBM (fragment order).  A lane's address of
+  // slice 0 of A and of its slice of B; slice 1 of A is 1 KB further.  Rows
+  // past the subset re-read the last row; columns run to the padded sample
+  // count (a multiple of 128, zero rows past n_ext). ----
+  gbyte *src_dh[2], *src_hh[2];
   auto blk = [](int64_t i, int64_t K) { return (i >> 5) * (K >> 5) * 1024 + (i & 31) * 8; };
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int r = 32 * (2 * (wave & 1) + q) + (lane & 31);
+  {
     const int64_t in_chunk = (lane >> 5) * 256;
-    if (wave < 2) {
-      const int64_t ie = min(row0 + r, a.n_sub - 1);
-      const int64_t i = a.sub_idx ? a.sub_idx[ie] : a.sub0 + ie;
-      src_dh[q] = (gbyte*)a.A0 + (blk(i, a.K2) + in_chunk) * ES;
-      src_hh[q] = (gbyte*)a.Ah0 + (blk(ie, a.KH) + in_chunk) * ES;
-    } else {
-      const int64_t e = col0 + r;
-      src_dh[q] = (gbyte*)a.B0 + (blk(e, a.K2) + in_chunk) * ES;
-      src_hh[q] = (gbyte*)a.Bh0 + (blk(e, a.KH) + in_chunk) * ES;
-    }
+    const int64_t ie = min(row0 + 32 * wave + (lane & 31), a.n_sub - 1);
+    const int64_t i = a.sub_idx ? a.sub_idx[ie] : a.sub0 + ie;
+    const int64_t e = col0 + 32 * (wave >> 1) + (lane & 31);
+    const int64_t slice = (wave & 1) * 1024;
+    src_dh[0] = (gbyte*)a.A0 + (blk(i, a.K2) + in_chunk) * ES;
+    src_hh[0] = (gbyte*)a.Ah0 + (blk(ie, a.KH) + in_chunk) * ES;
+    src_dh[1] = (gbyte*)a.B0 + (blk(e, a.K2) + in_chunk) * ES + slice;
+    src_hh[1] = (gbyte*)a.Bh0 + (blk(e, a.KH) + in_chunk) * ES + slice;
   }
   // chunks: NRT (h|h) blocks first, then the (d|h) chunks; chunk c sits in
-  // stage c mod NS, where this wave's part starts 4 KB x wave in
+  // stage c mod NS, where this wave's parts start at 2 KB x wave (A) and
+  // ARR + 1 KB x wave (B)
   const int ndh = a.n_chunks;
   const int nk = NRT + ndh;
-  const unsigned lds_wave =
-      __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lvoid*)(smem + wave * 4096));
-  // the 4 loads of chunk c (block q, slice s to stage offset (2 q + s) KB)
-  // sharing one M0 value: the immediate offset applies to the global and
-  // the LDS address alike.  The asm saves and restores M0 and waits the
-  // state an M0 write needs.
+  const unsigned lds_base = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lvoid*)smem);
+  const unsigned lds_a = lds_base + wave * 2048, lds_b = lds_base + BT::ARR + wave * 1024;
+  // the 3 loads of chunk c; the two of A share one M0 value: the immediate
+  // offset applies to the global and the LDS address alike.  The asm saves and
+  // restores M0 and waits the state an M0 write needs.
   auto issue = [&](int c) {
     gbyte* p0 = c < NRT ? src_hh[0] + (int64_t)c * 1024 * ES
                         : src_dh[0] + (int64_t)(c - NRT) * 1024 * ES;
     gbyte* p1 = c < NRT ? src_hh[1] + (int64_t)c * 1024 * ES
                         : src_dh[1] + (int64_t)(c - NRT) * 1024 * ES;
-    const unsigned base = lds_wave + (unsigned)((c % NS) * BT::STAGE);
+    const unsigned st = (unsigned)((c % NS) * BT::STAGE);
     unsigned m0_saved;
     __asm__ __volatile__(
         "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-        "global_load_lds_dwordx4 %2, off\n\t"
-        "global_load_lds_dwordx4 %2, off offset:1024\n\t"
-        "global_load_lds_dwordx4 %3, off offset:2048\n\t"
-        "global_load_lds_dwordx4 %3, off offset:3072\n\ts_mov_b32 m0, %0"
+        "global_load_lds_dwordx4 %3, off\n\t"
+        "global_load_lds_dwordx4 %3, off offset:1024\n\t"
+        "s_mov_b32 m0, %2\n\ts_nop 0\n\t"
+        "global_load_lds_dwordx4 %4, off\n\ts_mov_b32 m0, %0"
         : "=&s"(m0_saved)
-        : "s"(__builtin_amdgcn_readfirstlane(base)), "v"(p0), "v"(p1 - 2048)
+        : "s"(__builtin_amdgcn_readfirstlane(lds_a + st)),
+          "s"(__builtin_amdgcn_readfirstlane(lds_b + st)), "v"(p0), "v"(p1)
         : "memory");
   };
 
   // Fragments of one chunk for this wave: A rows 64 wm + 32 bm (FA: [bm]
-  // [slice]) and B rows 64 wn + 32 bn (FB: [slice], one per bn).  The
-  // products of a chunk run in two halves, bn = 0 then bn = 1.  During the
-  // first half the bn = 1 fragments of the same chunk are read, and the A
-  // and bn = 0 fragments of the next chunk.
+  // [slice]) and B rows 32 wn (FB: [slice]); while a chunk's products run the
+  // next one's are read.
   struct FA {
     uint4 v[2][2];
   };
@@ -251,22 +265,22 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
     uint4 v[2];
   };
   FA fa0, fa1;
-  FB fb0_0, fb0_1, fb1;
+  FB fb0, fb1;
   auto fa = [&](auto pi) -> FA& {
     if constexpr (decltype(pi)::value % 2 == 0) return fa0;
     else return fa1;
   };
-  auto fb0 = [&](auto pi) -> FB& {
-    if constexpr (decltype(pi)::value % 2 == 0) return fb0_0;
-    else return fb0_1;
+  auto fb = [&](auto pi) -> FB& {
+    if constexpr (decltype(pi)::value % 2 == 0) return fb0;
+    else return fb1;
   };
   auto stage_lane = [&](int c) { return smem + (c % NS) * BT::STAGE + lane * 16; };
-  auto read_a = [&](FA& f, int c, int k) {    // k: block (k >> 1), slice
-    const int bm = k >> 1, sl = k & 1;
-    f.v[bm][sl] = *(const uint4*)(stage_lane(c) + (2 * (2 * wm + bm) + sl) * 1024);
-  };
-  auto read_b = [&](FB& f, int c, int bn, int sl) {
-    f.v[sl] = *(const uint4*)(stage_lane(c) + BT::ARR + (2 * (2 * wn + bn) + sl) * 1024);
+  // read k of a chunk's six: A block k / 2, slice k mod 2, then B's slices
+  auto read_frag = [&](FA& f, FB& b, int c, int k) {
+    if (k < 4)
+      f.v[k >> 1][k & 1] = *(const uint4*)(stage_lane(c) + (4 * wm + k) * 1024);
+    else
+      b.v[k - 4] = *(const uint4*)(stage_lane(c) + BT::ARR + (2 * wn + k - 4) * 1024);
   };
   auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
 
@@ -274,17 +288,16 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
   // j + 1 and j + 2 have landed (every wave's loads) and every wave is done
   // with chunks j - 2 and j - 1, and issue chunks j + NS - 2, j + NS - 1 into
   // the stages those used (a barrier every second chunk); then the products
-  // of chunk j (NH per half; mf(fa, fb, bm, bn, k) issues product k of block
-  // (bm, bn)) with the fragment reads between them.  After the last chunk
-  // the reads fetch a stale stage, unused, so no branch sits between the
-  // products.
+  // of chunk j (NH per block; mf(fa, fb, bm, k) issues product k of block bm)
+  // with the fragment reads between them.  After the last chunk the reads
+  // fetch a stale stage, unused, so no branch sits between the products.
   auto step = [&](int j, auto pi, auto nh, auto&& mf) {
     constexpr int P = decltype(pi)::value % 2;
     constexpr int NH = decltype(nh)::value;
     FA& acur = fa(std::integral_constant<int, P>{});
     FA& anxt = fa(std::integral_constant<int, P + 1>{});
-    FB& bcur = fb0(std::integral_constant<int, P>{});
-    FB& bnxt = fb0(std::integral_constant<int, P + 1>{});
+    FB& bcur = fb(std::integral_constant<int, P>{});
+    FB& bnxt = fb(std::integral_constant<int, P + 1>{});
     if constexpr (P == 0) {
       // chunks j + 3 .. min(j + NS - 3, nk - 1) may stay in flight
       barrier_in_flight<NS - 3, LPC>(max(0, min(NS - 5, nk - 3 - j)));
@@ -293,99 +306,76 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
       if (j + NS - 1 < nk) issue(j + NS - 1);
       fence();
     }
-    // half 0: blocks (0, 0), (1, 0), a read after each of its products
     static_for<2 * NH>([&](auto ti) {
       constexpr int t = decltype(ti)::value;
-      mf(acur, bcur, t & 1, 0, t >> 1);
-      if constexpr (t < 2) read_b(fb1, j, 1, t);
-      else if constexpr (t < 6) read_a(anxt, j + 1, t - 2);
-      else if constexpr (t < 8) read_b(bnxt, j + 1, 0, t - 6);
+      mf(acur, bcur, t & 1, t >> 1);
+      if constexpr (t < 6) read_frag(anxt, bnxt, j + 1, t);
     });
-    static_for<8>([&](auto ki) {     // reads not placed between products
+    static_for<6>([&](auto ki) {     // reads not placed between products
       constexpr int k = decltype(ki)::value;
-      if constexpr (k >= 2 * NH) {
-        if constexpr (k < 2) read_b(fb1, j, 1, k);
-        else if constexpr (k < 6) read_a(anxt, j + 1, k - 2);
-        else read_b(bnxt, j + 1, 0, k - 6);
-      }
-    });
-    // half 1: blocks (0, 1), (1, 1)
-    static_for<2 * NH>([&](auto ti) {
-      constexpr int t = decltype(ti)::value;
-      mf(acur, fb1, t & 1, 1, t >> 1);
+      if constexpr (k >= 2 * NH) read_frag(anxt, bnxt, j + 1, k);
     });
   };
 
-  // prologue: chunks 0 .. NS - 3 in flight; once chunk 0 has landed, its A
-  // and bn = 0 fragments are read
+  // prologue: chunks 0 .. NS - 3 in flight; once chunk 0 has landed, its
+  // fragments are read
 #pragma unroll
   for (int c = 0; c < NS - 2; ++c)
     if (c < nk) issue(c);
-  barrier_in_flight<NS - 3, LPC>(min(NS - 3, nk - 1));   // (also makes rowq .. colt visible)
-  static_for<4>([&](auto ki) { read_a(fa0, 0, decltype(ki)::value); });
-  static_for<2>([&](auto ki) { read_b(fb0_0, 0, 0, decltype(ki)::value); });
+  barrier_in_flight<NS - 3, LPC>(min(NS - 3, nk - 1));   // (also makes rowq .. coln visible)
+  static_for<6>([&](auto ki) { read_frag(fa0, fb0, 0, decltype(ki)::value); });
 
   // ---- (h|h): lo0 = S0 - 2 sum |S_delta| per pair, output by output ----
-  Acc s0[2][2], sabs[2][2], sre[2][2], hacc[2][2];
-  auto mf_hh = [&](const FA& A, const FB& B, int bm, int bn, int k) {   // k: slice
-    mma<PREC>(hacc[bm][bn], A.v[bm][k], B.v[k]);
+  Acc s0[2], sabs[2], sre[2], hacc[2];
+  auto mf_hh = [&](const FA& A, const FB& B, int bm, int k) {   // k: slice
+    mma<PREC>(hacc[bm], A.v[bm][k], B.v[k]);
   };
   static_for<NRT>([&](auto ri) {
     constexpr int r = decltype(ri)::value;
 #pragma unroll
-    for (int bm = 0; bm < 2; ++bm)
-#pragma unroll
-      for (int bn = 0; bn < 2; ++bn) hacc[bm][bn] = Acc{};
+    for (int bm = 0; bm < 2; ++bm) hacc[bm] = Acc{};
     step(r, std::integral_constant<int, r>{}, std::integral_constant<int, 2>{}, mf_hh);
 #pragma unroll
-    for (int bm = 0; bm < 2; ++bm)
+    for (int bm = 0; bm < 2; ++bm) {
+      if constexpr (r == 0) {
+        s0[bm] = hacc[bm];
+        sabs[bm] = Acc{};
+      } else if constexpr (r % 2 == 1) {
+        sre[bm] = hacc[bm];
+      } else {
 #pragma unroll
-      for (int bn = 0; bn < 2; ++bn) {
-        if constexpr (r == 0) {
-          s0[bm][bn] = hacc[bm][bn];
-          sabs[bm][bn] = Acc{};
-        } else if constexpr (r % 2 == 1) {
-          sre[bm][bn] = hacc[bm][bn];
-        } else {
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const float x = sre[bm][bn][e], y = hacc[bm][bn][e];
-            sabs[bm][bn][e] += 2.f * __builtin_amdgcn_sqrtf(x * x + y * y);
-          }
-          pin(sabs[bm][bn]);
+        for (int e = 0; e < 16; ++e) {
+          const float x = sre[bm][e], y = hacc[bm][e];
+          sabs[bm][e] += 2.f * __builtin_amdgcn_sqrtf(x * x + y * y);
         }
+        pin(sabs[bm]);
       }
+    }
   });
   // lo0 with a margin for the rounding of the fold itself
-  Acc lo0[2][2];
+  Acc lo0[2];
 #pragma unroll
-  for (int bm = 0; bm < 2; ++bm)
+  for (int bm = 0; bm < 2; ++bm) {
 #pragma unroll
-    for (int bn = 0; bn < 2; ++bn)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float x = s0[bm][bn][e], sa = sabs[bm][bn][e];
-        lo0[bm][bn][e] = (x - sa) - 2e-5f * (fabsf(x) + sa);
-      }
-#pragma unroll
-  for (int bm = 0; bm < 2; ++bm)
-#pragma unroll
-    for (int bn = 0; bn < 2; ++bn) pin(lo0[bm][bn]);
+    for (int e = 0; e < 16; ++e) {
+      const float x = s0[bm][e], sa = sabs[bm][e];
+      lo0[bm][e] = (x - sa) - 2e-5f * (fabsf(x) + sa);
+    }
+    pin(lo0[bm]);
+  }
 
   // ---- (d|h): one m group at a time, |X_g| into U0 ----
-  Acc u0[2][2], acc[2][2][2];
+  Acc u0[2], acc[2][2];
 #pragma unroll
-  for (int bm = 0; bm < 2; ++bm)
-#pragma unroll
-    for (int bn = 0; bn < 2; ++bn) u0[bm][bn] = Acc{};
-  // product k (0..3) of block (bm, bn): with A = [hr | hi] and B_re =
-  // [Br | -Bi] by slice, B_im = [Bi | Br] = [-(B_re slice 1) | B_re slice 0]
+  for (int bm = 0; bm < 2; ++bm) u0[bm] = Acc{};
+  // product k (0..3) of block bm: with A = [hr | hi] and B_re = [Br | -Bi] by
+  // slice, B_im = [Bi | Br] = [-(B_re slice 1) | B_re slice 0]
   auto neg = [](const uint4& x) {
     return make_uint4(x.x ^ 0x80008000u, x.y ^ 0x80008000u, x.z ^ 0x80008000u, x.w ^ 0x80008000u);
   };
-  auto mf_dh = [&](const FA& A, const FB& B, int bm, int bn, int k) {
-    Acc& re = acc[bm][bn][0];
-    Acc& im = acc[bm][bn][1];
+  auto mf_dh = [&](const FA& A, const FB& B, int bm, int k) {
+    Acc& re = acc[bm][0];
+    Acc& im = acc[bm][1];
     switch (k) {
       case 0: mma<PREC>(re, A.v[bm][0], B.v[0]); break;
       case 1: mma<PREC>(im, A.v[bm][0], neg(B.v[1])); break;
@@ -397,12 +387,10 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
   static_for<G>([&](auto gi) {
     constexpr int g = decltype(gi)::value;
 #pragma unroll
-    for (int bm = 0; bm < 2; ++bm)
-#pragma unroll
-      for (int bn = 0; bn < 2; ++bn) {
-        acc[bm][bn][0] = Acc{};
-        acc[bm][bn][1] = Acc{};
-      }
+    for (int bm = 0; bm < 2; ++bm) {
+      acc[bm][0] = Acc{};
+      acc[bm][1] = Acc{};
+    }
     // each group spans a multiple of 4 chunks, so the fragment parity of
     // every step is static
     const int gend = a.mt.gk0[g + 1];
@@ -412,26 +400,27 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
            mf_dh);
     }
 #pragma unroll
-    for (int bm = 0; bm < 2; ++bm)
+    for (int bm = 0; bm < 2; ++bm) {
 #pragma unroll
-      for (int bn = 0; bn < 2; ++bn)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const float xr = acc[bm][bn][0][e], xi = acc[bm][bn][1][e];
-          u0[bm][bn][e] += __builtin_amdgcn_sqrtf(xr * xr + xi * xi);
-        }
-#pragma unroll
-    for (int bm = 0; bm < 2; ++bm)
-#pragma unroll
-      for (int bn = 0; bn < 2; ++bn) pin(u0[bm][bn]);
+      for (int e = 0; e < 16; ++e) {
+        const float xr = acc[bm][0][e], xi = acc[bm][1][e];
+        u0[bm][e] += __builtin_amdgcn_sqrtf(xr * xr + xi * xi);
+      }
+      pin(u0[bm]);
+    }
   });
 
-  // ---- bound every pair of this wave's tile ----
-  const int64_t tm = 2 * sm_ + wm, tn = 2 * sn_ + wn;
-  if (tm >= a.n_tiles_m || tn >= a.n_tiles_n) return;
+  // ---- bound every pair of this wave's half (columns 32 wn on) of its tile ----
+  __syncthreads();     // (the stages are free)
+  const int64_t tm = 2 * sm_ + wm, tn = sn_;
+  const bool tile_in = tm < a.n_tiles_m;
   const int64_t tile_id = tm * a.n_tiles_n + tn;
-  const int rows_in = (int)min((int64_t)64, a.n_sub - tm * 64);
+  const int rows_in = tile_in ? (int)min((int64_t)64, a.n_sub - tm * 64) : 0;
   const int cols_in = (int)min((int64_t)64, a.n_ext - tn * 64);
+  const int tc = 32 * wn + (lane & 31);
+  const double2 cq = colq[tc];
+  const float4 cn = coln[tc];
+  const bool col_in = tc < cols_in;
   // bound from the accumulators and a margin (q, ln w of the pair's row and
   // column in rq, cq)
   auto bound_of = [](double2 rq, double2 cq, float U0, float lo) {
@@ -454,34 +443,42 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
       f[k] = v.x; f[k + 1] = v.y; f[k + 2] = v.z; f[k + 3] = v.w;
     }
   };
+  // the factors of the wave's 64 rows, to its part of the stages, and of its
+  // lanes' columns
+  float* rowt = (float*)(smem + wave * BT::TIGHT_BYTES);
+  auto tight_factors = [&](float (&ct)[BT::NV]) {
+    float f[BT::NV];
+    row_factors(64 * wm + lane, f);
+#pragma unroll
+    for (int k = 0; k < BT::NV; k += 4)
+      *(float4*)(rowt + lane * BT::NV + k) = make_float4(f[k], f[k + 1], f[k + 2], f[k + 3]);
+    col_factors(tc, ct);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  auto row_of = [&](int bm, int e) { return 32 * bm + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3); };
   if (a.bound_out) {
     const int64_t plane = a.n_sub * a.n_ext;
+    float ct[BT::NV];
+    tight_factors(ct);
 #pragma unroll
     for (int bm = 0; bm < 2; ++bm)
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const int tr = 32 * bm + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+        const int tr = row_of(bm, e);
         const double2 rq = rowq[64 * wm + tr];
         const float4 rn = rown[64 * wm + tr];
         float rt[BT::NV];
-        load_nv(rowt + (64 * wm + tr) * BT::NV, rt);
-#pragma unroll
-        for (int bn = 0; bn < 2; ++bn) {
-          const int tc = 32 * bn + (lane & 31);
-          if (tr >= rows_in || tc >= cols_in) continue;
-          const double2 cq = colq[64 * wn + tc];
-          const float4 cn = coln[64 * wn + tc];
-          float ct[BT::NV];
-          load_nv(colt + (64 * wn + tc) * BT::NV, ct);
-          float du, dl;
-          tight(rt, ct, du, dl);
-          const float U0 = u0[bm][bn][e], lo = lo0[bm][bn][e];
-          const float Ul = U0 + (rn.x * cn.x + rn.y * cn.y), ll = lo - (rn.z * cn.z + rn.w * cn.w);
-          const float Ut = U0 + du, lt = lo - dl;
-          const int64_t o = (tm * 64 + tr) * a.n_ext + tn * 64 + tc;
-          a.bound_out[o] = ll > 0.f ? bound_of(rq, cq, Ul, ll) : INFINITY;
-          a.bound_out[plane + o] = lt > 0.f ? bound_of(rq, cq, Ut, lt) : INFINITY;
-        }
+        load_nv(rowt + tr * BT::NV, rt);
+        if (tr >= rows_in || !col_in) continue;
+        float du, dl;
+        tight(rt, ct, du, dl);
+        const float U0 = u0[bm][e], lo = lo0[bm][e];
+        const float Ul = U0 + (rn.x * cn.x + rn.y * cn.y), ll = lo - (rn.z * cn.z + rn.w * cn.w);
+        const float Ut = U0 + du, lt = lo - dl;
+        const int64_t o = (tm * 64 + tr) * a.n_ext + tn * 64 + tc;
+        a.bound_out[o] = ll > 0.f ? bound_of(rq, cq, Ul, ll) : INFINITY;
+        a.bound_out[plane + o] = lt > 0.f ? bound_of(rq, cq, Ut, lt) : INFINITY;
       }
     return;
   }
@@ -491,90 +488,78 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
   // weight plus its largest column weight, so each term exp(lw + bound -
   // m_ref) is at most 1 and a plain float sum holds them (its rounding, at
   // most ~1e-5 relative here, is far inside the bound's e^0.001 margin).
-  const float lw_max = wave_max((double)rowq[64 * wm + lane].y) + wave_max((double)colq[64 * wn + lane].y);
+  const float lw_max = wave_max((double)rowq[64 * wm + lane].y) + wave_max((double)colq[lane].y);
   const float m_ref = thr_f + lw_max;
   float dsum = 0.f, max_bound = -INFINITY;
   // first with the margin of whole rows; pairs it leaves (bit 16 bm + e of
-  // tmask[bn]) with the margin per group and output; survivors of both in
-  // smask
-  unsigned tmask[2] = {0u, 0u}, smask[2] = {0u, 0u};
-  double2 cq[2];
-  float4 cn[2];
-  bool col_in[2];
-#pragma unroll
-  for (int bn = 0; bn < 2; ++bn) {
-    const int tc = 32 * bn + (lane & 31);
-    cq[bn] = colq[64 * wn + tc];
-    cn[bn] = coln[64 * wn + tc];
-    col_in[bn] = tc < cols_in;
-  }
+  // tmask) with the margin per group and output; survivors of both in smask
+  unsigned tmask = 0u, smask = 0u;
 #pragma unroll
   for (int bm = 0; bm < 2; ++bm)
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const int tr = 32 * bm + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+      const int tr = row_of(bm, e);
       const double2 rq = rowq[64 * wm + tr];
       const float4 rn = rown[64 * wm + tr];
-#pragma unroll
-      for (int bn = 0; bn < 2; ++bn) {
-        const bool in = col_in[bn] && tr < rows_in;
-        const float U0 = u0[bm][bn][e] + (rn.x * cn[bn].x + rn.y * cn[bn].y);
-        const float lo = lo0[bm][bn][e] - (rn.z * cn[bn].z + rn.w * cn[bn].w);
-        const float bound = bound_of(rq, cq[bn], U0, lo);
-        const bool bounded = in && lo > 0.f && bound < thr_f;
-        const float x = (float)(rq.y + cq[bn].y) + bound;
-        dsum += bounded ? __expf(x - m_ref) : 0.f;
-        max_bound = bounded ? fmaxf(max_bound, x) : max_bound;
-        tmask[bn] |= (in && !bounded) ? 1u << (16 * bm + e) : 0u;
-      }
+      const bool in = col_in && tr < rows_in;
+      const float U0 = u0[bm][e] + (rn.x * cn.x + rn.y * cn.y);
+      const float lo = lo0[bm][e] - (rn.z * cn.z + rn.w * cn.w);
+      const float bound = bound_of(rq, cq, U0, lo);
+      const bool bounded = in && lo > 0.f && bound < thr_f;
+      const float x = (float)(rq.y + cq.y) + bound;
+      dsum += bounded ? __expf(x - m_ref) : 0.f;
+      max_bound = bounded ? fmaxf(max_bound, x) : max_bound;
+      tmask |= (in && !bounded) ? 1u << (16 * bm + e) : 0u;
     }
-  if (__ballot((tmask[0] | tmask[1]) != 0u)) {
-    float ct[2][BT::NV];
-#pragma unroll
-    for (int bn = 0; bn < 2; ++bn) load_nv(colt + (64 * wn + 32 * bn + (lane & 31)) * BT::NV, ct[bn]);
+  if (__ballot(tmask != 0u)) {
+    float ct[BT::NV];
+    tight_factors(ct);
 #pragma unroll
     for (int bm = 0; bm < 2; ++bm)
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const unsigned bit = 1u << (16 * bm + e);
-        if (!__ballot(((tmask[0] | tmask[1]) & bit) != 0u)) continue;
-        const int tr = 32 * bm + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+        if (!__ballot((tmask & bit) != 0u)) continue;
+        const int tr = row_of(bm, e);
         const double2 rq = rowq[64 * wm + tr];
         float rt[BT::NV];
-        load_nv(rowt + (64 * wm + tr) * BT::NV, rt);
-#pragma unroll
-        for (int bn = 0; bn < 2; ++bn) {
-          if (!(tmask[bn] & bit)) continue;
-          float du, dl;
-          tight(rt, ct[bn], du, dl);
-          const float lo = lo0[bm][bn][e] - dl;
-          const float bound = bound_of(rq, cq[bn], u0[bm][bn][e] + du, lo);
-          if (lo > 0.f && bound < thr_f) {
-            const float x = (float)(rq.y + cq[bn].y) + bound;
-            dsum += __expf(x - m_ref);
-            max_bound = fmaxf(max_bound, x);
-          } else {
-            smask[bn] |= bit;
-          }
+        load_nv(rowt + tr * BT::NV, rt);
+        if (!(tmask & bit)) continue;
+        float du, dl;
+        tight(rt, ct, du, dl);
+        const float lo = lo0[bm][e] - dl;
+        const float bound = bound_of(rq, cq, u0[bm][e] + du, lo);
+        if (lo > 0.f && bound < thr_f) {
+          const float x = (float)(rq.y + cq.y) + bound;
+          dsum += __expf(x - m_ref);
+          max_bound = fmaxf(max_bound, x);
+        } else {
+          smask |= bit;
         }
       }
   }
-  // survivors in a fixed order (bn, bm, element, lane): only the (bn, bit)
-  // columns in which some lane has one are visited
-  int n_surv = 0;
-  unsigned cols[2] = {0u, 0u};
-  if (__ballot((smask[0] | smask[1]) != 0u)) {
+  // survivors in a fixed order (column half, bm, element, lane): only the
+  // bits in which some lane has one are visited
+  int my_surv = 0;
+  unsigned bits = 0u;
+  if (__ballot(smask != 0u)) {
     auto or_i = [](int x, int y) { return x | y; };
-#pragma unroll
-    for (int bn = 0; bn < 2; ++bn) {
-      cols[bn] = (unsigned)__builtin_amdgcn_readlane(wave_reduce((int)smask[bn], 0, or_i), 63);
-      for (unsigned m = cols[bn]; m; m &= m - 1u)
-        n_surv += (int)__popcll(__ballot((smask[bn] >> __builtin_ctz(m)) & 1u));
-    }
+    bits = (unsigned)__builtin_amdgcn_readlane(wave_reduce((int)smask, 0, or_i), 63);
+    for (unsigned m = bits; m; m &= m - 1u)
+      my_surv += (int)__popcll(__ballot((smask >> __builtin_ctz(m)) & 1u));
   }
+  const float w_mb = wave_reduce(max_bound, (float)-INFINITY, [](float x, float y) { return fmaxf(x, y); });
+  const float w_ds = wave_reduce(dsum, 0.f, [](float x, float y) { return x + y; });
+  // the tile's two halves together
+  float4* part = (float4*)(smem + BT::PART_OFF);
+  if (lane == 63) part[wave] = make_float4(__int_as_float(my_surv), w_ds, w_mb, 0.f);
+  __syncthreads();
+  if (!tile_in) return;
+  const float4 p0 = part[2 * wm], p1 = part[2 * wm + 1];
+  const int n_first = __float_as_int(p0.x), n_surv = n_first + __float_as_int(p1.x);
   if (n_surv > a.surv_cap) {
     // the whole tile goes to the coefficient route
-    if (lane == 0) {
+    if (lane == 0 && wn == 0) {
       const unsigned long long k = atomicAdd((unsigned long long*)&a.state[4], 1ull);
       a.rerun[k] = (int)tile_id;
     }
@@ -584,50 +569,44 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
     // listed one by one for the survivor pass, which adds their evaluation
     // to the partial written below
     uint16_t* rec = a.surv + tile_id * kSurvCap;
-    int run = 0;
-#pragma unroll
-    for (int bn = 0; bn < 2; ++bn)
-      for (unsigned m = cols[bn]; m; m &= m - 1u) {
-        const int q = __builtin_ctz(m);
-        const unsigned long long bal = __ballot((smask[bn] >> q) & 1u);
-        if ((smask[bn] >> q) & 1u) {
-          const int slot = run + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32),
-                                                                __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
-          const int bm = q >> 4, e = q & 15;
-          const int tr = 32 * bm + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-          const int tc = 32 * bn + (lane & 31);
-          rec[slot] = (uint16_t)((tr << 8) | tc);
-        }
-        run += (int)__popcll(bal);
+    int run = wn ? n_first : 0;
+    for (unsigned m = bits; m; m &= m - 1u) {
+      const int q = __builtin_ctz(m);
+      const unsigned long long bal = __ballot((smask >> q) & 1u);
+      if ((smask >> q) & 1u) {
+        const int slot = run + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+        rec[slot] = (uint16_t)((row_of(q >> 4, q & 15) << 8) | tc);
       }
-    if (lane == 0) {
+      run += (int)__popcll(bal);
+    }
+    if (lane == 0 && wn == 0) {
       const unsigned long long k = atomicAdd((unsigned long long*)&a.state[5], 1ull);
       a.surv_list[2 * k] = (int)tile_id;
       a.surv_list[2 * k + 1] = n_surv;
     }
   }
   // the tile's partial: bounded mass (m_ref, sum), counts, largest bound
-  const float w_mb = wave_reduce(max_bound, (float)-INFINITY, [](float x, float y) { return fmaxf(x, y); });
-  const float w_ds = wave_reduce(dsum, 0.f, [](float x, float y) { return x + y; });
-  if (lane == 63) {
+  if (lane == 0 && wn == 0) {
     const int n_in = rows_in * cols_in;
+    const float ds = p0.y + p1.y;
     double* out = a.partials + tile_id * kNPart;
     out[0] = -INFINITY; out[1] = 0.0; out[2] = 0.0;          // no pair evaluated (yet)
-    out[3] = w_ds > 0.f ? (double)m_ref : -INFINITY;
-    out[4] = w_ds > 0.f ? (double)w_ds : 0.0;
+    out[3] = ds > 0.f ? (double)m_ref : -INFINITY;
+    out[4] = ds > 0.f ? (double)ds : 0.0;
     out[5] = 0.0; out[6] = 0.0; out[7] = (double)(n_in - n_surv);
-    out[8] = (double)w_mb; out[9] = -INFINITY; out[10] = (double)n_in; out[11] = 0.0;
+    out[8] = (double)fmaxf(p0.z, p1.z); out[9] = -INFINITY; out[10] = (double)n_in; out[11] = 0.0;
   }
 }
 
 template <int PREC, int G>
-__global__ __launch_bounds__(BoundTile::NT) void k_lnl_bound(FusedArgs a) {
+__global__ __launch_bounds__(BoundTile::NT, 2) void k_lnl_bound(FusedArgs a) {
   bound_pass_tile<PREC, G>(a, blockIdx.x, gridDim.x);
 }
 
 // the bound pass of several events in one launch
 template <int PREC, int G>
-__global__ __launch_bounds__(BoundTile::NT) void k_lnl_bound_packed(PackLaunch p) {
+__global__ __launch_bounds__(BoundTile::NT, 2) void k_lnl_bound_packed(PackLaunch p) {
   int64_t blk, nblk;
   int q;
   const int e = pack_locate(p, blockIdx.x, &blk, &nblk, &q);

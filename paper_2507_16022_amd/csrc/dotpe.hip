@@ -63,6 +63,8 @@ constexpr int64_t kSurvMinTiles = 2048;
 int64_t big_tiles(int64_t n_tiles_m, int64_t n_tiles_n) {
   return ((n_tiles_m + 1) / 2) * ((n_tiles_n + 1) / 2);
 }
+// the bound pass's workgroups, 128 rows x 64 columns each
+int64_t bound_wgs(int64_t n_tiles_m, int64_t n_tiles_n) { return (n_tiles_m + 1) / 2 * n_tiles_n; }
 constexpr int64_t kMargPer = 256;     // tiles summed by one thread of the marginal pass
 constexpr int kNormBlocks = 256;      // block sums of (d|d) over full-resolution data
 
@@ -1461,7 +1463,7 @@ static PassPlan pass_plan(const dotpe_event* ev, const FusedArgs& a) {
     const int64_t n_big = big_tiles(a.n_tiles_m, a.n_tiles_n);
     p.bound_pass = prec != kFP64 && n_big >= kBoundMinTiles &&
                    !(ev->flags & (DOTPE_FLAG_NO_BOUND_PASS | DOTPE_FLAG_RERUN_ALL));
-    p.cut_grid = round_up(p.bound_pass ? n_big : a.n_tiles, 8);
+    p.cut_grid = round_up(p.bound_pass ? bound_wgs(a.n_tiles_m, a.n_tiles_n) : a.n_tiles, 8);
     if (p.bound_pass && a.surv_cap > 0) p.surv_grid = std::min<int64_t>(kSurvGrid, (a.n_tiles + 3) / 4);
   }
   // coefficient route: chunks of coef_tiles work items, as many chunks as
@@ -2533,8 +2535,7 @@ int dotpe_debug_bound(dotpe_ctx* ctx, dotpe_event* ev, float* out) {
   if (rc) return rc;
   a.bound_out = buf;
   event_norms(ev, ev->stream);
-  const int64_t n_big = ((a.n_tiles_m + 1) / 2) * ((a.n_tiles_n + 1) / 2);
-  rc = launch_fused<kBound>(prec, a, round_up(n_big, 8), ev->stream);
+  rc = launch_fused<kBound>(prec, a, round_up(bound_wgs(a.n_tiles_m, a.n_tiles_n), 8), ev->stream);
   hipError_t e = rc ? hipSuccess : hipMemcpyAsync(out, buf, n, hipMemcpyDeviceToHost, ev->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ev->stream);
   (void)hipFree(buf);

@@ -14,7 +14,7 @@
 namespace dotpe {
 
 // mode: kPilot, kEvidence (the fast pass: fast must be true), kBound (split
-// precisions; `grid` counts 128 x 128 tiles), kSurvivors (split precisions;
+// precisions; `grid` counts 128 x 64 tiles), kSurvivors (split precisions;
 // workgroups of 4 waves that take the listed tiles in turn), kCoef (the
 // coefficient route: workgroups that take the chunk's work items in turn) and
 // after it kE2 (evidence), kEval (every pair written out) or kSample
