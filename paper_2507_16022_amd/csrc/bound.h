@@ -30,8 +30,8 @@
 // end of one (more cycles than the products) run beside the products of the
 // other.  With 64 x 64 pairs per wave, one wave per SIMD, the matrix cores
 // were busy for 37% of the cycles, now for 51%; the clock falls meanwhile
-// (2.1 to 1.8 GHz), so 65536 x 4096 pairs went from 3.72 to 3.21 ms and
-// 2^20 x 16384 from 208 to 192 ms (0.90 PFLOP/s of the hi products).
+// (2.1 to 1.8 GHz), so 65536 x 4096 pairs went from 3.72 to 3.15 ms and
+// 2^20 x 16384 from 208 to 188 ms (0.92 PFLOP/s of the hi products).
 //
 // Two waves share one tile of the fused kernel's grid (64 x 64 pairs), a half
 // of its columns each.  A tile all of whose pairs are bounded writes its
@@ -233,14 +233,11 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
   const int nk = NRT + ndh;
   const unsigned lds_base = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lvoid*)smem);
   const unsigned lds_a = lds_base + wave * 2048, lds_b = lds_base + BT::ARR + wave * 1024;
-  // the 3 loads of chunk c; the two of A share one M0 value: the immediate
-  // offset applies to the global and the LDS address alike.  The asm saves and
-  // restores M0 and waits the state an M0 write needs.
-  auto issue = [&](int c) {
-    gbyte* p0 = c < NRT ? src_hh[0] + (int64_t)c * 1024 * ES
-                        : src_dh[0] + (int64_t)(c - NRT) * 1024 * ES;
-    gbyte* p1 = c < NRT ? src_hh[1] + (int64_t)c * 1024 * ES
-                        : src_dh[1] + (int64_t)(c - NRT) * 1024 * ES;
+  // the 3 loads of an (h|h) block or a (d|h) chunk into stage c mod NS; the two
+  // of A share one M0 value: the immediate offset applies to the global and
+  // the LDS address alike.  The asm saves and restores M0 and waits the state
+  // an M0 write needs.
+  auto issue_from = [&](gbyte* p0, gbyte* p1, int c) {
     const unsigned st = (unsigned)((c % NS) * BT::STAGE);
     unsigned m0_saved;
     __asm__ __volatile__(
@@ -253,6 +250,21 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
         : "s"(__builtin_amdgcn_readfirstlane(lds_a + st)),
           "s"(__builtin_amdgcn_readfirstlane(lds_b + st)), "v"(p0), "v"(p1)
         : "memory");
+  };
+  // chunk c where its kind is known when compiled, and chunks in order from
+  // NRT on (the addresses then step by one chunk)
+  gbyte *next_a = src_dh[0], *next_b = src_dh[1];
+  auto issue_dh = [&](int c) {
+    issue_from(next_a, next_b, c);
+    next_a += 1024 * ES;
+    next_b += 1024 * ES;
+  };
+  auto issue = [&](auto ci) {
+    constexpr int c = decltype(ci)::value;
+    if constexpr (c < NRT)
+      issue_from(src_hh[0] + c * 1024 * ES, src_hh[1] + c * 1024 * ES, c);
+    else
+      issue_dh(c);
   };
 
   // Fragments of one chunk for this wave: A rows 64 wm + 32 bm (FA: [bm]
@@ -288,10 +300,11 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
   // j + 1 and j + 2 have landed (every wave's loads) and every wave is done
   // with chunks j - 2 and j - 1, and issue chunks j + NS - 2, j + NS - 1 into
   // the stages those used (a barrier every second chunk); then the products
-  // of chunk j (NH per block; mf(fa, fb, bm, k) issues product k of block bm)
+  // of chunk j (NH per block; mf(fa, fb, bm, k) issues product k of block bm;
+  // ahead() issues the chunks)
   // with the fragment reads between them.  After the last chunk the reads
   // fetch a stale stage, unused, so no branch sits between the products.
-  auto step = [&](int j, auto pi, auto nh, auto&& mf) {
+  auto step = [&](int j, auto pi, auto nh, auto&& mf, auto&& ahead) {
     constexpr int P = decltype(pi)::value % 2;
     constexpr int NH = decltype(nh)::value;
     FA& acur = fa(std::integral_constant<int, P>{});
@@ -302,8 +315,7 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
       // chunks j + 3 .. min(j + NS - 3, nk - 1) may stay in flight
       barrier_in_flight<NS - 3, LPC>(max(0, min(NS - 5, nk - 3 - j)));
       fence();
-      if (j + NS - 2 < nk) issue(j + NS - 2);
-      if (j + NS - 1 < nk) issue(j + NS - 1);
+      ahead();
       fence();
     }
     static_for<2 * NH>([&](auto ti) {
@@ -319,9 +331,9 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
 
   // prologue: chunks 0 .. NS - 3 in flight; once chunk 0 has landed, its
   // fragments are read
-#pragma unroll
-  for (int c = 0; c < NS - 2; ++c)
-    if (c < nk) issue(c);
+  static_for<NS - 2>([&](auto ci) {
+    if (decltype(ci)::value < nk) issue(ci);
+  });
   barrier_in_flight<NS - 3, LPC>(min(NS - 3, nk - 1));   // (also makes rowq .. coln visible)
   static_for<6>([&](auto ki) { read_frag(fa0, fb0, 0, decltype(ki)::value); });
 
@@ -334,7 +346,10 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
     constexpr int r = decltype(ri)::value;
 #pragma unroll
     for (int bm = 0; bm < 2; ++bm) hacc[bm] = Acc{};
-    step(r, std::integral_constant<int, r>{}, std::integral_constant<int, 2>{}, mf_hh);
+    step(r, std::integral_constant<int, r>{}, std::integral_constant<int, 2>{}, mf_hh, [&] {
+      if (r + NS - 2 < nk) issue(std::integral_constant<int, r + NS - 2>{});
+      if (r + NS - 1 < nk) issue(std::integral_constant<int, r + NS - 1>{});
+    });
 #pragma unroll
     for (int bm = 0; bm < 2; ++bm) {
       if constexpr (r == 0) {
@@ -373,9 +388,14 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
   auto neg = [](const uint4& x) {
     return make_uint4(x.x ^ 0x80008000u, x.y ^ 0x80008000u, x.z ^ 0x80008000u, x.w ^ 0x80008000u);
   };
-  auto mf_dh = [&](const FA& A, const FB& B, int bm, int k) {
+  // (FIRST: of a group's first chunk, where the accumulators start)
+  auto mf_dh = [&](auto first, const FA& A, const FB& B, int bm, int k) {
     Acc& re = acc[bm][0];
     Acc& im = acc[bm][1];
+    if constexpr (decltype(first)::value) {
+      if (k == 0) re = Acc{};
+      if (k == 1) im = Acc{};
+    }
     switch (k) {
       case 0: mma<PREC>(re, A.v[bm][0], B.v[0]); break;
       case 1: mma<PREC>(im, A.v[bm][0], neg(B.v[1])); break;
@@ -386,19 +406,25 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
   int ch = 0;
   static_for<G>([&](auto gi) {
     constexpr int g = decltype(gi)::value;
-#pragma unroll
-    for (int bm = 0; bm < 2; ++bm) {
-      acc[bm][0] = Acc{};
-      acc[bm][1] = Acc{};
-    }
     // each group spans a multiple of 4 chunks, so the fragment parity of
     // every step is static
     const int gend = a.mt.gk0[g + 1];
-    for (; ch < gend; ch += 2) {
-      step(NRT + ch, std::integral_constant<int, NRT>{}, std::integral_constant<int, 4>{}, mf_dh);
-      step(NRT + ch + 1, std::integral_constant<int, NRT + 1>{}, std::integral_constant<int, 4>{},
-           mf_dh);
-    }
+    auto two = [&](auto first) {
+      const int j = NRT + ch;
+      auto none = [] {};
+      auto more = [&] {
+        if (j + 1 + NS - 2 < nk) issue_dh(j + 1 + NS - 2);
+        if (j + 1 + NS - 1 < nk) issue_dh(j + 1 + NS - 1);
+      };
+      static_assert(NRT % 2 == 1, "a group's first step has no barrier");
+      step(j, std::integral_constant<int, NRT>{}, std::integral_constant<int, 4>{},
+           [&](const FA& A, const FB& B, int bm, int k) { mf_dh(first, A, B, bm, k); }, none);
+      step(j + 1, std::integral_constant<int, NRT + 1>{}, std::integral_constant<int, 4>{},
+           [&](const FA& A, const FB& B, int bm, int k) { mf_dh(std::false_type{}, A, B, bm, k); }, more);
+      ch += 2;
+    };
+    two(std::true_type{});
+    while (ch < gend) two(std::false_type{});
 #pragma unroll
     for (int bm = 0; bm < 2; ++bm) {
 #pragma unroll
