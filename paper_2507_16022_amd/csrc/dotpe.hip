@@ -1366,7 +1366,7 @@ int dotpe_event_bytes(const dotpe_ctx* ctx, const dotpe_bank* bk, const dotpe_ev
 
 // Persistent grids of the passes whose work is known on the device only
 constexpr int64_t kSurvGrid = 65536;  // workgroups of 4 waves, a listed tile per wave
-constexpr int64_t kCoefGrid = 1024;   // fused kernel, a tile per workgroup at a time
+constexpr int64_t kCoefGrid = 1024;   // a tile per workgroup at a time, or half a tile of a short list
 constexpr int64_t kE2Grid = 4096;
 
 int dotpe_eval_lnl(dotpe_ctx* ctx, dotpe_event* ev, double* lnl, double* ml_max, double* triples,
@@ -1403,7 +1403,7 @@ int dotpe_eval_lnl(dotpe_ctx* ctx, dotpe_event* ev, double* lnl, double* ml_max,
   rc = DOTPE_OK;
   for (a.work0 = 0; a.work0 < a.n_tiles && !rc; a.work0 += ev->coef_tiles) {
     const int64_t n = std::min(ev->coef_tiles, a.n_tiles - a.work0);
-    rc = launch_fused<kCoef>(ev->bank->prec, a, std::min(n, kCoefGrid), s);
+    rc = launch_fused<kCoef>(ev->bank->prec, a, std::min(2 * n, kCoefGrid), s);
     if (!rc) rc = launch_fused<kEval>(ev->bank->prec, a, std::min(n * kEvalParts, kE2Grid), s);
   }
   if (rc) { release(); return rc; }
@@ -1471,7 +1471,7 @@ static PassPlan pass_plan(const dotpe_event* ev, const FusedArgs& a) {
   // return at once
   const int64_t C = ev->coef_tiles;
   p.n_chunks = (a.n_tiles + C - 1) / C;
-  p.coef_grid = std::min(C, kCoefGrid);
+  p.coef_grid = std::min(2 * C, kCoefGrid);
   p.e2_grid = std::min(C, kE2Grid);
   return p;
 }
@@ -1517,6 +1517,16 @@ static int pass_tail(dotpe_event* ev, const FusedArgs& a, hipStream_t s, double*
   HIP_OK(hipMemcpyAsync(fo, ev->final_out, sizeof(double) * (kNPart + 3), hipMemcpyDeviceToHost, s));
   HIP_OK(hipMemcpyAsync(st, ev->state, sizeof(uint64_t) * 6, hipMemcpyDeviceToHost, s));
   return DOTPE_OK;
+}
+
+// the tiles left to the coefficient route in the order that shares operands.
+// Events of fewer than kOrderMinTiles run in one round of workgroups; above
+// kOrderMaxTiles the bitmap (a bit per tile) would not fit LDS.
+constexpr int64_t kOrderMinTiles = 1024, kOrderMaxTiles = 64 * 8192;
+static void order_list(const dotpe_event* ev, const FusedArgs& a, hipStream_t s) {
+  if (a.n_tiles < kOrderMinTiles || a.n_tiles > kOrderMaxTiles) return;
+  hipLaunchKernelGGL(k_order_list, dim3(1), dim3(1024), (size_t)((a.n_tiles + 31) / 32 * 4), s, ev->state,
+                     a.cut_delta, a.n_tiles_m, a.n_tiles_n, (int)kOrderMinTiles, ev->rerun);
 }
 
 // whether a pass with this state cuts (cut_on of the kernels)
@@ -1604,6 +1614,7 @@ static int evidence_pass(dotpe_ctx* ctx, dotpe_event* ev, double cut_delta,
   // an empty chunk's two kernels take 10 us, the wait 15 (65536 x 4096 pairs:
   // 32 chunks, none of them needed, 0.33 of 5.6 ms).
   int64_t n_chunks = pl.n_chunks;
+  if (pl.may_cut) order_list(ev, a, s);
   if (pl.may_cut && n_chunks > 2) {
     uint64_t st_cut[6];
     HIP_OK(hipMemcpyAsync(st_cut, ev->state, sizeof(st_cut), hipMemcpyDeviceToHost, s));
@@ -1757,6 +1768,8 @@ static int evidence_pass_packed(dotpe_ctx* ctx, dotpe_event* const* evs, int n,
   if ((rc = stage(kEvidence, 0,
                   [&](int k) { return pl[k].may_cut && !pl[k].bound_pass ? pl[k].cut_grid : 0; })))
     return rc;
+  for (int k = 0; k < n; ++k)
+    if (pl[k].may_cut) order_list(evs[k], pb->h_args[k], s);
   for (int64_t c = 0; c < max_chunks; ++c) {
     if ((rc = stage(kCoef, c, [&](int k) { return c < pl[k].n_chunks ? pl[k].coef_grid : 0; })))
       return rc;
@@ -2219,7 +2232,7 @@ int dotpe_sample_posterior(dotpe_ctx* ctx, dotpe_event* ev, int64_t n_samples, d
   for (int64_t c = 0; c * C < n_u; ++c) {
     a.work0 = c * C;
     const int64_t n = std::min(C, n_u - a.work0);
-    if ((rc = launch_fused<kCoef>(prec, a, std::min(n, kCoefGrid), s))) return rc;
+    if ((rc = launch_fused<kCoef>(prec, a, std::min(2 * n, kCoefGrid), s))) return rc;
     if ((rc = launch_fused<kSample>(prec, a, n, s))) return rc;
   }
   std::vector<double> h((size_t)ns * 6);

@@ -321,9 +321,27 @@ __device__ __forceinline__ int64_t coef_work_count(const FusedArgs& a) {
   if (a.work_list) return a.n_work_list;
   return cut_on(a) ? (int64_t)a.state[4] : a.n_tiles;
 }
+// The order in which the coefficient route takes tiles: bands of 8 tile rows,
+// down the columns of a band, so that 128 consecutive items share 8 row blocks
+// and 16 column blocks of operands.  place -> tile, tile -> place.
+__host__ __device__ __forceinline__ int64_t tile_at(int64_t n_tiles_m, int64_t n_tiles_n, int64_t place) {
+  const int64_t band = place / (8 * n_tiles_n), in = place - band * 8 * n_tiles_n;
+  const int64_t left = n_tiles_m - band * 8, rows = left < 8 ? left : 8;
+  return (band * 8 + in % rows) * n_tiles_n + in / rows;
+}
+__host__ __device__ __forceinline__ int64_t tile_place(int64_t n_tiles_m, int64_t n_tiles_n, int64_t tile) {
+  const int64_t tm = tile / n_tiles_n, tn = tile - tm * n_tiles_n, band = tm / 8;
+  const int64_t left = n_tiles_m - band * 8, rows = left < 8 ? left : 8;
+  return band * 8 * n_tiles_n + tn * rows + (tm - band * 8);
+}
 __device__ __forceinline__ int64_t coef_tile(const FusedArgs& a, int64_t q) {
   if (a.work_list) return a.work_list[q];
-  return cut_on(a) ? (int64_t)a.rerun[q] : q;
+  return cut_on(a) ? (int64_t)a.rerun[q] : tile_at(a.n_tiles_m, a.n_tiles_n, q);
+}
+// Consecutive workgroups run on different XCDs: each XCD takes a contiguous
+// part of every wg_count items, so that neighbouring tiles meet in one L2.
+__device__ __forceinline__ int64_t coef_first(int64_t wg_id, int64_t wg_count) {
+  return wg_count % 8 == 0 ? (wg_id % 8) * (wg_count / 8) + wg_id / 8 : wg_id;
 }
 
 // Wave-wide reductions through DPP lane moves (no LDS round trips): pairs
@@ -1353,7 +1371,7 @@ __device__ __forceinline__ void fused_grid_tile(const FusedArgs& a, unsigned cha
   if constexpr (MODE == kCoef) {
     // coefficient route: the workgroups take the chunk's work items in turn
     const int64_t end = min(a.work0 + a.coef_tiles, coef_work_count(a));
-    for (int64_t q = a.work0 + wg_id; q < end; q += wg_count) {
+    for (int64_t q = a.work0 + coef_first(wg_id, wg_count); q < end; q += wg_count) {
       const int64_t t = coef_tile(a, q);
       fused_tile<PREC, G, MODE, FAST>(a, smem, t / a.n_tiles_n, t % a.n_tiles_n, q - a.work0);
       __syncthreads();

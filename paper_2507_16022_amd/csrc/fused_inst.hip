@@ -93,6 +93,28 @@ hipError_t launch_bound_packed(const PackLaunch& p, hipStream_t s) {
   }
 }
 
+// the first half of the coefficient route: FP64 by the fused kernel
+template <int PREC, int G>
+hipError_t launch_coef(const FusedArgs& a, int64_t grid, hipStream_t s) {
+  if constexpr (PREC == kFP64) {
+    return launch_one<PREC, G, kCoef, false>(a, grid, s);
+  } else {
+    hipLaunchKernelGGL((k_coef<PREC, G>), dim3((unsigned)grid), dim3(CoefTile::NT), CoefTile::LDS_BYTES, s, a);
+    return hipGetLastError();
+  }
+}
+
+template <int PREC, int G>
+hipError_t launch_coef_packed(const PackLaunch& p, int n_phi, hipStream_t s) {
+  if constexpr (PREC == kFP64) {
+    return launch_one_packed<PREC, G, kCoef, false>(p, n_phi, s);
+  } else {
+    hipLaunchKernelGGL((k_coef_packed<PREC, G>), dim3((unsigned)p.off[p.n]), dim3(CoefTile::NT),
+                       CoefTile::LDS_BYTES, s, p);
+    return hipGetLastError();
+  }
+}
+
 template <int PREC, int G>
 hipError_t launch_any_packed(int mode, const PackLaunch& p, int n_phi, hipStream_t s) {
   if (p.n < 1 || p.n > kMaxPack || p.off[p.n] <= 0) return hipErrorInvalidValue;
@@ -100,7 +122,7 @@ hipError_t launch_any_packed(int mode, const PackLaunch& p, int n_phi, hipStream
     case kPilot: return launch_one_packed<PREC, G, kPilot, false>(p, n_phi, s);
     case kEvidence: return launch_one_packed<PREC, G, kEvidence, true>(p, n_phi, s);
     case kBound: return launch_bound_packed<PREC, G>(p, s);
-    case kCoef: return launch_one_packed<PREC, G, kCoef, false>(p, n_phi, s);
+    case kCoef: return launch_coef_packed<PREC, G>(p, n_phi, s);
     case kSurvivors:
     case kE2: return DOTPE_MARGP_NAME(DOTPE_INST_PREC, DOTPE_INST_G)(mode, p, n_phi, s);
   }
@@ -116,7 +138,7 @@ hipError_t launch_any(int mode, bool fast, const FusedArgs& a, int64_t grid, hip
       // coefficient route
       return fast ? launch_one<PREC, G, kEvidence, true>(a, grid, s) : hipErrorInvalidValue;
     case kBound: return launch_bound<PREC, G>(a, grid, s);
-    case kCoef: return launch_one<PREC, G, kCoef, false>(a, grid, s);
+    case kCoef: return launch_coef<PREC, G>(a, grid, s);
     case kSurvivors:
     case kE2:
     case kEval:

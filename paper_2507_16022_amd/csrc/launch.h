@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include "bound.h"
+#include "coef.h"
 #include "e2.h"
 #include "fused.h"
 

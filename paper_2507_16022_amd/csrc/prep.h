@@ -1368,4 +1368,45 @@ __global__ void k_fill_cand(double* __restrict__ c, int64_t from, int64_t to) {
   c[4 * i + 3] = 0;
 }
 
+// The coefficient route's list (rerun, state[4] tiles, in the order in which
+// the bound or fast pass's workgroups finished) in place order (tile_at), by a
+// bitmap in LDS: the tiles that run together then share their operands (8192
+// tiles of 8192 x 4096 pairs: the route's first half 0.52 -> 0.47 ms per 2048
+// and its second 0.51 -> 0.45).  One workgroup; short lists stay as they are.
+__global__ __launch_bounds__(1024) void k_order_list(const uint64_t* __restrict__ state, double cut_delta,
+                                                     int64_t n_tiles_m, int64_t n_tiles_n, int least,
+                                                     int* __restrict__ list) {
+  extern __shared__ unsigned bits[];     // a bit per place
+  __shared__ int wsum[16];
+  if (!(__longlong_as_double((long long)state[3]) - cut_delta > 0.0)) return;
+  const int64_t n_tiles = n_tiles_m * n_tiles_n;
+  const int n = (int)state[4], n_words = (int)((n_tiles + 31) / 32);
+  if (n < least || n > n_tiles) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int w = tid; w < n_words; w += 1024) bits[w] = 0u;
+  __syncthreads();
+  for (int k = tid; k < n; k += 1024) {
+    const int64_t p = tile_place(n_tiles_m, n_tiles_n, list[k]);
+    atomicOr(&bits[p >> 5], 1u << (p & 31));
+  }
+  __syncthreads();       // (the list has been read)
+  // each thread a run of words
+  const int per = (n_words + 1023) / 1024, w0 = min(tid * per, n_words), w1 = min(w0 + per, n_words);
+  int cnt = 0;
+  for (int w = w0; w < w1; ++w) cnt += __popc(bits[w]);
+  int incl = cnt;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int v = __shfl_up(incl, off, 64);
+    if (lane >= off) incl += v;
+  }
+  if (lane == 63) wsum[wave] = incl;
+  __syncthreads();
+  int at = incl - cnt;
+  for (int w = 0; w < wave; ++w) at += wsum[w];
+  for (int w = w0; w < w1; ++w)
+    for (unsigned m = bits[w]; m; m &= m - 1u)
+      list[at++] = (int)tile_at(n_tiles_m, n_tiles_n, (int64_t)w * 32 + __ffs(m) - 1);
+}
+
 }  // namespace dotpe
