@@ -818,18 +818,21 @@ __device__ __forceinline__ void survivor_pass(const FusedArgs& a, int64_t wg_id,
     const double dmd = read_lane(dm == -INFINITY ? -INFINITY : (double)dm, 63);
     const double dsd = read_lane((double)ds, 63);
     const int n_marg_all = __builtin_amdgcn_readlane(n_marg, 63);
-    // the survivors' p in the tile's row and column sums, relative to the
-    // tile maximum, in survivor order (the bound pass left the sums zero)
+    // the survivors' p in the tile's row and column sums (lane r: row r and
+    // column r), relative to the tile maximum, in survivor order
     const double tmax = read_lane(tile_max, 0);
-    for (int sidx = 0; sidx < n_surv; ++sidx) {
-      const double v = read_lane(my_lnp, sidx);
-      if (lane == 0 && v > -INFINITY) {
+    if (tmax > -INFINITY) {
+      double row_sum = 0.0, col_sum = 0.0;
+      for (int sidx = 0; sidx < n_surv; ++sidx) {
+        const double v = read_lane(my_lnp, sidx);
+        if (!(v > -INFINITY)) continue;
         const unsigned rc = a.surv[tile_id * kSurvCap + sidx];
-        double* rs = a.rowcol + tile_id * 128;
         const double x = exp(v - tmax);
-        rs[rc >> 8] += x;
-        rs[64 + (rc & 255)] += x;
+        row_sum += lane == (int)(rc >> 8) ? x : 0.0;
+        col_sum += lane == (int)(rc & 255) ? x : 0.0;
       }
+      a.rowcol[tile_id * 128 + lane] = row_sum;
+      a.rowcol[tile_id * 128 + 64 + lane] = col_sum;
     }
     if (lane == 0) {
       double* out = a.partials + tile_id * kNPart;

@@ -1476,11 +1476,9 @@ static PassPlan pass_plan(const dotpe_event* ev, const FusedArgs& a) {
   return p;
 }
 
-// the pass's first kernels: its state and the tiles' row and column sums
+// the pass's first kernel: its state
 static int pass_head(dotpe_event* ev, const FusedArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_reset_state, dim3(1), dim3(64), 0, s, ev->state);
-  hipLaunchKernelGGL(k_zero, dim3((unsigned)std::min<int64_t>(4096, (a.n_tiles * 128 + 255) / 256)),
-                     dim3(256), 0, s, ev->rowcol, a.n_tiles * 128);
   HIP_OK(hipGetLastError());
   return DOTPE_OK;
 }
@@ -1502,10 +1500,10 @@ static int pass_tail(dotpe_event* ev, const FusedArgs& a, hipStream_t s, double*
   tile_shape(prec, &tm, &tn);
   for (int rows = 1; rows >= 0; --rows) {
     const int64_t n_idx = rows ? ev->n_sub : ev->n_ext;
-    const int64_t nb = (n_idx + 255) / 256;
+    const int64_t nb = (n_idx + 255) / 256, nb64 = (n_idx + 63) / 64;
     const int64_t n_other = rows ? a.n_tiles_n : a.n_tiles_m;
     const int64_t n_parts = (n_other + kMargPer - 1) / kMargPer;
-    hipLaunchKernelGGL(k_marginal_part, dim3((unsigned)nb, (unsigned)n_parts), dim3(256), 0, s,
+    hipLaunchKernelGGL(k_marginal_part, dim3((unsigned)nb64, (unsigned)n_parts), dim3(256), 0, s,
                        ev->partials, ev->rowcol, ev->final_out, a.n_tiles_m, a.n_tiles_n, tm, tn,
                        n_idx, rows, kMargPer, ev->marg_part);
     hipLaunchKernelGGL(k_marginal_sq, dim3((unsigned)nb), dim3(256), 0, s, ev->marg_part, n_parts,
@@ -1795,6 +1793,39 @@ static int evidence_topk(dotpe_event* ev, uint64_t n_cand_raw, dotpe_evidence_re
   const double thr = r->max_ln_p - ev->topk_window;
   r->topk_count = 0;
   if (ev->top_k <= 0 || !topk || ncand <= 0) return DOTPE_OK;
+  const int64_t take = std::min<int64_t>(ev->top_k, ncand);
+  std::vector<double> h((take + 1) * 4);
+  auto report = [&](const double* rec) {
+    int cnt = 0;
+    for (int64_t q = 0; q < take; ++q, rec += 4) {
+      if (!(rec[0] >= thr)) break;
+      topk[cnt].ln_p = rec[0];
+      topk[cnt].i = (int64_t)rec[1];
+      topk[cnt].e = (int64_t)rec[2];
+      topk[cnt].o_best = (int32_t)rec[3];
+      topk[cnt].reserved = 0;
+      ++cnt;
+    }
+    r->topk_count = cnt;
+    return DOTPE_OK;
+  };
+  // few candidates, with room for the result behind them (else, or when too
+  // many lie within the window, the network below)
+  if (ncand <= kTopkMany && ncand + take + 1 <= ev->cand_cap) {
+    static std::once_flag few_once;
+    constexpr int few_lds = kTopkFit * 4 * (int)sizeof(double);
+    std::call_once(few_once, [] {
+      if (hipFuncSetAttribute((const void*)k_topk_few, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              few_lds) != hipSuccess)
+        (void)hipGetLastError();
+    });
+    double* out = ev->cand + 4 * ncand;
+    hipLaunchKernelGGL(k_topk_few, dim3(1), dim3(1024), few_lds, s, ev->cand, (int)ncand, thr, (int)take, out);
+    HIP_OK(hipGetLastError());
+    HIP_OK(hipMemcpyAsync(h.data(), out, (take + 1) * 32, hipMemcpyDeviceToHost, s));
+    HIP_OK(hipStreamSynchronize(s));
+    if (h[0] >= 0.0) return report(h.data() + 4);
+  }
   int64_t n2 = 1;
   while (n2 < ncand) n2 <<= 1;
   // the candidate buffer is a power of two at least as long as ncand
@@ -1803,7 +1834,6 @@ static int evidence_topk(dotpe_event* ev, uint64_t n_cand_raw, dotpe_evidence_re
   if (n2 > ncand)
     hipLaunchKernelGGL(k_fill_cand, dim3((unsigned)((n2 - ncand + 255) / 256)), dim3(256), 0, s,
                        buf, ncand, n2);
-  const int64_t take = std::min<int64_t>(ev->top_k, ncand);
   if (take <= kTopkChunk) {
     // sorted chunks, then pairwise merges keeping the best chunk of each pair
     const int C = (int)std::min<int64_t>(kTopkChunk, n2);
@@ -1830,21 +1860,9 @@ static int evidence_topk(dotpe_event* ev, uint64_t n_cand_raw, dotpe_evidence_re
                            buf, n2, j, k);
   }
   HIP_OK(hipGetLastError());
-  std::vector<double> h(take * 4);
   HIP_OK(hipMemcpyAsync(h.data(), buf, take * 32, hipMemcpyDeviceToHost, s));
   HIP_OK(hipStreamSynchronize(s));
-  int cnt = 0;
-  for (int64_t q = 0; q < take; ++q) {
-    if (!(h[4 * q] >= thr)) break;
-    topk[cnt].ln_p = h[4 * q];
-    topk[cnt].i = (int64_t)h[4 * q + 1];
-    topk[cnt].e = (int64_t)h[4 * q + 2];
-    topk[cnt].o_best = (int32_t)h[4 * q + 3];
-    topk[cnt].reserved = 0;
-    ++cnt;
-  }
-  r->topk_count = cnt;
-  return DOTPE_OK;
+  return report(h.data());
 }
 
 // passes with a growing cut_delta until the certificate meets the target

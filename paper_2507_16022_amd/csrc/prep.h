@@ -1189,6 +1189,55 @@ __global__ __launch_bounds__(256) void k_topk_chunks(double* __restrict__ c, int
   for (int t = threadIdx.x; t < C * 4; t += blockDim.x) g[t] = rec[t];
 }
 
+// Top-k of up to kTopkMany candidates by one workgroup: those within the
+// window (ln p >= thr; no other is reported) packed into LDS, then placed by
+// counting the better ones of each (few) or sorted by the bitonic network.
+// out: a record whose first value is their number, or -1 when they do not fit
+// (then nothing else is written and c stands), then `take` records, past the
+// last with ln p = -inf.  Sorting all candidates took 54 us at ~1000 of them
+// and 70 at 4096; with 16 of the ~1000 within the window this takes 16.
+constexpr int kTopkMany = 16384, kTopkFit = 2048, kTopkCount = 256;
+__global__ __launch_bounds__(1024) void k_topk_few(const double* __restrict__ c, int n, double thr, int take,
+                                                   double* __restrict__ out) {
+  extern __shared__ __align__(16) double rec[];     // [kTopkFit][4]
+  __shared__ int m_sh;
+  const int tid = threadIdx.x;
+  if (tid == 0) m_sh = 0;
+  __syncthreads();
+  for (int t = tid; t < n; t += 1024) {
+    const double v = c[4 * (int64_t)t];
+    if (!(v >= thr)) continue;
+    const int at = atomicAdd(&m_sh, 1);
+    if (at >= kTopkFit) continue;
+    for (int q = 0; q < 4; ++q) rec[4 * at + q] = c[4 * (int64_t)t + q];
+  }
+  __syncthreads();
+  const int m = m_sh;
+  if (tid == 0) out[0] = m > kTopkFit ? -1.0 : (double)m;
+  if (m > kTopkFit) return;
+  out += 4;
+  if (m <= kTopkCount) {
+    if (tid < m) {
+      const double* x = rec + 4 * tid;
+      int rank = 0;
+      for (int j = 0; j < m; ++j) rank += cand_before_lds(rec + 4 * j, x) ? 1 : 0;
+      if (rank < take)
+        for (int q = 0; q < 4; ++q) out[4 * (int64_t)rank + q] = x[q];
+    }
+  } else {
+    int C = 2 * kTopkCount;
+    while (C < m) C <<= 1;
+    for (int t = m + tid; t < C; t += 1024) {
+      rec[4 * t] = -INFINITY;
+      rec[4 * t + 1] = rec[4 * t + 2] = rec[4 * t + 3] = 0.0;
+    }
+    __syncthreads();
+    for (int k = 2; k <= C; k <<= 1) lds_bitonic_steps(rec, C, k, k >> 1);
+    for (int t = tid; t < 4 * min(m, take); t += 1024) out[t] = rec[t];
+  }
+  for (int t = m + tid; t < take; t += 1024) out[4 * (int64_t)t] = -INFINITY;
+}
+
 __global__ __launch_bounds__(256) void k_topk_merge(double* __restrict__ c, int C, int64_t s) {
   extern __shared__ __align__(16) double rec[];
   const int64_t a = 2 * (int64_t)blockIdx.x * s;
@@ -1208,36 +1257,51 @@ __global__ __launch_bounds__(256) void k_topk_merge(double* __restrict__ c, int 
   for (int t = threadIdx.x; t < C * 4; t += blockDim.x) A[t] = rec[t];
 }
 
-__global__ void k_zero(double* __restrict__ x, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    x[i] = 0.0;
-}
-
 // Marginals for eqs. int_ess and ext_ess: the sum of p_ie over one row i
 // (rows = 1) or one column e (rows = 0) of the pair matrix, from the tiles'
 // row and column sums scaled from each tile's maximum to the global maximum
 // M = final_out[9].  Block (x, c) sums the tiles c * q_per .. (c + 1) *
-// q_per - 1 along the row or column: part[c][x].
-__global__ void k_marginal_part(const double* __restrict__ partials, const double* __restrict__ rowcol,
-                                const double* __restrict__ final_out, int64_t n_tiles_m,
-                                int64_t n_tiles_n, int tm_rows, int tn_cols, int64_t n_idx, int rows,
-                                int64_t q_per, double* __restrict__ part) {
+// q_per - 1 along 64 rows or columns, its four waves a quarter of them each
+// (tiles without an evaluated pair have no sums): part[c][x].  The tiles'
+// factors are formed a tile per lane; with a thread per row, each forming
+// every factor in its loop, the two launches took 0.16 ms at 8192 x 4096
+// pairs and 0.01 at 256 x 512, all of it latency.
+__global__ __launch_bounds__(256) void k_marginal_part(
+    const double* __restrict__ partials, const double* __restrict__ rowcol,
+    const double* __restrict__ final_out, int64_t n_tiles_m, int64_t n_tiles_n, int tm_rows, int tn_cols,
+    int64_t n_idx, int rows, int64_t q_per, double* __restrict__ part) {
+  __shared__ double sh[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const double M = final_out[9];
-  const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (x >= n_idx) return;
-  const int64_t outer = rows ? x / tm_rows : x / tn_cols;
-  const int slot = rows ? (int)(x % tm_rows) : 64 + (int)(x % tn_cols);
-  const int64_t n_other = rows ? n_tiles_n : n_tiles_m;
-  const int64_t q0 = (int64_t)blockIdx.y * q_per, q1 = min(n_other, q0 + q_per);
+  const int64_t x = (int64_t)blockIdx.x * 64 + lane;
+  const int size = rows ? tm_rows : tn_cols;
+  const int slot = (rows ? 0 : 64) + (int)(x % size);
+  const int64_t n_outer = rows ? n_tiles_m : n_tiles_n, n_other = rows ? n_tiles_n : n_tiles_m;
+  // the tiles across of the lane's row or column: one or two in a wave
+  const int64_t outer0 = (int64_t)blockIdx.x * 64 / size;
+  const bool second = size < 64 && lane >= size;
+  const int64_t p0 = (int64_t)blockIdx.y * q_per, p1 = min(n_other, p0 + q_per);
+  const int64_t quarter = (p1 - p0 + 3) / 4, q0 = p0 + wave * quarter, q1 = min(p1, q0 + quarter);
+  auto tile = [&](int64_t q, int64_t outer) { return rows ? outer * n_tiles_n + q : q * n_tiles_n + outer; };
   double P = 0.0;
   if (M > -INFINITY)
-    for (int64_t q = q0; q < q1; ++q) {
-      const int64_t t = rows ? outer * n_tiles_n + q : q * n_tiles_n + outer;
-      const double mx = partials[t * kNPart + 9];
-      if (mx > -INFINITY) P += rowcol[t * 128 + slot] * exp(mx - M);
+    for (int64_t b = q0; b < q1; b += 64) {
+      auto factor = [&](int64_t outer) {
+        double mx = -INFINITY;
+        if (b + lane < q1 && outer < n_outer) mx = partials[tile(b + lane, outer) * kNPart + 9];
+        return mx > -INFINITY ? exp(mx - M) : 0.0;
+      };
+      const double f0 = factor(outer0), f1 = size < 64 ? factor(outer0 + 1) : 0.0;
+      for (unsigned long long m = __ballot(f0 > 0.0 || f1 > 0.0); m; m &= m - 1) {
+        const int j = __builtin_ctzll(m);
+        const double g0 = read_lane(f0, j), g1 = read_lane(f1, j), f = second ? g1 : g0;
+        if (f > 0.0 && x < n_idx) P += rowcol[tile(b + j, outer0 + (second ? 1 : 0)) * 128 + slot] * f;
+      }
     }
-  part[blockIdx.y * n_idx + x] = P;
+  sh[wave][lane] = P;
+  __syncthreads();
+  if (wave == 0 && x < n_idx)
+    part[blockIdx.y * n_idx + x] = sh[0][lane] + sh[1][lane] + sh[2][lane] + sh[3][lane];
 }
 
 // each index's marginal (the sum of its parts, in part order), squared;
