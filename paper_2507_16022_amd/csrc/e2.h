@@ -408,20 +408,22 @@ __device__ __forceinline__ void e2_pass(const FusedArgs& a, int64_t wg_id, int64
       }
       if (act) ev.ml_max = fmax(ev.ml_max, mn / (2.0 * md));
       const double lnp = lnw + lnl;
-      if (have) {
-        // top-k candidates within the window of the running maxima
-        const unsigned long long ob_bits = order_bits(lnp);
-        const unsigned long long prev = atomicMax(&tile_lnp_max, ob_bits);
-        const double tmax = order_value(prev > ob_bits ? prev : ob_bits);
-        append_candidate(a, lnp >= fmax(thr_topk_glob, tmax - a.topk_window), lnp, rowd[tr * 4 + 3],
-                         (double)(col0 + tc), ob);
+      const double mx = wave_max(have ? lnp : -INFINITY);
+      if (__any(have)) {
+        // top-k candidates within the window of the running maxima (the
+        // batch's own among them)
+        unsigned long long prev = 0ull;
+        if (lane == 0) prev = atomicMax(&tile_lnp_max, order_bits(mx));
+        const double tmax = fmax(mx, order_value((unsigned long long)__shfl((long long)prev, 0, 64)));
+        if (have)
+          append_candidate(a, lnp >= fmax(thr_topk_glob, tmax - a.topk_window), lnp, rowd[tr * 4 + 3],
+                           (double)(col0 + tc), ob);
       }
       // the row and column sums, a row of the batch at a time (a fixed order;
       // a row belongs to one wave)
       const bool sums = have && lnp != -INFINITY;
       unsigned long long todo = __ballot(sums);
       if (!todo) continue;
-      const double mx = wave_max(lnp);
       if (mx > wm) {
         const double f = wm == -INFINITY ? 0.0 : exp(wm - mx);
         ev.p.s *= f;

@@ -1468,9 +1468,27 @@ __global__ __launch_bounds__(1024) void k_order_list(const uint64_t* __restrict_
   __syncthreads();
   int at = incl - cnt;
   for (int w = 0; w < wave; ++w) at += wsum[w];
+  // runs of 128 entries (an XCD's part of a round) stay together, the runs
+  // themselves in steps of about 0.618 of their number: the running maxima,
+  // which decide what is kept as a top-k candidate, then come from all over
+  // the pair matrix early on
+  const int runs = n / 128;
+  int stride = max(1, (int)(0.618f * (float)runs));
+  for (;; ++stride) {      // (coprime; runs + 1 at the latest)
+    int x = runs, y = stride;
+    while (y) {
+      const int r = x % y;
+      x = y;
+      y = r;
+    }
+    if (x <= 1) break;
+  }
   for (int w = w0; w < w1; ++w)
-    for (unsigned m = bits[w]; m; m &= m - 1u)
-      list[at++] = (int)tile_at(n_tiles_m, n_tiles_n, (int64_t)w * 32 + __ffs(m) - 1);
+    for (unsigned m = bits[w]; m; m &= m - 1u, ++at) {
+      const int run = at / 128;
+      const int to = run < runs ? (int)((int64_t)run * stride % runs) * 128 + at % 128 : at;
+      list[to] = (int)tile_at(n_tiles_m, n_tiles_n, (int64_t)w * 32 + __ffs(m) - 1);
+    }
 }
 
 }  // namespace dotpe
