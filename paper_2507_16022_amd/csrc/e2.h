@@ -409,15 +409,23 @@ __device__ __forceinline__ void e2_pass(const FusedArgs& a, int64_t wg_id, int64
       if (act) ev.ml_max = fmax(ev.ml_max, mn / (2.0 * md));
       const double lnp = lnw + lnl;
       const double mx = wave_max(have ? lnp : -INFINITY);
-      if (__any(have)) {
-        // top-k candidates within the window of the running maxima (the
-        // batch's own among them)
+      // top-k candidates within the window of the running maxima: with the cut
+      // on, when a batch gathers its pairs from many rows, its own maximum is
+      // one of them; else each lane adds its own in turn
+      double tmax = -INFINITY;
+      if (on) {
         unsigned long long prev = 0ull;
-        if (lane == 0) prev = atomicMax(&tile_lnp_max, order_bits(mx));
-        const double tmax = fmax(mx, order_value((unsigned long long)__shfl((long long)prev, 0, 64)));
-        if (have)
-          append_candidate(a, lnp >= fmax(thr_topk_glob, tmax - a.topk_window), lnp, rowd[tr * 4 + 3],
-                           (double)(col0 + tc), ob);
+        if (lane == 0 && mx > -INFINITY) prev = atomicMax(&tile_lnp_max, order_bits(mx));
+        tmax = fmax(mx, order_value((unsigned long long)__shfl((long long)prev, 0, 64)));
+      }
+      if (have) {
+        if (!on) {
+          const unsigned long long own = order_bits(lnp);
+          const unsigned long long prev = atomicMax(&tile_lnp_max, own);
+          tmax = order_value(prev > own ? prev : own);
+        }
+        append_candidate(a, lnp >= fmax(thr_topk_glob, tmax - a.topk_window), lnp, rowd[tr * 4 + 3],
+                         (double)(col0 + tc), ob);
       }
       // the row and column sums, a row of the batch at a time (a fixed order;
       // a row belongs to one wave)
