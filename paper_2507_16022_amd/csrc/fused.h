@@ -1293,28 +1293,30 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, unsigned char* sm
 
   // The pilot starts from the largest lnL^ML any tile has found so far, which
   // is zero for the first tiles of a launch: then every pair and phase would be
-  // evaluated.  So a tile first evaluates, per lane, the pair with the largest
-  // bound, and bounds the rest by the largest lnL^ML of those (256 x 512
-  // pairs: 41 -> 24 us; a burst of 24 events 13.1 -> 12.6 ms).
-  if constexpr (MODE == kPilot) {
-    constexpr int NK = P::BM * P::BN * NE;
-    static_assert(NK <= 32 && NT <= TL::BATCH, "a pair per lane");
+  // evaluated.  In a launch of few tiles (FAST) a tile first evaluates, per
+  // lane, the pair with the largest bound, and bounds the rest by the largest
+  // lnL^ML of those (256 x 512 pairs: 41 -> 24 us; a burst of 24 events 13.1 ->
+  // 12.6 ms).  In one of many it costs more than the first tiles save (it
+  // spills 66 registers: 2^20 x 16384 pairs 9.9 -> 11.9 ms).
+  if constexpr (MODE == kPilot && FAST) {
+    // (among the first batch's pairs: the other half of the accumulators
+    // stays where it is)
+    constexpr int NK = TL::EPB;
+    static_assert(NT <= TL::BATCH, "a pair per lane");
     float top = -1.f;
     unsigned sm = 0;
-    static_for<P::BM>([&](auto bmi) {
-      static_for<P::BN>([&](auto bni) {
-        static_for<NE>([&](auto ri) {
-          constexpr int k = (decltype(bmi)::value * P::BN + decltype(bni)::value) * NE + decltype(ri)::value;
-          constexpr int bm = decltype(bmi)::value, bn = decltype(bni)::value, r = decltype(ri)::value;
-          const bool in = wn * BS * P::BN + bn * BS + (lane & (BS - 1)) < cols_in &&
-                          wm * BS * P::BM + bm * BS + rowmap(r) < rows_in;
-          float lo0;
-          float b = bound_at(bmi, bni, ri, lo0);
-          b = in ? (lo0 > 0.f ? b : INFINITY) : -1.f;
-          sm = b > top ? 1u << k : sm;
-          top = fmaxf(top, b);
-        });
-      });
+    static_for<NK>([&](auto ki) {
+      constexpr int k = decltype(ki)::value;
+      const auto bmi = std::integral_constant<int, k / NE / P::BN>{};
+      const auto bni = std::integral_constant<int, k / NE % P::BN>{};
+      const auto rr = std::integral_constant<int, k % NE>{};
+      const bool in = wn * BS * P::BN + decltype(bni)::value * BS + (lane & (BS - 1)) < cols_in &&
+                      wm * BS * P::BM + decltype(bmi)::value * BS + rowmap(k % NE) < rows_in;
+      float lo0;
+      float b = bound_at(bmi, bni, rr, lo0);
+      b = in ? (lo0 > 0.f ? b : INFINITY) : -1.f;
+      sm = b > top ? 1u << k : sm;
+      top = fmaxf(top, b);
     });
     int nsurv = 0;
     const int base = slot_base(sm, std::integral_constant<int, NK>{}, nsurv);
@@ -1337,7 +1339,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, unsigned char* sm
     use_bound = thr_ml > 0.0;
     thr_f = (float)thr_ml;
   }
-  if constexpr (FAST) {
+  if constexpr (MODE == kEvidence && FAST) {
     // every pair of the tile through E1 first, then one E2 once the
     // accumulators are dead.  A tile with more survivors than the record
     // area holds is left to the coefficient route: it is listed and

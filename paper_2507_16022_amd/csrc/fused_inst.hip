@@ -93,6 +93,10 @@ hipError_t launch_bound_packed(const PackLaunch& p, hipStream_t s) {
   }
 }
 
+// pilot tiles (of one event; in a packed launch of up to four times as many,
+// several events') that evaluate their most promising pairs first: two per CU
+constexpr int64_t kPilotFew = 512;
+
 // the first half of the coefficient route: FP64 by the fused kernel
 template <int PREC, int G>
 hipError_t launch_coef(const FusedArgs& a, int64_t grid, hipStream_t s) {
@@ -119,7 +123,9 @@ template <int PREC, int G>
 hipError_t launch_any_packed(int mode, const PackLaunch& p, int n_phi, hipStream_t s) {
   if (p.n < 1 || p.n > kMaxPack || p.off[p.n] <= 0) return hipErrorInvalidValue;
   switch (mode) {
-    case kPilot: return launch_one_packed<PREC, G, kPilot, false>(p, n_phi, s);
+    case kPilot:
+      return p.off[p.n] <= 4 * kPilotFew ? launch_one_packed<PREC, G, kPilot, true>(p, n_phi, s)
+                                         : launch_one_packed<PREC, G, kPilot, false>(p, n_phi, s);
     case kEvidence: return launch_one_packed<PREC, G, kEvidence, true>(p, n_phi, s);
     case kBound: return launch_bound_packed<PREC, G>(p, s);
     case kCoef: return launch_coef_packed<PREC, G>(p, n_phi, s);
@@ -132,7 +138,9 @@ hipError_t launch_any_packed(int mode, const PackLaunch& p, int n_phi, hipStream
 template <int PREC, int G>
 hipError_t launch_any(int mode, bool fast, const FusedArgs& a, int64_t grid, hipStream_t s) {
   switch (mode) {
-    case kPilot: return launch_one<PREC, G, kPilot, false>(a, grid, s);
+    case kPilot:
+      return grid <= kPilotFew ? launch_one<PREC, G, kPilot, true>(a, grid, s)
+                               : launch_one<PREC, G, kPilot, false>(a, grid, s);
     case kEvidence:
       // only the fast pass: without the cut every tile takes the
       // coefficient route
