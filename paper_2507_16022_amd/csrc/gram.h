@@ -72,17 +72,14 @@ __device__ __forceinline__ void gram_row(const void* r0, const void* r1, int n_b
     H x[BL];
   };
   for (int b0 = BL * l16; b0 < n_b; b0 += 16 * BL) {
-    float re[NC][BL], im[NC][BL];      // hi + lo spans at most 23 bits: exact in float
+    HB rh[NC], rl[NC], ih[NC], il[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const int o = (c * (n_bp / kChunk) + b0 / kChunk) * 32 + b0 % kChunk;
-      const HB a = *(const HB*)((const H*)r0 + o), al = *(const HB*)((const H*)r1 + o);
-      const HB m = *(const HB*)((const H*)r0 + o + 16), ml = *(const HB*)((const H*)r1 + o + 16);
-#pragma unroll
-      for (int j = 0; j < BL; ++j) {
-        re[c][j] = (float)a.x[j] + (float)al.x[j];
-        im[c][j] = -((float)m.x[j] + (float)ml.x[j]);
-      }
+      rh[c] = *(const HB*)((const H*)r0 + o);
+      rl[c] = *(const HB*)((const H*)r1 + o);
+      ih[c] = *(const HB*)((const H*)r0 + o + 16);
+      il[c] = *(const HB*)((const H*)r1 + o + 16);
     }
 #pragma unroll
     for (int j = 0; j < BL; ++j) {
@@ -90,11 +87,13 @@ __device__ __forceinline__ void gram_row(const void* r0, const void* r1, int n_b
       double wk[KD];
 #pragma unroll
       for (int k = 0; k < KD; ++k) wk[k] = k < nk ? w[k * n_b + b0 + j] : 0.0;
+      // (in double: lo may start far below hi's last place, so that hi + lo
+      // may take more than a float's 24 bits)
       double hr[NC], hi[NC];
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        hr[c] = (double)re[c][j];
-        hi[c] = (double)im[c][j];
+        hr[c] = (double)(float)rh[c].x[j] + (double)(float)rl[c].x[j];
+        hi[c] = -((double)(float)ih[c].x[j] + (double)(float)il[c].x[j]);
       }
       int p = 0, q = NP;
 #pragma unroll

@@ -819,8 +819,9 @@ __global__ void k_hh_precompute(int64_t n_sub, const int64_t* __restrict__ sub_i
                                 const int* __restrict__ terms, int KH, void* __restrict__ H0,
                                 void* __restrict__ H1, double* __restrict__ hscale,
                                 const void* __restrict__ R0, const void* __restrict__ R1) {
-  // the row [n_c][n_bp] then w [n_det][n_b], when they fit.  A split value
-  // hi + lo spans at most 23 significant bits, so float holds it exactly.
+  // the row [n_c][n_bp] then w [n_det][n_b], when they fit.  A staged split
+  // value hi + lo is rounded to a float's 24 bits (lo may start far below hi's
+  // last place), a quarter of what the split itself leaves out.
   typedef typename std::conditional<PREC == kFP64, double2, float2>::type RB;
   extern __shared__ __align__(16) unsigned char hh_smem[];
   RB* rowbuf = (RB*)hh_smem;
