@@ -472,8 +472,8 @@ void launch_hh_rows(dotpe_event* ev, const double* w) {
   ev->ah_norms_done = true;
 }
 
-// the row-side (h|h) operand from Gram sums a wave per row (split precisions,
-// plain bins)
+// the row-side (h|h) operand from Gram sums by 16 lanes per row (split
+// precisions, plain bins)
 template <int PREC>
 void launch_hh_rows(dotpe_event* ev, const double* w) {
   switch (ev->bank->n_c) {
@@ -488,13 +488,19 @@ void launch_hh_rows(dotpe_event* ev, const double* w) {
   }
 }
 
+// bytes of a row's amplitudes and the noise weights, which k_hh_precompute
+// keeps in LDS when they fit 64 KB (the kernel applies the same test)
+template <int PREC>
+size_t hh_stage_bytes(const dotpe_event* ev) {
+  const dotpe_bank* bk = ev->bank;
+  const size_t rb = PREC == kFP64 ? sizeof(double2) : sizeof(float2);   // staged row value
+  return (size_t)bk->n_c * (bk->n_bp + 1) * rb + (size_t)ev->n_det * (bk->n_b + 1) * sizeof(double);
+}
+
 template <int PREC>
 void launch_hh_block(dotpe_event* ev, const double* w, const double2* whh) {
   const dotpe_bank* bk = ev->bank;
-  // the row's amplitudes and the noise weights in LDS when they fit (the
-  // kernel applies the same test)
-  const size_t rb = PREC == kFP64 ? sizeof(double2) : sizeof(float2);   // staged row value
-  size_t sh = (size_t)bk->n_c * (bk->n_bp + 1) * rb + (size_t)ev->n_det * (bk->n_b + 1) * sizeof(double);
+  size_t sh = hh_stage_bytes<PREC>(ev);
   sh = sh > 65536 ? 0 : (sh + 15) / 16 * 16;
   // four waves per row, each summing a quarter of the bins (their partial
   // sums after the staged row)
@@ -514,6 +520,20 @@ void launch_hh_block(dotpe_event* ev, const double* w, const double2* whh) {
                      ev->Ah[1], ev->ah_scale, bk->R0, bk->R1);
 }
 
+// Whether plain bins of a split bank take a workgroup per row.  16 lanes per
+// row hold one detector's sums from six channels on (gram_dets) and pass over
+// the row once per detector; a wave of the block kernel takes 64 (detector,
+// channel pair) sums at a time.  The block kernel where it needs fewer rounds
+// and the row fits its LDS (it is ten times slower on rows that do not):
+// 65536 rows, 256 bins, 6 channels and 3 detectors 0.87 against 1.13 ms an
+// event, 8 and 3 1.40 against 1.49; 8 and 2, the same number of rounds, 1.27
+// against 1.10.
+template <int PREC>
+bool hh_by_block(const dotpe_event* ev) {
+  const ModeTables& mt = ev->bank->mt;
+  return gram_dets(mt.n_c) == 1 && (ev->n_det * mt.NP + 63) / 64 < ev->n_det && hh_stage_bytes<PREC>(ev) <= 65536;
+}
+
 template <int PREC>
 void launch_hh(dotpe_event* ev, const double* w, const double2* whh) {
   const dotpe_bank* bk = ev->bank;
@@ -521,7 +541,7 @@ void launch_hh(dotpe_event* ev, const double* w, const double2* whh) {
     launch_hh_block<PREC>(ev, w, whh);
   } else {
     static_assert(kMaxC == 8, "launch_hh_rows");
-    if (whh) launch_hh_block<PREC>(ev, w, whh);
+    if (whh || hh_by_block<PREC>(ev)) launch_hh_block<PREC>(ev, w, whh);
     else launch_hh_rows<PREC>(ev, w);
   }
   hipLaunchKernelGGL(k_build_Bhh<PREC>, dim3((unsigned)ev->n_ext_p), dim3(64), 0, ev->stream,

@@ -808,8 +808,9 @@ __device__ __forceinline__ double2 to_d2(float2 v) { return make_double2(v.x, v.
 // binning: sum_b W_kcc'b h_icb conj(h_ic'b), whh [n_det][NP][n_b]) for the
 // event's bank subset, from the same operand values the contraction uses,
 // written as the row-side (h|h) operand (n_sub rows of KH, op_index layout)
-// with a power-of-two row scale in the split precisions: FP64 banks and
-// relative binning (plain bins of split banks: k_hh_rows)
+// with a power-of-two row scale in the split precisions: FP64 banks, relative
+// binning, and plain bins of split banks with many channel pairs and detectors
+// (the others: k_hh_rows)
 template <int PREC>
 __global__ void k_hh_precompute(int64_t n_sub, const int64_t* __restrict__ sub_idx, int64_t sub0,
                                 const void* __restrict__ A0, const void* __restrict__ A1,
