@@ -111,12 +111,25 @@ __global__ __launch_bounds__(256, 2) void k_pre_gram(PreArgs a) {
 #pragma unroll
     for (int t = 0; t < N; ++t) v[t] = 0.0;
     for (int b = lane; b < a.n_b; b += 64) {
+      // (every load asked for before the first is used: the compiler
+      // otherwise waits for each channel in turn, 0.61 against 0.36 ms per
+      // 2^15 rows of six channels and three detectors)
+      H xr[NC][2], xi[NC][2];          // hi, lo
+      const H* p0 = r0 + b / kChunk * 32 + b % kChunk;
+      const H* p1 = r1 + b / kChunk * 32 + b % kChunk;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        xr[c][0] = p0[c * 2 * a.n_bp];
+        xr[c][1] = p1[c * 2 * a.n_bp];
+        xi[c][0] = p0[c * 2 * a.n_bp + 16];
+        xi[c][1] = p1[c * 2 * a.n_bp + 16];
+      }
+      __builtin_amdgcn_sched_barrier(0);
       double hr[NC], hi[NC];
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        const int o = (c * (a.n_bp / kChunk) + b / kChunk) * 32 + b % kChunk;
-        hr[c] = (double)(float)r0[o] + (double)(float)r1[o];
-        hi[c] = -((double)(float)r0[o + 16] + (double)(float)r1[o + 16]);
+        hr[c] = (double)(float)xr[c][0] + (double)(float)xr[c][1];
+        hi[c] = -((double)(float)xi[c][0] + (double)(float)xi[c][1]);
       }
       double w[KD];
 #pragma unroll
@@ -176,9 +189,9 @@ __device__ __forceinline__ float pre_term(float cn, float sn, float re, float im
 // sine), so the four phases share their products: seven operations per
 // channel and polarisation instead of twelve.  Negating a factor negates the
 // rounded result, so every sum is the one the plain loop forms.
-__host__ __device__ __forceinline__ bool pre_fours(int n) { return n >= 4 && (n & (n - 1)) == 0; }
+__host__ __device__ constexpr bool pre_fours(int n) { return n >= 4 && (n & (n - 1)) == 0; }
 // groups of four phases (o = 0 .. n / 4) or single phases, as the forms are stored
-__host__ __device__ __forceinline__ int pre_slots(int n) { return pre_fours(n) ? n + 4 : n; }
+__host__ __device__ constexpr int pre_slots(int n) { return pre_fours(n) ? n + 4 : n; }
 // phase o's place: group g = 0 .. n / 4 holds g, n - g, n / 2 + g, n / 2 - g
 __device__ __forceinline__ int pre_slot(int o, int n) {
   if (!pre_fours(n)) return o;
@@ -311,21 +324,29 @@ __global__ __launch_bounds__(256) void k_pre_factors(PreArgs a) {
   a.factors[t] = make_double2(0.5 * (yn + sg * yp), 0.5 * (yn - sg * yp));
 }
 
-// FOURS: pre_fours(n_phi)
-template <int PREC, int NC, bool FOURS>
-__global__ __launch_bounds__(64 * kPreMaxT / 32, NC <= 5 ? 2 : 1) void k_preselect(PreArgs a) {
+// bytes of k_preselect's dynamic LDS
+constexpr size_t pre_lds_bytes(int nc, int n_phi, bool shared) {
+  return sizeof(double) * ((size_t)kMaxM * n_phi * 2 + 64 * nc + 32 * (size_t)pre_slots(n_phi) * 2 +
+                           (kPreMaxT / 32) * 32) +
+         (shared ? (size_t)2 * nc * 4096 : 0);
+}
+
+// FOURS: pre_fours(n_phi); SHARED: the waves share the bank rows through LDS
+template <int PREC, int NC, bool FOURS, bool SHARED>
+__global__ __launch_bounds__(64 * kPreMaxT / 32, (SHARED && NC <= 5) || NC <= 3 ? 2 : 1) void k_preselect(PreArgs a) {
   typedef typename Pol<PREC>::Acc Acc;
   extern __shared__ __align__(16) double pls[];
   const int n_phi = a.n_phi;
   constexpr int NCP = pre_ncp(NC);
+  static_assert(NCP * sizeof(float2) <= kMaxM * 2 * sizeof(double), "csf fits the place of cs");
   const int slots = pre_slots(n_phi);
   double* cs = pls;                          // [kMaxM][n_phi][2] cos, sin of m phi_o
+  float2* csf = (float2*)pls;                // after the products: [n_phi][NCP] cos, sin of m_c phi_o in FP32
   double* kp = cs + kMaxM * n_phi * 2;       // [32][NC] K_c+
   double* kx = kp + 32 * NC;                 // [32][NC] K_cx / i
   float* qf = (float*)(kx + 32 * NC);        // [32][slots][4] H^+ / 2 as (cos, sin, a1, a2), by pre_slot
-  float2* csf = (float2*)(qf + 32 * slots * 4);   // [n_phi][NCP] cos, sin of m_c phi_o in FP32
-  double* red = (double*)(csf + n_phi * NCP);     // [NW][32]
-  unsigned char* stage = (unsigned char*)(red + (kPreMaxT / 32) * 32);   // [2][NC][4][1 KB]
+  double* red = (double*)(qf + 32 * slots * 4);   // [NW][32]
+  unsigned char* stage = (unsigned char*)(red + (kPreMaxT / 32) * 32);   // SHARED: [2][NC][4][1 KB]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nt = blockDim.x;
   // workgroup -> (row block, detector): consecutive ids go to the XCDs in
   // turn; each XCD takes a contiguous range with the detectors of one row
@@ -360,18 +381,12 @@ __global__ __launch_bounds__(64 * kPreMaxT / 32, NC <= 5 ? 2 : 1) void k_presele
           : "memory");
     }
   };
-  issue(0);
+  if constexpr (SHARED) issue(0);
   const int rows_in = (int)min((int64_t)32, a.chunk0 + a.n_chunk - rb0);
 
   for (int t = tid; t < kMaxM * n_phi; t += nt) {
     const int mm = t / n_phi + 1, o = t % n_phi;
-    double sn, cn;
-    sincospi(2.0 * (double)((mm * o) % n_phi) / n_phi, &sn, &cn);
-    cs[2 * t] = cn;
-    cs[2 * t + 1] = sn;
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-      if (a.m[c] == mm) csf[o * NCP + c] = make_float2((float)cn, (float)sn);
+    sincospi(2.0 * (double)((mm * o) % n_phi) / n_phi, &cs[2 * t + 1], &cs[2 * t]);
   }
   for (int t = tid; t < 32 * NC; t += nt) {
     const double2 f = t / NC < rows_in ? a.factors[(rb0 - a.chunk0) * NC + t] : make_double2(0.0, 0.0);
@@ -440,11 +455,12 @@ __global__ __launch_bounds__(64 * kPreMaxT / 32, NC <= 5 ? 2 : 1) void k_presele
     acc[c][0] = Acc{};
     acc[c][1] = Acc{};
   }
-  // The waves of the workgroup (grid times) share the bank rows: a bin chunk's
-  // A slices of every channel (hi, lo of both slices, NC x 4 KB) go straight
+  // SHARED: the waves of the workgroup (grid times) share the bank rows: a bin
+  // chunk's A slices of every channel (hi, lo of both slices, NC x 4 KB) go straight
   // into one of two LDS stages, shared out over the waves, while the chunk
-  // before is multiplied (each wave reading A from global memory for itself
-  // moved four times the bytes through the L1s: 5.5 of 7.8 ms per 2^18 rows).
+  // before is multiplied (each of four waves reading A from global memory for
+  // itself moved four times the bytes through the L1s: 5.5 of 7.8 ms per 2^18
+  // rows).
   // B is the wave's own: registers, a chunk ahead.  Two waves per SIMD (256
   // registers: 160 accumulators at five channels), so that one's epilogue,
   // all VALU, runs under another's products.
@@ -460,38 +476,80 @@ __global__ __launch_bounds__(64 * kPreMaxT / 32, NC <= 5 ? 2 : 1) void k_presele
   };
   // A = [Re conj h | Im conj h], B_re = [Br | -Bi], B_im = [Bi | Br]: 3 split
   // products per real product
-  auto compute = [&](int j, const FB& b) {
-    const uint4 nh1 = neg16(b.h1), nl1 = neg16(b.l1);
-    const unsigned char* st = stage + (j & 1) * (NC * 4096) + lane * 16;
-    static_for<NC>([&](auto ci) {
-      constexpr int c = decltype(ci)::value;
-      Acc &re = acc[c][0], &im = acc[c][1];
-      const uint4 h0 = *(const uint4*)(st + c * 4096), h1 = *(const uint4*)(st + c * 4096 + 1024);
-      const uint4 l0 = *(const uint4*)(st + c * 4096 + 2048), l1 = *(const uint4*)(st + c * 4096 + 3072);
-      mma<PREC>(re, l0, b.h0);  mma<PREC>(im, l0, nh1);
-      mma<PREC>(re, h0, b.l0);  mma<PREC>(im, h0, nl1);
-      mma<PREC>(re, h0, b.h0);  mma<PREC>(im, h0, nh1);
-      mma<PREC>(re, l1, b.h1);  mma<PREC>(im, l1, b.h0);
-      mma<PREC>(re, h1, b.l1);  mma<PREC>(im, h1, b.l0);
-      mma<PREC>(re, h1, b.h1);  mma<PREC>(im, h1, b.h0);
-    });
+  auto products = [&](Acc& re, Acc& im, const FB& b, const uint4& nh1, const uint4& nl1, const uint4& h0,
+                      const uint4& h1, const uint4& l0, const uint4& l1) {
+    mma<PREC>(re, l0, b.h0);  mma<PREC>(im, l0, nh1);
+    mma<PREC>(re, h0, b.l0);  mma<PREC>(im, h0, nl1);
+    mma<PREC>(re, h0, b.h0);  mma<PREC>(im, h0, nh1);
+    mma<PREC>(re, l1, b.h1);  mma<PREC>(im, l1, b.h0);
+    mma<PREC>(re, h1, b.l1);  mma<PREC>(im, h1, b.l0);
+    mma<PREC>(re, h1, b.h1);  mma<PREC>(im, h1, b.h0);
   };
   FB b0, b1;
   load_b(b0, 0);
-  for (int j = 0; j < nj; j += 2) {
-    // chunk j has landed (every wave's part), and every wave is done with j - 1
-    pipeline_barrier<0>();
-    issue(j + 1);
-    load_b(b1, j + 1);
-    compute(j, b0);
-    pipeline_barrier<0>();
-    if (j + 2 < nj) {
-      issue(j + 2);
-      load_b(b0, j + 2);
+  if constexpr (SHARED) {
+    auto compute = [&](int j, const FB& b) {
+      const uint4 nh1 = neg16(b.h1), nl1 = neg16(b.l1);
+      const unsigned char* st = stage + (j & 1) * (NC * 4096) + lane * 16;
+      static_for<NC>([&](auto ci) {
+        constexpr int c = decltype(ci)::value;
+        const uint4 h0 = *(const uint4*)(st + c * 4096), h1 = *(const uint4*)(st + c * 4096 + 1024);
+        const uint4 l0 = *(const uint4*)(st + c * 4096 + 2048), l1 = *(const uint4*)(st + c * 4096 + 3072);
+        products(acc[c][0], acc[c][1], b, nh1, nl1, h0, h1, l0, l1);
+      });
+    };
+    for (int j = 0; j < nj; j += 2) {
+      // chunk j has landed (every wave's part), and every wave is done with j - 1
+      pipeline_barrier<0>();
+      issue(j + 1);
+      load_b(b1, j + 1);
+      compute(j, b0);
+      pipeline_barrier<0>();
+      if (j + 2 < nj) {
+        issue(j + 2);
+        load_b(b0, j + 2);
+      }
+      compute(j + 1, b1);
     }
-    compute(j + 1, b1);
+  } else {
+    // each wave's own loads, a chunk ahead in registers (one wave per SIMD)
+    struct FA {
+      uint4 v[NC][4];      // hi 0, hi 1, lo 0, lo 1
+    };
+    auto load_a = [&](FA& f, int j) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          f.v[c][u] = ld16((u & 2) ? a.A1 : a.A0, abase + (int64_t)(c * nj + j) * 1024 + (u & 1) * 512);
+    };
+    auto compute = [&](const FA& f, const FB& b) {
+      const uint4 nh1 = neg16(b.h1), nl1 = neg16(b.l1);
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        products(acc[c][0], acc[c][1], b, nh1, nl1, f.v[c][0], f.v[c][1], f.v[c][2], f.v[c][3]);
+    };
+    FA f0, f1;
+    load_a(f0, 0);
+    for (int j = 0; j < nj; j += 2) {
+      load_a(f1, j + 1);
+      load_b(b1, j + 1);
+      compute(f0, b0);
+      if (j + 2 < nj) {
+        load_a(f0, j + 2);
+        load_b(b0, j + 2);
+      }
+      compute(f1, b1);
+    }
   }
-  __syncthreads();   // (the forms in qf are complete)
+  __syncthreads();   // (the forms in qf are complete, cs is no longer read)
+  for (int t = tid; t < n_phi * NC; t += nt) {
+    const int o = t / NC, c = t % NC;
+    double sn, cn;
+    sincospi(2.0 * (double)((a.m[c] * o) % n_phi) / n_phi, &sn, &cn);
+    csf[o * NCP + c] = make_float2((float)cn, (float)sn);
+  }
+  __syncthreads();
 
   // ---- epilogue: polarisation projections, 2x2 form, maximum ----
   // (in FP32: the accumulators are FP32 and the form is a sum of squares)
@@ -615,33 +673,52 @@ __global__ __launch_bounds__(256) void k_pre_write(PreArgs a) {
     if (f & (1u << q)) a.selected[pos++] = a.row0 + r0 + q;
 }
 
-template <int PREC, int NC, bool FOURS>
-hipError_t launch_pre_main(const PreArgs& a, hipStream_t s) {
-  auto lds_bytes = [](int n_phi) {
-    return sizeof(double) * ((size_t)kMaxM * n_phi * 2 + 64 * NC + 32 * (size_t)pre_slots(n_phi) * 2 +
-                             (size_t)n_phi * pre_ncp(NC) + (kPreMaxT / 32) * 32) +
-           2 * NC * 4096;
-  };
-  const size_t lds = lds_bytes(a.n_phi);
+// Whether the waves of a workgroup share the bank rows through LDS (else each
+// wave reads them for itself, a chunk ahead in registers).  Shared, with two to
+// five channels, the kernel runs two waves per SIMD, which pays when the LDS of
+// its stages and forms leaves room for six of the eight on a CU: five channels,
+// 2^15 rows, three detectors, 128 times, 32 phases 0.95 against 1.20 ms a call
+// (64 times 0.94 against 0.84; 128 phases, one workgroup per CU, 2.46 against
+// 2.42; 32 times, one wave per workgroup and nothing to share, 0.97 against
+// 0.67).  One channel has few loads to share (0.44 either way, 0.42 against 0.38
+// at 64 times), and six or seven leave one wave per SIMD on both paths, where
+// the barriers cost what the shared loads save (seven channels, 64 times: 2.39
+// against 1.78).  With eight the registers do not hold a chunk ahead (120
+// spilled), so shared from three waves on a CU (96 times 2.62 against 3.20).
+constexpr bool pre_shared(int nc, int n_t, int n_phi) {
+  if (n_t < 64 || nc == 1 || nc == 6 || nc == 7) return false;
+  const int room = nc <= 5 ? 8 : 4, want = nc <= 5 ? 6 : 3;
+  const int waves = n_t / 32 * (int)(160 * 1024 / pre_lds_bytes(nc, n_phi, true));
+  return (waves < room ? waves : room) >= want;
+}
+
+template <int PREC, int NC, bool FOURS, bool SHARED>
+hipError_t launch_pre_grid(const PreArgs& a, hipStream_t s) {
   static std::once_flag attr_once;
   std::call_once(attr_once, [&] {
-    if (hipFuncSetAttribute((const void*)k_preselect<PREC, NC, FOURS>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds_bytes(kMaxPhi)) != hipSuccess)
+    if (hipFuncSetAttribute((const void*)k_preselect<PREC, NC, FOURS, SHARED>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)pre_lds_bytes(NC, kMaxPhi, SHARED)) != hipSuccess)
       (void)hipGetLastError();
   });
-  hipLaunchKernelGGL((k_pre_factors<NC>), dim3((unsigned)((a.n_chunk * NC + 255) / 256)), dim3(256), 0, s,
-                     a);
-  hipLaunchKernelGGL((k_pre_gram<PREC, NC>), dim3((unsigned)((a.n_chunk + 3) / 4)), dim3(256), 0, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   const dim3 grid((unsigned)(((a.n_chunk + 31) / 32 * a.n_det + 7) / 8 * 8));
-  hipLaunchKernelGGL((k_preselect<PREC, NC, FOURS>), grid, dim3(64 * (a.n_t / 32)), lds, s, a);
+  hipLaunchKernelGGL((k_preselect<PREC, NC, FOURS, SHARED>), grid, dim3(64 * (a.n_t / 32)),
+                     pre_lds_bytes(NC, a.n_phi, SHARED), s, a);
   return hipGetLastError();
 }
 
 template <int PREC, int NC>
 hipError_t launch_pre_main(const PreArgs& a, hipStream_t s) {
-  return pre_fours(a.n_phi) ? launch_pre_main<PREC, NC, true>(a, s) : launch_pre_main<PREC, NC, false>(a, s);
+  hipLaunchKernelGGL((k_pre_factors<NC>), dim3((unsigned)((a.n_chunk * NC + 255) / 256)), dim3(256), 0, s,
+                     a);
+  hipLaunchKernelGGL((k_pre_gram<PREC, NC>), dim3((unsigned)((a.n_chunk + 3) / 4)), dim3(256), 0, s, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (pre_shared(NC, a.n_t, a.n_phi))
+    return pre_fours(a.n_phi) ? launch_pre_grid<PREC, NC, true, true>(a, s)
+                              : launch_pre_grid<PREC, NC, false, true>(a, s);
+  return pre_fours(a.n_phi) ? launch_pre_grid<PREC, NC, true, false>(a, s)
+                            : launch_pre_grid<PREC, NC, false, false>(a, s);
 }
 
 template <int PREC>
