@@ -454,22 +454,37 @@ NormRanges output_ranges(int G) {
   return r;
 }
 
-template <int PREC, int NC>
+// bytes of a row's amplitudes and the noise weights, which k_hh_precompute
+// keeps in LDS when they fit 64 KB (the kernel applies the same test)
+template <int PREC>
+size_t hh_stage_bytes(const dotpe_event* ev) {
+  const dotpe_bank* bk = ev->bank;
+  const size_t rb = PREC == kFP64 ? sizeof(double2) : sizeof(float2);   // staged row value
+  return (size_t)bk->n_c * (bk->n_bp + 1) * rb + (size_t)ev->n_det * (bk->n_b + 1) * sizeof(double);
+}
+
+template <int PREC, int NC, bool WHOLE>
 void launch_hh_rows(dotpe_event* ev, const double* w) {
   const dotpe_bank* bk = ev->bank;
   const size_t sh = (size_t)16 * ev->n_det * bk->mt.NP * 16;
   // (more than 64 KB with eight channels and many detectors)
   static std::once_flag attr_once;
   std::call_once(attr_once, [] {
-    if (hipFuncSetAttribute((const void*)k_hh_rows<PREC, NC>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    if (hipFuncSetAttribute((const void*)k_hh_rows<PREC, NC, WHOLE>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             16 * kMaxDet * (NC * (NC + 1) / 2) * 16) != hipSuccess)
       (void)hipGetLastError();
   });
-  hipLaunchKernelGGL((k_hh_rows<PREC, NC>), dim3((unsigned)((ev->n_sub + 15) / 16)), dim3(256), sh, ev->stream,
+  hipLaunchKernelGGL((k_hh_rows<PREC, NC, WHOLE>), dim3((unsigned)((ev->n_sub + 15) / 16)), dim3(256), sh, ev->stream,
                      ev->n_sub, ev->sub_idx, ev->sub0, bk->R0, bk->R1, bk->K2, bk->row_scale, bk->n_bp,
                      bk->n_b, ev->n_det, w, bk->mt, ev->hh_terms, ev->Ah[0], ev->Ah[1], ev->ah_scale,
                      ev->ah_nrm, hh_outputs(bk->mt.G));
   ev->ah_norms_done = true;
+}
+
+template <int PREC, int NC>
+void launch_hh_rows(dotpe_event* ev, const double* w) {
+  if (hh_stage_bytes<PREC>(ev) > 65536) launch_hh_rows<PREC, NC, true>(ev, w);
+  else launch_hh_rows<PREC, NC, false>(ev, w);
 }
 
 // the row-side (h|h) operand from Gram sums by 16 lanes per row (split
@@ -486,15 +501,6 @@ void launch_hh_rows(dotpe_event* ev, const double* w) {
     case 7: return launch_hh_rows<PREC, 7>(ev, w);
     default: return launch_hh_rows<PREC, 8>(ev, w);
   }
-}
-
-// bytes of a row's amplitudes and the noise weights, which k_hh_precompute
-// keeps in LDS when they fit 64 KB (the kernel applies the same test)
-template <int PREC>
-size_t hh_stage_bytes(const dotpe_event* ev) {
-  const dotpe_bank* bk = ev->bank;
-  const size_t rb = PREC == kFP64 ? sizeof(double2) : sizeof(float2);   // staged row value
-  return (size_t)bk->n_c * (bk->n_bp + 1) * rb + (size_t)ev->n_det * (bk->n_b + 1) * sizeof(double);
 }
 
 template <int PREC>

@@ -58,11 +58,21 @@ __device__ __forceinline__ void gram_reduce(double (&v)[N], int lane) {
   gram_halve<N3, 0xB1>(v, lane & 1);     // quad_perm 1,0,3,2: lane ^ 1
 }
 
+// A bank value hi + lo.  lo may start far below hi's last place, so the sum can
+// take more than a float's 24 bits: about one FP16 value in six loses some of
+// them, up to 2^-24 of the value, a quarter of what the split leaves out.
+// WHOLE: every bit.  (The kernel that stages rows in LDS keeps them as floats;
+// rows it would stage are rounded here as there, longer ones are whole on both.)
+template <bool WHOLE>
+__device__ __forceinline__ double gram_join(float hi, float lo) {
+  return WHOLE ? (double)hi + (double)lo : (double)(hi + lo);
+}
+
 // v += the Gram sums of the row whose hi and lo parts (conj(h), row-major, n_bp
 // bins per channel) start at r0, r1, for the detectors w[0 .. KD) (rows of n_b
 // weights; nk of them valid), this lane's bins.  v: per detector re of (c, c'
 // >= c) row by row, then im of (c, c' > c).
-template <int PREC, int NC, int KD>
+template <int PREC, int NC, int KD, bool WHOLE>
 __device__ __forceinline__ void gram_row(const void* r0, const void* r1, int n_b, int n_bp, const double* w,
                                          int nk, int l16, double (&v)[KD * gram_vals(NC)]) {
   typedef typename std::conditional<PREC == kFP16X2, _Float16, __bf16>::type H;
@@ -87,13 +97,11 @@ __device__ __forceinline__ void gram_row(const void* r0, const void* r1, int n_b
       double wk[KD];
 #pragma unroll
       for (int k = 0; k < KD; ++k) wk[k] = k < nk ? w[k * n_b + b0 + j] : 0.0;
-      // (in double: lo may start far below hi's last place, so that hi + lo
-      // may take more than a float's 24 bits)
       double hr[NC], hi[NC];
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        hr[c] = (double)(float)rh[c].x[j] + (double)(float)rl[c].x[j];
-        hi[c] = -((double)(float)ih[c].x[j] + (double)(float)il[c].x[j]);
+        hr[c] = gram_join<WHOLE>((float)rh[c].x[j], (float)rl[c].x[j]);
+        hi[c] = -gram_join<WHOLE>((float)ih[c].x[j], (float)il[c].x[j]);
       }
       int p = 0, q = NP;
 #pragma unroll
@@ -133,7 +141,7 @@ __device__ __forceinline__ int gram_place(int u) {
 // The Gram sums of one row per 16 lanes for n_det detectors to out [n_det][NP]
 // (re, im), times scale (the row's); every lane takes part, those of a row past
 // the end with live = false.  (The im of c = c' is zero.)
-template <int PREC, int NC>
+template <int PREC, int NC, bool WHOLE>
 __device__ __forceinline__ void gram_row_all(const void* r0, const void* r1, int n_b, int n_bp,
                                              const double* w, int n_det, double scale, int lane, double* out,
                                              bool live) {
@@ -144,7 +152,7 @@ __device__ __forceinline__ void gram_row_all(const void* r0, const void* r1, int
 #pragma unroll
     for (int q = 0; q < KD * NV; ++q) v[q] = 0.0;
     const int nk = min(KD, n_det - k0);
-    gram_row<PREC, NC, KD>(r0, r1, n_b, n_bp, w + (int64_t)k0 * n_b, nk, l16, v);
+    gram_row<PREC, NC, KD, WHOLE>(r0, r1, n_b, n_bp, w + (int64_t)k0 * n_b, nk, l16, v);
     gram_reduce(v, lane);
     if (!live) continue;
 #pragma unroll

@@ -972,7 +972,7 @@ __global__ void k_hh_precompute(int64_t n_sub, const int64_t* __restrict__ sub_i
 // row staged in LDS and five barriers took 9.8 ms at 2^20 rows, five channels,
 // three detectors; 4.4 ms now, against 2.5 ms to read the bank and write the
 // operand.
-template <int PREC, int NC>
+template <int PREC, int NC, bool WHOLE>
 __global__ __launch_bounds__(256, 2) void k_hh_rows(int64_t n_sub, const int64_t* __restrict__ sub_idx,
                                                     int64_t sub0, const void* __restrict__ R0,
                                                     const void* __restrict__ R1, int64_t K2,
@@ -991,7 +991,7 @@ __global__ __launch_bounds__(256, 2) void k_hh_rows(int64_t n_sub, const int64_t
   const int64_t i = sub_idx ? sub_idx[live ? ie : 0] : sub0 + (live ? ie : 0);
   double* G = hh_sums + (size_t)(threadIdx.x >> 4) * n_det * NP * 2;
   const double sc = row_scale[i];
-  gram_row_all<PREC, NC>((const uint16_t*)R0 + i * K2, (const uint16_t*)R1 + i * K2, n_b, n_bp, w, n_det,
+  gram_row_all<PREC, NC, WHOLE>((const uint16_t*)R0 + i * K2, (const uint16_t*)R1 + i * K2, n_b, n_bp, w, n_det,
                          sc * sc, lane, G, live);
   __syncthreads();
   if (!live) return;
