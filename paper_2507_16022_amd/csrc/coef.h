@@ -257,15 +257,25 @@ template <int PREC, int G>
 __device__ __forceinline__ void coef_pass(const FusedArgs& a, int64_t wg_id, int64_t wg_count) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int64_t end = min(a.work0 + a.coef_tiles, coef_work_count(a));
-  const int64_t first = coef_first(wg_id, wg_count);
-  if (2 * (end - a.work0) <= wg_count) {
-    // a list that leaves half of the workgroups idle: half a tile each
-    const int64_t q = a.work0 + first / 2;
-    if (q < end) coef_item<PREC, G, 1>(a, smem, q, (int)(first & 1));
+  const int64_t n = end - a.work0;
+  if (2 * n <= wg_count) {
+    // a list that leaves half of the workgroups idle: half a tile each, the
+    // halves of a tile on one XCD
+    const int64_t part = (n + 7) / 8, y = wg_id / 8;
+    int64_t at = wg_id / 2, half = wg_id & 1;
+    if (16 * part <= wg_count) {
+      at = y / 2 < part ? wg_id % 8 * part + y / 2 : n;
+      half = y & 1;
+    }
+    if (at < n) coef_item<PREC, G, 1>(a, smem, a.work0 + at, (int)half);
     return;
   }
 #pragma unroll 1
-  for (int64_t q = a.work0 + first; q < end; q += wg_count) coef_item<PREC, G, 2>(a, smem, q, 0);
+  for (int64_t q0 = a.work0; q0 < end; q0 += wg_count) {
+    const int64_t at = coef_place(wg_id, wg_count, min(wg_count, end - q0));
+    if (at < 0) break;
+    coef_item<PREC, G, 2>(a, smem, q0 + at, 0);
+  }
 }
 
 template <int PREC, int G>
