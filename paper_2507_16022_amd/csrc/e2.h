@@ -134,6 +134,25 @@ struct PairSlot {
   static constexpr int STRIDE = (UNITS | 1) * U;
 };
 
+// Kept phases per wave and turn of the distance rule: as LDS allows three
+// workgroups per CU.  FP64 slots are larger; with the phase table of 64 phases
+// and more only two fit, which then take more per turn (64 x 20000 pairs, 32
+// phases, all kept: this kernel 0.98 ms with 256 per turn and two workgroups,
+// 0.76 with 192 and three; 3000 x 3000, 128 phases a call of 21.3 ms with 256
+// per turn, 23.3 with 192).
+template <int PREC>
+__host__ __device__ constexpr int e2_turn(int n_phi) {
+  return PREC != kFP64 ? 512 : n_phi < 64 ? 192 : 256;
+}
+constexpr int kE2Waves = 4;
+// bytes of its dynamic LDS: the phase table, then per wave a turn's ln Lbar and
+// places
+template <int PREC>
+constexpr size_t e2_lds(int n_phi) {
+  return sizeof(double) * kMaxM * (size_t)n_phi * 2 +
+         kE2Waves * (size_t)e2_turn<PREC>(n_phi) * (sizeof(double) + sizeof(uint16_t));
+}
+
 // MODE kEvidence: the second half of an evidence pass; kEval: every pair's
 // ln L (and largest lnL^ML, and triples) of the tiles from work0 on.
 template <int PREC, int G, int MODE>
@@ -143,20 +162,15 @@ __device__ __forceinline__ void e2_pass(const FusedArgs& a, int64_t wg_id, int64
   constexpr bool EVAL = MODE == kEval;
   constexpr int NRT = (G == 1) ? 1 : kMaxNR;
   constexpr int NCO = 2 * G + NRT;
-  constexpr int TM = TL::TM, TN = TL::TN, NPT = TM * TN, NT = 256, NW = NT / 64, NK = NPT / NT;
-  static_assert(NPT % NT == 0 && (TN == 64 || TN == 32), "whole rows per wave");
+  constexpr int TM = TL::TM, TN = TL::TN, NPT = TM * TN, NT = 256, NW = kE2Waves, NK = NPT / NT;
+  static_assert(NT == 64 * NW && NPT % NT == 0 && (TN == 64 || TN == 32), "whole rows per wave");
   constexpr int PARTS = EVAL ? kEvalParts : 1;
   static_assert(NK % PARTS == 0, "whole turns per part");
   typedef PairSlot<AT, NCO> SL;
-  // kept phases per turn of the distance rule: as LDS allows three workgroups
-  // per CU
-  constexpr int CH = PREC == kFP64 ? 256 : 512;
   extern __shared__ __align__(16) double lds_cs[];     // [kMaxM][n_phi][2]
   __shared__ DistParams dp;
   __shared__ double rowd[TM * 4], cold[TN * 3], rowq[TM * 2], red[NW * kNPart];
   __shared__ __align__(16) AT slots[NW][64 * SL::STRIDE];
-  __shared__ double val[NW][CH];         // ln Lbar of the turn's kept phases
-  __shared__ uint16_t ent[NW][CH];       // slot << 8 | phase
   // sums of the waves' e^(ln p - m) by row and by column, m the wave's largest
   // ln p so far
   __shared__ double rsum[TM], csum[NW][TN], wmax[NW];
@@ -179,8 +193,10 @@ __device__ __forceinline__ void e2_pass(const FusedArgs& a, int64_t wg_id, int64
   const float thr_f = (float)thr_ml;
   const int64_t end = min(a.work0 + a.coef_tiles, coef_work_count(a));
   AT* const my_slots = slots[wave];
-  double* const my_val = val[wave];
-  uint16_t* const my_ent = ent[wave];
+  const int CH = e2_turn<PREC>(n_phi);
+  double* const val = lds_cs + kMaxM * n_phi * 2;
+  double* const my_val = val + wave * CH;                            // ln Lbar of the turn's kept phases
+  uint16_t* const my_ent = (uint16_t*)(val + NW * CH) + wave * CH;   // slot << 8 | phase
 
   // a pair's coefficients and scales from its slot
   struct Coef {

@@ -20,9 +20,6 @@
 namespace dotpe {
 namespace {
 
-// dynamic LDS of the second half of the coefficient route: the phase table
-size_t e2_lds(int n_phi) { return sizeof(double) * kMaxM * (size_t)n_phi * 2; }
-
 template <int PREC, int G>
 hipError_t launch_marg(int mode, const FusedArgs& a, int64_t grid, hipStream_t s) {
   switch (mode) {
@@ -35,11 +32,11 @@ hipError_t launch_marg(int mode, const FusedArgs& a, int64_t grid, hipStream_t s
       }
     case kE2:
       hipLaunchKernelGGL((k_e2_tiles<PREC, G, kEvidence>), dim3((unsigned)grid), dim3(256),
-                         e2_lds(a.n_phi), s, a);
+                         e2_lds<PREC>(a.n_phi), s, a);
       return hipGetLastError();
     case kEval:
       hipLaunchKernelGGL((k_e2_tiles<PREC, G, kEval>), dim3((unsigned)grid), dim3(256),
-                         e2_lds(a.n_phi), s, a);
+                         e2_lds<PREC>(a.n_phi), s, a);
       return hipGetLastError();
     case kSample:
       {
@@ -68,7 +65,7 @@ hipError_t launch_marg_packed(int mode, const PackLaunch& p, int n_phi, hipStrea
         return hipGetLastError();
       }
     case kE2:
-      hipLaunchKernelGGL((k_e2_tiles_packed<PREC, G>), grid, dim3(256), e2_lds(n_phi), s, p);
+      hipLaunchKernelGGL((k_e2_tiles_packed<PREC, G>), grid, dim3(256), e2_lds<PREC>(n_phi), s, p);
       return hipGetLastError();
   }
   return hipErrorInvalidValue;
