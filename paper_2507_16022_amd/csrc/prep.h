@@ -363,24 +363,24 @@ __global__ __launch_bounds__(256) void k_operand_norms(const void* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// relative-binning weights (App. A, eqs. dh_weights, hh_weights): a wave
-// per (k, c, b) of W^dh and per (k, c, c', b) of W^hh, its lanes over the
-// full-resolution points of the hat function s_b's support (from the node
-// before to the node after).  Reference of detector k: h0_c(f) exp(-2 pi i
-// f t0_k), so W^dh carries exp(2 pi i (f - f_b) t0_k), reduced in cycles,
-// and W^hh none.  Bound by the latency of its loads (21 MB that the L2s
-// hold, ~0.5 GFLOP): with a thread per weight, 3 x 5 channels x 256 nodes
-// were 90 workgroups of serial sums over ~1000 points, 2.0 ms at 2^17
-// frequencies (the call, host transfers included, 4.25 ms); with a wave per
-// weight the call takes 1.88 ms, most of it the transfers.
+// relative-binning weights (App. A, eqs. dh_weights, hh_weights): `lanes` lanes
+// (a power of two up to a wave) per (k, c, b) of W^dh and per (k, c, c', b) of
+// W^hh, over the full-resolution points of the hat function s_b's support
+// (from the node before to the node after).  Reference of detector k: h0_c(f)
+// exp(-2 pi i f t0_k), so W^dh carries exp(2 pi i (f - f_b) t0_k), reduced in
+// cycles, and W^hh none.  Bound by the latency of its loads (21 MB that the L2s
+// hold, ~0.5 GFLOP): with a thread per weight, 3 x 5 channels x 256 nodes were
+// 90 workgroups of serial sums over ~1000 points, 2.0 ms at 2^17 frequencies
+// (the call, host transfers included, 4.25 ms); with a wave per weight the call
+// takes 1.88 ms, most of it the transfers.
 // ---------------------------------------------------------------------------
-__global__ void k_rb_weights(int n_det, int n_c, int64_t n_full, int n_nodes,
+__global__ void k_rb_weights(int lanes, int n_det, int n_c, int64_t n_full, int n_nodes,
                              const double* __restrict__ f, const double2* __restrict__ d,
                              const double* __restrict__ w, const double2* __restrict__ h0,
                              const double* __restrict__ t0, const int64_t* __restrict__ node_idx,
                              double2* __restrict__ wdh, double2* __restrict__ whh) {
-  const int lane = threadIdx.x & 63;
-  const int64_t idx = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const int lane = threadIdx.x & (lanes - 1);
+  const int64_t idx = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / lanes;
   const int64_t n_dh = (int64_t)n_det * n_c * n_nodes;
   const int64_t n_hh = (int64_t)n_det * n_c * n_c * n_nodes;
   if (idx >= n_dh + n_hh) return;
@@ -401,7 +401,7 @@ __global__ void k_rb_weights(int n_det, int n_c, int64_t n_full, int n_nodes,
   const double fb = f[qb], flo = f[lo], fhi = f[hi];
   const double tk = t0 ? t0[k] : 0.0;
   double2 acc = make_double2(0.0, 0.0);
-  for (int64_t q = lo + lane; q <= hi; q += 64) {
+  for (int64_t q = lo + lane; q <= hi; q += lanes) {
     const double fq = f[q];
     const double s = q < qb ? (fq - flo) / (fb - flo) : q > qb ? (fhi - fq) / (fhi - fb) : 1.0;
     const double ws = w[(int64_t)k * n_full + q] * s;
@@ -417,10 +417,11 @@ __global__ void k_rb_weights(int n_det, int n_c, int64_t n_full, int n_nodes,
     acc.x += ws * v.x;
     acc.y += ws * v.y;
   }
-  auto add = [](double x, double y) { return x + y; };
-  acc.x = wave_reduce(acc.x, 0.0, add);
-  acc.y = wave_reduce(acc.y, 0.0, add);
-  if (lane != 63) return;          // the lane with the sums
+  for (int off = lanes / 2; off > 0; off /= 2) {
+    acc.x += __shfl_xor(acc.x, off, 64);
+    acc.y += __shfl_xor(acc.y, off, 64);
+  }
+  if (lane != 0) return;
   // divide by conj(h0_c(f_b)), or by h0_c(f_b) conj(h0_c'(f_b))
   double2 den = cconj(h0[(int64_t)c * n_full + qb]);
   if (!is_dh) den = cmul(h0[(int64_t)c * n_full + qb], cconj(h0[(int64_t)c2 * n_full + qb]));
