@@ -1547,10 +1547,19 @@ static int pass_tail(dotpe_event* ev, const FusedArgs& a, hipStream_t s, double*
 // Events of fewer than kOrderMinTiles run in one round of workgroups; above
 // kOrderMaxTiles the bitmap (a bit per tile) would not fit LDS.
 constexpr int64_t kOrderMinTiles = 1024, kOrderMaxTiles = 64 * 8192;
-static void order_list(const dotpe_event* ev, const FusedArgs& a, hipStream_t s) {
-  if (a.n_tiles < kOrderMinTiles || a.n_tiles > kOrderMaxTiles) return;
+static int order_list(const dotpe_event* ev, const FusedArgs& a, hipStream_t s) {
+  if (a.n_tiles < kOrderMinTiles || a.n_tiles > kOrderMaxTiles) return DOTPE_OK;
+  // (64 KB for the bitmap of the most tiles, and the kernel's own sums)
+  static std::once_flag attr_once;
+  std::call_once(attr_once, [] {
+    if (hipFuncSetAttribute((const void*)k_order_list, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)(kOrderMaxTiles / 8)) != hipSuccess)
+      (void)hipGetLastError();
+  });
   hipLaunchKernelGGL(k_order_list, dim3(1), dim3(1024), (size_t)((a.n_tiles + 31) / 32 * 4), s, ev->state,
                      a.cut_delta, a.n_tiles_m, a.n_tiles_n, (int)kOrderMinTiles, ev->rerun);
+  HIP_OK(hipGetLastError());
+  return DOTPE_OK;
 }
 
 // whether a pass with this state cuts (cut_on of the kernels)
@@ -1638,7 +1647,7 @@ static int evidence_pass(dotpe_ctx* ctx, dotpe_event* ev, double cut_delta,
   // an empty chunk's two kernels take 10 us, the wait 15 (65536 x 4096 pairs:
   // 32 chunks, none of them needed, 0.33 of 5.6 ms).
   int64_t n_chunks = pl.n_chunks;
-  if (pl.may_cut) order_list(ev, a, s);
+  if (pl.may_cut && (rc = order_list(ev, a, s))) return rc;
   if (pl.may_cut && n_chunks > 2) {
     uint64_t st_cut[6];
     HIP_OK(hipMemcpyAsync(st_cut, ev->state, sizeof(st_cut), hipMemcpyDeviceToHost, s));
@@ -1793,7 +1802,7 @@ static int evidence_pass_packed(dotpe_ctx* ctx, dotpe_event* const* evs, int n,
                   [&](int k) { return pl[k].may_cut && !pl[k].bound_pass ? pl[k].cut_grid : 0; })))
     return rc;
   for (int k = 0; k < n; ++k)
-    if (pl[k].may_cut) order_list(evs[k], pb->h_args[k], s);
+    if (pl[k].may_cut && (rc = order_list(evs[k], pb->h_args[k], s))) return rc;
   for (int64_t c = 0; c < max_chunks; ++c) {
     if ((rc = stage(kCoef, c, [&](int k) { return c < pl[k].n_chunks ? pl[k].coef_grid : 0; })))
       return rc;
