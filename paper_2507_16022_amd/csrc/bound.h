@@ -625,19 +625,10 @@ __device__ __forceinline__ void bound_pass_tile(const FusedArgs& a, int64_t wg_i
   }
 }
 
-// A launch of 2^24 workgroups (2^37 pairs) would pass the 2^32 work-items that a
-// dimension of a grid may have: the workgroups are counted along rows of 2^20,
-// as many as one dimension would number them where there is one row.
-constexpr int64_t kBoundGridRow = int64_t(1) << 20;
-inline dim3 bound_grid(int64_t n) {
-  if (n <= kBoundGridRow) return dim3((unsigned)n);
-  return dim3((unsigned)kBoundGridRow, (unsigned)((n + kBoundGridRow - 1) / kBoundGridRow));
-}
-__device__ __forceinline__ int64_t bound_wg() { return blockIdx.x + (int64_t)gridDim.x * blockIdx.y; }
-
+// (2^37 pairs take 2^24 workgroups of 256)
 template <int PREC, int G>
 __global__ __launch_bounds__(BoundTile::NT, 2) void k_lnl_bound(FusedArgs a) {
-  bound_pass_tile<PREC, G>(a, bound_wg(), (int64_t)gridDim.x * gridDim.y);
+  bound_pass_tile<PREC, G>(a, long_grid_wg(), (int64_t)gridDim.x * gridDim.y);
 }
 
 // the bound pass of several events in one launch
@@ -645,7 +636,7 @@ template <int PREC, int G>
 __global__ __launch_bounds__(BoundTile::NT, 2) void k_lnl_bound_packed(PackLaunch p) {
   int64_t blk, nblk;
   int q;
-  const int e = pack_locate(p, bound_wg(), &blk, &nblk, &q);
+  const int e = pack_locate(p, long_grid_wg(), &blk, &nblk, &q);
   if (blk >= nblk) return;         // (past the last event, in the last row of the grid)
   FusedArgs a = pack_args(p, e, q);
   bound_pass_tile<PREC, G>(a, blk, nblk);

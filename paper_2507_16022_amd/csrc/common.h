@@ -32,6 +32,16 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
+// A grid of n workgroups counted along rows of 2^20: one dimension of a grid may
+// not have 2^32 work-items, which 2^24 workgroups of 256 would be.  The numbers
+// are those of a grid of one dimension, in the same order; past n in the last row.
+constexpr int64_t kGridRow = int64_t(1) << 20;
+inline dim3 long_grid(int64_t n) {
+  if (n <= kGridRow) return dim3((unsigned)n);
+  return dim3((unsigned)kGridRow, (unsigned)((n + kGridRow - 1) / kGridRow));
+}
+__device__ __forceinline__ int64_t long_grid_wg() { return blockIdx.x + (int64_t)gridDim.x * blockIdx.y; }
+
 constexpr int kMaxC = 8;        // channels
 constexpr int kMaxG = 4;        // distinct m
 constexpr int kMaxDet = 8;

@@ -2484,7 +2484,7 @@ int dotpe_extrinsic_samples(dotpe_ctx* ctx, const dotpe_bank* bk, const dotpe_ex
   hipLaunchKernelGGL(k_prop_mass, dim3((unsigned)nb_cells), b256, 0, s, ml, rmax, tau, lnZ, g, mass,
                      supp);
   scan_inclusive(mass, nb_cells * C, blk, s);
-  hipLaunchKernelGGL(k_prop_draw, dim3((unsigned)((ns + 3) / 4)), b256, 0, s, ml, rmax, tau, lnZ,
+  hipLaunchKernelGGL(k_prop_draw, long_grid((ns + 3) / 4), b256, 0, s, ml, rmax, tau, lnZ,
                      (const double*)mass, nb_cells, g, ns, d->seed, draws);
   hipLaunchKernelGGL(k_prop_stats, dim3(1), dim3(1024), 0, s, (const double*)draws + 5 * ns, ns, supp,
                      nb_cells, SJ, stats);

@@ -53,7 +53,7 @@ hipError_t launch_bound(const FusedArgs& a, int64_t grid, hipStream_t s) {
                               BoundTile::LDS_BYTES) != hipSuccess)
         (void)hipGetLastError();
     });
-    hipLaunchKernelGGL((k_lnl_bound<PREC, G>), bound_grid(grid), dim3(BoundTile::NT),
+    hipLaunchKernelGGL((k_lnl_bound<PREC, G>), long_grid(grid), dim3(BoundTile::NT),
                        BoundTile::LDS_BYTES, s, a);
     return hipGetLastError();
   }
@@ -87,7 +87,7 @@ hipError_t launch_bound_packed(const PackLaunch& p, hipStream_t s) {
                               BoundTile::LDS_BYTES) != hipSuccess)
         (void)hipGetLastError();
     });
-    hipLaunchKernelGGL((k_lnl_bound_packed<PREC, G>), bound_grid(p.off[p.n]),
+    hipLaunchKernelGGL((k_lnl_bound_packed<PREC, G>), long_grid(p.off[p.n]),
                        dim3(BoundTile::NT), BoundTile::LDS_BYTES, s, p);
     return hipGetLastError();
   }

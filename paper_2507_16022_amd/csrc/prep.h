@@ -634,7 +634,7 @@ __global__ __launch_bounds__(256) void k_prop_draw(const double* __restrict__ ml
                                                     PropGeom g, int64_t n_s, uint64_t seed,
                                                     double* __restrict__ out) {
   const int lane = threadIdx.x & 63;
-  const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t q = long_grid_wg() * 4 + (threadIdx.x >> 6);
   if (q >= n_s) return;
   const unsigned SJ = (unsigned)g.S * g.J;
   const int c = (int)(q % g.C);
