@@ -711,7 +711,7 @@ __global__ __launch_bounds__(256) void k_sample_draws(FusedArgs a) {
     ((unsigned*)&dp)[t] = ((const unsigned*)a.dist.prm)[t];
   __syncthreads();
   const double thr_ml = cut_on(a) ? __longlong_as_double(a.state[3]) - a.cut_delta : -INFINITY;
-  const int64_t s = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t s = long_grid_wg() * 4 + wave;
   if (s >= a.n_samples) return;
   const int64_t item = (int64_t)a.sample_item[s] - a.work0;
   if (item < 0 || item >= a.coef_tiles) return;   // another chunk's

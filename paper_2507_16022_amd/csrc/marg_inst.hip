@@ -45,8 +45,7 @@ hipError_t launch_marg(int mode, const FusedArgs& a, int64_t grid, hipStream_t s
         hipLaunchKernelGGL((k_sample_pairs<PREC, G>), dim3((unsigned)(grid * (NPT / 256))), dim3(256),
                            0, s, a);
         hipLaunchKernelGGL((k_sample_cum<NPT>), dim3((unsigned)grid), dim3(256), 0, s, a);
-        hipLaunchKernelGGL((k_sample_draws<PREC, G>), dim3((unsigned)((a.n_samples + 3) / 4)),
-                           dim3(256), 0, s, a);
+        hipLaunchKernelGGL((k_sample_draws<PREC, G>), long_grid((a.n_samples + 3) / 4), dim3(256), 0, s, a);
       }
       return hipGetLastError();
   }
