@@ -195,7 +195,9 @@ struct dotpe_event {
   hipEvent_t ev_t[4] = {nullptr, nullptr, nullptr, nullptr};
   std::vector<void*> allocs;
   uint64_t bytes = 0;
-  std::mutex use;                // held by a call that fills coef or the pass's buffers
+  // held by a call that fills coef or the pass's buffers, from before it reads
+  // what the last pass left (events of a packed pass are the server's own)
+  std::mutex use;
 };
 
 namespace {
@@ -2200,13 +2202,13 @@ int dotpe_sample_posterior(dotpe_ctx* ctx, dotpe_event* ev, int64_t n_samples, d
                            uint64_t seed, dotpe_posterior_sample* out, int64_t capacity,
                            int64_t* n_out) {
   if (!ctx || !ev || !out || !n_out) return fail(DOTPE_E_INVALID_ARG, "NULL argument");
-  if (!ev->evaluated) return fail(DOTPE_E_INVALID_ARG, "call dotpe_evidence on the event first");
   if (!(u0 >= 0.0 && u0 < 1.0)) return fail(DOTPE_E_INVALID_ARG, "u0 must lie in [0, 1)");
   if (capacity < 1) return fail(DOTPE_E_INVALID_ARG, "capacity must be positive");
-  int64_t ns = n_samples > 0 ? n_samples : (int64_t)std::floor(0.5 * ev->last_n_eff);
-  ns = std::max<int64_t>(1, std::min(ns, capacity));
   HIP_OK(hipSetDevice(ctx->device));
   std::lock_guard<std::mutex> use(ev->use);
+  if (!ev->evaluated) return fail(DOTPE_E_INVALID_ARG, "call dotpe_evidence on the event first");
+  int64_t ns = n_samples > 0 ? n_samples : (int64_t)std::floor(0.5 * ev->last_n_eff);
+  ns = std::max<int64_t>(1, std::min(ns, capacity));
   hipStream_t s = ev->stream;
   const int prec = ev->bank->prec;
   FusedArgs a = make_args(ctx, ev);
