@@ -1489,7 +1489,16 @@ static PassPlan pass_plan(const dotpe_event* ev, const FusedArgs& a) {
     const int64_t npr = (a.n_tiles_m + a.pilot_stride - 1) / a.pilot_stride;
     p.pilot_grid = round_up(npr * a.n_tiles_n, 8);
     const int64_t n_big = big_tiles(a.n_tiles_m, a.n_tiles_n);
-    p.bound_pass = prec != kFP64 && n_big >= kBoundMinTiles &&
+    // below kSurvMinTiles only where the bounded mass cannot decide on another
+    // pass: every bounded pair lies cut_delta below the largest lnL^ML, so all
+    // of them together come to at most n_pairs e^-cut_delta of it, in practice
+    // to 1e-7 of that.  The bound pass's margin makes the certificate up to
+    // twelve times as wide (BF16x2), and where cut_target lay in between the
+    // event took two passes instead of one (8192 x 1100 pairs, cut_delta 4,
+    // cut_target 1e-3: 0.83 -> 1.69 ms).
+    const double n_pairs = (double)ev->n_sub * (double)ev->n_ext;
+    const bool tight = n_big < kSurvMinTiles && !(n_pairs * std::exp(-a.cut_delta) <= ev->cut_target);
+    p.bound_pass = prec != kFP64 && n_big >= kBoundMinTiles && !tight &&
                    !(ev->flags & (DOTPE_FLAG_NO_BOUND_PASS | DOTPE_FLAG_RERUN_ALL));
     p.cut_grid = round_up(p.bound_pass ? bound_wgs(a.n_tiles_m, a.n_tiles_n) : a.n_tiles, 8);
     if (p.bound_pass && a.surv_cap > 0) p.surv_grid = std::min<int64_t>(kSurvGrid, (a.n_tiles + 3) / 4);
