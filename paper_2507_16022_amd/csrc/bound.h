@@ -59,9 +59,9 @@ struct BoundTile {
   static constexpr int COLN_OFF = ROWN_OFF + TM * 16;    // float4 [TN]
   static constexpr int PART_OFF = COLN_OFF + TN * 16;    // float4 [4]: the waves' survivors and bounded mass
   static constexpr int LDS_BYTES = PART_OFF + 4 * 16;
-  // the margin factors per group and output of a wave's 64 rows and 32
-  // columns, where it needs them: in the stages, once the products are done
-  static constexpr int TIGHT_BYTES = (64 + 32) * NV * 4;
+  // the margin factors per group and output of a wave's 64 rows, where it needs
+  // them: in the stages, once the products are done (its columns' in registers)
+  static constexpr int TIGHT_BYTES = 64 * NV * 4;
   static_assert(4 * TIGHT_BYTES <= NS * STAGE, "factors fit the stages");
   static_assert(2 * LDS_BYTES <= 160 * 1024, "two workgroups per CU");
 };

@@ -49,12 +49,15 @@ int fail(int code, const char* fmt, ...) {
 
 int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
-// 128 x 128 tiles an event needs before the bound pass replaces the fused
-// kernel's fast epilogue: one per CU.  The pass takes one product per operand
-// pair instead of three, on tiles four times as large; with the operand norms
-// that it needs a call of 128 tiles takes as long either way (fast 0.081,
-// bound 0.063 ms), one of 256 tiles 0.155 against 0.075 ms for the pass and
-// one of 1920 tiles 1.13 against 0.53 ms.
+// 128 x 128 tiles (each two workgroups of the bound pass) an event needs before
+// the bound pass replaces the fused kernel's fast epilogue: it takes one product
+// per operand pair instead of three, but needs the operand norms and leaves more
+// tiles to the coefficient route.  Five modes, 256 bins, 32 phases, SNR 20, the
+// pass and a repeated call, bound against fast: 256 tiles 0.058 / 0.157 and 0.40
+// / 0.48 ms; 1920 tiles 0.38 / 1.05 and 1.87 / 2.38; (m, p) banks with
+// relative-binning weights, 1920 tiles 0.57 / 1.61 and 4.13 / 5.17; BF16x2, where
+// twice as many tiles are left, 0.37 / 1.01 and 2.36 / 2.32.  At 64 tiles the
+// calls take as long either way.
 // And the tiles it needs before the bound pass lists a tile's few survivors
 // for the survivor pass: with fewer, every tile with a survivor takes the
 // coefficient route, as after the fast pass.
@@ -65,7 +68,7 @@ int64_t big_tiles(int64_t n_tiles_m, int64_t n_tiles_n) {
 }
 // the bound pass's workgroups, 128 rows x 64 columns each
 int64_t bound_wgs(int64_t n_tiles_m, int64_t n_tiles_n) { return (n_tiles_m + 1) / 2 * n_tiles_n; }
-constexpr int64_t kMargPer = 256;     // tiles summed by one thread of the marginal pass
+constexpr int64_t kMargPer = 256;     // tiles along a row or column per block of the marginal pass
 constexpr int kNormBlocks = 256;      // block sums of (d|d) over full-resolution data
 
 }  // namespace
@@ -2387,8 +2390,8 @@ int dotpe_extrinsic_samples(dotpe_ctx* ctx, const dotpe_bank* bk, const dotpe_ex
   HIP_OK(hipSetDevice(ctx->device));
   hipStream_t s = d->stream ? (hipStream_t)d->stream : ctx->stream;
   const ModeTables& mt = bk->mt;
-  // the pre-selection's products, one intrinsic sample at a time, keeping
-  // each detector's per-time maxima
+  // the pre-selection's products of the intrinsic samples' rows, keeping each
+  // detector's per-time maxima
   PreArgs a;
   std::memset(&a, 0, sizeof(a));
   a.A0 = bk->A0;
@@ -2408,16 +2411,14 @@ int dotpe_extrinsic_samples(dotpe_ctx* ctx, const dotpe_bank* bk, const dotpe_ex
   }
   for (int g = 0; g < mt.G; ++g) a.gm[g] = mt.gm[g];
   a.G = mt.G;
-  a.n_rows = 1;
+  a.n_rows = C;
   a.n_det = nk;
   a.n_t = d->n_t;
   a.n_phi = d->n_phi;
   a.f = bk->f;
   a.dt = d->dt;
   a.K2p = 2 * (int64_t)bk->n_bp;
-  a.delta = 20.0;
   const int64_t n_grid = (int64_t)nk * d->n_t, ns = d->n_samples;
-  a.n_rows = C;
   // one device block for the call: the host inputs (copied as one piece),
   // then the series' and the proposals' buffers
   Carve m;

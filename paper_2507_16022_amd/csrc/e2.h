@@ -1,12 +1,12 @@
-// Second half of the coefficient route of an evidence pass.  The fused
-// kernel (mode kCoef) has stored the raw accumulators of every pair of the
-// chunk's tiles; this kernel bounds (E1) and evaluates (E2: per-phase
-// distance marginalisation, eq. lnl_dist_marginalized, and the phase
-// average) every pair and writes each tile's partial.  Apart from the
-// accumulators it holds a handful of doubles per lane, so several waves share
-// every SIMD and hide the latency of the distance rule's table reads, which
-// the fused kernel, one wave per SIMD, cannot.  The (i, e) matrix of ln L is
-// written by the same kernel without the cut and the sums.
+// Second half of the coefficient route of an evidence pass.  The first half
+// (k_coef; for FP64 banks the fused kernel in mode kCoef) has stored the raw
+// accumulators of every pair of the chunk's tiles; this kernel bounds (E1) and
+// evaluates (E2: per-phase distance marginalisation, eq. lnl_dist_marginalized,
+// and the phase average) every pair and writes each tile's partial.  Apart from
+// the accumulators it holds a handful of doubles per lane, so several waves share
+// every SIMD and hide the latency of the distance rule's table reads, which the
+// fused kernel, one wave per SIMD, cannot.  The (i, e) matrix of ln L is written
+// by the same kernel without the cut and the sums.
 #pragma once
 
 #include "fused.h"

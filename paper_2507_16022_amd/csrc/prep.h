@@ -923,7 +923,7 @@ __global__ void k_hh_precompute(int64_t n_sub, const int64_t* __restrict__ sub_i
       }
       acc.x += acc2.x;
       acc.y += acc2.y;
-    } else {
+    } else if constexpr (PREC == kFP64) {     // (split rows that long: k_hh_rows)
       for (int b = b_lo; b < b_hi; ++b) {
         double2 a = bank_value<PREC>(A0, A1, i, K2, c, b, n_bp);
         double2 a2 = bank_value<PREC>(A0, A1, i, K2, c2, b, n_bp);
