@@ -1223,7 +1223,9 @@ __global__ __launch_bounds__(1024) void k_topk_few(const double* __restrict__ c,
     if (tid < m) {
       const double* x = rec + 4 * tid;
       int rank = 0;
-      for (int j = 0; j < m; ++j) rank += cand_before_lds(rec + 4 * j, x) ? 1 : 0;
+      // (equal records, of a row that the subset names twice, in slot order)
+      for (int j = 0; j < m; ++j)
+        rank += cand_before_lds(rec + 4 * j, x) || (j < tid && !cand_before_lds(x, rec + 4 * j)) ? 1 : 0;
       if (rank < take)
         for (int q = 0; q < 4; ++q) out[4 * (int64_t)rank + q] = x[q];
     }
