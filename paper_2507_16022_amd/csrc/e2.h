@@ -135,28 +135,30 @@ struct PairSlot {
 };
 
 // Kept phases per wave and turn of the distance rule: as LDS allows three
-// workgroups per CU.  FP64 slots are larger; with the phase table of 64 phases
-// and more only two fit, which then take more per turn (64 x 20000 pairs, 32
-// phases, all kept: this kernel 0.98 ms with 256 per turn and two workgroups,
-// 0.76 with 192 and three; 3000 x 3000, 128 phases a call of 21.3 ms with 256
-// per turn, 23.3 with 192).
-template <int PREC>
-__host__ __device__ constexpr int e2_turn(int n_phi) {
-  return PREC != kFP64 ? 512 : n_phi < 64 ? 192 : 256;
+// workgroups per CU.  FP64 slots of four m groups are larger: 192 leave room for
+// three (64 x 20000 pairs, 32 phases, all kept: this kernel 0.98 ms with 256 and
+// two workgroups, 0.76 with 192), but not beside the phase table of 64 phases and
+// more (3000 x 3000, 128 phases a call of 21.3 ms with 256, 23.3 with 192), nor is
+// a third used by an event of two tiles per CU (64 x 64 pairs 0.56 against 0.61
+// ms a call).
+template <int PREC, int G>
+__host__ __device__ constexpr int e2_turn(int n_phi, bool few_tiles) {
+  return PREC != kFP64 ? 512 : G == kMaxG && n_phi < 64 && !few_tiles ? 192 : 256;
 }
+__host__ __device__ constexpr bool e2_few(int64_t n_tiles) { return n_tiles <= 512; }
 constexpr int kE2Waves = 4;
 // bytes of its dynamic LDS: the phase table, then per wave a turn's ln Lbar and
 // places
-template <int PREC>
-constexpr size_t e2_lds(int n_phi) {
+template <int PREC, int G>
+constexpr size_t e2_lds(int n_phi, bool few_tiles) {
   return sizeof(double) * kMaxM * (size_t)n_phi * 2 +
-         kE2Waves * (size_t)e2_turn<PREC>(n_phi) * (sizeof(double) + sizeof(uint16_t));
+         kE2Waves * (size_t)e2_turn<PREC, G>(n_phi, few_tiles) * (sizeof(double) + sizeof(uint16_t));
 }
 
 // MODE kEvidence: the second half of an evidence pass; kEval: every pair's
 // ln L (and largest lnL^ML, and triples) of the tiles from work0 on.
 template <int PREC, int G, int MODE>
-__device__ __forceinline__ void e2_pass(const FusedArgs& a, int64_t wg_id, int64_t wg_count) {
+__device__ __forceinline__ void e2_pass(const FusedArgs& a, bool few_tiles, int64_t wg_id, int64_t wg_count) {
   typedef Tile<PREC> TL;
   typedef typename std::conditional<PREC == kFP64, double, float>::type AT;
   constexpr bool EVAL = MODE == kEval;
@@ -193,7 +195,7 @@ __device__ __forceinline__ void e2_pass(const FusedArgs& a, int64_t wg_id, int64
   const float thr_f = (float)thr_ml;
   const int64_t end = min(a.work0 + a.coef_tiles, coef_work_count(a));
   AT* const my_slots = slots[wave];
-  const int CH = e2_turn<PREC>(n_phi);
+  const int CH = e2_turn<PREC, G>(n_phi, few_tiles);
   double* const val = lds_cs + kMaxM * n_phi * 2;
   double* const my_val = val + wave * CH;                            // ln Lbar of the turn's kept phases
   uint16_t* const my_ent = (uint16_t*)(val + NW * CH) + wave * CH;   // slot << 8 | phase
@@ -519,7 +521,7 @@ __device__ __forceinline__ void e2_pass(const FusedArgs& a, int64_t wg_id, int64
 
 template <int PREC, int G, int MODE>
 __global__ __launch_bounds__(256, 3) void k_e2_tiles(FusedArgs a) {
-  e2_pass<PREC, G, MODE>(a, blockIdx.x, gridDim.x);
+  e2_pass<PREC, G, MODE>(a, e2_few(a.n_tiles), blockIdx.x, gridDim.x);
 }
 
 // one chunk's second half of several events
@@ -530,7 +532,7 @@ __global__ __launch_bounds__(256, 3) void k_e2_tiles_packed(PackLaunch p) {
   const int e = pack_locate(p, blockIdx.x, &blk, &nblk, &q);
   FusedArgs a = pack_args(p, e, q);
   a.work0 = p.chunk * a.coef_tiles;
-  e2_pass<PREC, G, kEvidence>(a, blk, nblk);
+  e2_pass<PREC, G, kEvidence>(a, false, blk, nblk);
 }
 
 // ---------------------------------------------------------------------------

@@ -32,11 +32,11 @@ hipError_t launch_marg(int mode, const FusedArgs& a, int64_t grid, hipStream_t s
       }
     case kE2:
       hipLaunchKernelGGL((k_e2_tiles<PREC, G, kEvidence>), dim3((unsigned)grid), dim3(256),
-                         e2_lds<PREC>(a.n_phi), s, a);
+                         (e2_lds<PREC, G>(a.n_phi, e2_few(a.n_tiles))), s, a);
       return hipGetLastError();
     case kEval:
       hipLaunchKernelGGL((k_e2_tiles<PREC, G, kEval>), dim3((unsigned)grid), dim3(256),
-                         e2_lds<PREC>(a.n_phi), s, a);
+                         (e2_lds<PREC, G>(a.n_phi, e2_few(a.n_tiles))), s, a);
       return hipGetLastError();
     case kSample:
       {
@@ -64,7 +64,7 @@ hipError_t launch_marg_packed(int mode, const PackLaunch& p, int n_phi, hipStrea
         return hipGetLastError();
       }
     case kE2:
-      hipLaunchKernelGGL((k_e2_tiles_packed<PREC, G>), grid, dim3(256), e2_lds<PREC>(n_phi), s, p);
+      hipLaunchKernelGGL((k_e2_tiles_packed<PREC, G>), grid, dim3(256), (e2_lds<PREC, G>(n_phi, false)), s, p);
       return hipGetLastError();
   }
   return hipErrorInvalidValue;
