@@ -254,6 +254,10 @@ __device__ __forceinline__ void e2_pass(const FusedArgs& a, bool few_tiles, int6
     const double thr_topk_glob = EVAL ? 0.0 : order_value(a.state[1]) - a.topk_window;
     const int rows_in = (int)min((int64_t)TM, a.n_sub - row0);
     const int cols_in = (int)min((int64_t)TN, a.n_ext - col0);
+    // a tile of few pairs written out (fewer than half a pair per thread): the
+    // exponentials of their phases' sums in FP64 (in FP32 ln L is off by up to
+    // 3e-8, which counts where it is near zero)
+    const bool few = rows_in * cols_in < 128;
     const AT* cf = (const AT*)a.coef + (q - a.work0) * (int64_t)(NCO * NPT);
     EvAcc ev;
     ev.init();
@@ -313,17 +317,6 @@ __device__ __forceinline__ void e2_pass(const FusedArgs& a, bool few_tiles, int6
         tr = place / TN;
         tc = place % TN;
         lnw = rowd[tr * 4] + cold[tc * 3];
-      }
-      // Written out, the pairs of a part of the tile (16 rows of every 32, 8 with
-      // FP64 accumulators) that has fewer than 128 of them sum their phases with
-      // FP64 exponentials: in FP32 ln L is off by up to 5e-8, which counts where
-      // it is near zero, and in a few pairs' places they cost nothing.
-      bool few = false;
-      if (EVAL) {
-        constexpr int H = PREC == kFP64 ? 8 : 16;
-        const int r0 = tr % 32 / H * H;
-        const int rows = min(max(rows_in - r0, 0), H) + min(max(rows_in - 32 - r0, 0), H);
-        few = rows * cols_in < 128;
       }
       // phases in blocks of 32, or of 16 where all are kept: 64 pairs then fill
       // two turns, and half of the lanes have a pair in each turn's sums
@@ -419,11 +412,13 @@ __device__ __forceinline__ void e2_pass(const FusedArgs& a, bool few_tiles, int6
           }
           wave_sync();
           // a pair per lane: its phases of this turn, in order
-          int jb = -1;
-          for (int j = lo; j < at; ++j) {
-            if (EVAL && few) lse.add_f64(my_val[j - c0]);
-            else jb = lse.add(my_val[j - c0]) ? j : jb;
+          if (EVAL && few) {
+            for (int j = lo; j < at; ++j) lse.add_f64(my_val[j - c0]);
+            wave_sync();
+            continue;
           }
+          int jb = -1;
+          for (int j = lo; j < at; ++j) jb = lse.add(my_val[j - c0]) ? j : jb;
           if (jb >= 0) ob = on ? my_ent[jb - c0] & 255 : o0 + jb - off;
           wave_sync();
         }
