@@ -167,10 +167,6 @@ struct LsePh {
     m = up ? x : m;
     return up;
   }
-  // the same with the exponential in FP64
-  __device__ void add_f64(double x) {
-    if (x > -INFINITY) merge(x, 1.0, 1.0);
-  }
   __device__ void merge(double mb, double sb, double s2b) {
     if (mb == -INFINITY) return;
     if (m == -INFINITY) { m = mb; s = sb; s2 = s2b; return; }

@@ -254,10 +254,6 @@ __device__ __forceinline__ void e2_pass(const FusedArgs& a, bool few_tiles, int6
     const double thr_topk_glob = EVAL ? 0.0 : order_value(a.state[1]) - a.topk_window;
     const int rows_in = (int)min((int64_t)TM, a.n_sub - row0);
     const int cols_in = (int)min((int64_t)TN, a.n_ext - col0);
-    // a tile of few pairs written out (fewer than half a pair per thread): the
-    // exponentials of their phases' sums in FP64 (in FP32 ln L is off by up to
-    // 3e-8, which counts where it is near zero)
-    const bool few = rows_in * cols_in < 128;
     const AT* cf = (const AT*)a.coef + (q - a.work0) * (int64_t)(NCO * NPT);
     EvAcc ev;
     ev.init();
@@ -412,11 +408,6 @@ __device__ __forceinline__ void e2_pass(const FusedArgs& a, bool few_tiles, int6
           }
           wave_sync();
           // a pair per lane: its phases of this turn, in order
-          if (EVAL && few) {
-            for (int j = lo; j < at; ++j) lse.add_f64(my_val[j - c0]);
-            wave_sync();
-            continue;
-          }
           int jb = -1;
           for (int j = lo; j < at; ++j) jb = lse.add(my_val[j - c0]) ? j : jb;
           if (jb >= 0) ob = on ? my_ent[jb - c0] & 255 : o0 + jb - off;
