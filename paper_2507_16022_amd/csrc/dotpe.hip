@@ -1107,12 +1107,15 @@ uint64_t block_bytes(const std::vector<EvBuf>& v) {
 }
 
 // The device buffers of one call in one allocation, released on every return:
-// host inputs first (small ones copied to the device as one piece, long ones
-// from where they are), then work buffers.
+// small host inputs in front, copied to the device as one piece (whatever order
+// they are named in: with long ones between them the gaps were copied too, a call
+// of 20 rows of 900 bins 0.26 ms against 0.22), then long ones, copied from where
+// they are, and work buffers.
 struct Carve {
   struct Piece {
     void** p;
-    uint64_t off;
+    uint64_t off;        // within the small inputs, or behind them
+    bool small;
     const void* src;     // a long input
     size_t n;
   };
@@ -1124,18 +1127,19 @@ struct Carve {
   void* base = nullptr;
   uint64_t held = 0;
 
-  // (the small inputs before the long ones and the work buffers)
   template <class T>
   void in(const T** p, const T* src, size_t n) {
     const size_t bytes = n * sizeof(T);
-    add((void**)p, bytes);
     if (bytes > 65536) {
+      add((void**)p, bytes);
       pieces.back().src = src;
       pieces.back().n = bytes;
       return;
     }
-    host.resize(off);
-    std::memcpy(host.data() + pieces.back().off, src, bytes);
+    const size_t at = round_up(host.size(), kBlockAlign);
+    host.resize(at + bytes);
+    std::memcpy(host.data() + at, src, bytes);
+    pieces.push_back({(void**)p, at, true, nullptr, 0});
   }
   void reset() {
     pieces.clear();
@@ -1144,18 +1148,19 @@ struct Carve {
   }
   void add(void** p, size_t n) {
     off = round_up(off, kBlockAlign);
-    pieces.push_back({p, off, nullptr, 0});
+    pieces.push_back({p, off, false, nullptr, 0});
     off += n;
   }
   int alloc(dotpe_ctx* c, hipStream_t st) {
-    int rc = dev_alloc(c, &base, off, nullptr, &held);
+    const uint64_t head = round_up(host.size(), kBlockAlign);
+    int rc = dev_alloc(c, &base, head + off, nullptr, &held);
     if (rc) return rc;
     ctx = c;
     s = st;
-    for (Piece& x : pieces) *x.p = (char*)base + x.off;
+    for (Piece& x : pieces) *x.p = (char*)base + (x.small ? x.off : head + x.off);
     if (!host.empty()) HIP_OK(hipMemcpyAsync(base, host.data(), host.size(), hipMemcpyHostToDevice, s));
     for (Piece& x : pieces)
-      if (x.src) HIP_OK(hipMemcpyAsync((char*)base + x.off, x.src, x.n, hipMemcpyHostToDevice, s));
+      if (x.src) HIP_OK(hipMemcpyAsync(*x.p, x.src, x.n, hipMemcpyHostToDevice, s));
     return DOTPE_OK;
   }
   ~Carve() {
