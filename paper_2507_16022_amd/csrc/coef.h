@@ -14,6 +14,17 @@
 // to leave half of the workgroups idle is taken in halves of 32 rows instead,
 // which halves the time of its one round.
 //
+// Launches that the host knows to be of few tiles leave each workgroup most of a CU,
+// and then two stages wait for loads at every step, and the loads issued in front
+// of the products keep the matrix cores waiting.  So more stages and the loads
+// between the products: up to 128 tiles in halves (every half its own CU), up to
+// 512 by four waves of 32 x 32 pairs each (two halves on a CU would load 24 KB per
+// chunk, as fast as a CU's share of L2 gives it; a tile 16).  ln L matrices of one
+// phase, five modes, before and now: 512 bins, 200 tiles 0.139 -> 0.114 ms, 500
+// tiles 0.227 -> 0.191; 1700 bins, one tile 0.242 -> 0.187, 200 tiles 0.324 ->
+// 0.238; 256 bins, 256 tiles 0.109 -> 0.093.  (The fused kernel, four waves and
+// eight stages, one workgroup per CU: 0.117, 0.227, 0.201, 0.227, 0.097.)
+//
 // 2048 tiles of 5-mode, 256-bin operands take 0.30 ms (0.36 to 0.38 in the
 // fused kernel), if neighbouring tiles run together: with the list in the
 // order in which it was written half of the reads missed L2 and it took as
@@ -24,17 +35,26 @@
 
 namespace dotpe {
 
+// bytes of a chunk of 32 bm rows: A hi, A lo (2 KB per 32 rows each), B hi, B lo
+// (4 KB each)
+constexpr int coef_stage(int bm) { return bm * 4096 + 8192; }
 struct CoefTile {
   static constexpr int NT = 128;
-  static constexpr int STAGE = 16384;      // a chunk of A hi, A lo, B hi, B lo: 4 KB each
-  static constexpr int LDS_BYTES = 2 * STAGE;
+  static constexpr int HALF_NS = 3, FEW_NS = 6;      // stages of half a tile
+  static constexpr int MID_NS = 4;                   // of a tile by four waves
+  static constexpr int LDS_BYTES = HALF_NS * coef_stage(1);
+  static constexpr int FEW_BYTES = FEW_NS * coef_stage(1);
+  static constexpr int MID_BYTES = MID_NS * coef_stage(2);
+  static_assert(2 * coef_stage(2) <= LDS_BYTES && 4 * LDS_BYTES <= 160 * 1024, "four workgroups per CU");
+  static_assert(2 * MID_BYTES <= 160 * 1024, "two workgroups per CU");
 };
 
-// One tile (BM = 2) or the 32 rows `half` of one (BM = 1) of work item q, by
-// a workgroup of two waves, 32 BM x 32 pairs each.
-template <int PREC, int G, int BM>
+// Work item q, by a workgroup of NW waves, 32 BM x 32 pairs each, with NS stages:
+// the tile (NW BM = 4) or the 32 rows `half` of it (NW BM = 2).
+template <int PREC, int G, int NW, int BM, int NS>
 __device__ __forceinline__ void coef_item(const FusedArgs& a, unsigned char* smem, int64_t q, int half) {
   static_assert(PREC != kFP64, "split precisions only");
+  static_assert((NW == 2 && (BM == 1 || BM == 2)) || (NW == 4 && BM == 1), "a tile or half of one");
   typedef typename Pol<PREC>::Acc Acc;
   typedef __attribute__((address_space(1))) const unsigned char gbyte;
   typedef __attribute__((address_space(3))) void lvoid;
@@ -44,8 +64,9 @@ __device__ __forceinline__ void coef_item(const FusedArgs& a, unsigned char* sme
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ndh = a.n_chunks;                // (d|h) chunks (groups of a multiple of 4), then NRT (h|h) blocks
   const int nk = ndh + NRT;
-  const unsigned lds_wave =
-      __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lvoid*)smem) + wave * 8192;
+  constexpr int RB = NW * BM / 2;            // 32-row blocks
+  constexpr int STAGE = coef_stage(RB), ALO = 2048 * RB, BHI = 2 * ALO, BLO = BHI + 4096;
+  const int wm = NW == 4 ? wave >> 1 : 0, wn = wave & 1;      // the wave's rows and columns
 
   // fragments of one chunk: A blocks [bm][slice] and this wave's B block
   struct Frag {
@@ -57,123 +78,161 @@ __device__ __forceinline__ void coef_item(const FusedArgs& a, unsigned char* sme
     if constexpr (decltype(pi)::value % 2 == 0) return fr0;
     else return fr1;
   };
-  // read k (0 .. NF - 1) of a chunk's fragments from stage P
-  auto read_k = [&](Frag& f, auto pi, int k) {
-    const unsigned char* st = smem + (decltype(pi)::value % 2) * CoefTile::STAGE + lane * 16;
+  // byte offset of the stage after one at `at`
+  auto after = [](unsigned at) { return at == (NS - 1) * STAGE ? 0u : at + STAGE; };
+  // read k (0 .. NF - 1) of a chunk's fragments from the stage at `at`
+  auto read_k = [&](Frag& f, unsigned at, int k) {
+    const unsigned char* st = smem + at + lane * 16;
     const int x = k % (2 * BM);
-    if (k < 2 * BM) f.al[x >> 1][x & 1] = *(const uint4*)(st + 4096 + x * 1024);
-    else if (k < 4 * BM) f.ah[x >> 1][x & 1] = *(const uint4*)(st + x * 1024);
-    else if (k < 4 * BM + 2) f.bh[k & 1] = *(const uint4*)(st + 8192 + (2 * wave + (k & 1)) * 1024);
-    else f.bl[k & 1] = *(const uint4*)(st + 12288 + (2 * wave + (k & 1)) * 1024);
+    if (k < 2 * BM) f.al[x >> 1][x & 1] = *(const uint4*)(st + ALO + (2 * wm + x) * 1024);
+    else if (k < 4 * BM) f.ah[x >> 1][x & 1] = *(const uint4*)(st + (2 * wm + x) * 1024);
+    else if (k < 4 * BM + 2) f.bh[k & 1] = *(const uint4*)(st + BHI + (2 * wn + (k & 1)) * 1024);
+    else f.bl[k & 1] = *(const uint4*)(st + BLO + (2 * wn + (k & 1)) * 1024);
   };
   auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
 
   const int64_t t = coef_tile(a, q);
   const int64_t row0 = t / a.n_tiles_n * 64 + 32 * half, col0 = t % a.n_tiles_n * 64;
-  float* cf = (float*)a.coef + (q - a.work0) * (int64_t)(NCO * NPT) + half * 32 * 64 + 32 * wave +
+  float* cf = (float*)a.coef + (q - a.work0) * (int64_t)(NCO * NPT) + (half + wm) * 32 * 64 + 32 * wn +
               (lane & 31);
 
-  // ---- operand streams: wave 0 loads A, wave 1 B; of every chunk slices 0
-  // and 1 of its 32-row blocks (A: BM, B: two), hi and lo, 1 KB each as it
-  // sits in HBM (fragment order).  Rows past the subset re-read the last row
-  // (their pairs are never used); columns run to the padded sample count. ----
-  gbyte *p_hi[2] = {}, *p_lo[2] = {}, *h_hi[2] = {}, *h_lo[2] = {};
+  // ---- operand streams, 1 KB pieces as they sit in HBM (fragment order): of
+  // every chunk slices 0 and 1 of its 32-row blocks, hi and lo.  Rows past the
+  // subset re-read the last row (their pairs are never used); columns run to the
+  // padded sample count.  A stream is one (A hi, B lo, ..) of a 32-row block: its
+  // source steps by one chunk (2 KB), and to the (h|h) operand after the last
+  // (d|h) chunk; the immediate offset of the second load applies to the global and
+  // the LDS address alike.  The asm saves and restores M0 and waits the state an
+  // M0 write needs. ----
   auto blk = [](int64_t i, int64_t K) { return (i >> 5) * (K >> 5) * 1024 + (i & 31) * 8; };
-#pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    const int r = 32 * b + (lane & 31);
+  struct Stream {
+    gbyte *p, *hh;         // next chunk, first (h|h) block
+  };
+  auto stream = [&](bool is_a, int block, bool is_lo) {
+    const int r = 32 * block + (lane & 31);
     const int64_t in_chunk = (lane >> 5) * 256;
-    if (wave == 0) {
-      if (b >= BM) continue;
+    Stream t;
+    if (is_a) {
       const int64_t ie = min(row0 + r, a.n_sub - 1);
       const int64_t i = a.sub_idx ? a.sub_idx[ie] : a.sub0 + ie;
-      const int64_t od = (blk(i, a.K2) + in_chunk) * ES, oh = (blk(ie, a.KH) + in_chunk) * ES;
-      p_hi[b] = (gbyte*)a.A0 + od;
-      p_lo[b] = (gbyte*)a.A1 + od;
-      h_hi[b] = (gbyte*)a.Ah0 + oh;
-      h_lo[b] = (gbyte*)a.Ah1 + oh;
+      t.p = (gbyte*)(is_lo ? a.A1 : a.A0) + (blk(i, a.K2) + in_chunk) * ES;
+      t.hh = (gbyte*)(is_lo ? a.Ah1 : a.Ah0) + (blk(ie, a.KH) + in_chunk) * ES;
     } else {
       const int64_t e = col0 + r;
-      const int64_t od = (blk(e, a.K2) + in_chunk) * ES, oh = (blk(e, a.KH) + in_chunk) * ES;
-      p_hi[b] = (gbyte*)a.B0 + od;
-      p_lo[b] = (gbyte*)a.B1 + od;
-      h_hi[b] = (gbyte*)a.Bh0 + oh;
-      h_lo[b] = (gbyte*)a.Bh1 + oh;
+      t.p = (gbyte*)(is_lo ? a.B1 : a.B0) + (blk(e, a.K2) + in_chunk) * ES;
+      t.hh = (gbyte*)(is_lo ? a.Bh1 : a.Bh0) + (blk(e, a.KH) + in_chunk) * ES;
     }
-  }
-  // the loads of the next chunk (c), into stage c mod 2: the immediate offset
-  // applies to the global and the LDS address alike, so those of one array
-  // share an M0 value.  The asm saves and restores M0 and waits the state an M0
-  // write needs.
-  auto issue = [&](int c) {
-    const unsigned st = lds_wave + (unsigned)((c & 1) * CoefTile::STAGE);
-    unsigned m0_saved;
-    if (BM == 2 || wave == 1) {
-      __asm__ __volatile__(
-          "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-          "global_load_lds_dwordx4 %3, off\n\t"
-          "global_load_lds_dwordx4 %3, off offset:1024\n\t"
-          "global_load_lds_dwordx4 %4, off offset:2048\n\t"
-          "global_load_lds_dwordx4 %4, off offset:3072\n\t"
-          "s_mov_b32 m0, %2\n\ts_nop 0\n\t"
-          "global_load_lds_dwordx4 %5, off\n\t"
-          "global_load_lds_dwordx4 %5, off offset:1024\n\t"
-          "global_load_lds_dwordx4 %6, off offset:2048\n\t"
-          "global_load_lds_dwordx4 %6, off offset:3072\n\ts_mov_b32 m0, %0"
-          : "=&s"(m0_saved)
-          : "s"(__builtin_amdgcn_readfirstlane(st)), "s"(__builtin_amdgcn_readfirstlane(st + 4096)),
-            "v"(p_hi[0]), "v"(p_hi[1] - 2048), "v"(p_lo[0]), "v"(p_lo[1] - 2048)
-          : "memory");
-    } else {
-      __asm__ __volatile__(
-          "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-          "global_load_lds_dwordx4 %3, off\n\t"
-          "global_load_lds_dwordx4 %3, off offset:1024\n\t"
-          "s_mov_b32 m0, %2\n\ts_nop 0\n\t"
-          "global_load_lds_dwordx4 %4, off\n\t"
-          "global_load_lds_dwordx4 %4, off offset:1024\n\ts_mov_b32 m0, %0"
-          : "=&s"(m0_saved)
-          : "s"(__builtin_amdgcn_readfirstlane(st)), "s"(__builtin_amdgcn_readfirstlane(st + 4096)),
-            "v"(p_hi[0]), "v"(p_lo[0])
-          : "memory");
-    }
-    // the sources step by one chunk (2 KB), and to the (h|h) operands after
-    // the last (d|h) chunk
-    const bool to_hh = c + 1 == ndh;
+    return t;
+  };
+  auto next = [&](Stream& t, int c) {
+    t.p += 1024 * ES;
+    if (__builtin_expect(c + 1 == ndh, 0)) t.p = t.hh;
+  };
+  // Parts of a wave's loads, an M0 value each.  BM = 2: wave 0 loads A, wave 1 B,
+  // hi of both blocks, then lo.  Half a tile: each wave one part of A, then its
+  // block of B, hi and lo.  Four waves: a stream of A and one of B each.
+  constexpr int PARTS = NW == 2 && BM == 1 ? 3 : 2, PER = BM, LPW = 2 * PARTS * PER;
+  Stream str[PARTS * PER];
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lvoid*)smem);
+  unsigned place[PARTS];
+  if constexpr (BM == 2) {
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      p_hi[b] = to_hh ? h_hi[b] : p_hi[b] + 1024 * ES;
-      p_lo[b] = to_hh ? h_lo[b] : p_lo[b] + 1024 * ES;
-    }
+    for (int t = 0; t < 4; ++t) str[t] = stream(wave == 0, t & 1, t >= 2);
+    place[0] = lds0 + wave * BHI;
+    place[1] = place[0] + ALO;
+  } else if constexpr (NW == 2) {
+    str[0] = stream(true, 0, wave == 1);
+    str[1] = stream(false, wave, false);
+    str[2] = stream(false, wave, true);
+    place[0] = lds0 + wave * ALO;
+    place[1] = lds0 + BHI + wave * 2048;
+    place[2] = lds0 + BLO + wave * 2048;
+  } else {
+    str[0] = stream(true, wn, wm);
+    str[1] = stream(false, wn, wm);
+    place[0] = lds0 + wm * ALO + wn * 2048;
+    place[1] = lds0 + BHI + wm * (BLO - BHI) + wn * 2048;
+  }
+  // part t of the loads of the next chunk (c), into the stage at st
+  auto issue_part = [&](int c, unsigned st, auto ti) {
+    constexpr int t = decltype(ti)::value;
+    unsigned m0_saved;
+    if constexpr (PER == 2)
+      __asm__ __volatile__(
+          "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+          "global_load_lds_dwordx4 %2, off\n\t"
+          "global_load_lds_dwordx4 %2, off offset:1024\n\t"
+          "global_load_lds_dwordx4 %3, off offset:2048\n\t"
+          "global_load_lds_dwordx4 %3, off offset:3072\n\ts_mov_b32 m0, %0"
+          : "=&s"(m0_saved)
+          : "s"(__builtin_amdgcn_readfirstlane(place[t] + st)), "v"(str[2 * t].p), "v"(str[2 * t + 1].p - 2048)
+          : "memory");
+    else
+      __asm__ __volatile__(
+          "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+          "global_load_lds_dwordx4 %2, off\n\t"
+          "global_load_lds_dwordx4 %2, off offset:1024\n\ts_mov_b32 m0, %0"
+          : "=&s"(m0_saved)
+          : "s"(__builtin_amdgcn_readfirstlane(place[t] + st)), "v"(str[t].p)
+          : "memory");
+#pragma unroll
+    for (int q = 0; q < PER; ++q) next(str[PER * t + q], c);
+  };
+  auto issue = [&](int c, unsigned st) {
+    static_for<PARTS>([&](auto ti) { issue_part(c, st, ti); });
   };
 
-  // Step j (stage and fragment parity P = j mod 2): once every wave's loads
-  // of chunk j + 1 have landed and every wave has read chunk j's fragments,
-  // chunk j + 2 goes into that stage; then the products of chunk j (mf(f, k)
-  // issues product k of NMF) with the reads of chunk j + 1 between them.
+  // workgroup barrier with at most n (0 .. NS - 1) of the wave's chunks in flight:
+  // the loads complete in order, and a store among them only makes it wait longer
+  auto barrier = [&](int n) {
+    static_for<NS>([&](auto qi) {
+      constexpr int q = decltype(qi)::value;
+      if (n == q) pipeline_barrier<q * LPW>();
+    });
+  };
+  unsigned cur_st = 0;         // the stage of chunk j
+
+  // Step j (fragment parity P = j mod 2): once every wave's loads of chunk j + 1
+  // have landed (up to j + NS - 1 may stay in flight) and every wave has read
+  // chunk j's fragments, chunk j + NS goes into that stage; the products of chunk j
+  // (mf(f, k) issues product k of NMF) have the reads of chunk j + 1 between them,
+  // and with more than two stages the loads as well (in front of the products they
+  // keep the matrix cores waiting where no other wave shares the SIMD).
   auto step = [&](int j, auto pi, auto nmf, auto ahead, auto&& mf) {
     constexpr int P = decltype(pi)::value % 2, NMF = decltype(nmf)::value;
     constexpr int NR = decltype(ahead)::value ? NF : 0;
     Frag& cur = frag(std::integral_constant<int, P>{});
     Frag& nxt = frag(std::integral_constant<int, P + 1>{});
     if constexpr (NR > 0) {
-      pipeline_barrier<0>();
+      if constexpr (NS == 2) pipeline_barrier<0>();
+      else if (j + NS <= nk) pipeline_barrier<(NS - 2) * LPW>();
+      else barrier(nk - 2 - j);
       fence();
-      if (j + 2 < nk) issue(j + 2);
-      fence();
+      if constexpr (NS == 2) {
+        if (j + NS < nk) issue(j + NS, cur_st);
+        fence();
+      }
     }
+    const unsigned nxt_st = after(cur_st);
     static_for<(NMF > NR ? NMF : NR)>([&](auto ti) {
       constexpr int x = decltype(ti)::value;
       if constexpr (x < NMF) mf(cur, x);
-      if constexpr (x < NR) read_k(nxt, std::integral_constant<int, P + 1>{}, x);
+      if constexpr (x < NR) read_k(nxt, nxt_st, x);
+      if constexpr (NS > 2 && NR > 0 && x >= NMF - 4 && x < NMF - 4 + PARTS) {
+        fence();
+        if (j + NS < nk) issue_part(j + NS, cur_st, std::integral_constant<int, x - (NMF - 4)>{});
+        fence();
+      }
     });
+    cur_st = nxt_st;
   };
 
   __syncthreads();       // (the last tile's stages are no longer read)
-  issue(0);
-  issue(1);
-  pipeline_barrier<4 * BM>();   // chunk 0 has landed
-  static_for<NF>([&](auto ki) { read_k(fr0, std::integral_constant<int, 0>{}, decltype(ki)::value); });
+  static_for<NS>([&](auto ci) {
+    if (decltype(ci)::value < nk) issue(decltype(ci)::value, decltype(ci)::value * STAGE);
+  });
+  barrier(min(NS, nk) - 1);     // chunk 0 has landed
+  static_for<NF>([&](auto ki) { read_k(fr0, 0, decltype(ki)::value); });
 
   // component c of the wave's pairs from block bm's accumulator
   auto store = [&](int c, int bm, const Acc& v) {
@@ -253,34 +312,62 @@ __device__ __forceinline__ void coef_item(const FusedArgs& a, unsigned char* sme
   });
 }
 
+// n tiles in halves, the two of a tile on one XCD; 2 n at most the workgroups
+template <int PREC, int G, int NS>
+__device__ __forceinline__ void coef_halves(const FusedArgs& a, unsigned char* smem, int64_t n, int64_t wg_id,
+                                            int64_t wg_count) {
+  const int64_t part = (n + 7) / 8, y = wg_id / 8;
+  int64_t at = wg_id / 2, half = wg_id & 1;
+  if (16 * part <= wg_count) {
+    at = y / 2 < part ? wg_id % 8 * part + y / 2 : n;
+    half = y & 1;
+  }
+  if (at < n) coef_item<PREC, G, 2, 1, NS>(a, smem, a.work0 + at, (int)half);
+}
+
 template <int PREC, int G>
 __device__ __forceinline__ void coef_pass(const FusedArgs& a, int64_t wg_id, int64_t wg_count) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int64_t end = min(a.work0 + a.coef_tiles, coef_work_count(a));
   const int64_t n = end - a.work0;
   if (2 * n <= wg_count) {
-    // a list that leaves half of the workgroups idle: half a tile each, the
-    // halves of a tile on one XCD
-    const int64_t part = (n + 7) / 8, y = wg_id / 8;
-    int64_t at = wg_id / 2, half = wg_id & 1;
-    if (16 * part <= wg_count) {
-      at = y / 2 < part ? wg_id % 8 * part + y / 2 : n;
-      half = y & 1;
-    }
-    if (at < n) coef_item<PREC, G, 1>(a, smem, a.work0 + at, (int)half);
+    // a list that leaves half of the workgroups idle
+    coef_halves<PREC, G, CoefTile::HALF_NS>(a, smem, n, wg_id, wg_count);
     return;
   }
 #pragma unroll 1
   for (int64_t q0 = a.work0; q0 < end; q0 += wg_count) {
     const int64_t at = coef_place(wg_id, wg_count, min(wg_count, end - q0));
     if (at < 0) break;
-    coef_item<PREC, G, 2>(a, smem, q0 + at, 0);
+    coef_item<PREC, G, 2, 2, 2>(a, smem, q0 + at, 0);
   }
 }
 
 template <int PREC, int G>
 __global__ __launch_bounds__(CoefTile::NT, 2) void k_coef(FusedArgs a) {
   coef_pass<PREC, G>(a, blockIdx.x, gridDim.x);
+}
+
+// Launches that the host knows to be of few tiles: in halves where each then has
+// a CU; up to two tiles per CU by four waves each.
+constexpr int64_t kCoefFew = 128, kCoefMid = 512;
+template <int PREC, int G>
+__global__ __launch_bounds__(CoefTile::NT, 1) void k_coef_few(FusedArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int64_t n = min(a.work0 + a.coef_tiles, coef_work_count(a)) - a.work0;
+  coef_halves<PREC, G, CoefTile::FEW_NS>(a, smem, n, blockIdx.x, gridDim.x);
+}
+template <int PREC, int G>
+__global__ __launch_bounds__(2 * CoefTile::NT, 2) void k_coef_mid(FusedArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int64_t n = min(a.work0 + a.coef_tiles, coef_work_count(a)) - a.work0;
+  const int64_t at = coef_place(blockIdx.x, gridDim.x, n);
+  if (at >= 0) coef_item<PREC, G, 4, 1, CoefTile::MID_NS>(a, smem, a.work0 + at, 0);
+}
+// the most tiles that a launch may have to take
+inline int64_t coef_most(const FusedArgs& a) {
+  const int64_t left = (a.work_list ? a.n_work_list : a.n_tiles) - a.work0;
+  return left < a.coef_tiles ? left : a.coef_tiles;
 }
 
 // one chunk's first half of several events
