@@ -4,57 +4,46 @@
 //
 // An accumulator is complete when its m group's chunks (or its (h|h) block)
 // are, so it is stored there and then and a wave needs one group's at a time:
-// 64 x 32 pairs per wave in 2 x 32 accumulator registers (the fused kernel
-// holds all 240 of a tile's 32 x 32 pairs until its epilogue, one wave per
-// SIMD).  A workgroup of two waves takes a tile, with two stages of 16 KB in
-// LDS; four workgroups share a CU, so one's loads, barriers and stores run
-// beside the products of the others, and a chunk's loads have the products of
-// two waves to arrive in.  64 x 32 pairs per wave read 12 KB from LDS for 24
-// products (32 x 32: 8 KB for 12, the LDS rate's limit).  A list short enough
-// to leave half of the workgroups idle is taken in halves of 32 rows instead,
-// which halves the time of its one round.
+// 32 x 32 pairs per wave in 32 accumulator registers (the fused kernel holds all
+// 240 until its epilogue, one wave per SIMD).  A workgroup of four waves takes a
+// tile, with four stages of 16 KB in LDS, and two share a CU: a chunk's loads have
+// the products of three others to arrive in, and sit between them (in front of
+// them they kept the matrix cores waiting).  An event of at most 128 tiles is taken
+// in halves of 32 rows by two waves each, with six stages (more halves than CUs
+// would load 24 KB per chunk and CU, all that a CU's share of L2 gives it; a tile
+// 16).
 //
-// Launches that the host knows to be of few tiles leave each workgroup most of a CU,
-// and then two stages wait for loads at every step, and the loads issued in front
-// of the products keep the matrix cores waiting.  So more stages and the loads
-// between the products: up to 128 tiles in halves (every half its own CU), up to
-// 512 by four waves of 32 x 32 pairs each (two halves on a CU would load 24 KB per
-// chunk, as fast as a CU's share of L2 gives it; a tile 16).  ln L matrices of one
-// phase, five modes, before and now: 512 bins, 200 tiles 0.139 -> 0.114 ms, 500
-// tiles 0.227 -> 0.191; 1700 bins, one tile 0.242 -> 0.187, 200 tiles 0.324 ->
-// 0.238; 256 bins, 256 tiles 0.109 -> 0.093.  (The fused kernel, four waves and
-// eight stages, one workgroup per CU: 0.117, 0.227, 0.201, 0.227, 0.097.)
-//
-// 2048 tiles of 5-mode, 256-bin operands take 0.30 ms (0.36 to 0.38 in the
-// fused kernel), if neighbouring tiles run together: with the list in the
-// order in which it was written half of the reads missed L2 and it took as
-// long as before.
+// ln L matrices of one phase, five modes, in ms by tiles; in brackets the fused
+// kernel (four waves, eight stages, one workgroup per CU), then 64 x 32 pairs per
+// wave with two stages and four workgroups per CU (what this replaced), now:
+//   256 bins: 64 tiles (0.094, 0.070) 0.061, 256 (0.097, 0.109) 0.093, 600 (0.257,
+//     0.242) 0.182, 4096 (1.27, 1.24) 1.18
+//   1700 bins: 1 (0.201, 0.242) 0.187, 200 (0.227, 0.324) 0.238, 1024 (0.93, 1.01)
+//     0.88, 4096 (3.59, 4.12) 3.47
+// Neighbouring tiles have to run together: with the list in the order in which it
+// was written half of the reads missed L2.
 #pragma once
 
 #include "fused.h"
 
 namespace dotpe {
 
-// bytes of a chunk of 32 bm rows: A hi, A lo (2 KB per 32 rows each), B hi, B lo
+// bytes of a chunk of 32 rb rows: A hi, A lo (2 KB per 32 rows each), B hi, B lo
 // (4 KB each)
-constexpr int coef_stage(int bm) { return bm * 4096 + 8192; }
+constexpr int coef_stage(int rb) { return rb * 4096 + 8192; }
 struct CoefTile {
-  static constexpr int NT = 128;
-  static constexpr int HALF_NS = 3, FEW_NS = 6;      // stages of half a tile
-  static constexpr int MID_NS = 4;                   // of a tile by four waves
-  static constexpr int LDS_BYTES = HALF_NS * coef_stage(1);
-  static constexpr int FEW_BYTES = FEW_NS * coef_stage(1);
-  static constexpr int MID_BYTES = MID_NS * coef_stage(2);
-  static_assert(2 * coef_stage(2) <= LDS_BYTES && 4 * LDS_BYTES <= 160 * 1024, "four workgroups per CU");
-  static_assert(2 * MID_BYTES <= 160 * 1024, "two workgroups per CU");
+  static constexpr int NT = 256, NS = 4;             // a tile by four waves
+  static constexpr int HALF_NT = 128, HALF_NS = 6;   // half of one by two
+  static constexpr int LDS_BYTES = NS * coef_stage(2), HALF_BYTES = HALF_NS * coef_stage(1);
+  static_assert(LDS_BYTES <= 64 * 1024, "no attribute, two workgroups per CU");
 };
 
-// Work item q, by a workgroup of NW waves, 32 BM x 32 pairs each, with NS stages:
-// the tile (NW BM = 4) or the 32 rows `half` of it (NW BM = 2).
-template <int PREC, int G, int NW, int BM, int NS>
+// Work item q, by a workgroup of NW waves, 32 x 32 pairs each, with NS stages: the
+// tile (four waves) or the 32 rows `half` of it (two).
+template <int PREC, int G, int NW, int NS>
 __device__ __forceinline__ void coef_item(const FusedArgs& a, unsigned char* smem, int64_t q, int half) {
   static_assert(PREC != kFP64, "split precisions only");
-  static_assert((NW == 2 && (BM == 1 || BM == 2)) || (NW == 4 && BM == 1), "a tile or half of one");
+  static_assert(NW == 2 || NW == 4, "a tile or half of one");
   typedef typename Pol<PREC>::Acc Acc;
   typedef __attribute__((address_space(1))) const unsigned char gbyte;
   typedef __attribute__((address_space(3))) void lvoid;
@@ -64,15 +53,14 @@ __device__ __forceinline__ void coef_item(const FusedArgs& a, unsigned char* sme
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ndh = a.n_chunks;                // (d|h) chunks (groups of a multiple of 4), then NRT (h|h) blocks
   const int nk = ndh + NRT;
-  constexpr int RB = NW * BM / 2;            // 32-row blocks
-  constexpr int STAGE = coef_stage(RB), ALO = 2048 * RB, BHI = 2 * ALO, BLO = BHI + 4096;
-  const int wm = NW == 4 ? wave >> 1 : 0, wn = wave & 1;      // the wave's rows and columns
+  constexpr int STAGE = coef_stage(NW / 2), ALO = 1024 * NW, BHI = 2 * ALO, BLO = BHI + 4096;
+  const int wm = wave >> 1, wn = wave & 1;   // the wave's rows (of a tile) and columns
 
-  // fragments of one chunk: A blocks [bm][slice] and this wave's B block
+  // fragments of one chunk, [slice]
   struct Frag {
-    uint4 ah[BM][2], al[BM][2], bh[2], bl[2];
+    uint4 ah[2], al[2], bh[2], bl[2];
   };
-  constexpr int NF = 4 * BM + 4;
+  constexpr int NF = 8;
   Frag fr0, fr1;
   auto frag = [&](auto pi) -> Frag& {
     if constexpr (decltype(pi)::value % 2 == 0) return fr0;
@@ -83,11 +71,11 @@ __device__ __forceinline__ void coef_item(const FusedArgs& a, unsigned char* sme
   // read k (0 .. NF - 1) of a chunk's fragments from the stage at `at`
   auto read_k = [&](Frag& f, unsigned at, int k) {
     const unsigned char* st = smem + at + lane * 16;
-    const int x = k % (2 * BM);
-    if (k < 2 * BM) f.al[x >> 1][x & 1] = *(const uint4*)(st + ALO + (2 * wm + x) * 1024);
-    else if (k < 4 * BM) f.ah[x >> 1][x & 1] = *(const uint4*)(st + (2 * wm + x) * 1024);
-    else if (k < 4 * BM + 2) f.bh[k & 1] = *(const uint4*)(st + BHI + (2 * wn + (k & 1)) * 1024);
-    else f.bl[k & 1] = *(const uint4*)(st + BLO + (2 * wn + (k & 1)) * 1024);
+    const int sl = k & 1;
+    if (k < 2) f.al[sl] = *(const uint4*)(st + ALO + (2 * wm + sl) * 1024);
+    else if (k < 4) f.ah[sl] = *(const uint4*)(st + (2 * wm + sl) * 1024);
+    else if (k < 6) f.bh[sl] = *(const uint4*)(st + BHI + (2 * wn + sl) * 1024);
+    else f.bl[sl] = *(const uint4*)(st + BLO + (2 * wn + sl) * 1024);
   };
   auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
 
@@ -124,62 +112,38 @@ __device__ __forceinline__ void coef_item(const FusedArgs& a, unsigned char* sme
     }
     return t;
   };
-  auto next = [&](Stream& t, int c) {
-    t.p += 1024 * ES;
-    if (__builtin_expect(c + 1 == ndh, 0)) t.p = t.hh;
-  };
-  // Parts of a wave's loads, an M0 value each.  BM = 2: wave 0 loads A, wave 1 B,
-  // hi of both blocks, then lo.  Half a tile: each wave one part of A, then its
-  // block of B, hi and lo.  Four waves: a stream of A and one of B each.
-  constexpr int PARTS = NW == 2 && BM == 1 ? 3 : 2, PER = BM, LPW = 2 * PARTS * PER;
-  Stream str[PARTS * PER];
+  // A wave's loads: a tile's waves have a stream of A and one of B each; of half a
+  // tile's each has one part of A and its block of B, hi and lo.
+  constexpr int NSTR = NW == 4 ? 2 : 3, LPW = 2 * NSTR;
+  Stream str[NSTR];
+  unsigned place[NSTR];        // its LDS address in stage 0
   const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lvoid*)smem);
-  unsigned place[PARTS];
-  if constexpr (BM == 2) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t) str[t] = stream(wave == 0, t & 1, t >= 2);
-    place[0] = lds0 + wave * BHI;
-    place[1] = place[0] + ALO;
-  } else if constexpr (NW == 2) {
-    str[0] = stream(true, 0, wave == 1);
-    str[1] = stream(false, wave, false);
-    str[2] = stream(false, wave, true);
-    place[0] = lds0 + wave * ALO;
-    place[1] = lds0 + BHI + wave * 2048;
-    place[2] = lds0 + BLO + wave * 2048;
-  } else {
+  if constexpr (NW == 4) {
     str[0] = stream(true, wn, wm);
     str[1] = stream(false, wn, wm);
     place[0] = lds0 + wm * ALO + wn * 2048;
     place[1] = lds0 + BHI + wm * (BLO - BHI) + wn * 2048;
+  } else {
+    str[0] = stream(true, 0, wn);
+    str[1] = stream(false, wn, false);
+    str[2] = stream(false, wn, true);
+    place[0] = lds0 + wn * ALO;
+    place[1] = lds0 + BHI + wn * 2048;
+    place[2] = lds0 + BLO + wn * 2048;
   }
-  // part t of the loads of the next chunk (c), into the stage at st
+  // stream t of the next chunk (c), into the stage at st
   auto issue_part = [&](int c, unsigned st, auto ti) {
     constexpr int t = decltype(ti)::value;
     unsigned m0_saved;
-    if constexpr (PER == 2)
-      __asm__ __volatile__(
-          "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-          "global_load_lds_dwordx4 %2, off\n\t"
-          "global_load_lds_dwordx4 %2, off offset:1024\n\t"
-          "global_load_lds_dwordx4 %3, off offset:2048\n\t"
-          "global_load_lds_dwordx4 %3, off offset:3072\n\ts_mov_b32 m0, %0"
-          : "=&s"(m0_saved)
-          : "s"(__builtin_amdgcn_readfirstlane(place[t] + st)), "v"(str[2 * t].p), "v"(str[2 * t + 1].p - 2048)
-          : "memory");
-    else
-      __asm__ __volatile__(
-          "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-          "global_load_lds_dwordx4 %2, off\n\t"
-          "global_load_lds_dwordx4 %2, off offset:1024\n\ts_mov_b32 m0, %0"
-          : "=&s"(m0_saved)
-          : "s"(__builtin_amdgcn_readfirstlane(place[t] + st)), "v"(str[t].p)
-          : "memory");
-#pragma unroll
-    for (int q = 0; q < PER; ++q) next(str[PER * t + q], c);
-  };
-  auto issue = [&](int c, unsigned st) {
-    static_for<PARTS>([&](auto ti) { issue_part(c, st, ti); });
+    __asm__ __volatile__(
+        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+        "global_load_lds_dwordx4 %2, off\n\t"
+        "global_load_lds_dwordx4 %2, off offset:1024\n\ts_mov_b32 m0, %0"
+        : "=&s"(m0_saved)
+        : "s"(__builtin_amdgcn_readfirstlane(place[t] + st)), "v"(str[t].p)
+        : "memory");
+    str[t].p += 1024 * ES;
+    if (__builtin_expect(c + 1 == ndh, 0)) str[t].p = str[t].hh;
   };
 
   // workgroup barrier with at most n (0 .. NS - 1) of the wave's chunks in flight:
@@ -194,31 +158,25 @@ __device__ __forceinline__ void coef_item(const FusedArgs& a, unsigned char* sme
 
   // Step j (fragment parity P = j mod 2): once every wave's loads of chunk j + 1
   // have landed (up to j + NS - 1 may stay in flight) and every wave has read
-  // chunk j's fragments, chunk j + NS goes into that stage; the products of chunk j
-  // (mf(f, k) issues product k of NMF) have the reads of chunk j + 1 between them,
-  // and with more than two stages the loads as well (in front of the products they
-  // keep the matrix cores waiting where no other wave shares the SIMD).
+  // chunk j's fragments, the products of chunk j (mf(f, k) issues product k of NMF)
+  // with the reads of chunk j + 1 and then the loads of chunk j + NS, into the
+  // stage of chunk j, between them.
   auto step = [&](int j, auto pi, auto nmf, auto ahead, auto&& mf) {
     constexpr int P = decltype(pi)::value % 2, NMF = decltype(nmf)::value;
     constexpr int NR = decltype(ahead)::value ? NF : 0;
     Frag& cur = frag(std::integral_constant<int, P>{});
     Frag& nxt = frag(std::integral_constant<int, P + 1>{});
     if constexpr (NR > 0) {
-      if constexpr (NS == 2) pipeline_barrier<0>();
-      else if (j + NS <= nk) pipeline_barrier<(NS - 2) * LPW>();
+      if (j + NS <= nk) pipeline_barrier<(NS - 2) * LPW>();
       else barrier(nk - 2 - j);
       fence();
-      if constexpr (NS == 2) {
-        if (j + NS < nk) issue(j + NS, cur_st);
-        fence();
-      }
     }
     const unsigned nxt_st = after(cur_st);
     static_for<(NMF > NR ? NMF : NR)>([&](auto ti) {
       constexpr int x = decltype(ti)::value;
       if constexpr (x < NMF) mf(cur, x);
       if constexpr (x < NR) read_k(nxt, nxt_st, x);
-      if constexpr (NS > 2 && NR > 0 && x >= NMF - 4 && x < NMF - 4 + PARTS) {
+      if constexpr (NR > 0 && x >= NMF - 4 && x < NMF - 4 + NSTR) {
         fence();
         if (j + NS < nk) issue_part(j + NS, cur_st, std::integral_constant<int, x - (NMF - 4)>{});
         fence();
@@ -229,16 +187,17 @@ __device__ __forceinline__ void coef_item(const FusedArgs& a, unsigned char* sme
 
   __syncthreads();       // (the last tile's stages are no longer read)
   static_for<NS>([&](auto ci) {
-    if (decltype(ci)::value < nk) issue(decltype(ci)::value, decltype(ci)::value * STAGE);
+    constexpr int c = decltype(ci)::value;
+    if (c < nk) static_for<NSTR>([&](auto ti) { issue_part(c, c * STAGE, ti); });
   });
   barrier(min(NS, nk) - 1);     // chunk 0 has landed
   static_for<NF>([&](auto ki) { read_k(fr0, 0, decltype(ki)::value); });
 
-  // component c of the wave's pairs from block bm's accumulator
-  auto store = [&](int c, int bm, const Acc& v) {
+  // component c of the wave's pairs from its accumulator
+  auto store = [&](int c, const Acc& v) {
 #pragma unroll
     for (int e = 0; e < 16; ++e)
-      cf[c * NPT + (32 * bm + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)) * 64] = v[e];
+      cf[c * NPT + (8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)) * 64] = v[e];
   };
 
   // ---- (d|h), a group at a time.  With A = [hr | hi] and B_re = [Br | -Bi]
@@ -249,7 +208,7 @@ __device__ __forceinline__ void coef_item(const FusedArgs& a, unsigned char* sme
   int ch = 0;
   static_for<G>([&](auto gi) {
     constexpr int g = decltype(gi)::value;
-    Acc re[BM], im[BM];
+    Acc re, im;
     const int gend = a.mt.gk0[g + 1];
     auto dh = [&](auto pi, auto first) {
       const Frag& f = frag(pi);
@@ -257,25 +216,24 @@ __device__ __forceinline__ void coef_item(const FusedArgs& a, unsigned char* sme
         return make_uint4(x.x ^ 0x80008000u, x.y ^ 0x80008000u, x.z ^ 0x80008000u, x.w ^ 0x80008000u);
       };
       const uint4 nbh = neg(f.bh[1]), nbl = neg(f.bl[1]);
-      step(ch, pi, std::integral_constant<int, 12 * BM>{}, std::true_type{}, [&](const Frag& f, int x) {
-        const int bm = x % BM, k = x / BM;
+      step(ch, pi, std::integral_constant<int, 12>{}, std::true_type{}, [&](const Frag& f, int k) {
         if constexpr (decltype(first)::value) {
-          if (k == 0) re[bm] = Acc{};
-          if (k == 1) im[bm] = Acc{};
+          if (k == 0) re = Acc{};
+          if (k == 1) im = Acc{};
         }
         switch (k) {
-          case 0: mma<PREC>(re[bm], f.al[bm][0], f.bh[0]); break;
-          case 1: mma<PREC>(im[bm], f.al[bm][0], nbh); break;
-          case 2: mma<PREC>(re[bm], f.ah[bm][0], f.bl[0]); break;
-          case 3: mma<PREC>(im[bm], f.ah[bm][0], nbl); break;
-          case 4: mma<PREC>(re[bm], f.ah[bm][0], f.bh[0]); break;
-          case 5: mma<PREC>(im[bm], f.ah[bm][0], nbh); break;
-          case 6: mma<PREC>(re[bm], f.al[bm][1], f.bh[1]); break;
-          case 7: mma<PREC>(im[bm], f.al[bm][1], f.bh[0]); break;
-          case 8: mma<PREC>(re[bm], f.ah[bm][1], f.bl[1]); break;
-          case 9: mma<PREC>(im[bm], f.ah[bm][1], f.bl[0]); break;
-          case 10: mma<PREC>(re[bm], f.ah[bm][1], f.bh[1]); break;
-          default: mma<PREC>(im[bm], f.ah[bm][1], f.bh[0]); break;
+          case 0: mma<PREC>(re, f.al[0], f.bh[0]); break;
+          case 1: mma<PREC>(im, f.al[0], nbh); break;
+          case 2: mma<PREC>(re, f.ah[0], f.bl[0]); break;
+          case 3: mma<PREC>(im, f.ah[0], nbl); break;
+          case 4: mma<PREC>(re, f.ah[0], f.bh[0]); break;
+          case 5: mma<PREC>(im, f.ah[0], nbh); break;
+          case 6: mma<PREC>(re, f.al[1], f.bh[1]); break;
+          case 7: mma<PREC>(im, f.al[1], f.bh[0]); break;
+          case 8: mma<PREC>(re, f.ah[1], f.bl[1]); break;
+          case 9: mma<PREC>(im, f.ah[1], f.bl[0]); break;
+          case 10: mma<PREC>(re, f.ah[1], f.bh[1]); break;
+          default: mma<PREC>(im, f.ah[1], f.bh[0]); break;
         }
       });
       ++ch;
@@ -288,58 +246,36 @@ __device__ __forceinline__ void coef_item(const FusedArgs& a, unsigned char* sme
       dh(even, std::false_type{});
       dh(odd, std::false_type{});
     }
-#pragma unroll
-    for (int bm = 0; bm < BM; ++bm) {
-      store(2 * g, bm, re[bm]);
-      store(2 * g + 1, bm, im[bm]);
-    }
+    store(2 * g, re);
+    store(2 * g + 1, im);
   });
   // ---- (h|h) block r: the real product of the row and column operands ----
   static_for<NRT>([&](auto ri) {
     constexpr int r = decltype(ri)::value;
-    Acc h[BM] = {};
-    step(ndh + r, ri, std::integral_constant<int, 6 * BM>{}, std::bool_constant<(r + 1 < NRT)>{},
+    Acc h = {};
+    step(ndh + r, ri, std::integral_constant<int, 6>{}, std::bool_constant<(r + 1 < NRT)>{},
          [&](const Frag& f, int x) {
-           const int bm = x % BM, sl = x / (3 * BM);
-           switch ((x / BM) % 3) {
-             case 0: mma<PREC>(h[bm], f.al[bm][sl], f.bh[sl]); break;
-             case 1: mma<PREC>(h[bm], f.ah[bm][sl], f.bl[sl]); break;
-             default: mma<PREC>(h[bm], f.ah[bm][sl], f.bh[sl]); break;
+           const int sl = x / 3;
+           switch (x % 3) {
+             case 0: mma<PREC>(h, f.al[sl], f.bh[sl]); break;
+             case 1: mma<PREC>(h, f.ah[sl], f.bl[sl]); break;
+             default: mma<PREC>(h, f.ah[sl], f.bh[sl]); break;
            }
          });
-#pragma unroll
-    for (int bm = 0; bm < BM; ++bm) store(2 * G + r, bm, h[bm]);
+    store(2 * G + r, h);
   });
 }
 
-// n tiles in halves, the two of a tile on one XCD; 2 n at most the workgroups
-template <int PREC, int G, int NS>
-__device__ __forceinline__ void coef_halves(const FusedArgs& a, unsigned char* smem, int64_t n, int64_t wg_id,
-                                            int64_t wg_count) {
-  const int64_t part = (n + 7) / 8, y = wg_id / 8;
-  int64_t at = wg_id / 2, half = wg_id & 1;
-  if (16 * part <= wg_count) {
-    at = y / 2 < part ? wg_id % 8 * part + y / 2 : n;
-    half = y & 1;
-  }
-  if (at < n) coef_item<PREC, G, 2, 1, NS>(a, smem, a.work0 + at, (int)half);
-}
-
+// the chunk's tiles, the workgroups in turn
 template <int PREC, int G>
 __device__ __forceinline__ void coef_pass(const FusedArgs& a, int64_t wg_id, int64_t wg_count) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int64_t end = min(a.work0 + a.coef_tiles, coef_work_count(a));
-  const int64_t n = end - a.work0;
-  if (2 * n <= wg_count) {
-    // a list that leaves half of the workgroups idle
-    coef_halves<PREC, G, CoefTile::HALF_NS>(a, smem, n, wg_id, wg_count);
-    return;
-  }
 #pragma unroll 1
   for (int64_t q0 = a.work0; q0 < end; q0 += wg_count) {
     const int64_t at = coef_place(wg_id, wg_count, min(wg_count, end - q0));
     if (at < 0) break;
-    coef_item<PREC, G, 2, 2, 2>(a, smem, q0 + at, 0);
+    coef_item<PREC, G, 4, CoefTile::NS>(a, smem, q0 + at, 0);
   }
 }
 
@@ -348,26 +284,24 @@ __global__ __launch_bounds__(CoefTile::NT, 2) void k_coef(FusedArgs a) {
   coef_pass<PREC, G>(a, blockIdx.x, gridDim.x);
 }
 
-// Launches that the host knows to be of few tiles: in halves where each then has
-// a CU; up to two tiles per CU by four waves each.
-constexpr int64_t kCoefFew = 128, kCoefMid = 512;
-template <int PREC, int G>
-__global__ __launch_bounds__(CoefTile::NT, 1) void k_coef_few(FusedArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int64_t n = min(a.work0 + a.coef_tiles, coef_work_count(a)) - a.work0;
-  coef_halves<PREC, G, CoefTile::FEW_NS>(a, smem, n, blockIdx.x, gridDim.x);
-}
-template <int PREC, int G>
-__global__ __launch_bounds__(2 * CoefTile::NT, 2) void k_coef_mid(FusedArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int64_t n = min(a.work0 + a.coef_tiles, coef_work_count(a)) - a.work0;
-  const int64_t at = coef_place(blockIdx.x, gridDim.x, n);
-  if (at >= 0) coef_item<PREC, G, 4, 1, CoefTile::MID_NS>(a, smem, a.work0 + at, 0);
-}
-// the most tiles that a launch may have to take
+// Launches of few tiles, in halves: two workgroups for each of the most tiles that
+// the launch may have to take (known to the host), the two of a tile on one XCD.
+constexpr int64_t kCoefFew = 128;
 inline int64_t coef_most(const FusedArgs& a) {
   const int64_t left = (a.work_list ? a.n_work_list : a.n_tiles) - a.work0;
   return left < a.coef_tiles ? left : a.coef_tiles;
+}
+template <int PREC, int G>
+__global__ __launch_bounds__(CoefTile::HALF_NT, 1) void k_coef_few(FusedArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int64_t n = min(a.work0 + a.coef_tiles, coef_work_count(a)) - a.work0;
+  const int64_t wg_id = blockIdx.x, part = (n + 7) / 8, y = wg_id / 8;
+  int64_t at = wg_id / 2, half = wg_id & 1;
+  if (16 * part <= (int64_t)gridDim.x) {
+    at = y / 2 < part ? wg_id % 8 * part + y / 2 : n;
+    half = y & 1;
+  }
+  if (at < n) coef_item<PREC, G, 2, CoefTile::HALF_NS>(a, smem, a.work0 + at, (int)half);
 }
 
 // one chunk's first half of several events

@@ -1402,7 +1402,9 @@ int dotpe_event_bytes(const dotpe_ctx* ctx, const dotpe_bank* bk, const dotpe_ev
 
 // Persistent grids of the passes whose work is known on the device only
 constexpr int64_t kSurvGrid = 65536;  // workgroups of 4 waves, a listed tile per wave
-constexpr int64_t kCoefGrid = 1024;   // a tile per workgroup at a time, or half a tile of a short list
+// a tile per workgroup at a time: split banks two workgroups per CU; FP64 banks'
+// 32 x 32 tiles, which need fewer
+static int64_t coef_grid(int prec, int64_t n) { return prec == kFP64 ? std::min<int64_t>(2 * n, 1024) : std::min<int64_t>(n, 512); }
 constexpr int64_t kE2Grid = 4096;
 
 int dotpe_eval_lnl(dotpe_ctx* ctx, dotpe_event* ev, double* lnl, double* ml_max, double* triples,
@@ -1439,7 +1441,7 @@ int dotpe_eval_lnl(dotpe_ctx* ctx, dotpe_event* ev, double* lnl, double* ml_max,
   rc = DOTPE_OK;
   for (a.work0 = 0; a.work0 < a.n_tiles && !rc; a.work0 += ev->coef_tiles) {
     const int64_t n = std::min(ev->coef_tiles, a.n_tiles - a.work0);
-    rc = launch_fused<kCoef>(ev->bank->prec, a, std::min(2 * n, kCoefGrid), s);
+    rc = launch_fused<kCoef>(ev->bank->prec, a, coef_grid(ev->bank->prec, n), s);
     if (!rc) rc = launch_fused<kEval>(ev->bank->prec, a, std::min(n * kEvalParts, kE2Grid), s);
   }
   if (rc) { release(); return rc; }
@@ -1516,7 +1518,7 @@ static PassPlan pass_plan(const dotpe_event* ev, const FusedArgs& a) {
   // return at once
   const int64_t C = ev->coef_tiles;
   p.n_chunks = (a.n_tiles + C - 1) / C;
-  p.coef_grid = std::min(2 * C, kCoefGrid);
+  p.coef_grid = coef_grid(prec, C);
   p.e2_grid = std::min(C, kE2Grid);
   return p;
 }
@@ -2304,7 +2306,7 @@ int dotpe_sample_posterior(dotpe_ctx* ctx, dotpe_event* ev, int64_t n_samples, d
   for (int64_t c = 0; c * C < n_u; ++c) {
     a.work0 = c * C;
     const int64_t n = std::min(C, n_u - a.work0);
-    if ((rc = launch_fused<kCoef>(prec, a, std::min(2 * n, kCoefGrid), s))) return rc;
+    if ((rc = launch_fused<kCoef>(prec, a, coef_grid(prec, n), s))) return rc;
     if ((rc = launch_fused<kSample>(prec, a, n, s))) return rc;
   }
   std::vector<double> h((size_t)ns * 6);

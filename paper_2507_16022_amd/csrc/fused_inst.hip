@@ -106,16 +106,11 @@ hipError_t launch_coef(const FusedArgs& a, int64_t grid, hipStream_t s) {
     static std::once_flag attr_once;
     std::call_once(attr_once, [] {
       if (hipFuncSetAttribute((const void*)k_coef_few<PREC, G>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              CoefTile::FEW_BYTES) != hipSuccess)
+                              CoefTile::HALF_BYTES) != hipSuccess)
         (void)hipGetLastError();
     });
-    hipLaunchKernelGGL((k_coef_few<PREC, G>), dim3((unsigned)(2 * coef_most(a))), dim3(CoefTile::NT),
-                       CoefTile::FEW_BYTES, s, a);
-    return hipGetLastError();
-  } else if (coef_most(a) <= kCoefMid) {
-    static_assert(CoefTile::MID_BYTES <= 64 * 1024, "no attribute needed");
-    hipLaunchKernelGGL((k_coef_mid<PREC, G>), dim3((unsigned)coef_most(a)), dim3(2 * CoefTile::NT),
-                       CoefTile::MID_BYTES, s, a);
+    hipLaunchKernelGGL((k_coef_few<PREC, G>), dim3((unsigned)(2 * coef_most(a))), dim3(CoefTile::HALF_NT),
+                       CoefTile::HALF_BYTES, s, a);
     return hipGetLastError();
   } else {
     hipLaunchKernelGGL((k_coef<PREC, G>), dim3((unsigned)grid), dim3(CoefTile::NT), CoefTile::LDS_BYTES, s, a);
