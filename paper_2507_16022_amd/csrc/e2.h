@@ -147,12 +147,13 @@ __host__ __device__ constexpr int e2_turn(int n_phi, bool few_tiles) {
 }
 __host__ __device__ constexpr bool e2_few(int64_t n_tiles) { return n_tiles <= 512; }
 constexpr int kE2Waves = 4;
-// bytes of its dynamic LDS: the phase table, then per wave a turn's ln Lbar and
-// places
+// bytes of its dynamic LDS: the phase table, then for FP64 per wave a turn's
+// ln Lbar and places (those of split banks, whose turns have one length, at fixed
+// addresses)
 template <int PREC, int G>
 constexpr size_t e2_lds(int n_phi, bool few_tiles) {
-  return sizeof(double) * kMaxM * (size_t)n_phi * 2 +
-         kE2Waves * (size_t)e2_turn<PREC, G>(n_phi, few_tiles) * (sizeof(double) + sizeof(uint16_t));
+  const size_t turn = PREC == kFP64 ? e2_turn<PREC, G>(n_phi, few_tiles) : 0;
+  return sizeof(double) * kMaxM * (size_t)n_phi * 2 + kE2Waves * turn * (sizeof(double) + sizeof(uint16_t));
 }
 
 // MODE kEvidence: the second half of an evidence pass; kEval: every pair's
@@ -195,10 +196,14 @@ __device__ __forceinline__ void e2_pass(const FusedArgs& a, bool few_tiles, int6
   const float thr_f = (float)thr_ml;
   const int64_t end = min(a.work0 + a.coef_tiles, coef_work_count(a));
   AT* const my_slots = slots[wave];
+  // per wave ln Lbar of the turn's kept phases, and their slot << 8 | phase
   const int CH = e2_turn<PREC, G>(n_phi, few_tiles);
+  constexpr int FIX = PREC == kFP64 ? 1 : e2_turn<PREC, G>(0, false);
+  __shared__ double val_fix[NW][FIX];
+  __shared__ uint16_t ent_fix[NW][FIX];
   double* const val = lds_cs + kMaxM * n_phi * 2;
-  double* const my_val = val + wave * CH;                            // ln Lbar of the turn's kept phases
-  uint16_t* const my_ent = (uint16_t*)(val + NW * CH) + wave * CH;   // slot << 8 | phase
+  double* const my_val = PREC == kFP64 ? val + wave * CH : val_fix[wave];
+  uint16_t* const my_ent = PREC == kFP64 ? (uint16_t*)(val + NW * CH) + wave * CH : ent_fix[wave];
 
   // a pair's coefficients and scales from its slot
   struct Coef {
