@@ -971,7 +971,7 @@ __global__ void k_hh_precompute(int64_t n_sub, const int64_t* __restrict__ sub_i
 // margin takes (nrm [n_sub][n_nrm], as k_operand_norms).  A workgroup per row
 // with a lane per (detector, channel pair) and a third of the lanes idle, the
 // row staged in LDS and five barriers took 9.8 ms at 2^20 rows, five channels,
-// three detectors; 4.4 ms now, against 2.5 ms to read the bank and write the
+// three detectors; 3.4 ms now, against 2.5 ms to read the bank and write the
 // operand.
 template <int PREC, int NC, bool WHOLE>
 __global__ __launch_bounds__(256, 2) void k_hh_rows(int64_t n_sub, const int64_t* __restrict__ sub_idx,
