@@ -141,10 +141,17 @@ struct PairSlot {
 // more (3000 x 3000, 128 phases a call of 21.3 ms with 256, 23.3 with 192), nor is
 // a third used by an event of two tiles per CU (64 x 64 pairs 0.56 against 0.61
 // ms a call).
-template <int PREC, int G>
+// Split banks: 512, and 384 in a pass of three or four m groups whose phase table
+// would not fit beside that three times (MANY: 520 tiles of 100 phases, all kept,
+// an evidence call of 4.78 ms with 512 and two workgroups per CU, 3.58 with 384;
+// 1920 tiles 10.3 and 8.9; but 256 tiles, which two per CU take in one round, 2.41
+// and 2.55).
+template <int PREC, int G, bool MANY = false>
 __host__ __device__ constexpr int e2_turn(int n_phi, bool few_tiles) {
-  return PREC != kFP64 ? 512 : G == kMaxG && n_phi < 64 && !few_tiles ? 192 : 256;
+  return PREC != kFP64 ? (MANY ? 384 : 512) : G == kMaxG && n_phi < 64 && !few_tiles ? 192 : 256;
 }
+template <int PREC, int G>
+constexpr bool e2_many(int n_phi, bool few_tiles) { return PREC != kFP64 && G >= 3 && n_phi > 78 && !few_tiles; }
 __host__ __device__ constexpr bool e2_few(int64_t n_tiles) { return n_tiles <= 512; }
 constexpr int kE2Waves = 4;
 // bytes of its dynamic LDS: the phase table, then for FP64 per wave a turn's
@@ -158,7 +165,7 @@ constexpr size_t e2_lds(int n_phi, bool few_tiles) {
 
 // MODE kEvidence: the second half of an evidence pass; kEval: every pair's
 // ln L (and largest lnL^ML, and triples) of the tiles from work0 on.
-template <int PREC, int G, int MODE>
+template <int PREC, int G, int MODE, bool MANY = false>
 __device__ __forceinline__ void e2_pass(const FusedArgs& a, bool few_tiles, int64_t wg_id, int64_t wg_count) {
   typedef Tile<PREC> TL;
   typedef typename std::conditional<PREC == kFP64, double, float>::type AT;
@@ -197,8 +204,8 @@ __device__ __forceinline__ void e2_pass(const FusedArgs& a, bool few_tiles, int6
   const int64_t end = min(a.work0 + a.coef_tiles, coef_work_count(a));
   AT* const my_slots = slots[wave];
   // per wave ln Lbar of the turn's kept phases, and their slot << 8 | phase
-  const int CH = e2_turn<PREC, G>(n_phi, few_tiles);
-  constexpr int FIX = PREC == kFP64 ? 1 : e2_turn<PREC, G>(0, false);
+  const int CH = e2_turn<PREC, G, MANY>(n_phi, few_tiles);
+  constexpr int FIX = PREC == kFP64 ? 1 : e2_turn<PREC, G, MANY>(0, false);
   __shared__ double val_fix[NW][FIX];
   __shared__ uint16_t ent_fix[NW][FIX];
   double* const val = lds_cs + kMaxM * n_phi * 2;
@@ -510,20 +517,20 @@ __device__ __forceinline__ void e2_pass(const FusedArgs& a, bool few_tiles, int6
   }
 }
 
-template <int PREC, int G, int MODE>
+template <int PREC, int G, int MODE, bool MANY = false>
 __global__ __launch_bounds__(256, 3) void k_e2_tiles(FusedArgs a) {
-  e2_pass<PREC, G, MODE>(a, e2_few(a.n_tiles), blockIdx.x, gridDim.x);
+  e2_pass<PREC, G, MODE, MANY>(a, e2_few(a.n_tiles), blockIdx.x, gridDim.x);
 }
 
 // one chunk's second half of several events
-template <int PREC, int G>
+template <int PREC, int G, bool MANY>
 __global__ __launch_bounds__(256, 3) void k_e2_tiles_packed(PackLaunch p) {
   int64_t blk, nblk;
   int q;
   const int e = pack_locate(p, blockIdx.x, &blk, &nblk, &q);
   FusedArgs a = pack_args(p, e, q);
   a.work0 = p.chunk * a.coef_tiles;
-  e2_pass<PREC, G, kEvidence>(a, false, blk, nblk);
+  e2_pass<PREC, G, kEvidence, MANY>(a, false, blk, nblk);
 }
 
 // ---------------------------------------------------------------------------

@@ -31,6 +31,13 @@ hipError_t launch_marg(int mode, const FusedArgs& a, int64_t grid, hipStream_t s
         return hipGetLastError();
       }
     case kE2:
+      if constexpr (e2_many<PREC, G>(kMaxPhi, false)) {
+        if (e2_many<PREC, G>(a.n_phi, e2_few(a.n_tiles))) {
+          hipLaunchKernelGGL((k_e2_tiles<PREC, G, kEvidence, true>), dim3((unsigned)grid), dim3(256),
+                             (e2_lds<PREC, G>(a.n_phi, false)), s, a);
+          return hipGetLastError();
+        }
+      }
       hipLaunchKernelGGL((k_e2_tiles<PREC, G, kEvidence>), dim3((unsigned)grid), dim3(256),
                          (e2_lds<PREC, G>(a.n_phi, e2_few(a.n_tiles))), s, a);
       return hipGetLastError();
@@ -64,7 +71,13 @@ hipError_t launch_marg_packed(int mode, const PackLaunch& p, int n_phi, hipStrea
         return hipGetLastError();
       }
     case kE2:
-      hipLaunchKernelGGL((k_e2_tiles_packed<PREC, G>), grid, dim3(256), (e2_lds<PREC, G>(n_phi, false)), s, p);
+      if constexpr (e2_many<PREC, G>(kMaxPhi, false)) {
+        if (e2_many<PREC, G>(n_phi, false)) {
+          hipLaunchKernelGGL((k_e2_tiles_packed<PREC, G, true>), grid, dim3(256), (e2_lds<PREC, G>(n_phi, false)), s, p);
+          return hipGetLastError();
+        }
+      }
+      hipLaunchKernelGGL((k_e2_tiles_packed<PREC, G, false>), grid, dim3(256), (e2_lds<PREC, G>(n_phi, false)), s, p);
       return hipGetLastError();
   }
   return hipErrorInvalidValue;
