@@ -30,8 +30,8 @@
 // end of one (more cycles than the products) run beside the products of the
 // other.  With 64 x 64 pairs per wave, one wave per SIMD, the matrix cores
 // were busy for 37% of the cycles, now for 50%; the clock falls meanwhile
-// (2.36 to 1.98 GHz), so 65536 x 4096 pairs went from 3.72 to 3.15 ms and
-// 2^20 x 16384 from 213 to 176 ms (1.04 PFLOP/s of the hi products).
+// (2.36 to 1.9 GHz), so 65536 x 4096 pairs went from 3.72 to 3.15 ms and
+// 2^20 x 16384 from 213 to 176-183 ms (1.0 PFLOP/s of the hi products).
 //
 // Two waves share one tile of the fused kernel's grid (64 x 64 pairs), a half
 // of its columns each.  A tile all of whose pairs are bounded writes its
